@@ -303,6 +303,26 @@ int sage_attn_pv_int8_cross_split_fwd(const int8_t* q_i8, const float* q_scale,
                                       int block_q, int block_k, int n_splits, void* stream);
 
 /*
+ * The whole of Algorithm 1 in one call, for programs that have Q, K and V in fp16 and want O: the
+ * pre-passes of K and Q (and, with pv_int8, of V) and the attention, on intermediates the library lays
+ * out inside one workspace.  One call and one buffer instead of three or four, and a plan that may fuse
+ * stages, which the separate calls cannot; O is the separate calls' O up to the order of the
+ * floating-point sums.
+ *   q_f16 [B,H,Nq,D], k_f16, v_f16 [B,H,Nkv,D] in, o_f16 [B,H,Nq,D] out, fp16
+ *   workspace  device, >= sage_attention_workspace() bytes (same arguments), 256-byte aligned; scratch, contents
+ *              undefined on entry and exit; may be NULL when that size is 0
+ *   causal     as in sage_attn_cross_fwd (mask aligned at the end; needs Nq <= Nkv)
+ *   block_q, block_k   1, 32, 64 or 128 and 1, 64 or 128: tokens per scale
+ *   pv_int8    0: FP16 second product; non-zero: the INT8 one of sage_attn_pv_int8_fwd
+ * sage_attention_workspace returns 0 for arguments the call would reject.  Limits and error codes as in the
+ * separate calls.
+ */
+size_t sage_attention_workspace(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k, int pv_int8);
+int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, void* o_f16,
+                       void* workspace, size_t workspace_bytes, int B, int H, int Nq, int Nkv, int D, int causal,
+                       float sm_scale, int block_q, int block_k, int pv_int8, void* stream);
+
+/*
  * Test hook: the raw int32 scores S^ = Q^ K^^T (Algorithm 1, the Matmul inside the S update)
  * produced by the same matrix-instruction code path as sage_attn_fwd, without mask.
  *   s_i32   out [B,H,N,N] int32 -- O(N^2) memory: meant for small N or for sub-problems.

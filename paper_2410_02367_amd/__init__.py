@@ -10,6 +10,8 @@ from .binding import (  # noqa: F401
     load,
     sage_attn_cross_fwd,
     sage_attn_cross_split_fwd,
+    sage_attention_fwd,
+    sage_attention_workspace,
     sage_attn_fwd,
     sage_attn_pv_int8_cross_fwd,
     sage_attn_pv_int8_cross_split_fwd,

@@ -294,6 +294,78 @@ int sage_quant_v(const void* v_f16, int8_t* v_i8t, float* v_scale, void* workspa
     return e == hipSuccess ? SAGE_OK : SAGE_ERR_LAUNCH;
 }
 
+// ---- the whole pass in one call
+namespace {
+// The parts of the caller's workspace, in order, each on a 256-byte boundary.  Sizes of parts that the plan
+// does not use are 0.
+struct AttentionPlan {
+    size_t q_i8, q_scale, k_i8, k_scale, parts, v_i8t, v_scale, v_amax, split;      // byte offsets
+    size_t split_bytes, total;
+};
+AttentionPlan plan_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k, bool pv_int8) {
+    AttentionPlan p;
+    size_t at = 0;
+    auto take = [&at](size_t bytes) { const size_t here = at; at = (at + bytes + 255) / 256 * 256; return here; };
+    const size_t BH = (size_t)B * H;
+    p.q_i8 = take(BH * Nq * D);
+    p.q_scale = take(BH * ((Nq + block_q - 1) / block_q) * sizeof(float));
+    p.k_i8 = take(BH * Nkv * D);
+    p.k_scale = take(BH * ((Nkv + block_k - 1) / block_k) * sizeof(float));
+    p.parts = take(sage_smooth_quant_k_workspace(B, H, Nkv, D));
+    p.v_i8t = take(pv_int8 ? BH * D * (size_t)sage_quant_v_pitch(Nkv) : 0);
+    p.v_scale = take(pv_int8 ? BH * D * sizeof(float) : 0);
+    p.v_amax = take(pv_int8 ? sage_quant_v_workspace(B, H, Nkv, D) : 0);
+    p.split_bytes = Nq != Nkv ? sage_attn_split_workspace(B, H, Nq, Nkv, D, causal, 0) : 0;
+    p.split = take(p.split_bytes);
+    p.total = at;
+    return p;
+}
+int check_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k) {
+    if (int e = check_shape(B, H, Nq, D)) return e;
+    if (int e = check_shape(B, H, Nkv, D)) return e;
+    if (causal && Nq > Nkv) return SAGE_ERR_UNSUPPORTED;
+    if (!quant_block_ok(block_q)) return SAGE_ERR_UNSUPPORTED;
+    if (block_k != 1 && block_k != 64 && block_k != 128) return SAGE_ERR_UNSUPPORTED;
+    return SAGE_OK;
+}
+}  // namespace
+
+size_t sage_attention_workspace(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k, int pv_int8) {
+    if (check_attention(B, H, Nq, Nkv, D, causal, block_q, block_k)) return 0;
+    return plan_attention(B, H, Nq, Nkv, D, causal, block_q, block_k, pv_int8 != 0).total;
+}
+
+int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, void* o_f16,
+                       void* workspace, size_t workspace_bytes, int B, int H, int Nq, int Nkv, int D, int causal,
+                       float sm_scale, int block_q, int block_k, int pv_int8, void* stream) {
+    if (!q_f16 || !k_f16 || !v_f16 || !o_f16) return SAGE_ERR_NULL;
+    if (int e = check_attention(B, H, Nq, Nkv, D, causal, block_q, block_k)) return e;
+    if (!std::isfinite(sm_scale) || !(sm_scale > 0.0f)) return SAGE_ERR_VALUE;
+    const AttentionPlan p = plan_attention(B, H, Nq, Nkv, D, causal, block_q, block_k, pv_int8 != 0);
+    if (p.total > 0 && !workspace) return SAGE_ERR_NULL;
+    if (workspace_bytes < p.total) return SAGE_ERR_WORKSPACE;
+    if (!aligned(q_f16, 16) || !aligned(k_f16, 16) || !aligned(v_f16, 16) || !aligned(o_f16, 16) || !aligned(workspace, 256))
+        return SAGE_ERR_ALIGN;
+    unsigned char* w = (unsigned char*)workspace;
+    int8_t* q_i8 = (int8_t*)(w + p.q_i8);
+    int8_t* k_i8 = (int8_t*)(w + p.k_i8);
+    float* q_scale = (float*)(w + p.q_scale);
+    float* k_scale = (float*)(w + p.k_scale);
+    hipError_t e = sage::launch_quant_qk(q_f16, k_f16, q_i8, q_scale, k_i8, k_scale, nullptr, (long long*)(w + p.parts),
+                                         B * H, Nq, Nkv, D, sm_scale, block_q, block_k, (hipStream_t)stream);
+    if (e != hipSuccess) return SAGE_ERR_LAUNCH;
+    const void* v = v_f16;
+    float* v_scale = nullptr;
+    if (pv_int8) {
+        v = w + p.v_i8t;
+        v_scale = (float*)(w + p.v_scale);
+        e = sage::launch_quant_v(v_f16, (int8_t*)(w + p.v_i8t), v_scale, (unsigned*)(w + p.v_amax), B * H, Nkv, D, (hipStream_t)stream);
+        if (e != hipSuccess) return SAGE_ERR_LAUNCH;
+    }
+    return attn_impl(pv_int8 != 0, Nq != Nkv, q_i8, q_scale, k_i8, k_scale, v, v_scale, o_f16, w + p.split, p.split_bytes,
+                     B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, 0, stream);
+}
+
 int sage_microbench(int kind, int waves_per_simd, int workgroups, int iters,
                     const int32_t* data, uint64_t* out, void* stream) {
     if (!data || !out) return SAGE_ERR_NULL;

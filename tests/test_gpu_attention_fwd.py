@@ -1,0 +1,84 @@
+"""sage_attention_fwd / sageattn() (the whole pass in one call) against the CPU oracle, at the sizes where its
+plan changes or a tile ends: one token, edges of 32-row wavefronts, 64-key tiles and 128-row workgroups, the
+limits of the single-launch path, different lengths, every granularity, both second products."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2410_02367_amd as sage
+import sage_inputs as si
+from gpu_util import ABS_TOL, assert_output_close, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# B, H, Nq, Nkv, D, causal, block_q, block_k
+CASES = [
+    (1, 1, 1, 1, 64, True, 128, 64),
+    (2, 3, 31, 31, 128, False, 128, 64),
+    (1, 2, 33, 33, 64, True, 32, 64),
+    (2, 2, 64, 64, 128, True, 64, 128),
+    (1, 3, 129, 129, 128, True, 128, 64),
+    (2, 2, 197, 197, 64, False, 128, 64),
+    (1, 2, 256, 256, 64, False, 64, 64),
+    (1, 2, 256, 256, 128, True, 128, 128),
+    (2, 1, 257, 257, 128, False, 128, 64),
+    (1, 2, 300, 300, 64, True, 1, 1),
+    (1, 2, 200, 200, 128, False, 1, 1),
+    (1, 2, 150, 150, 128, True, 1, 64),
+    (1, 2, 250, 250, 64, False, 128, 1),
+    (2, 2, 512, 512, 64, True, 128, 64),
+    (1, 2, 513, 513, 128, True, 64, 64),
+    (1, 3, 1105, 1105, 64, False, 128, 64),
+    (1, 2, 1409, 1409, 128, True, 32, 128),
+    (1, 2, 77, 200, 64, False, 128, 64),
+    (1, 2, 700, 77, 128, False, 128, 64),
+    (1, 2, 40, 256, 128, True, 128, 64),
+    (1, 2, 130, 500, 64, True, 64, 64),
+    (1, 2, 5, 1500, 128, True, 128, 64),
+]
+
+
+def inputs(i, B, H, Nq, Nkv, D):
+    w = si.custom(f"fwd{i}", B, H, max(Nq, Nkv), D, False, 128, 64, k_noise=1.0, k_bias=3.0, seed=si.BASE_SEED + 900 + i)
+    q, k, v = si.full(w)
+    return np.ascontiguousarray(q[:, :, :Nq]), np.ascontiguousarray(k[:, :, :Nkv]), np.ascontiguousarray(v[:, :, :Nkv]), w.sm_scale
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_whole_pass_matches_the_oracle(i):
+    B, H, Nq, Nkv, D, causal, bq, bk = CASES[i]
+    print(f"[case] B{B} H{H} Nq{Nq} Nkv{Nkv} D{D} causal={causal} scales {bq}x{bk}", flush=True)
+    q, k, v, sm = inputs(i, B, H, Nq, Nkv, D)
+    need = sage.sage_attention_workspace(B, H, Nq, Nkv, D, causal, bq, bk)
+    ws = torch.full((max(need, 1),), 0xFF, dtype=torch.uint8, device="cuda")      # contents on entry are ignored
+    out = torch.full((B, H, Nq, D), float("nan"), dtype=torch.float16, device="cuda")
+    sage.sage_attention_fwd(to_dev(q), to_dev(k), to_dev(v), causal, sm, bq, bk, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    kq, ks, _ = oracle.smooth_quant_k(k, bk)
+    qq, qs = oracle.quant_q(q, sm, bq)
+    lq, lk = max(bq, 64) if bq != 1 else 128, max(bk, 64) if bk != 1 else 64
+    ref = oracle.attn_l2_cross(qq, qs, kq, ks, v, causal, lq, lk, gran_q=bq, gran_k=bk)
+    assert_output_close(out.cpu().numpy(), ref, f"case {i}")
+    if Nq == Nkv:
+        o8 = sage.sageattn(to_dev(q), to_dev(k), to_dev(v), causal, sm, bq, bk, pv_int8=True)
+        torch.cuda.synchronize()
+        vq, vs = oracle.quant_v(v)
+        ref8, l_ref = oracle.attn_pv8(qq, qs, kq, ks, vq, vs, causal, 128, 64, gran_q=bq, gran_k=bk, return_l=True)
+        # a code of P~ on the edge may fall either way: two codes of one key at most (small outputs: no share is asked)
+        diff = np.abs(o8.cpu().numpy().astype(np.float64) - ref8.astype(np.float64))
+        assert np.all(diff <= ABS_TOL + 2.0 * vs[:, :, None, :] / l_ref[..., None]), float(diff.max())
+
+
+def test_mismatched_tensors_are_refused_before_any_launch():
+    q = torch.zeros(1, 2, 64, 64, dtype=torch.float16, device="cuda")
+    with pytest.raises(ValueError):
+        sage.sageattn(q, q[:, :1].contiguous(), q[:, :1].contiguous())
+    with pytest.raises(TypeError):
+        sage.sageattn(q, q, q[:, :, :32].contiguous())
+    with pytest.raises(TypeError):
+        sage.sageattn(q, q.float(), q)
+    with pytest.raises(TypeError):
+        sage.sageattn(q.transpose(1, 2), q.transpose(1, 2), q.transpose(1, 2))
+    with pytest.raises(sage.SageError):
+        sage.sageattn(q, q, q, block_k=32)

@@ -204,3 +204,23 @@ def test_microbench_call_validates_its_arguments(lib):
     assert lib.sage_microbench(0, 1, 256, 10, odd, good, None) == 5
     assert lib.sage_default_sm_scale(64) == 0.125 and lib.sage_default_sm_scale(0) == 0.0
     assert abs(lib.sage_default_sm_scale(128) - 128 ** -0.5) < 1e-8
+
+
+def test_whole_pass_call_validates_and_sizes_its_workspace(lib):
+    f = ctypes.c_float
+    sz = ctypes.c_size_t
+    good = ctypes.c_void_p(0x1000)
+    call = lib.sage_attention_fwd
+    shape = (1, 2, 4096, 4096, 128, 0)
+    need = lib.sage_attention_workspace(*shape, 128, 64, 0)
+    assert need > 0 and lib.sage_attention_workspace(*shape, 128, 64, 1) >= need
+    assert lib.sage_attention_workspace(*shape, 128, 32, 0) == 0
+    assert lib.sage_attention_workspace(1, 2, 65, 64, 128, 1, 128, 64, 0) == 0
+    assert call(good, good, None, good, good, sz(need), *shape, f(0.125), 128, 64, 0, None) == 1
+    assert call(good, good, good, good, None, sz(need), *shape, f(0.125), 128, 64, 0, None) == 1
+    assert call(good, good, good, good, good, sz(need), 1, 2, 0, 64, 128, 0, f(0.125), 128, 64, 0, None) == 2
+    assert call(good, good, good, good, good, sz(need), 1, 2, 65, 64, 128, 1, f(0.125), 128, 64, 0, None) == 3
+    assert call(good, good, good, good, good, sz(need), *shape, f(0.125), 128, 32, 0, None) == 3
+    assert call(good, good, good, good, good, sz(need - 1), *shape, f(0.125), 128, 64, 0, None) == 4
+    assert call(good, good, good, good, ctypes.c_void_p(0x1010), sz(need), *shape, f(0.125), 128, 64, 0, None) == 5
+    assert call(good, good, good, good, good, sz(need), *shape, f(0.0), 128, 64, 0, None) == 7
