@@ -178,11 +178,11 @@ namespace {
 // The six attention entry points differ in the second product (v is V in fp16, or V^^T in INT8 with
 // v_scale), in whether the two lengths may differ, and in whether the keys are cut into chunks
 // (split: n_splits requested chunks and a workspace; otherwise one chunk, no workspace).
-int attn_impl(bool pv_int8, bool split, const int8_t* q_i8, const float* q_scale, const int8_t* k_i8,
+int attn_impl(bool pv_int8, bool split, const sage::Queries& q, const int8_t* k_i8,
               const float* k_scale, const void* v, const float* v_scale, void* o_f16,
               void* workspace, size_t workspace_bytes, int B, int H, int Nq, int Nkv, int D, int causal,
               float sm_scale, int block_q, int block_k, int n_splits, void* stream) {
-    if (!q_i8 || !q_scale || !k_i8 || !k_scale || !v || !o_f16 || (pv_int8 && !v_scale)) return SAGE_ERR_NULL;
+    if ((!q.f16 && (!q.i8 || !q.scale)) || !k_i8 || !k_scale || !v || !o_f16 || (pv_int8 && !v_scale)) return SAGE_ERR_NULL;
     if (int e = check_shape(B, H, Nq, D)) return e;
     if (int e = check_shape(B, H, Nkv, D)) return e;
     if (causal && Nq > Nkv) return SAGE_ERR_UNSUPPORTED;        // a query before the first key would see nothing
@@ -195,8 +195,8 @@ int attn_impl(bool pv_int8, bool split, const int8_t* q_i8, const float* q_scale
     const size_t need = split ? sage_attn_split_workspace(B, H, Nq, Nkv, D, causal, n_splits) : 0;
     if (need > 0 && !workspace) return SAGE_ERR_NULL;
     if (workspace_bytes < need) return SAGE_ERR_WORKSPACE;
-    if (!aligned(q_i8, 16) || !aligned(k_i8, 16) || !aligned(v, 16) || !aligned(o_f16, 16) ||
-        !aligned(q_scale, 4) || !aligned(k_scale, 4) || (pv_int8 && !aligned(v_scale, 16)) ||
+    if (!aligned(q.i8, 16) || !aligned(q.f16, 16) || !aligned(k_i8, 16) || !aligned(v, 16) || !aligned(o_f16, 16) ||
+        !aligned(q.scale, 4) || !aligned(k_scale, 4) || (pv_int8 && !aligned(v_scale, 16)) ||
         (need > 0 && !aligned(workspace, 16)))
         return SAGE_ERR_ALIGN;
     const int c = causal ? 1 : 0, BH = B * H;
@@ -204,13 +204,13 @@ int attn_impl(bool pv_int8, bool split, const int8_t* q_i8, const float* q_scale
     hipError_t e;
     if (pv_int8) {
         const int8_t* vt = (const int8_t*)v;
-        e = split ? sage::launch_attn_pv8_split(q_i8, q_scale, k_i8, k_scale, vt, v_scale, o_f16, workspace, BH, Nq, Nkv, D, c,
+        e = split ? sage::launch_attn_pv8_split(q, k_i8, k_scale, vt, v_scale, o_f16, workspace, BH, Nq, Nkv, D, c,
                                                 block_q, block_k, n_splits, st)
-                  : sage::launch_attn_pv8(q_i8, q_scale, k_i8, k_scale, vt, v_scale, o_f16, BH, Nq, Nkv, D, c, block_q, block_k, st);
+                  : sage::launch_attn_pv8(q, k_i8, k_scale, vt, v_scale, o_f16, BH, Nq, Nkv, D, c, block_q, block_k, st);
     } else {
-        e = split ? sage::launch_attn_split(q_i8, q_scale, k_i8, k_scale, v, o_f16, workspace, BH, Nq, Nkv, D, c,
+        e = split ? sage::launch_attn_split(q, k_i8, k_scale, v, o_f16, workspace, BH, Nq, Nkv, D, c,
                                             block_q, block_k, n_splits, st)
-                  : sage::launch_attn(q_i8, q_scale, k_i8, k_scale, v, o_f16, nullptr, BH, Nq, Nkv, D, c, block_q, block_k, st);
+                  : sage::launch_attn(q, k_i8, k_scale, v, o_f16, nullptr, BH, Nq, Nkv, D, c, block_q, block_k, st);
     }
     return e == hipSuccess ? SAGE_OK : SAGE_ERR_LAUNCH;
 }
@@ -231,14 +231,14 @@ size_t sage_attn_split_workspace(int B, int H, int Nq, int Nkv, int D, int causa
 int sage_attn_fwd(const int8_t* q_i8, const float* q_scale, const int8_t* k_i8, const float* k_scale,
                   const void* v_f16, void* o_f16, int B, int H, int N, int D, int causal,
                   float sm_scale, int block_q, int block_k, void* stream) {
-    return attn_impl(false, false, q_i8, q_scale, k_i8, k_scale, v_f16, nullptr, o_f16, nullptr, 0,
+    return attn_impl(false, false, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_f16, nullptr, o_f16, nullptr, 0,
                      B, H, N, N, D, causal, sm_scale, block_q, block_k, 1, stream);
 }
 
 int sage_attn_cross_fwd(const int8_t* q_i8, const float* q_scale, const int8_t* k_i8, const float* k_scale,
                         const void* v_f16, void* o_f16, int B, int H, int Nq, int Nkv, int D, int causal,
                         float sm_scale, int block_q, int block_k, void* stream) {
-    return attn_impl(false, false, q_i8, q_scale, k_i8, k_scale, v_f16, nullptr, o_f16, nullptr, 0,
+    return attn_impl(false, false, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_f16, nullptr, o_f16, nullptr, 0,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, 1, stream);
 }
 
@@ -246,7 +246,7 @@ int sage_attn_cross_split_fwd(const int8_t* q_i8, const float* q_scale, const in
                               const void* v_f16, void* o_f16, void* workspace, size_t workspace_bytes,
                               int B, int H, int Nq, int Nkv, int D, int causal, float sm_scale,
                               int block_q, int block_k, int n_splits, void* stream) {
-    return attn_impl(false, true, q_i8, q_scale, k_i8, k_scale, v_f16, nullptr, o_f16, workspace, workspace_bytes,
+    return attn_impl(false, true, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_f16, nullptr, o_f16, workspace, workspace_bytes,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, n_splits, stream);
 }
 
@@ -254,7 +254,7 @@ int sage_attn_pv_int8_fwd(const int8_t* q_i8, const float* q_scale, const int8_t
                           const int8_t* v_i8t, const float* v_scale, void* o_f16,
                           int B, int H, int N, int D, int causal, float sm_scale,
                           int block_q, int block_k, void* stream) {
-    return attn_impl(true, false, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, o_f16, nullptr, 0,
+    return attn_impl(true, false, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_i8t, v_scale, o_f16, nullptr, 0,
                      B, H, N, N, D, causal, sm_scale, block_q, block_k, 1, stream);
 }
 
@@ -262,7 +262,7 @@ int sage_attn_pv_int8_cross_fwd(const int8_t* q_i8, const float* q_scale, const 
                                 const int8_t* v_i8t, const float* v_scale, void* o_f16,
                                 int B, int H, int Nq, int Nkv, int D, int causal, float sm_scale,
                                 int block_q, int block_k, void* stream) {
-    return attn_impl(true, false, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, o_f16, nullptr, 0,
+    return attn_impl(true, false, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_i8t, v_scale, o_f16, nullptr, 0,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, 1, stream);
 }
 
@@ -271,7 +271,7 @@ int sage_attn_pv_int8_cross_split_fwd(const int8_t* q_i8, const float* q_scale, 
                                       void* workspace, size_t workspace_bytes,
                                       int B, int H, int Nq, int Nkv, int D, int causal, float sm_scale,
                                       int block_q, int block_k, int n_splits, void* stream) {
-    return attn_impl(true, true, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, o_f16, workspace, workspace_bytes,
+    return attn_impl(true, true, {q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_i8t, v_scale, o_f16, workspace, workspace_bytes,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, n_splits, stream);
 }
 
@@ -299,16 +299,14 @@ namespace {
 // The parts of the caller's workspace, in order, each on a 256-byte boundary.  Sizes of parts that the plan
 // does not use are 0.
 struct AttentionPlan {
-    size_t q_i8, q_scale, k_i8, k_scale, parts, v_i8t, v_scale, v_amax, split;      // byte offsets
+    size_t k_i8, k_scale, parts, v_i8t, v_scale, v_amax, split;      // byte offsets
     size_t split_bytes, total;
 };
-AttentionPlan plan_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k, bool pv_int8) {
+AttentionPlan plan_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_k, bool pv_int8) {
     AttentionPlan p;
     size_t at = 0;
     auto take = [&at](size_t bytes) { const size_t here = at; at = (at + bytes + 255) / 256 * 256; return here; };
     const size_t BH = (size_t)B * H;
-    p.q_i8 = take(BH * Nq * D);
-    p.q_scale = take(BH * ((Nq + block_q - 1) / block_q) * sizeof(float));
     p.k_i8 = take(BH * Nkv * D);
     p.k_scale = take(BH * ((Nkv + block_k - 1) / block_k) * sizeof(float));
     p.parts = take(sage_smooth_quant_k_workspace(B, H, Nkv, D));
@@ -332,7 +330,7 @@ int check_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_
 
 size_t sage_attention_workspace(int B, int H, int Nq, int Nkv, int D, int causal, int block_q, int block_k, int pv_int8) {
     if (check_attention(B, H, Nq, Nkv, D, causal, block_q, block_k)) return 0;
-    return plan_attention(B, H, Nq, Nkv, D, causal, block_q, block_k, pv_int8 != 0).total;
+    return plan_attention(B, H, Nq, Nkv, D, causal, block_k, pv_int8 != 0).total;
 }
 
 int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, void* o_f16,
@@ -341,18 +339,17 @@ int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, 
     if (!q_f16 || !k_f16 || !v_f16 || !o_f16) return SAGE_ERR_NULL;
     if (int e = check_attention(B, H, Nq, Nkv, D, causal, block_q, block_k)) return e;
     if (!std::isfinite(sm_scale) || !(sm_scale > 0.0f)) return SAGE_ERR_VALUE;
-    const AttentionPlan p = plan_attention(B, H, Nq, Nkv, D, causal, block_q, block_k, pv_int8 != 0);
+    const AttentionPlan p = plan_attention(B, H, Nq, Nkv, D, causal, block_k, pv_int8 != 0);
     if (p.total > 0 && !workspace) return SAGE_ERR_NULL;
     if (workspace_bytes < p.total) return SAGE_ERR_WORKSPACE;
     if (!aligned(q_f16, 16) || !aligned(k_f16, 16) || !aligned(v_f16, 16) || !aligned(o_f16, 16) || !aligned(workspace, 256))
         return SAGE_ERR_ALIGN;
     unsigned char* w = (unsigned char*)workspace;
-    int8_t* q_i8 = (int8_t*)(w + p.q_i8);
     int8_t* k_i8 = (int8_t*)(w + p.k_i8);
-    float* q_scale = (float*)(w + p.q_scale);
     float* k_scale = (float*)(w + p.k_scale);
-    hipError_t e = sage::launch_quant_qk(q_f16, k_f16, q_i8, q_scale, k_i8, k_scale, nullptr, (long long*)(w + p.parts),
-                                         B * H, Nq, Nkv, D, sm_scale, block_q, block_k, (hipStream_t)stream);
+    // Q is quantized by the attention kernel itself (see Queries)
+    hipError_t e = sage::launch_smooth_quant_k(k_f16, k_i8, k_scale, nullptr, (long long*)(w + p.parts), B * H, Nkv, D, block_k,
+                                               nullptr, nullptr, (hipStream_t)stream);
     if (e != hipSuccess) return SAGE_ERR_LAUNCH;
     const void* v = v_f16;
     float* v_scale = nullptr;
@@ -362,7 +359,7 @@ int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, 
         e = sage::launch_quant_v(v_f16, (int8_t*)(w + p.v_i8t), v_scale, (unsigned*)(w + p.v_amax), B * H, Nkv, D, (hipStream_t)stream);
         if (e != hipSuccess) return SAGE_ERR_LAUNCH;
     }
-    return attn_impl(pv_int8 != 0, Nq != Nkv, q_i8, q_scale, k_i8, k_scale, v, v_scale, o_f16, w + p.split, p.split_bytes,
+    return attn_impl(pv_int8 != 0, Nq != Nkv, {nullptr, nullptr, q_f16, sm_scale}, k_i8, k_scale, v, v_scale, o_f16, w + p.split, p.split_bytes,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, 0, stream);
 }
 
@@ -387,7 +384,7 @@ int sage_attn_qk_i32_debug(const int8_t* q_i8, const int8_t* k_i8, int32_t* s_i3
     if (wg_rows != 0 && wg_rows != 128 && wg_rows != 256) return SAGE_ERR_UNSUPPORTED;
     if (!aligned(q_i8, 16) || !aligned(k_i8, 16) || !aligned(s_i32, 4)) return SAGE_ERR_ALIGN;
     // scales are not read by the dump path; pass the tensor pointers as placeholders of valid memory
-    hipError_t e = sage::launch_attn(q_i8, (const float*)q_i8, k_i8, (const float*)k_i8, nullptr, nullptr, s_i32,
+    hipError_t e = sage::launch_attn({q_i8, (const float*)q_i8, nullptr, 0.0f}, k_i8, (const float*)k_i8, nullptr, nullptr, s_i32,
                                      B * H, N, N, D, 0, block_q, block_k, (hipStream_t)stream, wg_rows);
     return e == hipSuccess ? SAGE_OK : SAGE_ERR_LAUNCH;
 }
@@ -401,7 +398,7 @@ int sage_attn_clock_debug(const int8_t* q_i8, const float* q_scale, const int8_t
     if (!aligned(q_i8, 16) || !aligned(k_i8, 16) || !aligned(v_f16, 16) || !aligned(o_f16, 16) ||
         !aligned(q_scale, 4) || !aligned(k_scale, 4) || !aligned(clocks, 8))
         return SAGE_ERR_ALIGN;
-    hipError_t e = sage::launch_attn_clocks(q_i8, q_scale, k_i8, k_scale, v_f16, o_f16, (unsigned long long*)clocks,
+    hipError_t e = sage::launch_attn_clocks({q_i8, q_scale, nullptr, 0.0f}, k_i8, k_scale, v_f16, o_f16, (unsigned long long*)clocks,
                                             B * H, N, causal ? 1 : 0, block_q, block_k, (hipStream_t)stream);
     return e == hipSuccess ? SAGE_OK : SAGE_ERR_LAUNCH;
 }

@@ -75,6 +75,7 @@
 //     multiplies V, and costs no VALU issue slot.  (Dot-product instructions such as v_dot2c run on the
 //     matrix pipe as well, but block it for VALU work -- measured.)
 #include "sage_internal.h"
+#include "sage_device.h"
 #include <type_traits>
 #include <utility>
 
@@ -236,7 +237,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const _Float16* __restrict__ vg, _Float16* __restrict__ og,
                  int32_t* __restrict__ sdump, float* __restrict__ lse, unsigned long long* __restrict__ clocks,
                  int Nq, int Nkv, int shift_q, int shift_k, int tiles_q, int per_xcd, long total_tiles,
-                 int BH, int n_splits, int chunk, int tm_group) {
+                 int BH, int n_splits, int chunk, int tm_group,
+                 const _Float16* __restrict__ qf, float sm_scale) {
     constexpr int NWAVES = NW, NTHREADS = NW * 64;
     constexpr int QTILE = NW * WROWS;   // query rows per workgroup
     constexpr int KROW = D;             // bytes per K^ row in LDS
@@ -252,7 +254,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     constexpr int KCH = KROW / 16, VCH = VROW / 16;             // chunks per row
     static_assert(!(KTOK && DUMP), "the score dump has no scales");
     constexpr int KSL = KTOK ? 2 * 2 * KTILE * 4 : 0;           // per-key (a, b) factors, two tiles
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * KB + 2 * VB + KSL];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * KB + 2 * VB + KSL + NW * 4];      // NW floats: QueryRows
 
     // Workgroup -> (slab, query tile).  Consecutive workgroup ids land on the 8 XCDs in turn; give
     // each XCD a contiguous range of the (slab-major, heaviest-query-tile-first) order so that the
@@ -296,23 +298,41 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     const int nbq = (Nq + (1 << shift_q) - 1) >> shift_q, nbk = (Nkv + (1 << shift_k) - 1) >> shift_k;
 
     // Q^ operands (B matrix of S^T = K^ Q^^T) stay in accumulator registers for the whole kernel.
+    // They are read as codes, or made here from fp16 rows (qf): a query is read once by the launch either way,
+    // and the quantizer's own pass over Q (2 bytes read and 1 written per element, 1 read again) is saved.
     v4i qreg[QS][KS];
     float dq[QS];
+    if (!DUMP && QS == 1 && qf != nullptr) {
+        QueryRows<KS> rows;
+        const int q_row = qrow0 + ql;
+        rows.fetch(qf + (slab_q + q_row) * D, g, q_row < Nq);
+        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
+        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
+        dq[0] = amax / 127.0f * LOG2E;
 #pragma unroll
-    for (int qs = 0; qs < QS; ++qs) {
-        const int q_row = qrow0 + 32 * qs + ql;
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qreg[qs][ks] = (v4i){0, 0, 0, 0};
-            if (q_row < Nq) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
-            pin_a(qreg[qs][ks]);
-        }
-        dq[qs] = 0.0f;
-        if (!DUMP) {
-            const int rc = q_row < Nq ? q_row : Nq - 1;           // the lane's own query: any block_q down to 1
-            dq[qs] = qsc[(size_t)bh * nbq + (rc >> shift_q)] * LOG2E;
+            for (int i = 0; i < 4; ++i) qreg[0][ks][i] = (int)rows.word(ks, i, sm_scale, rcp);
+    } else {
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) {
+            const int q_row = qrow0 + 32 * qs + ql;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                qreg[qs][ks] = (v4i){0, 0, 0, 0};
+                if (q_row < Nq) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
+            }
+            dq[qs] = 0.0f;
+            if (!DUMP) {
+                const int rc = q_row < Nq ? q_row : Nq - 1;           // the lane's own query: any block_q down to 1
+                dq[qs] = qsc[(size_t)bh * nbq + (rc >> shift_q)] * LOG2E;
+            }
         }
     }
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) pin_a(qreg[qs][ks]);
     v16f acc_o[QS][DT];      // O^T accumulators
     // Row sums l, accumulated on the matrix pipe (see l_mfma): registers 0 and 1 hold the sums of the
     // queries lane % 16 and 16 + lane % 16 over all keys so far.
@@ -975,7 +995,7 @@ int tile_major_group(long total_tiles, int tiles_q, long unit_bytes) {
 }
 
 template <int D, int NW>
-static hipError_t launch_dn(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* kscale,
                             const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                             int block_q, int block_k, const SplitPlan& sp, hipStream_t st,
                             unsigned long long* clocks = nullptr) {
@@ -989,7 +1009,7 @@ static hipError_t launch_dn(const int8_t* qq, const float* qscale, const int8_t*
     _Float16* op = (_Float16*)o;
     const bool ktok = block_k == 1;
     const int tm_group = causal && !sdump ? tile_major_group(total, tiles_q, (long)(sp.n_splits > 1 ? sp.chunk : N) * 3 * D) : 0;
-#define SAGE_ARGS qq, qscale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, tm_group
+#define SAGE_ARGS q.i8, q.scale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, tm_group, (const _Float16*)q.f16, q.sm_scale
 #define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
     if (clocks != nullptr) {
         // the measurement build exists for the headline shape only: D = 128, 256-row workgroups, block scales
@@ -1022,7 +1042,7 @@ static hipError_t launch_dn(const int8_t* qq, const float* qscale, const int8_t*
 }
 
 template <int D>
-static hipError_t launch_d(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* kscale,
                            const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                            int block_q, int block_k, const SplitPlan& sp, hipStream_t st, int wg_rows = 0,
                            unsigned long long* clocks = nullptr) {
@@ -1039,23 +1059,23 @@ static hipError_t launch_d(const int8_t* qq, const float* qscale, const int8_t* 
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only
-    if (small) return launch_dn<D, 4>(qq, qscale, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);
-    return launch_dn<D, 8>(qq, qscale, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st, clocks);
+    if (small) return launch_dn<D, 4>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);
+    return launch_dn<D, 8>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st, clocks);
 }
 
-hipError_t launch_attn(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn(const Queries& q, const int8_t* kq, const float* kscale,
                        const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int D, int causal,
                        int block_q, int block_k, hipStream_t st, int wg_rows) {
     const SplitPlan whole = {1, 0, nullptr};
-    if (D == 64) return launch_d<64>(qq, qscale, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
-    return launch_d<128>(qq, qscale, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
+    if (D == 64) return launch_d<64>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
+    return launch_d<128>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
 }
 
-hipError_t launch_attn_clocks(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_clocks(const Queries& q, const int8_t* kq, const float* kscale,
                               const void* v, void* o, unsigned long long* clocks, int BH, int N, int causal,
                               int block_q, int block_k, hipStream_t st) {
     const SplitPlan whole = {1, 0, nullptr};
-    return launch_d<128>(qq, qscale, kq, kscale, v, o, nullptr, BH, N, N, causal, block_q, block_k, whole, st, 0, clocks);
+    return launch_d<128>(q, kq, kscale, v, o, nullptr, BH, N, N, causal, block_q, block_k, whole, st, 0, clocks);
 }
 
 // ---- split over the keys ------------------------------------------------------------------------
@@ -1127,18 +1147,18 @@ hipError_t launch_merge_splits(const void* part, const float* lse, void* o, long
     return hipGetLastError();
 }
 
-hipError_t launch_attn_split(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* kscale,
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
                              int block_q, int block_k, int requested, hipStream_t st) {
     SplitPlan sp = plan_split(BH, Nq, N, causal, requested);
-    if (sp.n_splits == 1) return launch_attn(qq, qscale, kq, kscale, v, o, nullptr, BH, Nq, N, D, causal, block_q, block_k, st);
+    if (sp.n_splits == 1) return launch_attn(q, kq, kscale, v, o, nullptr, BH, Nq, N, D, causal, block_q, block_k, st);
     const long rows = (long)BH * Nq;
     // workspace: partial O [n_splits, BH, Nq, D] fp16, then lse [n_splits, BH, Nq] fp32
     _Float16* part = (_Float16*)workspace;
     sp.lse = (float*)((char*)workspace + (size_t)sp.n_splits * rows * D * sizeof(_Float16));
     hipError_t e = D == 64
-        ? launch_d<64>(qq, qscale, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st)
-        : launch_d<128>(qq, qscale, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
+        ? launch_d<64>(q, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st)
+        : launch_d<128>(q, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
     if (e != hipSuccess) return e;
     return launch_merge_splits(part, sp.lse, o, rows, D, sp.n_splits, st);
 }

@@ -34,6 +34,7 @@
 // 8-15 % from 32K up (flushes are rare there), 3-6 % slower below 8K; it is bound by VALU issue
 // (about 264 VALU instructions against 16 matrix instructions per 32 x 64 step).
 #include "sage_internal.h"
+#include "sage_device.h"
 #include <type_traits>
 
 namespace sage {
@@ -81,7 +82,8 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
                      const int8_t* __restrict__ vt, const float* __restrict__ vsc,
                      _Float16* __restrict__ og, float* __restrict__ lse,
                      int Nq, int Nkv, int Np, int shift_q, int shift_k, int tiles_q, int per_xcd, long total_tiles,
-                     int BH, int n_splits, int chunk, int tm_group) {
+                     int BH, int n_splits, int chunk, int tm_group,
+                     const _Float16* __restrict__ qf, float sm_scale) {
     constexpr int NT = 256, QTILE = 128, KT = 64;
     constexpr int KS = D / 32, DT = D / 32;
     constexpr int KB = KT * D, VB = D * KT;            // bytes per K^ tile / V^^T tile
@@ -97,7 +99,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     constexpr int QREG = D == 64 ? 0 : (CAUSAL ? 2 : KS);
     constexpr int QB = QREG < KS ? QTILE * D : 0;
     constexpr int QOFF = 3 * (KB + VB) + 3 * KSL;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[QOFF + QB];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[QOFF + QB + 16];        // 4 floats: QueryRows
 
     // workgroup -> (slab, query tile): contiguous ranges per XCD, heaviest query tiles first
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -133,12 +135,30 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     const int nbq = (Nq + (1 << shift_q) - 1) >> shift_q, nbk = (Nkv + (1 << shift_k) - 1) >> shift_k;
 
     p4i qreg[QREG > 0 ? QREG : 1];
+    float dq;
+    if (qf != nullptr) {
+        // fp16 rows, quantized here: steps below QREG to registers, the others to the wavefront's own rows of the LDS copy
+        QueryRows<KS> rows;
+        rows.fetch(qf + (slab_q + q_row) * D, h, q_row < Nq);
+        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + QOFF + QB));
+        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
+        dq = amax / 127.0f * PV8_LOG2E;
 #pragma unroll
-    for (int ks = 0; ks < QREG; ++ks) {
-        qreg[ks] = (p4i){0, 0, 0, 0};
-        if (q_row < Nq) qreg[ks] = *(const p4i*)(qi + (slab_q + q_row) * D + ks * 32 + h * 16);
+        for (int ks = 0; ks < KS; ++ks) {
+            p4i code;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) code[i] = (int)rows.word(ks, i, sm_scale, rcp);
+            if (ks < QREG) qreg[ks] = code;
+            else *(p4i*)(lds + QOFF + wave * (32 * D) + ql * D + (((2 * ks + h) ^ k_swz8<D>(ql)) * 16)) = code;
+        }
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < QREG; ++ks) {
+            qreg[ks] = (p4i){0, 0, 0, 0};
+            if (q_row < Nq) qreg[ks] = *(const p4i*)(qi + (slab_q + q_row) * D + ks * 32 + h * 16);
+        }
+        dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
     }
-    const float dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
     const float* __restrict__ ksc_bh = ksc + (size_t)bh * nbk + (k0 >> shift_k);
 
     const int kv_tiles_all = (N + KT - 1) / KT;
@@ -163,7 +183,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     const p4i v_desc = pv8_descriptor(vt + (size_t)bh * D * Np + k0, (unsigned)D * Np - (unsigned)k0);
     const p4i ks_desc = pv8_descriptor(ksc_bh, (unsigned)N * 4u);      // per-token variant: N scales; past the end reads 0
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
-    if (QREG < KS) {
+    if (QREG < KS && qf == nullptr) {
         // same row pitch and chunk swizzle as a K^ tile (no key permutation); rows past Nq read as zero
         const p4i q_desc = pv8_descriptor(qi + slab_q * D, (unsigned)Nq * D);
 #pragma unroll
@@ -414,7 +434,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
 }
 
 template <int D>
-static hipError_t launch_pv8_d(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+static hipError_t launch_pv8_d(const Queries& q, const int8_t* kq, const float* kscale,
                                const int8_t* vt, const float* vscale, void* o, int BH, int Nq, int N, int causal,
                                int shift_q, int shift_k, bool ktok, const SplitPlan& sp, hipStream_t st) {
     const int tiles_q = (Nq + 127) / 128, Np = 64 * ((N + 63) / 64);
@@ -423,8 +443,8 @@ static hipError_t launch_pv8_d(const int8_t* qq, const float* qscale, const int8
     const dim3 grid((unsigned)(per_xcd * 8)), block(256);
     const int tm_group = causal ? tile_major_group(total, tiles_q, (long)(sp.n_splits > 1 ? sp.chunk : N) * 2 * D) : 0;
 #define SAGE_PV8_S(C, K, S) sage_attn_pv8_kernel<D, C, K, S><<<grid, block, 0, st>>>( \
-        qq, qscale, kq, kscale, vt, vscale, (_Float16*)o, sp.lse, Nq, N, Np, shift_q, shift_k, tiles_q, per_xcd, total, \
-        BH, sp.n_splits, sp.chunk, tm_group)
+        q.i8, q.scale, kq, kscale, vt, vscale, (_Float16*)o, sp.lse, Nq, N, Np, shift_q, shift_k, tiles_q, per_xcd, total, \
+        BH, sp.n_splits, sp.chunk, tm_group, (const _Float16*)q.f16, q.sm_scale)
 #define SAGE_PV8(C, K) do { if (sp.n_splits > 1) SAGE_PV8_S(C, K, true); else SAGE_PV8_S(C, K, false); } while (0)
     if (causal) { if (ktok) SAGE_PV8(true, true); else SAGE_PV8(true, false); }
     else        { if (ktok) SAGE_PV8(false, true); else SAGE_PV8(false, false); }
@@ -433,34 +453,34 @@ static hipError_t launch_pv8_d(const int8_t* qq, const float* qscale, const int8
     return hipGetLastError();
 }
 
-static hipError_t launch_pv8_plan(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+static hipError_t launch_pv8_plan(const Queries& q, const int8_t* kq, const float* kscale,
                                   const int8_t* vt, const float* vscale, void* o, int BH, int Nq, int N, int D, int causal,
                                   int block_q, int block_k, const SplitPlan& sp, hipStream_t st) {
     int shift_q = 0, shift_k = 0;
     while ((1 << shift_q) < block_q) ++shift_q;
     while ((1 << shift_k) < block_k) ++shift_k;
     const bool ktok = block_k == 1;
-    if (D == 64) return launch_pv8_d<64>(qq, qscale, kq, kscale, vt, vscale, o, BH, Nq, N, causal, shift_q, shift_k, ktok, sp, st);
-    return launch_pv8_d<128>(qq, qscale, kq, kscale, vt, vscale, o, BH, Nq, N, causal, shift_q, shift_k, ktok, sp, st);
+    if (D == 64) return launch_pv8_d<64>(q, kq, kscale, vt, vscale, o, BH, Nq, N, causal, shift_q, shift_k, ktok, sp, st);
+    return launch_pv8_d<128>(q, kq, kscale, vt, vscale, o, BH, Nq, N, causal, shift_q, shift_k, ktok, sp, st);
 }
 
-hipError_t launch_attn_pv8(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_pv8(const Queries& q, const int8_t* kq, const float* kscale,
                            const int8_t* vt, const float* vscale, void* o, int BH, int Nq, int N, int D, int causal,
                            int block_q, int block_k, hipStream_t st) {
     const SplitPlan whole = {1, 0, nullptr};
-    return launch_pv8_plan(qq, qscale, kq, kscale, vt, vscale, o, BH, Nq, N, D, causal, block_q, block_k, whole, st);
+    return launch_pv8_plan(q, kq, kscale, vt, vscale, o, BH, Nq, N, D, causal, block_q, block_k, whole, st);
 }
 
 // The keys cut into chunks, as in launch_attn_split(): same plan, same workspace layout, same merge
 // (the common factor 127 of the chunks' denominators cancels in the weights).
-hipError_t launch_attn_pv8_split(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_pv8_split(const Queries& q, const int8_t* kq, const float* kscale,
                                  const int8_t* vt, const float* vscale, void* o, void* workspace, int BH, int Nq, int N,
                                  int D, int causal, int block_q, int block_k, int requested, hipStream_t st) {
     SplitPlan sp = plan_split(BH, Nq, N, causal, requested);
-    if (sp.n_splits == 1) return launch_attn_pv8(qq, qscale, kq, kscale, vt, vscale, o, BH, Nq, N, D, causal, block_q, block_k, st);
+    if (sp.n_splits == 1) return launch_attn_pv8(q, kq, kscale, vt, vscale, o, BH, Nq, N, D, causal, block_q, block_k, st);
     const long rows = (long)BH * Nq;
     sp.lse = (float*)((char*)workspace + (size_t)sp.n_splits * rows * D * sizeof(_Float16));
-    hipError_t e = launch_pv8_plan(qq, qscale, kq, kscale, vt, vscale, workspace, BH, Nq, N, D, causal, block_q, block_k, sp, st);
+    hipError_t e = launch_pv8_plan(q, kq, kscale, vt, vscale, workspace, BH, Nq, N, D, causal, block_q, block_k, sp, st);
     if (e != hipSuccess) return e;
     return launch_merge_splits(workspace, sp.lse, o, rows, D, sp.n_splits, st);
 }

@@ -25,17 +25,26 @@ hipError_t launch_quant_qk(const void* q, const void* k, int8_t* qq, float* qsca
                            float* kmean, long long* parts, int BH, int Nq, int Nkv, int D, float sm_scale,
                            int block_q, int block_k, hipStream_t st);
 
+// The queries of an attention launch: quantized (i8, scale), or fp16 rows that the attention kernel quantizes
+// itself (f16 != nullptr; then i8 and scale are not read).
+struct Queries {
+    const int8_t* i8;
+    const float* scale;
+    const void* f16;
+    float sm_scale;
+};
+
 // Fused attention (MFMA-bound): Nq query rows against N keys per slab.  sdump != nullptr selects the
 // int32 score dump; for the dump, wg_rows (128 or 256) names the workgroup shape instead of leaving
 // it to the launcher (0).
-hipError_t launch_attn(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn(const Queries& q, const int8_t* kq, const float* kscale,
                        const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int D, int causal,
                        int block_q, int block_k, hipStream_t st, int wg_rows = 0);
 // Measurement build of the same kernel (D = 128, 256-row workgroups, one scale per key block): also
 // writes, per wavefront, [shader-clock ticks, 100 MHz ticks, raises of the running maximum, key tiles
 // visited] to clocks[(workgroup * 8 + wavefront) * 4 ..], workgroup = slab * ceil(N / 256) + query tile
 // counted from the last.
-hipError_t launch_attn_clocks(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_clocks(const Queries& q, const int8_t* kq, const float* kscale,
                               const void* v, void* o, unsigned long long* clocks, int BH, int N, int causal,
                               int block_q, int block_k, hipStream_t st);
 
@@ -51,12 +60,12 @@ struct SplitPlan {
 // slabs an XCD interleaves tile-major in a causal launch (0: none); see sage_attn.hip
 int tile_major_group(long total_tiles, int tiles_q, long unit_bytes);
 SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested);
-hipError_t launch_attn_split(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* kscale,
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
                              int block_q, int block_k, int requested, hipStream_t st);
 
 hipError_t launch_merge_splits(const void* part, const float* lse, void* o, long rows, int D, int n_splits, hipStream_t st);
-hipError_t launch_attn_pv8_split(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_pv8_split(const Queries& q, const int8_t* kq, const float* kscale,
                                  const int8_t* vt, const float* vscale, void* o, void* workspace, int BH, int Nq, int N,
                                  int D, int causal, int block_q, int block_k, int requested, hipStream_t st);
 
@@ -64,7 +73,7 @@ hipError_t launch_attn_pv8_split(const int8_t* qq, const float* qscale, const in
 // 64 * ceil(N / 64)) and the attention kernel that consumes it.
 hipError_t launch_quant_v(const void* v, int8_t* vt, float* vscale, unsigned* amax_bits,
                           int BH, int N, int D, hipStream_t st);
-hipError_t launch_attn_pv8(const int8_t* qq, const float* qscale, const int8_t* kq, const float* kscale,
+hipError_t launch_attn_pv8(const Queries& q, const int8_t* kq, const float* kscale,
                            const int8_t* vt, const float* vscale, void* o, int BH, int Nq, int N, int D, int causal,
                            int block_q, int block_k, hipStream_t st);
 
