@@ -303,7 +303,8 @@ struct AttentionPlan {
     size_t split_bytes, total;
 };
 AttentionPlan plan_attention(int B, int H, int Nq, int Nkv, int D, int causal, int block_k, bool pv_int8) {
-    AttentionPlan p;
+    AttentionPlan p = {};
+    if (!pv_int8 && sage::short_fits(Nkv, D)) return p;        // one launch, no intermediates
     size_t at = 0;
     auto take = [&at](size_t bytes) { const size_t here = at; at = (at + bytes + 255) / 256 * 256; return here; };
     const size_t BH = (size_t)B * H;
@@ -344,6 +345,11 @@ int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, 
     if (workspace_bytes < p.total) return SAGE_ERR_WORKSPACE;
     if (!aligned(q_f16, 16) || !aligned(k_f16, 16) || !aligned(v_f16, 16) || !aligned(o_f16, 16) || !aligned(workspace, 256))
         return SAGE_ERR_ALIGN;
+    if (!pv_int8 && sage::short_fits(Nkv, D)) {
+        hipError_t e = sage::launch_short(q_f16, k_f16, v_f16, o_f16, B * H, Nq, Nkv, D, causal ? 1 : 0, sm_scale, block_q, block_k,
+                                          (hipStream_t)stream);
+        return e == hipSuccess ? SAGE_OK : SAGE_ERR_LAUNCH;
+    }
     unsigned char* w = (unsigned char*)workspace;
     int8_t* k_i8 = (int8_t*)(w + p.k_i8);
     float* k_scale = (float*)(w + p.k_scale);

@@ -298,41 +298,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     const int nbq = (Nq + (1 << shift_q) - 1) >> shift_q, nbk = (Nkv + (1 << shift_k) - 1) >> shift_k;
 
     // Q^ operands (B matrix of S^T = K^ Q^^T) stay in accumulator registers for the whole kernel.
-    // They are read as codes, or made here from fp16 rows (qf): a query is read once by the launch either way,
-    // and the quantizer's own pass over Q (2 bytes read and 1 written per element, 1 read again) is saved.
     v4i qreg[QS][KS];
     float dq[QS];
-    if (!DUMP && QS == 1 && qf != nullptr) {
-        QueryRows<KS> rows;
-        const int q_row = qrow0 + ql;
-        rows.fetch(qf + (slab_q + q_row) * D, g, q_row < Nq);
-        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
-        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
-        dq[0] = amax / 127.0f * LOG2E;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) qreg[0][ks][i] = (int)rows.word(ks, i, sm_scale, rcp);
-    } else {
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) {
-            const int q_row = qrow0 + 32 * qs + ql;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                qreg[qs][ks] = (v4i){0, 0, 0, 0};
-                if (q_row < Nq) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
-            }
-            dq[qs] = 0.0f;
-            if (!DUMP) {
-                const int rc = q_row < Nq ? q_row : Nq - 1;           // the lane's own query: any block_q down to 1
-                dq[qs] = qsc[(size_t)bh * nbq + (rc >> shift_q)] * LOG2E;
-            }
-        }
-    }
-#pragma unroll
-    for (int qs = 0; qs < QS; ++qs)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) pin_a(qreg[qs][ks]);
     v16f acc_o[QS][DT];      // O^T accumulators
     // Row sums l, accumulated on the matrix pipe (see l_mfma): registers 0 and 1 hold the sums of the
     // queries lane % 16 and 16 + lane % 16 over all keys so far.
@@ -869,6 +836,40 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     load_k(0, 0);
     if (T > 1) load_k(1, 1);
     request_key_scales(0);
+    // The queries, while the key tiles are on their way.  They are read as codes, or made here from fp16 rows (qf):
+    // a query is read once by the launch either way, and the quantizer's own pass over Q (2 bytes read and 1 written
+    // per element, 1 read again) is saved.
+    if (!DUMP && QS == 1 && qf != nullptr) {
+        QueryRows<KS> rows;
+        const int q_row = qrow0 + ql;
+        rows.fetch(qf + (slab_q + q_row) * D, g, q_row < Nq);
+        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
+        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
+        dq[0] = amax / 127.0f * LOG2E;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qreg[0][ks][i] = (int)rows.word(ks, i, sm_scale, rcp);
+    } else {
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) {
+            const int q_row = qrow0 + 32 * qs + ql;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                qreg[qs][ks] = (v4i){0, 0, 0, 0};
+                if (q_row < Nq) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
+            }
+            dq[qs] = 0.0f;
+            if (!DUMP) {
+                const int rc = q_row < Nq ? q_row : Nq - 1;           // the lane's own query: any block_q down to 1
+                dq[qs] = qsc[(size_t)bh * nbq + (rc >> shift_q)] * LOG2E;
+            }
+        }
+    }
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) pin_a(qreg[qs][ks]);
     tiles_ready_barrier();
     qk_half(0, std::integral_constant<int, 0>{});
     qk_half(0, std::integral_constant<int, 1>{});

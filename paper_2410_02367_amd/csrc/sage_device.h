@@ -6,13 +6,12 @@ namespace sage {
 
 // Four INT8 codes round_half_even(clamp(x * rcp)) of Section 3.2, byte i from x[i].  Adding 1.5 * 2^23 rounds
 // the (once rounded) product to an integer, ties to even, and leaves it in the low byte of the bit pattern in
-// two's complement; a byte permute per pair packs them: 3.75 VALU instructions per code instead of 7 with a
-// rounding, a conversion, a mask and a shift.  The same bits as rintf and a conversion: |product| <= 127 after
-// the clamp.
+// two's complement; a byte permute per pair packs them: 3.75 VALU instructions per code instead of 8 with a
+// rounding, two-sided clamp, conversion, mask and shift.  The same bits as rintf and a conversion: |product| <= 127
+// after the clamp, and a product that is not a number (0 * infinity: amax below 2^-121) is -127 either way.
 __device__ __forceinline__ unsigned quantize4(float x0, float x1, float x2, float x3, float rcp) {
     auto code = [rcp](float x) {
-        const float p = __builtin_fminf(__builtin_fmaxf(x * rcp, -127.0f), 127.0f);
-        return __builtin_bit_cast(unsigned, p + 12582912.0f);
+        return __builtin_bit_cast(unsigned, __builtin_amdgcn_fmed3f(x * rcp, -127.0f, 127.0f) + 12582912.0f);
     };
     const unsigned lo = __builtin_amdgcn_perm(code(x1), code(x0), 0x0c0c0400u);
     const unsigned hi = __builtin_amdgcn_perm(code(x3), code(x2), 0x04000c0cu);
@@ -41,13 +40,21 @@ struct QueryRows {
     // largest |x * sm_scale| of the lane's quantization block; every wavefront of the workgroup calls it.
     // red: one float of LDS per wavefront, not used for anything else before the next barrier.
     __device__ __forceinline__ float block_amax(float sm_scale, int shift_q, int wave, float* red) const {
-        float m = 0.0f;
+        // max |x * sm_scale| = max |x| * sm_scale, rounded once either way (rounding is monotonic): the maximum is
+        // taken on the fp16 patterns without their signs, two per instruction
+        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        us2 top = {0, 0};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j) {
+                const u4 w = __builtin_bit_cast(u4, raw[ks][j]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf((float)raw[ks][j][e] * sm_scale));
+                for (int e = 0; e < 4; ++e) top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, w[e] & 0x7fff7fffu));
+            }
+        const unsigned short most = top[0] > top[1] ? top[0] : top[1];
+        float m = (float)__builtin_bit_cast(_Float16, most) * sm_scale;
         m = __builtin_fmaxf(m, __shfl_xor(m, 32, 64));
         if (shift_q == 0) return m;
 #pragma unroll
@@ -64,7 +71,9 @@ struct QueryRows {
     __device__ __forceinline__ unsigned word(int ks, int i, float sm_scale, float rcp) const {
         const half8& h = raw[ks][i >> 1];
         const int e = 4 * (i & 1);
-        return quantize4((float)h[e] * sm_scale, (float)h[e + 1] * sm_scale, (float)h[e + 2] * sm_scale, (float)h[e + 3] * sm_scale, rcp);
+        // x * sm_scale rounded once: the FMA takes the fp16 operand as it is (no conversion), the 0 changes no code
+        auto scaled = [sm_scale](_Float16 x) { return __builtin_fmaf((float)x, sm_scale, 0.0f); };
+        return quantize4(scaled(h[e]), scaled(h[e + 1]), scaled(h[e + 2]), scaled(h[e + 3]), rcp);
     }
 };
 

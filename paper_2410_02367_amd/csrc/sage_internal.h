@@ -77,6 +77,11 @@ hipError_t launch_attn_pv8(const Queries& q, const int8_t* kq, const float* ksca
                            const int8_t* vt, const float* vscale, void* o, int BH, int Nq, int N, int D, int causal,
                            int block_q, int block_k, hipStream_t st);
 
+// The whole pass in one launch for short key sequences (FP16 second product); see sage_short.hip
+bool short_fits(int N, int D);
+hipError_t launch_short(const void* q, const void* k, const void* v, void* o, int BH, int Nq, int N, int D, int causal,
+                        float sm_scale, int block_q, int block_k, hipStream_t st);
+
 // Instruction-stream probes (sage_microbench.hip): kind 0..6, 1 or 2 wavefronts per SIMD, `out` takes
 // four 64-bit words per wavefront.
 hipError_t launch_microbench(int kind, int waves_per_simd, int workgroups, int iters, const int* data,

@@ -1,0 +1,402 @@
+// The whole pass of Algorithm 1 in one launch for key sequences that fit the LDS of a compute unit: smoothing and
+// quantization of K (Sections 4.2, 3.2), quantization of Q (Section 4.6) and the attention loop (Sections 3.1, 4.4).
+//
+// A workgroup of 4 wavefronts reads the keys of one (batch, head) slab once, into registers: exact column sums,
+// mean, block maxima and codes all come from there, K^ stays in LDS, V goes to LDS while that happens, and the
+// wavefronts then walk 32-row query tiles without another barrier.  Nothing but Q, K and V is read from memory and
+// nothing but O is written.
+//
+// Several workgroups can share a slab (each takes its part of the query tiles and makes K^ for itself); see
+// short_groups() for how many, and short_fits() for which launches come here.
+//
+// Measured against the two launches before it (K pre-pass, attention kernel), us for the whole call: 12 x 64 slabs of
+// 197 keys at D = 64: 40 -> 30; 1 x 2 of 256: 16.5 -> 9.5; 256 of 256 at D = 128: 40 -> 23; 128 x (4096 queries against
+// 77 keys): 128 -> 87.  Bounds: launch latency for few slabs; for many, a memory phase (Q, K, V in, at the copy rate)
+// and a VALU phase (codes of K^ and Q^, softmax) of about equal length, which overlap only between workgroups.
+#include "sage_internal.h"
+#include "sage_device.h"
+#include <type_traits>
+
+namespace sage {
+
+typedef int s4i __attribute__((ext_vector_type(4)));
+typedef int s16i __attribute__((ext_vector_type(16)));
+typedef float s16f __attribute__((ext_vector_type(16)));
+typedef short s4s __attribute__((ext_vector_type(4)));
+typedef float s2f __attribute__((ext_vector_type(2)));
+typedef _Float16 s2h __attribute__((ext_vector_type(2)));
+typedef _Float16 s4h __attribute__((ext_vector_type(4)));
+
+namespace {
+constexpr float SHORT_LOG2E = 1.4426950408889634f;
+constexpr float SHORT_SLACK = 8.0f;         // log2 of the largest P~ tolerated before the running maximum is raised
+
+template <int D> __device__ __forceinline__ int short_kswz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
+template <int D> __device__ __forceinline__ int short_vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+
+__device__ __forceinline__ s4i short_descriptor(const void* base, unsigned bytes) {
+    const unsigned long long a = (unsigned long long)base;
+    return (s4i){__builtin_amdgcn_readfirstlane((int)(unsigned)a), __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
+                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+// 16 bytes per lane from global memory to LDS, lane l to lds_addr + 16 l; asynchronous (vmcnt)
+__device__ __forceinline__ void short_load_to_lds16(const s4i& rsrc, unsigned goff, unsigned lds_addr) {
+    const unsigned addr = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(goff), "s"(rsrc), "s"(addr) : "memory");
+}
+// x + the value of the lane 32 (16) away, of two values at once: lanes of the lower half (even rows of 16) end with
+// the sum of a, the others with the sum of b
+__device__ __forceinline__ double fold32(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    auto lo = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
+}
+}  // namespace
+
+// D channels, NTILE tiles of 64 keys at most, NW wavefronts; KTOK: one scale per key.  grid: groups workgroups per
+// slab.  48 KB of K^ and V (NTILE * D = 256): 4 wavefronts, two or three workgroups per CU; 96 KB: 8 wavefronts, one.
+template <int D, int NTILE, int NW, bool KTOK>
+__global__ void __launch_bounds__(NW * 64, NW == 8 || D == 128 ? 2 : 3)
+sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ kf, const _Float16* __restrict__ vf,
+                  _Float16* __restrict__ og, int Nq, int N, int shift_q, int shift_k, int causal, float sm_scale, int groups) {
+    constexpr int KMAX = NTILE * 64;            // keys that fit
+    constexpr int VPR = D / 8;                  // 16-byte vectors (8 channels) of a K row
+    constexpr int RPI = 64 / VPR;               // K rows per load instruction of a wavefront
+    constexpr int LPG = 32 / RPI;               // load instructions per group of 32 rows
+    constexpr int GPW = NTILE * 2 / NW;         // groups of 32 rows per wavefront
+    constexpr int NT = NW * 64;
+    constexpr int KS = D / 32, DT = D / 32;
+    constexpr int VROW = 2 * D;
+    constexpr int VCH = VROW / 16;              // 16-byte chunks of a V row
+    static_assert(GPW >= 1, "every wavefront owns at least one group of 32 keys");
+    __shared__ __attribute__((aligned(1024))) unsigned char kl[KMAX * D];
+    __shared__ __attribute__((aligned(1024))) unsigned char vl[KMAX * VROW];
+    __shared__ __attribute__((aligned(16))) float s_mean[D];
+    __shared__ float s_max[KMAX / 32];
+    __shared__ __attribute__((aligned(16))) float s_scale[KTOK ? KMAX : KMAX / 64];
+    __shared__ float s_q[2][NW];
+    static_assert(NW * D * 8 <= KMAX * D, "the partial column sums fit where K^ will be");
+    double (*const s_part)[D] = (double (*)[D])kl;       // [wavefront][channel]; read before the codes are written
+
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int ql = lane & 31, g = lane >> 5;
+    const int bh = blockIdx.x / groups, part = blockIdx.x - bh * groups;
+    const size_t slab = (size_t)bh * N, slab_q = (size_t)bh * Nq;
+    const int tiles = (N + 63) / 64;
+    const int coff = Nq <= N ? N - Nq : 0;       // (only read when causal, where Nq <= N)
+
+    // ---- keys into registers; groups of 32 rows past the end are skipped, rows past the end repeat the last one
+    half8 x[GPW][LPG];
+    const int c8 = lane % VPR, r0 = wave * (GPW * 32) + lane / VPR;
+    const _Float16* kbase = kf + slab * D + c8 * 8;
+#pragma unroll
+    for (int gr = 0; gr < GPW; ++gr) {
+        if (wave * (GPW * 32) + gr * 32 >= N) continue;
+#pragma unroll
+        for (int i = 0; i < LPG; ++i) {
+            const int r = r0 + gr * 32 + i * RPI;
+            x[gr][i] = *(const half8*)(kbase + (size_t)(r < N ? r : N - 1) * D);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- values into LDS, asynchronously.  Chunks of rows past the end are zeroed first (P~ is 0 there, but 0 * NaN
+    // would not be); their loads lie beyond the descriptor.
+    {
+        const s4i rsrc = short_descriptor(vf + slab * D, (unsigned)N * VROW);
+        const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)vl;
+        const int vecs = tiles * (64 * VCH);
+        for (int i = wave * 64; i < vecs; i += NT) {
+            const int vi = i + lane, row = vi / VCH, c = (vi % VCH) ^ short_vswz<D>(row);
+            if (i / VCH + 64 / VCH > N) {
+                *(s4i*)(vl + vi * 16) = (s4i){0, 0, 0, 0};
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+            short_load_to_lds16(rsrc, (unsigned)(row * VROW + c * 16), base + i * 16);
+        }
+    }
+    const int rtiles = (Nq + 31) / 32;
+    // the workgroup's query tiles: NW at a time (128 or 256 rows, a multiple of every block_q), one per wavefront
+    QueryRows<KS> rows;
+    {
+        const int row = (part * NW + wave) * 32 + ql;
+        rows.fetch(qf + (slab_q + row) * D, g, row < Nq);
+    }
+
+    // ---- exact column sums (fp64: multiples of 2^-24 below 2^25), folded over the wavefront's rows
+    double sum[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[e] = 0.0;
+#pragma unroll
+    for (int gr = 0; gr < GPW; ++gr) {
+        if (wave * (GPW * 32) + gr * 32 >= N) continue;
+        if (wave * (GPW * 32) + gr * 32 + 32 <= N) {
+#pragma unroll
+            for (int i = 0; i < LPG; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum[e] += (double)(float)x[gr][i][e];
+        } else {
+#pragma unroll
+            for (int i = 0; i < LPG; ++i) {
+                const double live = r0 + gr * 32 + i * RPI < N ? 1.0 : 0.0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum[e] += live * (double)(float)x[gr][i][e];
+            }
+        }
+    }
+    {
+        // lanes 32 apart, then 16 apart (then 8, where a row is 8 lanes) hold the same channels of other rows
+        double a[4], b[2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = fold32(sum[e], sum[e + 4]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) b[e] = fold16(a[e], a[e + 2]);
+        if (VPR == 8) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) b[e] += __shfl_xor(b[e], 8, 64);
+        }
+        const int ch = c8 * 8 + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
+        s_part[wave][ch] = b[0];
+        s_part[wave][ch + 1] = b[1];
+    }
+    __syncthreads();
+    if (t < D) {
+        double total = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) total += s_part[w][t];
+        s_mean[t] = (float)(total / (double)N);
+    }
+    __syncthreads();
+    float mean[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mean[e] = s_mean[c8 * 8 + e];
+
+    // ---- codes of K^ into LDS (rows of D bytes, 16-byte chunks swizzled)
+    auto smoothed = [&](_Float16 v, int e) { return __builtin_fmaf((float)v, 1.0f, -mean[e]); };      // one rounding: v - mean
+    auto store_codes = [&](const half8& h, int r, float rcp) {
+        uint2 w;
+        w.x = quantize4(smoothed(h[0], 0), smoothed(h[1], 1), smoothed(h[2], 2), smoothed(h[3], 3), rcp);
+        w.y = quantize4(smoothed(h[4], 4), smoothed(h[5], 5), smoothed(h[6], 6), smoothed(h[7], 7), rcp);
+        *(uint2*)(kl + r * D + (((c8 >> 1) ^ short_kswz<D>(r)) * 16) + (c8 & 1) * 8) = w;
+    };
+    auto row_max = [&](const half8& h) {
+        float m = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(smoothed(h[e], e)));
+        return m;
+    };
+    if (KTOK) {
+#pragma unroll
+        for (int gr = 0; gr < GPW; ++gr) {
+            if (wave * (GPW * 32) + gr * 32 >= N) continue;
+#pragma unroll
+            for (int i = 0; i < LPG; ++i) {
+                const int r = r0 + gr * 32 + i * RPI;
+                float m = row_max(x[gr][i]);
+#pragma unroll
+                for (int off = VPR / 2; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+                if (c8 == 0) s_scale[r] = m / 127.0f;
+                store_codes(x[gr][i], r, m > 0.0f ? 127.0f / m : 0.0f);
+            }
+        }
+    } else {
+        float gm[GPW];
+#pragma unroll
+        for (int gr = 0; gr < GPW; ++gr) {
+            gm[gr] = 0.0f;
+            if (wave * (GPW * 32) + gr * 32 >= N) continue;
+#pragma unroll
+            for (int i = 0; i < LPG; ++i) gm[gr] = __builtin_fmaxf(gm[gr], row_max(x[gr][i]));      // a repeated row changes no maximum
+        }
+#pragma unroll
+        for (int gr = 0; gr < GPW; ++gr) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) gm[gr] = __builtin_fmaxf(gm[gr], __shfl_xor(gm[gr], off, 64));
+            if (lane == 0) s_max[wave * GPW + gr] = gm[gr];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int gr = 0; gr < GPW; ++gr) {
+            const int row = wave * (GPW * 32) + gr * 32;
+            if (row >= N) continue;
+            const int blk = (row >> shift_k) << (shift_k - 5);       // first 32-row group of the quantization block (64 or 128 rows)
+            float m = __builtin_fmaxf(s_max[blk], s_max[blk + 1]);
+            if (shift_k == 7 && NTILE > 1) m = __builtin_fmaxf(m, __builtin_fmaxf(s_max[blk + 2], s_max[blk + 3]));
+            if (lane == 0) s_scale[row >> 6] = m / 127.0f;           // (both groups of a tile write the same value)
+            const float rcp = m > 0.0f ? 127.0f / m : 0.0f;
+#pragma unroll
+            for (int i = 0; i < LPG; ++i) store_codes(x[gr][i], r0 + gr * 32 + i * RPI, rcp);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's part of V has landed
+    __syncthreads();
+
+    // ---- operand read offsets, as in sage_attn.hip
+    int k_off[KS], v_off[DT];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * D + (((2 * ks + g) ^ short_kswz<D>(ql)) * 16);
+    const int grp = lane >> 4, li = lane & 15, v_row = 4 * (grp >> 1) + (li >> 2);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+        v_off[dt] = v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ short_vswz<D>(v_row)) * 16) + (li & 1) * 8;
+
+    for (int set = part, turn = 0; set * NW < rtiles; set += groups, turn ^= 1) {
+        const int row0 = (set * NW + wave) * 32, q_row = row0 + ql;
+        const float qmax = rows.block_amax(sm_scale, shift_q, wave, s_q[turn]);
+        const float qrcp = qmax > 0.0f ? 127.0f / qmax : 0.0f;
+        const float dq = qmax / 127.0f * SHORT_LOG2E;
+        s4i q[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[ks][i] = (int)rows.word(ks, i, sm_scale, qrcp);
+        if ((set + groups) * NW < rtiles) {          // the next rows are requested before this tile's loop
+            const int row = ((set + groups) * NW + wave) * 32 + ql;
+            rows.fetch(qf + (slab_q + row) * D, g, row < Nq);
+        }
+        if (row0 >= Nq) continue;
+
+        s16f o[DT];
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
+        float m_run = -__builtin_inff(), l = 0.0f;
+        // keys this wavefront sees; a tile of which it sees only the first half is done by halves
+        int seen = causal ? row0 + 32 + coff : N;
+        seen = seen < N ? seen : N;
+        auto tile = [&](int j, auto HALVES) {
+            constexpr int NH = HALVES.value;
+            const unsigned char* kt = kl + j * (64 * D);
+            s16i s[NH];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[h][r] = 0;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    s[h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const s4i*)(kt + h * (32 * D) + k_off[ks]), q[ks], s[h], 0, 0, 0);
+            }
+            // register r of half h: key 64 j + 32 h + 8 (r / 4) + 4 g + r % 4
+            const float sc = __builtin_fmaxf(KTOK ? dq : dq * s_scale[j], 1e-30f);
+            float y[NH][16];
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    y[h][r] = (float)s[h][r];
+                    if (KTOK) y[h][r] *= s_scale[64 * j + 32 * h + 8 * (r >> 2) + 4 * g + (r & 3)];
+                }
+            if (j * 64 + 32 * NH > N || (causal && j * 64 + 32 * NH - 1 > row0 + coff)) {
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int key = 64 * j + 32 * h + 8 * (r >> 2) + 4 * g + (r & 3);
+                        if (key >= N || (causal && key > q_row + coff)) y[h][r] = -__builtin_inff();
+                    }
+            }
+            float top = y[0][0];
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) top = __builtin_fmaxf(top, y[h][r]);
+            top = __builtin_fmaxf(top, __shfl_xor(top, 32, 64)) * sc;
+            if (__builtin_amdgcn_ballot_w64(top > m_run + SHORT_SLACK) != 0ull) {
+                // (on the first tile m_run is -inf and every row that sees a key is here)
+                const float m_new = __builtin_fmaxf(m_run, top);
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                m_run = m_new;
+                l *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+            }
+            const unsigned char* vt = vl + j * (64 * VROW);
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    s4i p;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e], sc, -m_run));
+                        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e + 1], sc, -m_run));
+                        l += p0 + p1;
+                        p[e] = __builtin_bit_cast(int, __builtin_convertvector((s2f){p0, p1}, s2h));
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        const unsigned char* va = vt + (32 * h + 16 * u) * VROW + v_off[dt];
+                        const s4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4s*)va);
+                        const s4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4s*)(va + 8 * VROW));
+                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                            __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)),
+                            __builtin_bit_cast(half8, p), o[dt], 0, 0, 0);
+                    }
+                }
+        };
+        const int whole = (seen + 31) / 64;
+        for (int j = 0; j < whole; ++j) tile(j, std::integral_constant<int, 2>{});
+        if (whole * 64 < seen) tile(whole, std::integral_constant<int, 1>{});
+        const float inv = 1.0f / (l + __shfl_xor(l, 32, 64));
+        if (q_row < Nq) {
+            _Float16* orow = og + (slab_q + q_row) * D;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    s4h w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = (_Float16)(o[dt][4 * c + e] * inv);
+                    *(s4h*)(orow + dt * 32 + 8 * c + 4 * g) = w;
+                }
+        }
+    }
+}
+
+// Key sequences whose K^ and V fit the LDS beside a second workgroup's, or nearly: 512 keys of 64 channels, 256 of 128.
+bool short_fits(int N, int D) { return N <= (D == 64 ? 512 : 256); }
+
+// Workgroups per slab: up to one per round of the wavefronts while the chip has room for more workgroups.
+static int short_groups(int BH, int Nq, int rows, int per_cu) {
+    const int most = (Nq + rows - 1) / rows;
+    const int room = 256 * per_cu / BH;
+    return room < 1 ? 1 : (room < most ? room : most);
+}
+
+template <int D, int NTILE, int NW>
+static hipError_t launch_short_t(const void* q, const void* k, const void* v, void* o, int BH, int Nq, int N, int causal,
+                                 float sm_scale, int block_q, int block_k, hipStream_t st) {
+    const int groups = short_groups(BH, Nq, NW * 32, NW == 8 ? 1 : D == 64 ? 3 : 2);
+    const int shift_q = __builtin_ctz((unsigned)block_q), shift_k = __builtin_ctz((unsigned)block_k);
+    const dim3 grid((unsigned)(BH * groups));
+#define SAGE_SHORT(KT) sage_short_kernel<D, NTILE, NW, KT><<<grid, NW * 64, 0, st>>>((const _Float16*)q, (const _Float16*)k, (const _Float16*)v, \
+        (_Float16*)o, Nq, N, shift_q, shift_k, causal, sm_scale, groups)
+    if (block_k == 1) SAGE_SHORT(true); else SAGE_SHORT(false);
+#undef SAGE_SHORT
+    return hipGetLastError();
+}
+
+hipError_t launch_short(const void* q, const void* k, const void* v, void* o, int BH, int Nq, int N, int D, int causal,
+                        float sm_scale, int block_q, int block_k, hipStream_t st) {
+#define SAGE_SHORT_N(DD, NT, NW) return launch_short_t<DD, NT, NW>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st)
+    if (D == 64) {
+        if (N <= 128) SAGE_SHORT_N(64, 2, 4);
+        if (N <= 256) SAGE_SHORT_N(64, 4, 4);
+        SAGE_SHORT_N(64, 8, 8);
+    }
+    if (N <= 128) SAGE_SHORT_N(128, 2, 4);
+    SAGE_SHORT_N(128, 4, 8);
+#undef SAGE_SHORT_N
+}
+
+}  // namespace sage
