@@ -955,19 +955,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         for (int dt = 0; dt < DT; ++dt) refresh(acc_o[qs][dt]);
         const float l_row = (lane & 16) ? acc_l[qs][1] : acc_l[qs][0];       // the lane's own query, all keys
         const float inv = 1.0f / l_row;
-        if (q_row < Nq) {
-            if (lse != nullptr && g == 0) lse[slab_o + q_row] = m_run[qs] + __builtin_amdgcn_logf(l_row);
-            _Float16* orow = og + (slab_o + q_row) * D;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    v4h w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = (_Float16)(acc_o[qs][dt][4 * rq + e] * inv);
-                    *(v4h*)(orow + dt * 32 + 8 * rq + 4 * g) = w;
-                }
-        }
+        if (lse != nullptr && g == 0 && q_row < Nq) lse[slab_o + q_row] = m_run[qs] + __builtin_amdgcn_logf(l_row);
+        if (qrow0 + 32 * qs < Nq)
+            store_rows<D>(og + (slab_o + qrow0 + 32 * qs) * D, Nq - qrow0 - 32 * qs, lane, lse == nullptr,
+                          [&](int dt, int r) { return acc_o[qs][dt][r] * inv; });
     }
     if constexpr (CLOCKS) {
         if (lane == 0) {

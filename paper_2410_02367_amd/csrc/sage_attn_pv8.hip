@@ -409,27 +409,15 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     // ---- epilogue: O = (O_fp32 + A) * delta_V[c] / sum(127 P~)
     const float lt = l127 + lane32_partner(l127);
     const float inv = 1.0f / lt, g_run = 1.0f / ginv;
-    int q_out = q_row;
-    if (SPLIT) asm volatile("" : "+v"(q_out));       // the output addresses are formed here, not carried through the loop
+    int q_out = qrow0;
+    if (SPLIT) asm volatile("" : "+s"(q_out));       // the output addresses are formed here, not carried through the loop
+    if (SPLIT && h == 0 && q_out + ql < Nq) lse[slab_o + q_out + ql] = m_run + __builtin_amdgcn_logf(lt);
     if (q_out < Nq) {
-        if (SPLIT && h == 0) lse[slab_o + q_out] = m_run + __builtin_amdgcn_logf(lt);
-        _Float16* orow = og + (slab_o + q_out) * D;
-        const float* dv = vsc + (size_t)bh * D;
-#pragma unroll
-        for (int cb = 0; cb < DT; ++cb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int ch = 32 * cb + 8 * g + 4 * h;
-                const float4 d4 = *(const float4*)(dv + ch);
-                const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
-                p4h o4;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const float tot = __builtin_fmaf(of[cb][4 * g + b], g_run, (float)acc[cb][4 * g + b]);
-                    o4[b] = (_Float16)(tot * (dd[b] * inv));
-                }
-                *(p4h*)(orow + ch) = o4;
-            }
+        // channels 32 cb + 8 g + 4 h .. + 3: register 4 g .. + 3 of block cb
+        const float* dv = vsc + (size_t)bh * D + 4 * h;
+        store_rows<D>(og + (slab_o + q_out) * D, Nq - q_out, lane, !SPLIT, [&](int cb, int r) {
+            return __builtin_fmaf(of[cb][r], g_run, (float)acc[cb][r]) * (dv[32 * cb + 8 * (r >> 2) + (r & 3)] * inv);
+        });
     }
 }
 

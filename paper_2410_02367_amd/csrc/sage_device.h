@@ -77,4 +77,50 @@ struct QueryRows {
     }
 };
 
+// Stores a wavefront's 32 output rows (fp16, D channels).  As the matrix instructions leave O^T, a lane owns one row
+// and holds 4 consecutive channels (8 bytes) at a time; stored like that, an instruction writes 16 bytes to each of 32
+// rows, and the stores of a workgroup were 11 % of the time of a 1536-token sequence.  Two register swaps with the
+// lanes 32 and 16 away collect 16 bytes per lane and 64 bytes per row: half the store instructions, a quarter of the
+// row segments.
+// value(dt, r): register r of the lane's block of channels 32 dt ..: row lane % 32, channel 8 (r / 4) + 4 (lane / 32) + r % 4.
+// rows: how many of the 32 rows exist.  final: the output itself, which nobody on this XCD reads again, goes past the
+// L2 that holds K^ and V (1-3 % up to 4K tokens); partial results, which a merge reads next, stay in it.
+template <int D, class F>
+__device__ __forceinline__ void store_rows(_Float16* out, int rows, int lane, bool final, F&& value) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    const int row = lane & 15, chunk = 2 * ((lane >> 4) & 1) + (lane >> 5);
+    _Float16* const at = out + (size_t)row * D + 8 * chunk;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+        i4 c[2];                // chunk 2 k + lane / 32 of the lane's row, 8 channels
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const f2 x = {value(dt, 8 * k + 2 * i), value(dt, 8 * k + 2 * i + 1)};
+                const f2 y = {value(dt, 8 * k + 4 + 2 * i), value(dt, 8 * k + 4 + 2 * i + 1)};
+                auto s = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(int, __builtin_convertvector(x, h2)),
+                                                          __builtin_bit_cast(int, __builtin_convertvector(y, h2)), false, false);
+                c[k][i] = s[0];
+                c[k][2 + i] = s[1];
+            }
+        i4 w[2];                // rows 0 .. 15 and 16 .. 31: chunk `chunk` of row `row`
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            auto s = __builtin_amdgcn_permlane16_swap(c[0][m], c[1][m], false, false);
+            w[0][m] = s[0];
+            w[1][m] = s[1];
+        }
+        if (final) {
+            if (row < rows) __builtin_nontemporal_store(w[0], (i4*)(at + 32 * dt));
+            if (row + 16 < rows) __builtin_nontemporal_store(w[1], (i4*)(at + 16 * D + 32 * dt));
+        } else {
+            if (row < rows) *(i4*)(at + 32 * dt) = w[0];
+            if (row + 16 < rows) *(i4*)(at + 16 * D + 32 * dt) = w[1];
+        }
+    }
+}
+
 }  // namespace sage

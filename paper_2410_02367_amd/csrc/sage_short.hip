@@ -348,18 +348,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         for (int j = 0; j < whole; ++j) tile(j, std::integral_constant<int, 2>{});
         if (whole * 64 < seen) tile(whole, std::integral_constant<int, 1>{});
         const float inv = 1.0f / (l + __shfl_xor(l, 32, 64));
-        if (q_row < Nq) {
-            _Float16* orow = og + (slab_q + q_row) * D;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    s4h w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = (_Float16)(o[dt][4 * c + e] * inv);
-                    *(s4h*)(orow + dt * 32 + 8 * c + 4 * g) = w;
-                }
-        }
+        store_rows<D>(og + (slab_q + row0) * D, Nq - row0, lane, true, [&](int dt, int r) { return o[dt][r] * inv; });
     }
 }
 
