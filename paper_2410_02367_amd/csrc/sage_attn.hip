@@ -237,7 +237,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const _Float16* __restrict__ vg, _Float16* __restrict__ og,
                  int32_t* __restrict__ sdump, float* __restrict__ lse, unsigned long long* __restrict__ clocks,
                  int Nq, int Nkv, int shift_q, int shift_k, int tiles_q, int per_xcd, long total_tiles,
-                 int BH, int n_splits, int chunk, int tm_group,
+                 int BH, int n_splits, int chunk, CausalOrder order,
                  const _Float16* __restrict__ qf, float sm_scale) {
     constexpr int NWAVES = NW, NTHREADS = NW * 64;
     constexpr int QTILE = NW * WROWS;   // query rows per workgroup
@@ -257,22 +257,17 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * KB + 2 * VB + KSL + NW * 4];      // NW floats: QueryRows
 
     // Workgroup -> (slab, query tile).  Consecutive workgroup ids land on the 8 XCDs in turn; give
-    // each XCD a contiguous range of the (slab-major, heaviest-query-tile-first) order so that the
-    // workgroups resident on one XCD share K^/V in its L2.
+    // each XCD a contiguous range of the slab-major order so that the workgroups resident on one XCD share
+    // K^/V in its L2.  With a causal mask the tiles differ in weight by up to tiles_q : 1: see causal_item().
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const long gidx = (long)xcd * per_xcd + slot;
-    if (slot >= per_xcd || gidx >= total_tiles) return;
-    int unit = (int)(gidx / tiles_q);                // (slab, key chunk), chunk fastest
-    int qt = tiles_q - 1 - (int)(gidx % tiles_q);
-    // With a causal mask the query tiles of a slab differ in weight by up to tiles_q : 1, and slab-major the
-    // last slab's light tiles fill in behind the other slabs' heavy ones: the tail of the launch is as long
-    // as a heavy tile.  tm_group > 0 (chosen by the launcher, see tile_major_group()): the XCD's range, a
-    // whole number of slabs, is walked in groups of tm_group slabs, tile-major inside a group -- the heaviest
-    // query tile of each of the group's slabs first, the lightest ones last.
-    if (tm_group > 0) {
-        const int gi = slot / (tm_group * tiles_q), r = slot % (tm_group * tiles_q);
-        unit = xcd * (per_xcd / tiles_q) + gi * tm_group + r % tm_group;
-        qt = tiles_q - 1 - r / tm_group;
+    int unit, qt;                                     // (slab, key chunk), chunk fastest; query tile
+    if (order.group > 0) {
+        if (!causal_item(xcd, slot, tiles_q, order, unit, qt)) return;
+    } else {
+        const long gidx = (long)xcd * per_xcd + slot;
+        if (slot >= per_xcd || gidx >= total_tiles) return;
+        unit = (int)(gidx / tiles_q);
+        qt = tiles_q - 1 - (int)(gidx % tiles_q);
     }
     const int bh = unit / n_splits, split = unit - bh * n_splits;
 
@@ -971,19 +966,28 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     }
 }
 
-// Causal launches: how many slabs (units) an XCD interleaves tile-major (0: none, slab-major as without a
-// mask).  Only when every XCD's range is a whole number of units -- otherwise the ranges cut through slabs,
-// which is what balances the XCDs then -- and only as many as keep their K^ and V (unit_bytes each) inside
-// the XCD's 4 MB L2 together: interleaving more trades the shorter tail for re-fetches from HBM (measured at
-// 16K keys, 6 MB per slab: 2.2 x the HBM traffic for 0-4 % of time, depending on the box; at 1.5K keys, where
-// 16 slabs fit, +14 % and no extra traffic).
-int tile_major_group(long total_tiles, int tiles_q, long unit_bytes) {
-    if (total_tiles % (8l * tiles_q) != 0) return 0;
-    const int units_per_xcd = (int)(total_tiles / 8 / tiles_q);
-    const long fit = (4l << 20) / (unit_bytes > 0 ? unit_bytes : 1);
-    int g = (int)(fit < units_per_xcd ? fit : units_per_xcd);
-    while (g > 1 && units_per_xcd % g != 0) --g;
-    return g > 1 ? g : 0;
+// Causal launches: as many units per XCD and pass as keep their K^ and V (unit_bytes each) within 8 MB together, twice
+// the XCD's L2 -- the workgroups of a unit walk its keys at about the same pace, so less than all of it is live --
+// in passes of equal size.  More units per pass make the tail of a launch shorter (it ends on light tiles), more bytes
+// make K^ and V come from memory again.  Measured, us of the attention kernel at 0 (no interleaving) / 4 / 8 / 16 MB:
+// 4x32x1536x128: 94 / 85 / 79 / 78; 2x20x3000x128: 100 / 101 / 84 / 85; 2x32x4096x128: 237 / 227 / 213 / 218;
+// 1x32x16384x128: one unit either way up to 8, 1549 / 1547 / 1547 / 1538.
+CausalOrder causal_order(int units, long unit_bytes) {
+    const long fit = unit_bytes > 0 ? (8l << 20) / unit_bytes : 1;
+    const int per_xcd = (units + 7) / 8;
+    const int most = fit < 1 ? 1 : (fit < per_xcd ? (int)fit : per_xcd);
+    const int group = (per_xcd + (per_xcd + most - 1) / most - 1) / ((per_xcd + most - 1) / most);
+    return {group, units / (8 * group), units % (8 * group)};
+}
+// Items of the XCD that has the most of them.
+int causal_items_per_xcd(const CausalOrder& o, int tiles_q) {
+    int most = 0;
+    for (int x = 0; x < 8 && o.rest > 0; ++x) {
+        int n = tiles_q / 8 * o.rest, first;
+        for (int k = 0; k < tiles_q % 8; ++k) n += causal_share(x, o.rest, ((k & 1) << 2) | (k & 2) | (k >> 2), first);
+        most = n > most ? n : most;
+    }
+    return o.full * o.group * tiles_q + most;
 }
 
 template <int D, int NW>
@@ -994,14 +998,18 @@ static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* ksc
     constexpr int QTILE = NW * WROWS, NTHREADS = NW * 64;
     const int tiles_q = (Nq + QTILE - 1) / QTILE;
     const long total = (long)BH * sp.n_splits * tiles_q;
-    const int per_xcd = (int)((total + 7) / 8);
+    CausalOrder order = {0, 0, 0};
+    int per_xcd = (int)((total + 7) / 8);
+    if (causal && !sdump) {
+        order = causal_order(BH * sp.n_splits, (long)(sp.n_splits > 1 ? sp.chunk : N) * 3 * D);
+        per_xcd = causal_items_per_xcd(order, tiles_q);
+    }
     dim3 grid((unsigned)(per_xcd * 8));
     const int shift_q = __builtin_ctz((unsigned)block_q), shift_k = __builtin_ctz((unsigned)block_k);
     const _Float16* vp = (const _Float16*)v;
     _Float16* op = (_Float16*)o;
     const bool ktok = block_k == 1;
-    const int tm_group = causal && !sdump ? tile_major_group(total, tiles_q, (long)(sp.n_splits > 1 ? sp.chunk : N) * 3 * D) : 0;
-#define SAGE_ARGS q.i8, q.scale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, tm_group, (const _Float16*)q.f16, q.sm_scale
+#define SAGE_ARGS q.i8, q.scale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, order, (const _Float16*)q.f16, q.sm_scale
 #define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
     if (clocks != nullptr) {
         // the measurement build exists for the headline shape only: D = 128, 256-row workgroups, block scales

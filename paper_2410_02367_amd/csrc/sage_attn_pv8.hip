@@ -82,7 +82,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
                      const int8_t* __restrict__ vt, const float* __restrict__ vsc,
                      _Float16* __restrict__ og, float* __restrict__ lse,
                      int Nq, int Nkv, int Np, int shift_q, int shift_k, int tiles_q, int per_xcd, long total_tiles,
-                     int BH, int n_splits, int chunk, int tm_group,
+                     int BH, int n_splits, int chunk, CausalOrder order,
                      const _Float16* __restrict__ qf, float sm_scale) {
     constexpr int NT = 256, QTILE = 128, KT = 64;
     constexpr int KS = D / 32, DT = D / 32;
@@ -101,17 +101,16 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     constexpr int QOFF = 3 * (KB + VB) + 3 * KSL;
     __shared__ __attribute__((aligned(16))) unsigned char lds[QOFF + QB + 16];        // 4 floats: QueryRows
 
-    // workgroup -> (slab, query tile): contiguous ranges per XCD, heaviest query tiles first
+    // workgroup -> (slab, query tile): contiguous ranges per XCD, or heaviest tiles first (see causal_item())
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const long gidx = (long)xcd * per_xcd + slot;
-    if (slot >= per_xcd || gidx >= total_tiles) return;
-    int unit = (int)(gidx / tiles_q);                // (slab, key chunk), chunk fastest
-    int qt = tiles_q - 1 - (int)(gidx % tiles_q);
-    // causal launches: groups of tm_group slabs walked tile-major, heaviest query tiles first (see sage_attn.hip)
-    if (tm_group > 0) {
-        const int gi = slot / (tm_group * tiles_q), r = slot % (tm_group * tiles_q);
-        unit = xcd * (per_xcd / tiles_q) + gi * tm_group + r % tm_group;
-        qt = tiles_q - 1 - r / tm_group;
+    int unit, qt;                                     // (slab, key chunk), chunk fastest; query tile
+    if (CAUSAL) {
+        if (!causal_item(xcd, slot, tiles_q, order, unit, qt)) return;
+    } else {
+        const long gidx = (long)xcd * per_xcd + slot;
+        if (slot >= per_xcd || gidx >= total_tiles) return;
+        unit = (int)(gidx / tiles_q);
+        qt = tiles_q - 1 - (int)(gidx % tiles_q);
     }
     const int bh = SPLIT ? unit / n_splits : unit, split = SPLIT ? unit - bh * n_splits : 0;
 
@@ -427,12 +426,16 @@ static hipError_t launch_pv8_d(const Queries& q, const int8_t* kq, const float* 
                                int shift_q, int shift_k, bool ktok, const SplitPlan& sp, hipStream_t st) {
     const int tiles_q = (Nq + 127) / 128, Np = 64 * ((N + 63) / 64);
     const long total = (long)BH * sp.n_splits * tiles_q;
-    const int per_xcd = (int)((total + 7) / 8);
+    CausalOrder order = {0, 0, 0};
+    int per_xcd = (int)((total + 7) / 8);
+    if (causal) {
+        order = causal_order(BH * sp.n_splits, (long)(sp.n_splits > 1 ? sp.chunk : N) * 2 * D);
+        per_xcd = causal_items_per_xcd(order, tiles_q);
+    }
     const dim3 grid((unsigned)(per_xcd * 8)), block(256);
-    const int tm_group = causal ? tile_major_group(total, tiles_q, (long)(sp.n_splits > 1 ? sp.chunk : N) * 2 * D) : 0;
 #define SAGE_PV8_S(C, K, S) sage_attn_pv8_kernel<D, C, K, S><<<grid, block, 0, st>>>( \
         q.i8, q.scale, kq, kscale, vt, vscale, (_Float16*)o, sp.lse, Nq, N, Np, shift_q, shift_k, tiles_q, per_xcd, total, \
-        BH, sp.n_splits, sp.chunk, tm_group, (const _Float16*)q.f16, q.sm_scale)
+        BH, sp.n_splits, sp.chunk, order, (const _Float16*)q.f16, q.sm_scale)
 #define SAGE_PV8(C, K) do { if (sp.n_splits > 1) SAGE_PV8_S(C, K, true); else SAGE_PV8_S(C, K, false); } while (0)
     if (causal) { if (ktok) SAGE_PV8(true, true); else SAGE_PV8(true, false); }
     else        { if (ktok) SAGE_PV8(false, true); else SAGE_PV8(false, false); }

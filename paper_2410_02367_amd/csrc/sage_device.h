@@ -18,6 +18,45 @@ __device__ __forceinline__ unsigned quantize4(float x0, float x1, float x2, floa
     return lo | hi;
 }
 
+// Causal launches: item `slot` of an XCD -> (unit, query tile).  A unit is a (batch, head) slab or a key chunk of one; a
+// tile's weight grows with qt, so the order is heaviest tile first over `group` units of the XCD at a time (one pass),
+// whose K^ and V the WGs on the XCD then walk together; see causal_order().  Units left over after the passes of 8 *
+// group are shared by all XCDs: with U of them, query tile number r (from the heaviest) of unit s goes to XCD
+// (8 s + e) / U, where e runs through 0 .. 7 as r does, in bit-reversed order -- every XCD gets U / 8 of the tiles of every
+// weight, and a unit's tiles stay on as few XCDs as that allows.  Returns false where the XCD has no such item.
+struct CausalOrder {
+    int group, full, rest;      // units per XCD and pass; passes; units left over
+};
+__host__ __device__ __forceinline__ int causal_share(int xcd, int rest, int e, int& first) {
+    const int lo = xcd * rest - e, hi = lo + rest;         // units s with lo <= 8 s < hi
+    first = (lo + 7) >> 3;
+    return ((hi + 7) >> 3) - first;
+}
+__device__ __forceinline__ bool causal_item(int xcd, int slot, int tiles_q, const CausalOrder& o, int& unit, int& qt) {
+    const int pass_items = o.group * tiles_q;
+    const int pass = slot / pass_items;
+    if (pass < o.full) {
+        const int i = slot - pass * pass_items, r = i / o.group;
+        unit = (pass * 8 + xcd) * o.group + (i - r * o.group);
+        qt = tiles_q - 1 - r;
+        return true;
+    }
+    if (o.rest == 0) return false;
+    const int i = slot - o.full * pass_items, block = i / o.rest;
+    int at = i - block * o.rest, r = 8 * block;
+    for (int k = 0; k < 8; ++k, ++r) {
+        int first;
+        const int n = causal_share(xcd, o.rest, ((k & 1) << 2) | (k & 2) | (k >> 2), first);
+        if (at < n) {
+            unit = o.full * 8 * o.group + first + at;
+            qt = tiles_q - 1 - r;
+            return qt >= 0;
+        }
+        at -= n;
+    }
+    return false;
+}
+
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 // The fp16 rows of a wavefront's 32 queries quantized where they are used (Section 4.6: the quantizer fused

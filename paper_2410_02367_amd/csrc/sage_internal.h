@@ -57,8 +57,10 @@ struct SplitPlan {
     int chunk;
     float* lse;
 };
-// slabs an XCD interleaves tile-major in a causal launch (0: none); see sage_attn.hip
-int tile_major_group(long total_tiles, int tiles_q, long unit_bytes);
+// the order of a causal launch's work on the XCDs; see sage_device.h and sage_attn.hip
+struct CausalOrder;
+CausalOrder causal_order(int units, long unit_bytes);
+int causal_items_per_xcd(const CausalOrder& o, int tiles_q);
 SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested);
 hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* kscale,
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
