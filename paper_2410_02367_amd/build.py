@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsage.so")
 SOURCES = ["sage_api.hip", "sage_prepass.hip", "sage_prepass_v.hip", "sage_attn.hip", "sage_attn_pv8.hip",
-           "sage_short.hip", "sage_microbench.hip"]
+           "sage_decode.hip", "sage_short.hip", "sage_microbench.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -266,7 +266,7 @@ def verify_attention_isa(extra=()) -> None:
     with tempfile.TemporaryDirectory() as tmp:
         for src, check in (("sage_attn.hip", check_attention_asm), ("sage_attn_pv8.hip", check_pv8_asm),
                            ("sage_prepass.hip", check_no_spills), ("sage_prepass_v.hip", check_no_spills),
-                           ("sage_short.hip", check_no_spills)):
+                           ("sage_short.hip", check_no_spills), ("sage_decode.hip", check_no_spills)):
             out = os.path.join(tmp, src + ".s")
             cmd = [hipcc(), *flags, *extra, "-S", "--cuda-device-only", "-o", out, os.path.join(CSRC, src)]
             res = subprocess.run(cmd, capture_output=True, text=True)

@@ -836,8 +836,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // per element, 1 read again) is saved.
     if (!DUMP && QS == 1 && qf != nullptr) {
         QueryRows<KS> rows;
-        const int q_row = qrow0 + ql;
-        rows.fetch(qf + (slab_q + q_row) * D, g, q_row < Nq);
+        const int q_row = qrow0 + ql < Nq ? qrow0 + ql : Nq - 1;
+        rows.fetch(qf + (slab_q + q_row) * D, g);
         const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
         const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
         dq[0] = amax / 127.0f * LOG2E;
@@ -848,17 +848,11 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     } else {
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
-            const int q_row = qrow0 + 32 * qs + ql;
+            // (lanes past the last row repeat it: their results are not stored)
+            const int q_row = qrow0 + 32 * qs + ql < Nq ? qrow0 + 32 * qs + ql : Nq - 1;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                qreg[qs][ks] = (v4i){0, 0, 0, 0};
-                if (q_row < Nq) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
-            }
-            dq[qs] = 0.0f;
-            if (!DUMP) {
-                const int rc = q_row < Nq ? q_row : Nq - 1;           // the lane's own query: any block_q down to 1
-                dq[qs] = qsc[(size_t)bh * nbq + (rc >> shift_q)] * LOG2E;
-            }
+            for (int ks = 0; ks < KS; ++ks) qreg[qs][ks] = *(const v4i*)(qi + (slab_q + q_row) * D + ks * 32 + g * 16);
+            dq[qs] = DUMP ? 0.0f : qsc[(size_t)bh * nbq + (q_row >> shift_q)] * LOG2E;       // any block_q down to 1
         }
     }
 #pragma unroll
@@ -1067,6 +1061,7 @@ hipError_t launch_attn(const Queries& q, const int8_t* kq, const float* kscale,
                        const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int D, int causal,
                        int block_q, int block_k, hipStream_t st, int wg_rows) {
     const SplitPlan whole = {1, 0, nullptr};
+    if (!sdump && decode_fits(Nq)) return launch_decode(q, kq, kscale, v, o, BH, Nq, N, D, causal, block_q, block_k, whole, st);
     if (D == 64) return launch_d<64>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
     return launch_d<128>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
 }
@@ -1087,11 +1082,12 @@ hipError_t launch_attn_clocks(const Queries& q, const int8_t* kq, const float* k
 // which is the attention over all keys: w_s is the chunk's share of the softmax denominator.
 SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested) {
     if (requested <= 0) {
-        // One 128-row workgroup per CU (measured: 256 to 512 workgroups are the fastest at every
-        // shape tried; the launch is memory-bound from there on, and more chunks only add partial
-        // results to write and merge); chunks of at least 8 key tiles.
+        // With one query tile per slab (at most 128 rows) the launch is bound by memory: one 128-row workgroup per CU; more
+        // chunks only add partial results to write and merge.  With more rows it is bound by the matrix pipe, which
+        // wants two workgroups on every CU, and no more: 32 slabs of 512 rows against 16K keys, us at 2 / 4 / 6 / 8
+        // chunks: 129 / 115 / 123 / 122; of 256 rows at 4 / 8 / 12: 74 / 68 / 76.  Chunks of at least 8 key tiles.
         const long wg = (long)BH * ((Nq + 127) / 128);
-        long want = (256 + wg - 1) / wg;
+        const long want = Nq <= 128 ? (256 + wg - 1) / wg : 512 / wg;
         const long most = N / 512 < 64 ? N / 512 : 64;
         requested = (int)(want < most ? want : most);
     }
@@ -1113,40 +1109,6 @@ SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested) {
     return {n, chunk, nullptr};
 }
 
-template <int D>
-__global__ void __launch_bounds__(256) merge_splits_kernel(const _Float16* __restrict__ part, const float* __restrict__ lse,
-                                                           _Float16* __restrict__ og, long rows, int n_splits) {
-    constexpr int TPR = D / 8;                         // threads per row, 8 channels each
-    const long row = (long)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
-    const int c8 = threadIdx.x % TPR;
-    if (row >= rows) return;
-    float top = -__builtin_inff();
-    for (int s = 0; s < n_splits; ++s) top = __builtin_fmaxf(top, lse[(size_t)s * rows + row]);
-    float acc[8], wsum = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-    for (int s = 0; s < n_splits; ++s) {
-        const float w = __builtin_amdgcn_exp2f(lse[(size_t)s * rows + row] - top);
-        const v8h x = *(const v8h*)(part + ((size_t)s * rows + row) * D + c8 * 8);
-        wsum += w;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = __builtin_fmaf(w, (float)x[e], acc[e]);
-    }
-    const float inv = 1.0f / wsum;
-    v8h y;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = (_Float16)(acc[e] * inv);
-    *(v8h*)(og + (size_t)row * D + c8 * 8) = y;
-}
-
-hipError_t launch_merge_splits(const void* part, const float* lse, void* o, long rows, int D, int n_splits, hipStream_t st) {
-    const _Float16* pp = (const _Float16*)part;
-    _Float16* op = (_Float16*)o;
-    if (D == 64) merge_splits_kernel<64><<<(unsigned)((rows + 31) / 32), 256, 0, st>>>(pp, lse, op, rows, n_splits);
-    else merge_splits_kernel<128><<<(unsigned)((rows + 15) / 16), 256, 0, st>>>(pp, lse, op, rows, n_splits);
-    return hipGetLastError();
-}
-
 hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* kscale,
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
                              int block_q, int block_k, int requested, hipStream_t st) {
@@ -1156,7 +1118,9 @@ hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* ks
     // workspace: partial O [n_splits, BH, Nq, D] fp16, then lse [n_splits, BH, Nq] fp32
     _Float16* part = (_Float16*)workspace;
     sp.lse = (float*)((char*)workspace + (size_t)sp.n_splits * rows * D * sizeof(_Float16));
-    hipError_t e = D == 64
+    hipError_t e = decode_fits(Nq)
+        ? launch_decode(q, kq, kscale, v, part, BH, Nq, N, D, causal, block_q, block_k, sp, st)
+        : D == 64
         ? launch_d<64>(q, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st)
         : launch_d<128>(q, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
     if (e != hipSuccess) return e;

@@ -138,7 +138,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     if (qf != nullptr) {
         // fp16 rows, quantized here: steps below QREG to registers, the others to the wavefront's own rows of the LDS copy
         QueryRows<KS> rows;
-        rows.fetch(qf + (slab_q + q_row) * D, h, q_row < Nq);
+        rows.fetch(qf + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D, h);
         const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + QOFF + QB));
         const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
         dq = amax / 127.0f * PV8_LOG2E;
@@ -152,10 +152,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         }
     } else {
 #pragma unroll
-        for (int ks = 0; ks < QREG; ++ks) {
-            qreg[ks] = (p4i){0, 0, 0, 0};
-            if (q_row < Nq) qreg[ks] = *(const p4i*)(qi + (slab_q + q_row) * D + ks * 32 + h * 16);
-        }
+        for (int ks = 0; ks < QREG; ++ks) qreg[ks] = *(const p4i*)(qi + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D + ks * 32 + h * 16);
         dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
     }
     const float* __restrict__ ksc_bh = ksc + (size_t)bh * nbk + (k0 >> shift_k);

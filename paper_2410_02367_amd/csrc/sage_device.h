@@ -67,14 +67,14 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 template <int KS>
 struct QueryRows {
     half8 raw[KS][2];
-    __device__ __forceinline__ void fetch(const _Float16* row, int half, bool live) {
+    // row: the lane's row; lanes past the last row fetch that row again, which changes no maximum they share with a
+    // row that exists (a condition around the loads would make them wait for each other)
+    __device__ __forceinline__ void fetch(const _Float16* row, int half) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                raw[ks][j] = (half8){0, 0, 0, 0, 0, 0, 0, 0};
-                if (live) raw[ks][j] = *(const half8*)(row + 32 * ks + 16 * half + 8 * j);
-            }
+            for (int j = 0; j < 2; ++j) raw[ks][j] = *(const half8*)(row + 32 * ks + 16 * half + 8 * j);
+        __builtin_amdgcn_sched_barrier(0);
     }
     // largest |x * sm_scale| of the lane's quantization block; every wavefront of the workgroup calls it.
     // red: one float of LDS per wavefront, not used for anything else before the next barrier.

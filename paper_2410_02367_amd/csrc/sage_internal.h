@@ -66,6 +66,11 @@ hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* ks
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
                              int block_q, int block_k, int requested, hipStream_t st);
 
+// The same for at most 32 query rows per slab (sage_decode.hip): sp.lse == nullptr writes o, else partial results
+bool decode_fits(int Nq);
+hipError_t launch_decode(const Queries& q, const int8_t* kq, const float* kscale, const void* v, void* o, int BH, int Nq, int N,
+                         int D, int causal, int block_q, int block_k, const SplitPlan& sp, hipStream_t st);
+
 hipError_t launch_merge_splits(const void* part, const float* lse, void* o, long rows, int D, int n_splits, hipStream_t st);
 hipError_t launch_attn_pv8_split(const Queries& q, const int8_t* kq, const float* kscale,
                                  const int8_t* vt, const float* vscale, void* o, void* workspace, int BH, int Nq, int N,

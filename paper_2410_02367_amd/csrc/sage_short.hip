@@ -127,7 +127,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     QueryRows<KS> rows;
     {
         const int row = (part * NW + wave) * 32 + ql;
-        rows.fetch(qf + (slab_q + row) * D, g, row < Nq);
+        rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
     }
 
     // ---- exact column sums (fp64: multiples of 2^-24 below 2^25), folded over the wavefront's rows
@@ -259,7 +259,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
             for (int i = 0; i < 4; ++i) q[ks][i] = (int)rows.word(ks, i, sm_scale, qrcp);
         if ((set + groups) * NW < rtiles) {          // the next rows are requested before this tile's loop
             const int row = ((set + groups) * NW + wave) * 32 + ql;
-            rows.fetch(qf + (slab_q + row) * D, g, row < Nq);
+            rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
         }
         if (row0 >= Nq) continue;
 
