@@ -1016,20 +1016,18 @@ static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* ksc
             return hipErrorInvalidValue;
         }
     }
-    // per-token key scales need a few more registers than 4-wavefront workgroups at D = 128 have
-    // (two workgroups per CU: 128 + 128 registers); launch_d() never asks for that combination
-    constexpr bool KTOK_OK = !(D == 128 && NW == 4);
-    if (sdump) SAGE_LAUNCH(false, true, false);
-    else if (ktok) {
-        if constexpr (KTOK_OK) {
+    if (sdump) { SAGE_LAUNCH(false, true, false); return hipGetLastError(); }
+    // (D = 64 comes in 128-row workgroups only; the score dump is built in both shapes of either head dimension)
+    if constexpr (D == 64 && NW == 8) {
+        return hipErrorInvalidValue;
+    } else {
+        if (ktok) {
             if (causal) SAGE_LAUNCH(true, false, true);
             else SAGE_LAUNCH(false, false, true);
-        } else {
-            return hipErrorInvalidValue;
         }
+        else if (causal) SAGE_LAUNCH(true, false, false);
+        else SAGE_LAUNCH(false, false, false);
     }
-    else if (causal) SAGE_LAUNCH(true, false, false);
-    else SAGE_LAUNCH(false, false, false);
 #undef SAGE_LAUNCH
 #undef SAGE_ARGS
     return hipGetLastError();
@@ -1041,15 +1039,17 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
                            int block_q, int block_k, const SplitPlan& sp, hipStream_t st, int wg_rows = 0,
                            unsigned long long* clocks = nullptr) {
     // 256-row workgroups (8 wavefronts sharing one set of LDS tiles) for long sequences at D = 128;
-    // 128-row workgroups, two or three per CU, for D = 64, whenever the larger tile would leave CUs
-    // without work (fewer than two workgroups per CU), and for short sequences, where a workgroup
-    // visits few tiles and the finer causal staircase and the independent progress of the small
-    // workgroups matter more than the sharing (measured at D = 128: +30 % at N = 1K causal, +11 %
-    // non-causal; +19 % / +2 % at 2K; +4 % / -3 % at 4K).
+    // 128-row workgroups, two or three per CU, for D = 64, for short sequences, where a workgroup visits few tiles and
+    // the finer causal staircase and the independent progress of the small workgroups matter more than the sharing (at
+    // D = 128: 1536 keys causal 80 us instead of 91; equal from 4K causal and 1K non-causal on), and where a launch of
+    // the larger ones would end on a round that leaves many CUs idle: 30 slabs of 3000 rows are 1.4 rounds, 115 us
+    // with small workgroups instead of 132.  (A causal launch fills its tail with light tiles: only below two rounds.)
     const long big_tiles = (long)BH * sp.n_splits * ((Nq + 8 * WROWS - 1) / (8 * WROWS));
+    const long rounds = (big_tiles + 255) / 256;
     const int n_seen = sp.n_splits > 1 ? sp.chunk : N;           // keys a workgroup walks
     const bool short_seq = n_seen <= 2048 || (causal && n_seen <= 4096);
-    bool small = QS == 1 && (D == 64 || ((big_tiles < 2 * 256 || short_seq) && block_k != 1 && !sdump));
+    const bool idle_cus = big_tiles < 2 * 256 || (!causal && 10 * big_tiles < 9 * 256 * rounds);
+    bool small = QS == 1 && (D == 64 || ((idle_cus || short_seq) && !sdump));
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only
