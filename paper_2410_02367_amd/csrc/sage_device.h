@@ -18,6 +18,21 @@ __device__ __forceinline__ unsigned quantize4(float x0, float x1, float x2, floa
     return lo | hi;
 }
 
+// x + the value of the lane 32 (16) away, of two values at once: lanes of the lower half (even rows of 16) end with
+// the sum of a, the others with the sum of b
+__device__ __forceinline__ double fold32(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    auto lo = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
+}
+
 // Causal launches: item `slot` of an XCD -> (unit, query tile).  A unit is a (batch, head) slab or a key chunk of one; a
 // tile's weight grows with qt, so the order is heaviest tile first over `group` units of the XCD at a time (one pass),
 // whose K^ and V the WGs on the XCD then walk together; see causal_order().  Units left over after the passes of 8 *

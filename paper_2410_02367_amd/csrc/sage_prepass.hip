@@ -13,61 +13,83 @@
 // The K side is two launches: partial column sums per chunk of tokens, then the quantizer, whose
 // workgroups add the partial sums of their slab (no clearing pass, no atomics).
 #include "sage_internal.h"
-#include <hip/hip_fp16.h>
+#include "sage_device.h"
 
 namespace sage {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef half8 h8;
 
-// The 8 channels 8*c8 .. 8*c8+7 of one token row (fp16 [D]).  With ROPE the row passes through the
+// What a thread owns of a token row (fp16 [D]): without RoPE the 8 channels 8*c8 .. 8*c8+7, c8 < D/8; with ROPE the 8
+// channels 8*c8 .., c8 < D/16, and their partners D/2 further on.  With ROPE the row passes through the
 // rotary embedding first (Section 4.6: the quantizer is fused into the operator that produces Q
 // and K): channel c < D/2 is paired with c + D/2,
 //     y[c] = x[c] cos[c] - x[c+D/2] sin[c],    y[c+D/2] = x[c+D/2] cos[c] + x[c] sin[c],
 // every product and the sum rounded to fp32, y rounded to fp16 -- the tensor an unfused RoPE kernel
 // would have stored, so that the fused pre-pass returns exactly what the unfused one returns.
-// cos_row / sin_row point at the D/2 fp32 table entries of the token's position.  The partner
-// chunk is a second 16-byte load from the same cache line(s).
-// The loads and the arithmetic are separate steps (fetch_row8 / finish_row8), so that a kernel can have
+// cos_row / sin_row point at the D/2 fp32 table entries of the token's position.  Owning both halves of a pair
+// makes a row two loads of data and four of table per 16 channels (each half by itself: per 8 channels, and the
+// tables, which come from the L2, were two thirds of what a kernel read: 1.5 times the time at 33 million elements).
+// The loads and the arithmetic are separate steps (fetch_row / finish_row), so that a kernel can have
 // the loads of several rows in flight before it rotates the first one.
+template <bool ROPE> constexpr int CHUNKS_OWNED = ROPE ? 2 : 1;
+template <bool ROPE> struct Row { h8 x[CHUNKS_OWNED<ROPE>]; };
 template <bool ROPE> struct RowRaw;
 template <> struct RowRaw<false> { h8 own; };
 template <> struct RowRaw<true> { h8 own, partner; float4 c0, c1, s0, s1; };
+// first channel of chunk j of the thread
+template <int D> __device__ __forceinline__ int channel(int c8, int j) { return c8 * 8 + j * (D / 2); }
 
 template <int D, bool ROPE>
-__device__ __forceinline__ RowRaw<ROPE> fetch_row8(const _Float16* __restrict__ row, int c8,
-                                                   const float* __restrict__ cos_row, const float* __restrict__ sin_row) {
+__device__ __forceinline__ RowRaw<ROPE> fetch_row(const _Float16* __restrict__ row, int c8,
+                                                  const float* __restrict__ cos_row, const float* __restrict__ sin_row) {
     RowRaw<ROPE> r;
     r.own = *(const h8*)(row + c8 * 8);
     if constexpr (ROPE) {
-        constexpr int HALF = D / 2;
-        const int c = c8 * 8;
-        const bool upper = c >= HALF;
-        const int cp = upper ? c - HALF : c + HALF, ct = upper ? c - HALF : c;
-        r.partner = *(const h8*)(row + cp);
-        r.c0 = *(const float4*)(cos_row + ct); r.c1 = *(const float4*)(cos_row + ct + 4);
-        r.s0 = *(const float4*)(sin_row + ct); r.s1 = *(const float4*)(sin_row + ct + 4);
+        r.partner = *(const h8*)(row + channel<D>(c8, 1));
+        r.c0 = *(const float4*)(cos_row + c8 * 8); r.c1 = *(const float4*)(cos_row + c8 * 8 + 4);
+        r.s0 = *(const float4*)(sin_row + c8 * 8); r.s1 = *(const float4*)(sin_row + c8 * 8 + 4);
     }
     return r;
 }
-template <int D, bool ROPE>
-__device__ __forceinline__ h8 finish_row8(const RowRaw<ROPE>& r, int c8) {
+template <bool ROPE>
+__device__ __forceinline__ Row<ROPE> finish_row(const RowRaw<ROPE>& r) {
+    Row<ROPE> y;
     if constexpr (!ROPE) {
-        return r.own;
+        y.x[0] = r.own;
     } else {
-        const bool upper = c8 * 8 >= D / 2;
         const float cs[8] = {r.c0.x, r.c0.y, r.c0.z, r.c0.w, r.c1.x, r.c1.y, r.c1.z, r.c1.w};
         const float sn[8] = {r.s0.x, r.s0.y, r.s0.z, r.s0.w, r.s1.x, r.s1.y, r.s1.z, r.s1.w};
-        h8 y;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float oc = (float)r.own[e] * cs[e], ps = (float)r.partner[e] * sn[e];
-            y[e] = (_Float16)(upper ? oc + ps : oc - ps);
+            const float a = (float)r.own[e], b = (float)r.partner[e];
+            y.x[0][e] = (_Float16)(a * cs[e] - b * sn[e]);
+            y.x[1][e] = (_Float16)(b * cs[e] + a * sn[e]);
         }
-        return y;
     }
+    return y;
 }
 // rows in flight per thread where a kernel batches them: a fetched row is 4 registers, 24 with RoPE
-template <bool ROPE> constexpr int rows_in_flight(int plain) { return ROPE ? (plain < 4 ? plain : 4) : plain; }
+template <bool ROPE> constexpr int rows_in_flight(int plain) { return ROPE ? (plain < 2 ? plain : 2) : plain; }
+// 8 codes of a chunk, from x - mean (K; mean: 8 values) or x * sm_scale (Q): one fp32 rounding (the FMAs take the fp16
+// operand as it is), then Section 3.2's quantizer
+template <bool IS_K>
+__device__ __forceinline__ float scaled(_Float16 x, float mean_e, float sm_scale) {
+    return IS_K ? __builtin_fmaf((float)x, 1.0f, -mean_e) : __builtin_fmaf((float)x, sm_scale, 0.0f);
+}
+template <bool IS_K>
+__device__ __forceinline__ uint2 codes8(const h8& x, const float* mean, float sm_scale, float rcp) {
+    float f[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = scaled<IS_K>(x[e], IS_K ? mean[e] : 0.0f, sm_scale);
+    return make_uint2(quantize4(f[0], f[1], f[2], f[3], rcp), quantize4(f[4], f[5], f[6], f[7], rcp));
+}
+template <bool IS_K>
+__device__ __forceinline__ float amax8(const h8& x, const float* mean, float sm_scale) {
+    float m = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(scaled<IS_K>(x[e], IS_K ? mean[e] : 0.0f, sm_scale)));
+    return m;
+}
 
 // Exact column sums, first level: the workgroup (chunk p, slab bh) of grid (P, BH) sums the rows
 // p * chunk .. of its slab and leaves the D sums as 64-bit integers at part[(bh * P + p) * D ..];
@@ -83,7 +105,8 @@ __device__ __forceinline__ void k_colsum_body(const _Float16* __restrict__ k,
                                               long long* __restrict__ part_out, int N, int chunk,
                                               const float* __restrict__ cs, const float* __restrict__ sn,
                                               int bx, int P, int bh) {
-    constexpr int VPR = D / 8;          // 16-byte vectors per token row
+    constexpr int CH = CHUNKS_OWNED<ROPE>;
+    constexpr int VPR = D / 8 / CH;     // threads per token row
     constexpr int RG = NT / VPR;        // row groups per workgroup
     constexpr int BATCH = rows_in_flight<ROPE>(8);      // rows per thread in flight
     const int t = threadIdx.x, c8 = t % VPR, rg = t / VPR;
@@ -97,9 +120,11 @@ __device__ __forceinline__ void k_colsum_body(const _Float16* __restrict__ k,
     // instructions per element (two conversions, one addition) instead of eight for an integer split,
     // which is what lets this kernel run at the memory rate.
     static_assert(RG >= 16, "at most 2^13 rows per thread in a chunk of 2^17");
-    double acc_d[8];
+    double acc_d[CH][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc_d[e] = 0.0;
+    for (int j = 0; j < CH; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc_d[j][e] = 0.0;
     // whole batches first (no row needs a check: every chunk but a slab's last is whole batches), then
     // at most one ragged batch whose rows past the end are fetched from the last row and not added
     const int whole = row_begin + (row_end - row_begin) / (BATCH * RG) * (BATCH * RG);
@@ -108,16 +133,18 @@ __device__ __forceinline__ void k_colsum_body(const _Float16* __restrict__ k,
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             const int r = r0 + i * RG;
-            xr[i] = fetch_row8<D, ROPE>(base + (size_t)r * D, c8, cs + (size_t)r * (D / 2), sn + (size_t)r * (D / 2));
+            xr[i] = fetch_row<D, ROPE>(base + (size_t)r * D, c8, cs + (size_t)r * (D / 2), sn + (size_t)r * (D / 2));
         }
         // every load of the batch is issued before the first is used: without this fence the compiler's
         // scheduler sinks each load to its use -- one load in flight instead of eight, a third slower
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
-            const h8 x = finish_row8<D, ROPE>(xr[i], c8);
+            const Row<ROPE> row = finish_row<ROPE>(xr[i]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc_d[e] += (double)(float)x[e];
+            for (int j = 0; j < CH; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc_d[j][e] += (double)(float)row.x[j][e];
         }
     }
     if (whole < row_end) {
@@ -126,33 +153,34 @@ __device__ __forceinline__ void k_colsum_body(const _Float16* __restrict__ k,
         for (int i = 0; i < BATCH; ++i) {
             const int r = whole + rg + i * RG;
             const int rc = r < row_end ? r : row_end - 1;
-            xr[i] = fetch_row8<D, ROPE>(base + (size_t)rc * D, c8, cs + (size_t)rc * (D / 2), sn + (size_t)rc * (D / 2));
+            xr[i] = fetch_row<D, ROPE>(base + (size_t)rc * D, c8, cs + (size_t)rc * (D / 2), sn + (size_t)rc * (D / 2));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             const double live = whole + rg + i * RG < row_end ? 1.0 : 0.0;
-            const h8 x = finish_row8<D, ROPE>(xr[i], c8);
+            const Row<ROPE> row = finish_row<ROPE>(xr[i]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc_d[e] += live * (double)(float)x[e];
+            for (int j = 0; j < CH; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc_d[j][e] += live * (double)(float)row.x[j][e];
         }
     }
     // exact conversion to a count of 2^-24 units: |v| < 2^53 is split into a 27-bit and a 26-bit part
-    long long acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const double v = acc_d[e] * 16777216.0;
-        const double hi = __builtin_trunc(v * 0x1p-26);
-        const double lo = v - hi * 0x1p26;
-        acc[e] = (long long)(int)hi * (1ll << 26) + (long long)(int)lo;
-    }
     __shared__ long long part[RG][D];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[rg][c8 * 8 + e] = acc[e];
+    for (int j = 0; j < CH; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double v = acc_d[j][e] * 16777216.0;
+            const double hi = __builtin_trunc(v * 0x1p-26);
+            const double lo = v - hi * 0x1p26;
+            part[rg][channel<D>(c8, j) + e] = (long long)(int)hi * (1ll << 26) + (long long)(int)lo;
+        }
     __syncthreads();
     if (t < D) {
         long long s = 0;
-#pragma unroll 4
+#pragma unroll 16
         for (int g = 0; g < RG; ++g) s += part[g][t];
         part_out[((size_t)bh * P + bx) * D + t] = s;
     }
@@ -171,7 +199,7 @@ __device__ __forceinline__ float slab_mean(const long long* __restrict__ parts, 
     if (c >= D) return 0.0f;
     const long long* p = parts + (size_t)bh * P * D + c;
     long long s = 0;
-#pragma unroll 4
+#pragma unroll 8
     for (int i = 0; i < P; ++i) s += p[(size_t)i * D];
     const double avg = (double)s / (double)N;
     return (float)(avg * 0x1p-24);
@@ -204,7 +232,8 @@ __device__ __forceinline__ void quant_block_body(const _Float16* __restrict__ x,
                                                  int N, int block, float sm_scale,
                                                  const float* __restrict__ cs, const float* __restrict__ sn,
                                                  int bx, int gx, int bh) {
-    constexpr int VPR = D / 8;
+    constexpr int CH = CHUNKS_OWNED<ROPE>;
+    constexpr int VPR = D / 8 / CH;
     constexpr int RSTEP = NT / VPR;
     const int t = threadIdx.x, c8 = t % VPR, rbase = t / VPR;
     const int nblk = (N + block - 1) / block;
@@ -220,18 +249,18 @@ __device__ __forceinline__ void quant_block_body(const _Float16* __restrict__ x,
         for (int i = 0; i < LPT; ++i) {
             const int r = rbase + i * RSTEP;
             const int rc = r < rows ? r : rows - 1;
-            dst[i] = fetch_row8<D, ROPE>(xb + (size_t)rc * D, c8, cs + (size_t)(row0 + rc) * (D / 2),
-                                         sn + (size_t)(row0 + rc) * (D / 2));
+            dst[i] = fetch_row<D, ROPE>(xb + (size_t)rc * D, c8, cs + (size_t)(row0 + rc) * (D / 2),
+                                        sn + (size_t)(row0 + rc) * (D / 2));
         }
         __builtin_amdgcn_sched_barrier(0);       // all loads of the block issued here, none sunk to its use
     };
     static_assert(!ROPE || LPT <= 4, "a fetched row is 24 registers with RoPE");
     RowRaw<ROPE> ahead[LPT];       // the loads of the block after the current one (or of the first)
-    h8 raw[LPT];                   // the current block's rows, rotated if ROPE
+    Row<ROPE> raw[LPT];            // the current block's rows, rotated if ROPE
     int g = bx;                    // the launcher never starts more workgroups than there are blocks
     fetch_block(g, ahead);         // in flight while the mean is formed
 
-    float mean[8];
+    float mean[CH][8];
     if (IS_K) {
         if (t < D) {
             const float m = slab_mean<D>(parts, bh, P, N, t);
@@ -240,28 +269,25 @@ __device__ __forceinline__ void quant_block_body(const _Float16* __restrict__ x,
         }
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) mean[e] = s_mean[c8 * 8 + e];
+        for (int j = 0; j < CH; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mean[j][e] = s_mean[channel<D>(c8, j) + e];
     }
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) raw[i] = finish_row8<D, ROPE>(ahead[i], c8);
+    for (int i = 0; i < LPT; ++i) raw[i] = finish_row<ROPE>(ahead[i]);
 
     for (int turn = 0; g < nblk; g += gx, turn ^= 1) {
         const int row0 = g * block;
         const int rows = (N - row0 < block) ? (N - row0) : block;
-        const size_t slab = ((size_t)bh * N + row0) * D + c8 * 8;
+        const size_t slab = ((size_t)bh * N + row0) * D;
         // the next block of this workgroup is requested before this one is reduced and stored
         const bool more = g + gx < nblk;
         if (more) fetch_block(g + gx, ahead);
         float amax = 0.0f;
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
+        for (int i = 0; i < LPT; ++i)       // a clamped row repeats a row of the block: the maximum is unchanged
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {       // a clamped row repeats a row of the block: the maximum is unchanged
-                float f = (float)raw[i][e];
-                f = IS_K ? (f - mean[e]) : (f * sm_scale);
-                amax = __builtin_fmaxf(amax, __builtin_fabsf(f));
-            }
-        }
+            for (int j = 0; j < CH; ++j) amax = __builtin_fmaxf(amax, amax8<IS_K>(raw[i].x[j], mean[j], sm_scale));
         amax = wg_max<NT>(amax, s_red[turn]);       // alternating buffers: one barrier per block is enough
         const float delta = amax / 127.0f;
         const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
@@ -271,21 +297,14 @@ __device__ __forceinline__ void quant_block_body(const _Float16* __restrict__ x,
         for (int i = 0; i < LPT; ++i) {
             const int r = rbase + i * RSTEP;
             if (r < rows) {
-                unsigned w[2] = {0u, 0u};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float f = (float)raw[i][e];
-                    f = IS_K ? (f - mean[e]) : (f * sm_scale);
-                    float q = __builtin_rintf(f * rcp);                 // round half to even
-                    q = __builtin_fminf(__builtin_fmaxf(q, -127.0f), 127.0f);
-                    w[e >> 2] |= ((unsigned)((int)q) & 0xffu) << (8 * (e & 3));
-                }
-                *(uint2*)(xq + slab + (size_t)r * D) = make_uint2(w[0], w[1]);
+                for (int j = 0; j < CH; ++j)
+                    *(uint2*)(xq + slab + (size_t)r * D + channel<D>(c8, j)) = codes8<IS_K>(raw[i].x[j], mean[j], sm_scale, rcp);
             }
         }
         if (more) {
 #pragma unroll
-            for (int i = 0; i < LPT; ++i) raw[i] = finish_row8<D, ROPE>(ahead[i], c8);
+            for (int i = 0; i < LPT; ++i) raw[i] = finish_row<ROPE>(ahead[i]);
         }
     }
 }
@@ -299,12 +318,13 @@ __global__ void __launch_bounds__(NT) quant_block_kernel(const _Float16* __restr
                                              blockIdx.x, gridDim.x, blockIdx.y);
 }
 
-// Per-token quantizer (Section 3.2): one scale per token row.  D/8 adjacent lanes own a row
-// (16 bytes each); the row's absmax is a butterfly over those lanes.  A workgroup takes groups of
+// Per-token quantizer (Section 3.2): one scale per token row.  D/8 (with RoPE D/16) adjacent lanes own a row; the row's absmax is a butterfly over those lanes.  A workgroup takes groups of
 // TOK_ROWS consecutive tokens (group blockIdx.x, blockIdx.x + gridDim.x, ...), TOK_LPT rows per
 // thread, all loads of a group issued before the first use (rows past N fetched from row N - 1 and
 // not stored).
-constexpr int TOK_LPT = 8;
+// rows per thread and group: 8, with RoPE 2 (24 registers each, in flight while the group before is quantized)
+template <bool ROPE> constexpr int TOK_LPT = ROPE ? 2 : 8;
+template <int D, bool ROPE> constexpr int TOK_ROWS = 256 / (D / 8 / CHUNKS_OWNED<ROPE>) * TOK_LPT<ROPE>;
 template <int D, bool IS_K, bool ROPE>
 __device__ __forceinline__ void quant_token_body(const _Float16* __restrict__ x,
                                                  int8_t* __restrict__ xq,
@@ -314,14 +334,27 @@ __device__ __forceinline__ void quant_token_body(const _Float16* __restrict__ x,
                                                  int N, float sm_scale,
                                                  const float* __restrict__ cs, const float* __restrict__ sn,
                                                  int bx, int gx, int bh) {
-    constexpr int VPR = D / 8;
+    constexpr int CH = CHUNKS_OWNED<ROPE>;
+    constexpr int VPR = D / 8 / CH;
     constexpr int RSTEP = 256 / VPR;
-    constexpr int ROWS = RSTEP * TOK_LPT;
+    constexpr int LPT = TOK_LPT<ROPE>, ROWS = TOK_ROWS<D, ROPE>;
     const int t = threadIdx.x, c8 = t % VPR, rbase = t / VPR;
     const int ngrp = (N + ROWS - 1) / ROWS;
 
     __shared__ float s_mean[D];
-    float mean[8];
+    const _Float16* xs = x + (size_t)bh * N * D;
+    RowRaw<ROPE> ahead[LPT];
+    auto fetch_group = [&](int grp) {
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int r = grp * ROWS + rbase + i * RSTEP;
+            const int rc = r < N ? r : N - 1;
+            ahead[i] = fetch_row<D, ROPE>(xs + (size_t)rc * D, c8, cs + (size_t)rc * (D / 2), sn + (size_t)rc * (D / 2));
+        }
+        __builtin_amdgcn_sched_barrier(0);       // all loads of the group issued here, none sunk to its use
+    };
+    fetch_group(bx);               // in flight while the mean is formed
+    float mean[CH][8];
     if (IS_K) {
         if (t < D) {
             const float m = slab_mean<D>(parts, bh, P, N, t);
@@ -330,51 +363,33 @@ __device__ __forceinline__ void quant_token_body(const _Float16* __restrict__ x,
         }
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) mean[e] = s_mean[c8 * 8 + e];
+        for (int j = 0; j < CH; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mean[j][e] = s_mean[channel<D>(c8, j) + e];
     }
 
     for (int grp = bx; grp < ngrp; grp += gx) {
         const int row0 = grp * ROWS;
-        const _Float16* xs = x + (size_t)bh * N * D;
-        constexpr int SUB = rows_in_flight<ROPE>(TOK_LPT);     // rows fetched together
+        Row<ROPE> raw[LPT];
 #pragma unroll
-        for (int i0 = 0; i0 < TOK_LPT; i0 += SUB) {
-        RowRaw<ROPE> fetched[SUB];
+        for (int i = 0; i < LPT; ++i) raw[i] = finish_row<ROPE>(ahead[i]);
+        if (grp + gx < ngrp) fetch_group(grp + gx);       // requested before this group is reduced and stored
 #pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-            const int r = row0 + rbase + (i0 + i) * RSTEP;
-            const int rc = r < N ? r : N - 1;
-            fetched[i] = fetch_row8<D, ROPE>(xs + (size_t)rc * D, c8, cs + (size_t)rc * (D / 2), sn + (size_t)rc * (D / 2));
-        }
-        __builtin_amdgcn_sched_barrier(0);       // all loads of the batch issued here, none sunk to its use
-#pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-            const int r = row0 + rbase + (i0 + i) * RSTEP;
-            const h8 raw = finish_row8<D, ROPE>(fetched[i], c8);
-            float f[8];
+        for (int i = 0; i < LPT; ++i) {
+            const int r = row0 + rbase + i * RSTEP;
             float amax = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                f[e] = (float)raw[e];
-                f[e] = IS_K ? (f[e] - mean[e]) : (f[e] * sm_scale);
-                amax = __builtin_fmaxf(amax, __builtin_fabsf(f[e]));
-            }
+            for (int j = 0; j < CH; ++j) amax = __builtin_fmaxf(amax, amax8<IS_K>(raw[i].x[j], mean[j], sm_scale));
 #pragma unroll
             for (int off = VPR / 2; off >= 1; off >>= 1) amax = __builtin_fmaxf(amax, __shfl_xor(amax, off, 64));
             const float delta = amax / 127.0f;
             const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
             if (r < N) {
                 if (c8 == 0) scale[(size_t)bh * N + r] = delta;
-                unsigned w[2] = {0u, 0u};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float q = __builtin_rintf(f[e] * rcp);                 // round half to even
-                    q = __builtin_fminf(__builtin_fmaxf(q, -127.0f), 127.0f);
-                    w[e >> 2] |= ((unsigned)((int)q) & 0xffu) << (8 * (e & 3));
-                }
-                *(uint2*)(xq + ((size_t)bh * N + r) * D + c8 * 8) = make_uint2(w[0], w[1]);
+                for (int j = 0; j < CH; ++j)
+                    *(uint2*)(xq + ((size_t)bh * N + r) * D + channel<D>(c8, j)) = codes8<IS_K>(raw[i].x[j], mean[j], sm_scale, rcp);
             }
-        }
         }
     }
 }
@@ -389,35 +404,38 @@ __global__ void __launch_bounds__(256) quant_token_kernel(const _Float16* __rest
 
 // Short sequences (N <= SMALL_N): the whole K pre-pass of one (batch, head) slab in ONE workgroup
 // and one launch.  The slab is read ONCE, all loads in flight together, and stays in registers
-// (at most SMALL_N / RG rows of 16 bytes per thread): exact column sums, mean, per-block (or
-// per-token) maxima and the quantization all work on those registers -- one memory round trip, two
-// barriers.  The results are the same bits as the wide kernels' (the integer sum does not depend on
-// how it is split).  Beyond a few blocks per slab one workgroup per slab loses against the wide
-// launches (measured: faster at N = 197, slower at N = 1105), hence the low limit.
+// (at most SMALL_N / RG rows per thread) for the exact column sums, the mean, the block (or token) maxima and the codes --
+// one memory round trip, four barriers.  The results are the same bits as the wide kernels' (exact sums do not depend on
+// how they are split).  It is all latency, so a slab gets NT = 1024 threads and the column sums are folded inside
+// the wavefronts by register swaps (with 256 threads and a column of 16 partial sums per thread in LDS: 14 us at 300
+// keys of 128 channels, 8.6 at 256 of 64).
 constexpr int SMALL_N = 512;
-template <int D, bool ROPE>
+constexpr int SMALL_NT = 1024;
+template <int D, bool ROPE, int NT>
 __device__ __forceinline__ void k_small_body(const _Float16* __restrict__ k,
                                              int8_t* __restrict__ kq,
                                              float* __restrict__ scale,
                                              float* __restrict__ k_mean,
                                              int N, int block,
                                              const float* __restrict__ cs, const float* __restrict__ sn, int bh) {
-    constexpr int VPR = D / 8;
-    constexpr int RG = 256 / VPR;
+    constexpr int CH = CHUNKS_OWNED<ROPE>;
+    constexpr int VPR = D / 8 / CH;
+    constexpr int RG = NT / VPR, NW = NT / 64;
+    constexpr int RPW = 64 / VPR;                            // rows of a register set in one wavefront
     constexpr int HALF = D / 2;
-    constexpr int MAXR = SMALL_N / RG;        // rows per thread: row rg + i * RG in register set i
-    constexpr int MAXB = SMALL_N / 32;        // blocks per slab at the smallest block size
-    const int t = threadIdx.x, c8 = t % VPR, rg = t / VPR;
+    constexpr int MAXR = (SMALL_N + RG - 1) / RG;            // rows per thread: row rg + i * RG in register set i
+    const int t = threadIdx.x, c8 = t % VPR, rg = t / VPR, lane = t & 63, wave = t >> 6;
     const _Float16* base = k + ((size_t)bh * N) * D;
 
-    __shared__ long long part[RG][D];
+    __shared__ double s_part[NW][D];
     __shared__ float s_mean[D];
-    __shared__ float s_red[MAXB][4];
+    __shared__ __attribute__((aligned(16))) float s_red[MAXR * NW];      // largest of RPW rows: rows RPW * index ..
+    __shared__ float s_block[SMALL_N / 32];
 
     // register sets 0 .. nset - 1 hold rows (a wave-uniform count); a row past N inside the last set is
     // fetched from row N - 1 (no per-lane branch around a load) and left out of every sum and maximum
     const int nset = (N + RG - 1) / RG;
-    h8 x[MAXR];
+    Row<ROPE> x[MAXR];
     constexpr int SUB = rows_in_flight<ROPE>(MAXR);       // without RoPE the whole slab is requested at once
 #pragma unroll
     for (int i0 = 0; i0 < MAXR; i0 += SUB) {
@@ -426,64 +444,68 @@ __device__ __forceinline__ void k_small_body(const _Float16* __restrict__ k,
         for (int i = 0; i < SUB; ++i) {
             if (i0 + i < nset) {
                 const int r = rg + (i0 + i) * RG, rc = r < N ? r : N - 1;
-                fetched[i] = fetch_row8<D, ROPE>(base + (size_t)rc * D, c8, cs + (size_t)rc * HALF, sn + (size_t)rc * HALF);
+                fetched[i] = fetch_row<D, ROPE>(base + (size_t)rc * D, c8, cs + (size_t)rc * HALF, sn + (size_t)rc * HALF);
             }
         }
         __builtin_amdgcn_sched_barrier(0);       // requested before anything is used
 #pragma unroll
         for (int i = 0; i < SUB; ++i)
-            if (i0 + i < nset) x[i0 + i] = finish_row8<D, ROPE>(fetched[i], c8);
+            if (i0 + i < nset) x[i0 + i] = finish_row<ROPE>(fetched[i]);
     }
-    // ---- exact column sums in fp64: multiples of 2^-24 below 2^16 in magnitude, at most 32 per thread --
-    // every partial sum fits 53 bits; then an exact conversion to a count of 2^-24 units
-    double acc_d[8];
+    // ---- exact column sums in fp64: multiples of 2^-24 below 2^16 in magnitude, 512 of them fit 53 bits in any order.
+    // Lanes 32, 16 (8, 4) apart hold the same channels of other rows.
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc_d[e] = 0.0;
+    for (int j = 0; j < CH; ++j) {
+        double acc[8];
 #pragma unroll
-    for (int i = 0; i < MAXR; ++i) {
-        if (i < nset) {
-            const double live = rg + i * RG < N ? 1.0 : 0.0;
+        for (int e = 0; e < 8; ++e) acc[e] = 0.0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc_d[e] += live * (double)(float)x[i][e];
+        for (int i = 0; i < MAXR; ++i) {
+            if (i < nset) {
+                const double live = rg + i * RG < N ? 1.0 : 0.0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = __builtin_fma(live, (double)(float)x[i].x[j][e], acc[e]);
+            }
         }
-    }
+        double a[4], b[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const double v = acc_d[e] * 16777216.0;          // |v| < 2^46
-        const double hi = __builtin_trunc(v * 0x1p-26);
-        const double lo = v - hi * 0x1p26;
-        part[rg][c8 * 8 + e] = (long long)(int)hi * (1ll << 26) + (long long)(int)lo;
+        for (int e = 0; e < 4; ++e) a[e] = fold32(acc[e], acc[e + 4]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) b[e] = fold16(a[e], a[e + 2]);
+#pragma unroll
+        for (int off = 8; off >= VPR; off >>= 1)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) b[e] += __shfl_xor(b[e], off, 64);
+        const int c = channel<D>(c8, j) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
+        s_part[wave][c] = b[0];
+        s_part[wave][c + 1] = b[1];
     }
     __syncthreads();
     if (t < D) {
-        long long sum = 0;
-#pragma unroll 4
-        for (int g = 0; g < RG; ++g) sum += part[g][t];
-        const double avg = (double)sum / (double)N;
-        const float m = (float)(avg * 0x1p-24);
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += s_part[w][t];
+        const float m = (float)(sum / (double)N);
         s_mean[t] = m;
         if (k_mean != nullptr) k_mean[(size_t)bh * D + t] = m;
     }
     __syncthreads();
-    float mean[8];
+    float mean[CH][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mean[e] = s_mean[c8 * 8 + e];
+    for (int j = 0; j < CH; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mean[j][e] = s_mean[channel<D>(c8, j) + e];
 
-    int8_t* qbase = kq + ((size_t)bh * N) * D + c8 * 8;
-    auto quantize_row = [&](const h8& raw, float rcp, int r) {
-        unsigned w[2] = {0u, 0u};
+    int8_t* qbase = kq + ((size_t)bh * N) * D;
+    auto quantize_row = [&](const Row<ROPE>& raw, float rcp, int r) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float q = __builtin_rintf(((float)raw[e] - mean[e]) * rcp);     // round half to even
-            q = __builtin_fminf(__builtin_fmaxf(q, -127.0f), 127.0f);
-            w[e >> 2] |= ((unsigned)((int)q) & 0xffu) << (8 * (e & 3));
-        }
-        *(uint2*)(qbase + (size_t)r * D) = make_uint2(w[0], w[1]);
+        for (int j = 0; j < CH; ++j)
+            *(uint2*)(qbase + (size_t)r * D + channel<D>(c8, j)) = codes8<true>(raw.x[j], mean[j], 1.0f, rcp);
     };
-    auto row_amax = [&](const h8& raw) {
+    auto row_amax = [&](const Row<ROPE>& raw) {
         float a = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) a = __builtin_fmaxf(a, __builtin_fabsf((float)raw[e] - mean[e]));
+        for (int j = 0; j < CH; ++j) a = __builtin_fmaxf(a, amax8<true>(raw.x[j], mean[j], 1.0f));
         return a;
     };
 
@@ -505,50 +527,48 @@ __device__ __forceinline__ void k_small_body(const _Float16* __restrict__ k,
         return;
     }
 
-    // per-block scales.  block = lpt * RG rows: register sets lpt * g .. lpt * g + lpt - 1 of every thread are
-    // block g (lpt a power of two; the same for every thread).  Every thread folds its rows of a block, the
-    // wavefront reduces by shuffles and leaves its maximum in LDS; after ONE barrier every block's maximum
-    // is the largest of four words.  (A row past N holds zeros: |0 - mean| may exceed the block's true
-    // maximum, so such rows are left out.)
+    // per-block scales.  Every wavefront leaves the maximum of its RPW rows of each register set in LDS (a multiple of
+    // RPW rows is a block, whatever its size); one thread per block takes the largest of the block's words.  A repeated
+    // row changes no maximum: it is the last row, which belongs to the last block with it or to no block.
     const int nblk = (N + block - 1) / block;
-    const int lpt = block / RG;
-    const int wave = t >> 6;
-    float cur = 0.0f;
 #pragma unroll
     for (int i = 0; i < MAXR; ++i) {
         if (i < nset) {
-            const float a = row_amax(x[i]);
-            cur = rg + i * RG < N ? __builtin_fmaxf(cur, a) : cur;
-        }
-        if (((i + 1) & (lpt - 1)) == 0 && i / lpt < nblk) {          // last register set of block i / lpt (uniform)
-            float m = cur;
+            float m = row_amax(x[i]);
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
-            if ((t & 63) == 0) s_red[i / lpt][wave] = m;
-            cur = 0.0f;
+            if (lane == 0) s_red[i * NW + wave] = rg + i * RG < N ? m : 0.0f;
         }
     }
     __syncthreads();
     if (t < nblk) {
-        const float amax = __builtin_fmaxf(__builtin_fmaxf(s_red[t][0], s_red[t][1]), __builtin_fmaxf(s_red[t][2], s_red[t][3]));
-        scale[(size_t)bh * nblk + t] = amax / 127.0f;
+        float m = 0.0f;
+        const int first = t * (block / RPW), last = (N + RPW - 1) / RPW;
+        for (int e = 0; e < block / RPW; ++e)
+            if (first + e < last) m = __builtin_fmaxf(m, s_red[first + e]);
+        s_block[t] = m;
+        scale[(size_t)bh * nblk + t] = m / 127.0f;
     }
+    __syncthreads();
+    const int shift = __builtin_ctz((unsigned)block);
 #pragma unroll
     for (int i = 0; i < MAXR; ++i) {
         if (i < nset) {
-            const int r = rg + i * RG, g = i / lpt;
-            const float amax = __builtin_fmaxf(__builtin_fmaxf(s_red[g][0], s_red[g][1]), __builtin_fmaxf(s_red[g][2], s_red[g][3]));
-            if (r < N) quantize_row(x[i], amax > 0.0f ? 127.0f / amax : 0.0f, r);
+            const int r = rg + i * RG;
+            if (r < N) {
+                const float amax = s_block[r >> shift];
+                quantize_row(x[i], amax > 0.0f ? 127.0f / amax : 0.0f, r);
+            }
         }
     }
 }
 
 template <int D, bool ROPE>
-__global__ void __launch_bounds__(256) k_small_kernel(const _Float16* __restrict__ k, int8_t* __restrict__ kq,
-                                                      float* __restrict__ scale, float* __restrict__ k_mean,
-                                                      int N, int block,
-                                                      const float* __restrict__ cs, const float* __restrict__ sn) {
-    k_small_body<D, ROPE>(k, kq, scale, k_mean, N, block, cs, sn, blockIdx.x);
+__global__ void __launch_bounds__(SMALL_NT) k_small_kernel(const _Float16* __restrict__ k, int8_t* __restrict__ kq,
+                                                           float* __restrict__ scale, float* __restrict__ k_mean,
+                                                           int N, int block,
+                                                           const float* __restrict__ cs, const float* __restrict__ sn) {
+    k_small_body<D, ROPE, SMALL_NT>(k, kq, scale, k_mean, N, block, cs, sn, blockIdx.x);
 }
 
 // Workgroups per slab of the quantizer kernels: enough to fill the chip a few times over, few
@@ -564,22 +584,22 @@ static hipError_t launch_quant(const void* x, int8_t* xq, float* scale, float* m
                                hipStream_t st) {
     const _Float16* xp = (const _Float16*)x;
     if (block == 1) {
-        constexpr int ROWS = (256 / (D / 8)) * TOK_LPT;
-        const int ngrp = (N + ROWS - 1) / ROWS;
+        const int ngrp = (N + TOK_ROWS<D, ROPE> - 1) / TOK_ROWS<D, ROPE>;
         quant_token_kernel<D, IS_K, ROPE><<<dim3(IS_K ? quant_groups(BH, ngrp) : ngrp, BH), 256, 0, st>>>(
             xp, xq, scale, mean, parts, P, N, sm_scale, cs, sn);
         return hipGetLastError();
     }
     const int nblk = (N + block - 1) / block;
     dim3 grid(quant_groups(BH, nblk), BH);
-#define SAGE_QUANT(LPT) quant_block_kernel<D, LPT, IS_K, ROPE><<<grid, 256, 0, st>>>(xp, xq, scale, mean, parts, P, N, block, sm_scale, cs, sn)
+#define SAGE_QUANT(LPT, NT) quant_block_kernel<D, LPT, IS_K, ROPE, NT><<<grid, NT, 0, st>>>(xp, xq, scale, mean, parts, P, N, block, sm_scale, cs, sn)
+    // (a thread owns twice the channels with RoPE, hence half the rows; where that is half a row, half the threads repeat one)
     switch (block * D / 2048) {
-        case 1: SAGE_QUANT(1); break;
-        case 2: SAGE_QUANT(2); break;
-        case 4: SAGE_QUANT(4); break;
-        // the largest block (128 tokens x 128 channels) runs with 512 threads of 4 rows each: twice the
+        case 1: SAGE_QUANT(1, 256); break;
+        case 2: if constexpr (ROPE) SAGE_QUANT(1, 256); else SAGE_QUANT(2, 256); break;
+        case 4: if constexpr (ROPE) SAGE_QUANT(2, 256); else SAGE_QUANT(4, 256); break;
+        // the largest block (128 tokens x 128 channels) runs with 512 threads: twice the
         // loads in flight per block and half the work per thread behind the block-wide maximum
-        case 8: quant_block_kernel<D, 4, IS_K, ROPE, 512><<<grid, 512, 0, st>>>(xp, xq, scale, mean, parts, P, N, block, sm_scale, cs, sn); break;
+        case 8: if constexpr (ROPE) SAGE_QUANT(2, 512); else SAGE_QUANT(4, 512); break;
         default: return hipErrorInvalidValue;
     }
 #undef SAGE_QUANT
@@ -636,11 +656,11 @@ hipError_t launch_smooth_quant_k(const void* k, int8_t* kq, float* kscale, float
     if (N <= SMALL_N) {
         const _Float16* kp = (const _Float16*)k;
         if (D == 64) {
-            if (rope) k_small_kernel<64, true><<<BH, 256, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
-            else k_small_kernel<64, false><<<BH, 256, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
+            if (rope) k_small_kernel<64, true><<<BH, SMALL_NT, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
+            else k_small_kernel<64, false><<<BH, SMALL_NT, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
         } else {
-            if (rope) k_small_kernel<128, true><<<BH, 256, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
-            else k_small_kernel<128, false><<<BH, 256, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
+            if (rope) k_small_kernel<128, true><<<BH, SMALL_NT, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
+            else k_small_kernel<128, false><<<BH, SMALL_NT, 0, st>>>(kp, kq, kscale, kmean, N, block, cs, sn);
         }
         return hipGetLastError();
     }
@@ -666,7 +686,7 @@ __global__ void __launch_bounds__(NT) qk_first_block_kernel(const _Float16* __re
                                                              float* __restrict__ qscale, int Nq, int block_q, float sm_scale) {
     const int bx = blockIdx.x, bh = blockIdx.y;
     if (bx < n_k) {
-        if constexpr (SMALL_K) k_small_body<D, false>(k, kq, kscale, kmean, Nkv, block_k, nullptr, nullptr, bh);
+        if constexpr (SMALL_K) k_small_body<D, false, NT>(k, kq, kscale, kmean, Nkv, block_k, nullptr, nullptr, bh);
         else k_colsum_body<D, false, NT>(k, parts, Nkv, chunk, nullptr, nullptr, bx, n_k, bh);
     } else {
         quant_block_body<D, LPT, false, false, NT>(q, qq, qscale, nullptr, nullptr, 0, Nq, block_q, sm_scale, nullptr, nullptr,
@@ -681,7 +701,7 @@ __global__ void __launch_bounds__(256) qk_first_token_kernel(const _Float16* __r
                                                              float* __restrict__ qscale, int Nq, float sm_scale) {
     const int bx = blockIdx.x, bh = blockIdx.y;
     if (bx < n_k) {
-        if constexpr (SMALL_K) k_small_body<D, false>(k, kq, kscale, kmean, Nkv, block_k, nullptr, nullptr, bh);
+        if constexpr (SMALL_K) k_small_body<D, false, 256>(k, kq, kscale, kmean, Nkv, block_k, nullptr, nullptr, bh);
         else k_colsum_body<D, false, 256>(k, parts, Nkv, chunk, nullptr, nullptr, bx, n_k, bh);
     } else {
         quant_token_body<D, false, false>(q, qq, qscale, nullptr, nullptr, 0, Nq, sm_scale, nullptr, nullptr,
@@ -697,8 +717,7 @@ static hipError_t quant_qk_first(const void* q, const void* k, int8_t* qq, float
     const _Float16* kp = (const _Float16*)k;
     const int n_k = SMALL_K ? 1 : cp.parts;
     if (block_q == 1) {
-        constexpr int ROWS = (256 / (D / 8)) * TOK_LPT;
-        const int ngrp = (Nq + ROWS - 1) / ROWS;
+        const int ngrp = (Nq + TOK_ROWS<D, false> - 1) / TOK_ROWS<D, false>;
         qk_first_token_kernel<D, SMALL_K><<<dim3(n_k + ngrp, BH), 256, 0, st>>>(kp, parts, kq, kscale, kmean, Nkv, cp.chunk,
                                                                                block_k, n_k, qp, qq, qscale, Nq, sm_scale);
         return hipGetLastError();
@@ -711,9 +730,7 @@ static hipError_t quant_qk_first(const void* q, const void* k, int8_t* qq, float
         case 2: SAGE_QK(2, 256); break;
         case 4: SAGE_QK(4, 256); break;
         case 8:
-            // (the single-workgroup K job is written for 256 threads: 8 rows per thread on the Q side there)
-            if constexpr (SMALL_K) SAGE_QK(8, 256);
-            else SAGE_QK(4, 512);
+            SAGE_QK(4, 512);
             break;
         default: return hipErrorInvalidValue;
     }

@@ -44,20 +44,6 @@ __device__ __forceinline__ void short_load_to_lds16(const s4i& rsrc, unsigned go
     const unsigned addr = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr);
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(goff), "s"(rsrc), "s"(addr) : "memory");
 }
-// x + the value of the lane 32 (16) away, of two values at once: lanes of the lower half (even rows of 16) end with
-// the sum of a, the others with the sum of b
-__device__ __forceinline__ double fold32(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
-    auto lo = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
-    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
-}
-__device__ __forceinline__ double fold16(double a, double b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
-    auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
-    return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
-}
 }  // namespace
 
 // D channels, NTILE tiles of 64 keys at most, NW wavefronts; KTOK: one scale per key.  grid: groups workgroups per
