@@ -81,6 +81,7 @@ __device__ __forceinline__ uint2 codes8(const h8& x, const float* mean, float sm
     float f[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = scaled<IS_K>(x[e], IS_K ? mean[e] : 0.0f, sm_scale);
+    if (IS_K) return make_uint2(quantize4_k(f[0], f[1], f[2], f[3], rcp), quantize4_k(f[4], f[5], f[6], f[7], rcp));
     return make_uint2(quantize4(f[0], f[1], f[2], f[3], rcp), quantize4(f[4], f[5], f[6], f[7], rcp));
 }
 template <bool IS_K>

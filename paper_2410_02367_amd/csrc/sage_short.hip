@@ -30,6 +30,11 @@ typedef _Float16 s4h __attribute__((ext_vector_type(4)));
 namespace {
 constexpr float SHORT_LOG2E = 1.4426950408889634f;
 constexpr float SHORT_SLACK = 8.0f;         // log2 of the largest P~ tolerated before the running maximum is raised
+constexpr int SHORT_MAGIC_I = 0x4B400000;    // 12582912.0f = 1.5 * 2^23
+constexpr float SHORT_MAGIC = 12582912.0f;
+typedef float s4f __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float as_f(unsigned v) { return __builtin_bit_cast(float, v); }
+__device__ __forceinline__ unsigned as_u(float v) { return __builtin_bit_cast(unsigned, v); }
 
 template <int D> __device__ __forceinline__ int short_kswz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
 template <int D> __device__ __forceinline__ int short_vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
@@ -67,6 +72,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     __shared__ __attribute__((aligned(16))) float s_mean[D];
     __shared__ float s_max[KMAX / 32];
     __shared__ __attribute__((aligned(16))) float s_scale[KTOK ? KMAX : KMAX / 64];
+    __shared__ __attribute__((aligned(16))) float s_bias[KTOK ? KMAX : 4];       // -12582912 * s_scale
     __shared__ float s_q[2][NW];
     static_assert(NW * D * 8 <= KMAX * D, "the partial column sums fit where K^ will be");
     double (*const s_part)[D] = (double (*)[D])kl;       // [wavefront][channel]; read before the codes are written
@@ -116,24 +122,23 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
     }
 
-    // ---- exact column sums (fp64: multiples of 2^-24 below 2^25), folded over the wavefront's rows
+    // ---- exact column sums (fp64: multiples of 2^-24 below 2^25), folded over the wavefront's rows.  The keys stay in
+    // registers as fp32 from here on: every conversion is made once.
+    float xs[GPW][LPG][8];
     double sum[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) sum[e] = 0.0;
 #pragma unroll
     for (int gr = 0; gr < GPW; ++gr) {
         if (wave * (GPW * 32) + gr * 32 >= N) continue;
-        if (wave * (GPW * 32) + gr * 32 + 32 <= N) {
+        const bool whole = wave * (GPW * 32) + gr * 32 + 32 <= N;
 #pragma unroll
-            for (int i = 0; i < LPG; ++i)
+        for (int i = 0; i < LPG; ++i) {
+            const double live = whole || r0 + gr * 32 + i * RPI < N ? 1.0 : 0.0;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) sum[e] += (double)(float)x[gr][i][e];
-        } else {
-#pragma unroll
-            for (int i = 0; i < LPG; ++i) {
-                const double live = r0 + gr * 32 + i * RPI < N ? 1.0 : 0.0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sum[e] += live * (double)(float)x[gr][i][e];
+            for (int e = 0; e < 8; ++e) {
+                xs[gr][i][e] = (float)x[gr][i][e];
+                sum[e] = __builtin_fma(live, (double)xs[gr][i][e], sum[e]);
             }
         }
     }
@@ -165,17 +170,21 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     for (int e = 0; e < 8; ++e) mean[e] = s_mean[c8 * 8 + e];
 
     // ---- codes of K^ into LDS (rows of D bytes, 16-byte chunks swizzled)
-    auto smoothed = [&](_Float16 v, int e) { return __builtin_fmaf((float)v, 1.0f, -mean[e]); };      // one rounding: v - mean
-    auto store_codes = [&](const half8& h, int r, float rcp) {
-        uint2 w;
-        w.x = quantize4(smoothed(h[0], 0), smoothed(h[1], 1), smoothed(h[2], 2), smoothed(h[3], 3), rcp);
-        w.y = quantize4(smoothed(h[4], 4), smoothed(h[5], 5), smoothed(h[6], 6), smoothed(h[7], 7), rcp);
+#pragma unroll
+    for (int gr = 0; gr < GPW; ++gr) {
+        if (wave * (GPW * 32) + gr * 32 >= N) continue;
+#pragma unroll
+        for (int i = 0; i < LPG; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xs[gr][i][e] -= mean[e];
+    }
+    auto store_codes = [&](const float (&f)[8], int r, float rcp) {
+        const uint2 w = make_uint2(quantize4_k(f[0], f[1], f[2], f[3], rcp), quantize4_k(f[4], f[5], f[6], f[7], rcp));
         *(uint2*)(kl + r * D + (((c8 >> 1) ^ short_kswz<D>(r)) * 16) + (c8 & 1) * 8) = w;
     };
-    auto row_max = [&](const half8& h) {
-        float m = 0.0f;
+    auto row_max = [&](float m, const float (&f)[8]) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(smoothed(h[e], e)));
+        for (int e = 0; e < 8; e += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(f[e])), __builtin_fabsf(f[e + 1]));
         return m;
     };
     if (KTOK) {
@@ -185,11 +194,16 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
 #pragma unroll
             for (int i = 0; i < LPG; ++i) {
                 const int r = r0 + gr * 32 + i * RPI;
-                float m = row_max(x[gr][i]);
+                float m = row_max(0.0f, xs[gr][i]);
 #pragma unroll
                 for (int off = VPR / 2; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
-                if (c8 == 0) s_scale[r] = m / 127.0f;
-                store_codes(x[gr][i], r, m > 0.0f ? 127.0f / m : 0.0f);
+                if (c8 == 0) {
+                    // 22 significant bits, so that 12582912 * a is exact; not 0, so that -inf * a is not NaN
+                    const float a = as_f(as_u(__builtin_fmaxf(m / 127.0f, 1e-30f)) & ~3u);
+                    s_scale[r] = a;
+                    s_bias[r] = -SHORT_MAGIC * a;
+                }
+                store_codes(xs[gr][i], r, m > 0.0f ? 127.0f / m : 0.0f);
             }
         }
     } else {
@@ -199,7 +213,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
             gm[gr] = 0.0f;
             if (wave * (GPW * 32) + gr * 32 >= N) continue;
 #pragma unroll
-            for (int i = 0; i < LPG; ++i) gm[gr] = __builtin_fmaxf(gm[gr], row_max(x[gr][i]));      // a repeated row changes no maximum
+            for (int i = 0; i < LPG; ++i) gm[gr] = row_max(gm[gr], xs[gr][i]);      // a repeated row changes no maximum
         }
 #pragma unroll
         for (int gr = 0; gr < GPW; ++gr) {
@@ -218,7 +232,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
             if (lane == 0) s_scale[row >> 6] = m / 127.0f;           // (both groups of a tile write the same value)
             const float rcp = m > 0.0f ? 127.0f / m : 0.0f;
 #pragma unroll
-            for (int i = 0; i < LPG; ++i) store_codes(x[gr][i], r0 + gr * 32 + i * RPI, rcp);
+            for (int i = 0; i < LPG; ++i) store_codes(xs[gr][i], r0 + gr * 32 + i * RPI, rcp);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's part of V has landed
@@ -232,6 +246,13 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
         v_off[dt] = v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ short_vswz<D>(v_row)) * 16) + (li & 1) * 8;
+
+    // seed of the scores and selector of the row sums, as in sage_attn.hip
+    s16i magic;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) magic[r] = SHORT_MAGIC_I;
+    const int sel_word = (((lane >> 4) ^ lane) & 1) ? 0 : 0x3C003C00;
+    const s4i sel = {sel_word, sel_word, sel_word, sel_word};
 
     for (int set = part, turn = 0; set * NW < rtiles; set += groups, turn ^= 1) {
         const int row0 = (set * NW + wave) * 32, q_row = row0 + ql;
@@ -254,7 +275,8 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
-        float m_run = -__builtin_inff(), l = 0.0f;
+        s4f lsum = {0.0f, 0.0f, 0.0f, 0.0f};       // registers 0, 1: sums of the queries lane % 16, 16 + lane % 16
+        float m_run = -__builtin_inff();
         // keys this wavefront sees; a tile of which it sees only the first half is done by halves
         int seen = causal ? row0 + 32 + coff : N;
         seen = seen < N ? seen : N;
@@ -265,42 +287,73 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
 #pragma unroll
             for (int h = 0; h < NH; ++h) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[h][r] = 0;
-#pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
-                    s[h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const s4i*)(kt + h * (32 * D) + k_off[ks]), q[ks], s[h], 0, 0, 0);
+                    s[h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const s4i*)(kt + h * (32 * D) + k_off[ks]), q[ks], ks == 0 ? magic : s[h], 0, 0, 0);
             }
             // register r of half h: key 64 j + 32 h + 8 (r / 4) + 4 g + r % 4
-            const float sc = __builtin_fmaxf(KTOK ? dq : dq * s_scale[j], 1e-30f);
-            float y[NH][16];
-#pragma unroll
-            for (int h = 0; h < NH; ++h)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    y[h][r] = (float)s[h][r];
-                    if (KTOK) y[h][r] *= s_scale[64 * j + 32 * h + 8 * (r >> 2) + 4 * g + (r & 3)];
-                }
+            const float sc = KTOK ? __builtin_fmaxf(dq, 1e-30f) : as_f(as_u(__builtin_fmaxf(dq * s_scale[j], 1e-30f)) & ~3u);
             if (j * 64 + 32 * NH > N || (causal && j * 64 + 32 * NH - 1 > row0 + coff)) {
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int key = 64 * j + 32 * h + 8 * (r >> 2) + 4 * g + (r & 3);
-                        if (key >= N || (causal && key > q_row + coff)) y[h][r] = -__builtin_inff();
+                        if (key >= N || (causal && key > q_row + coff)) s[h][r] = (int)0xFF800000;       // -inf, and below every score
                     }
             }
-            float top = y[0][0];
+            // the argument of exp2 is y * sc + bias, y the seeded score (KTOK: the score times delta_K); see sage_attn.hip
+            // for why it is rounded once, and why that needs the running maximum on the grid of 12582912 * sc
+            float y[NH][16], bias;
+            bool off_grid = false, want;
+            float mf = 0.0f;
+            int mi = 0;
+            if (KTOK) {
+                const float* ka = s_scale + 64 * j + 4 * g;
+                const float* kb = s_bias + 64 * j + 4 * g;
+                mf = -__builtin_inff();
 #pragma unroll
-            for (int h = 0; h < NH; ++h)
+                for (int h = 0; h < NH; ++h)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) top = __builtin_fmaxf(top, y[h][r]);
-            top = __builtin_fmaxf(top, __shfl_xor(top, 32, 64)) * sc;
-            if (__builtin_amdgcn_ballot_w64(top > m_run + SHORT_SLACK) != 0ull) {
+                    for (int c = 0; c < 4; ++c) {
+                        const s4f a = *(const s4f*)(ka + 32 * h + 8 * c), b = *(const s4f*)(kb + 32 * h + 8 * c);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) y[h][4 * c + e] = __builtin_fmaf(as_f((unsigned)s[h][4 * c + e]), a[e], b[e]);
+                        mf = __builtin_fmaxf(__builtin_fmaxf(mf, y[h][4 * c]), y[h][4 * c + 1]);
+                        mf = __builtin_fmaxf(__builtin_fmaxf(mf, y[h][4 * c + 2]), y[h][4 * c + 3]);
+                    }
+                bias = -m_run;
+                want = __builtin_fmaf(mf, sc, bias) > SHORT_SLACK;
+            } else {
+                mi = s[0][0];
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; r += 2) mi = max(max(mi, (int)s[h][r]), (int)s[h][r + 1]);
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) y[h][r] = as_f((unsigned)s[h][r]);
+                const float at = __builtin_fmaf(SHORT_MAGIC, sc, m_run);
+                bias = -at;
+                off_grid = __builtin_fmaf(-SHORT_MAGIC, sc, at) != m_run;
+                want = off_grid || __builtin_fmaf(as_f((unsigned)mi), sc, bias) > SHORT_SLACK;
+            }
+            if (__builtin_amdgcn_ballot_w64(want) != 0ull) {
                 // (on the first tile m_run is -inf and every row that sees a key is here)
-                const float m_new = __builtin_fmaxf(m_run, top);
+                float top;
+                if (KTOK) {
+                    auto x = __builtin_amdgcn_permlane32_swap(as_u(mf), as_u(mf), false, false);
+                    top = __builtin_fmaxf(as_f(x[0]), as_f(x[1])) * sc;
+                } else {
+                    auto x = __builtin_amdgcn_permlane32_swap((unsigned)mi, (unsigned)mi, false, false);
+                    top = (as_f((unsigned)max((int)x[0], (int)x[1])) - SHORT_MAGIC) * sc;
+                }
+                float m_new = __builtin_fmaxf(m_run, top);
+                if (!KTOK) m_new = __builtin_fmaf(-SHORT_MAGIC, sc, __builtin_fmaf(SHORT_MAGIC, sc, m_new));
                 const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
-                l *= alpha;
+                bias = KTOK ? -m_run : -__builtin_fmaf(SHORT_MAGIC, sc, m_run);
+                lsum *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -314,11 +367,12 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
                     s4i p;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e], sc, -m_run));
-                        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e + 1], sc, -m_run));
-                        l += p0 + p1;
+                        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e], sc, bias));
+                        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[h][8 * u + 2 * e + 1], sc, bias));
                         p[e] = __builtin_bit_cast(int, __builtin_convertvector((s2f){p0, p1}, s2h));
                     }
+                    // row sums on the matrix pipe (l_mfma of sage_attn.hip)
+                    lsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, sel), __builtin_bit_cast(half8, p), lsum, 0, 0, 0);
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
                         const unsigned char* va = vt + (32 * h + 16 * u) * VROW + v_off[dt];
@@ -333,7 +387,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         const int whole = (seen + 31) / 64;
         for (int j = 0; j < whole; ++j) tile(j, std::integral_constant<int, 2>{});
         if (whole * 64 < seen) tile(whole, std::integral_constant<int, 1>{});
-        const float inv = 1.0f / (l + __shfl_xor(l, 32, 64));
+        const float inv = 1.0f / ((lane & 16) ? lsum[1] : lsum[0]);
         store_rows<D>(og + (slab_q + row0) * D, Nq - row0, lane, true, [&](int dt, int r) { return o[dt][r] * inv; });
     }
 }
