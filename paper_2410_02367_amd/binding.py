@@ -1,4 +1,9 @@
-"""ctypes binding of libsage.so (declared in include/sage.h).  Argument marshalling only."""
+"""Binding of libsage.so (declared in include/sage.h).  Argument marshalling only.
+
+Every wrapper first offers its arguments to the extension module (csrc/binding.cpp), which checks them, allocates what
+the caller did not pass and calls the library, all in native code: a call is 4-6 us of host time, 3 of them the launch,
+instead of 6-20.  What the module does not take (it answers None) goes on in Python, through ctypes, and meets its
+error there."""
 from __future__ import annotations
 
 import ctypes
@@ -9,6 +14,14 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libsage.so")
 _lib = None
+_native = None
+
+# the calls the extension module makes, in the order of its table
+_NATIVE_CALLS = ("sage_quant_q", "sage_rope_quant_q", "sage_smooth_quant_k_workspace", "sage_smooth_quant_k",
+                 "sage_rope_smooth_quant_k", "sage_quant_qk", "sage_quant_v_workspace", "sage_quant_v",
+                 "sage_attn_split_workspace", "sage_attn_cross_fwd", "sage_attn_cross_split_fwd",
+                 "sage_attn_pv_int8_cross_fwd", "sage_attn_pv_int8_cross_split_fwd", "sage_attention_workspace",
+                 "sage_attention_fwd")
 
 EXPORTS = ("sage_status_string", "sage_source_hash", "sage_default_sm_scale", "sage_quant_q", "sage_smooth_quant_k_workspace",
            "sage_smooth_quant_k", "sage_quant_qk", "sage_smooth_quant_k_noalloc", "sage_rope_quant_q", "sage_rope_smooth_quant_k",
@@ -108,8 +121,46 @@ def load() -> ctypes.CDLL:
     lib.sage_attention_fwd.argtypes = [c_void_p] * 5 + [c_size_t] + [c_int] * 6 + [c_float, c_int, c_int, c_int, c_void_p]
     lib.sage_microbench.restype = c_int
     lib.sage_microbench.argtypes = [c_int, c_int, c_int, c_int, c_void_p, c_void_p, c_void_p]
+    _open_native(lib)
     _lib = lib
     return lib
+
+
+def _open_native(lib) -> None:
+    """Load the extension module (rebuilt first if it does not belong to the sources beside it, as the library is) and
+    hand it the library's entry points."""
+    global _native
+    import importlib.util
+    from . import build as _build
+    if _build.native_is_stale():
+        try:
+            _build.build_native()
+        except FileNotFoundError:
+            raise RuntimeError(f"{_build.NATIVE} is missing or was not built from the present sources, and there is no g++ to rebuild it")
+    spec = importlib.util.spec_from_file_location("_sage_native", _build.NATIVE)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    # (torch._C has these two in builds with a GPU back end only; without one no tensor passes the module's checks)
+    module.init(getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None),
+                *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+    _native = module
+
+
+def _fast():
+    if _native is None:
+        load()
+    return _native
+
+
+def _answer(r, where: str):
+    """What the extension module returned for a call it made: the outputs, or the library's status."""
+    if type(r) is int:
+        raise SageError(r, where)
+    return r
+
+
+def _handle(stream):
+    return None if stream is None else _stream(stream)
 
 
 def sage_status_string(status: int) -> str:
@@ -153,6 +204,9 @@ def _rope_tables(cos, sin, N: int, D: int):
 def sage_rope_quant_q(q: torch.Tensor, rope_cos, rope_sin, sm_scale: float, block_q: int = 128,
                       q_i8=None, q_scale=None, stream=None):
     """sage_quant_q on RoPE(Q), the rotation applied on the fly (tables [N, D/2] fp32)."""
+    r = _fast().quant_q(q, rope_cos, rope_sin, sm_scale, block_q, q_i8, q_scale, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_rope_quant_q")
     B, H, N, D = q.shape
     pc, ps = _rope_tables(rope_cos, rope_sin, N, D)
     if q_i8 is None:
@@ -170,6 +224,9 @@ def sage_rope_quant_q(q: torch.Tensor, rope_cos, rope_sin, sm_scale: float, bloc
 def sage_rope_smooth_quant_k(k: torch.Tensor, rope_cos, rope_sin, block_k: int = 64, k_i8=None, k_scale=None,
                              k_mean=None, workspace=None, stream=None):
     """sage_smooth_quant_k on RoPE(K), the rotation applied on the fly (tables [N, D/2] fp32)."""
+    r = _fast().smooth_quant_k(k, rope_cos, rope_sin, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_rope_smooth_quant_k")
     B, H, N, D = k.shape
     pc, ps = _rope_tables(rope_cos, rope_sin, N, D)
     if k_i8 is None:
@@ -193,6 +250,9 @@ def sage_rope_smooth_quant_k(k: torch.Tensor, rope_cos, rope_sin, block_k: int =
 
 def sage_quant_q(q: torch.Tensor, sm_scale: float, block_q: int = 128, q_i8=None, q_scale=None, stream=None):
     """psi_Q(Q * sm_scale) -> (q_i8 [B,H,N,D] int8, q_scale [B,H,ceil(N/block_q)] fp32); block_q = 1: per token."""
+    r = _fast().quant_q(q, None, None, sm_scale, block_q, q_i8, q_scale, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_quant_q")
     B, H, N, D = q.shape
     if q_i8 is None:
         q_i8 = torch.empty((B, H, N, D), dtype=torch.int8, device=q.device)
@@ -213,6 +273,9 @@ def sage_smooth_quant_k_workspace(B: int, H: int, N: int, D: int) -> int:
 def sage_smooth_quant_k(k: torch.Tensor, block_k: int = 64, k_i8=None, k_scale=None, k_mean=None,
                         workspace=None, stream=None):
     """phi_K(K) -> (k_i8 int8, k_scale [B,H,ceil(N/block_k)] fp32, k_mean [B,H,D] fp32); block_k = 1: per token."""
+    r = _fast().smooth_quant_k(k, None, None, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_smooth_quant_k")
     B, H, N, D = k.shape
     if k_i8 is None:
         k_i8 = torch.empty((B, H, N, D), dtype=torch.int8, device=k.device)
@@ -235,6 +298,9 @@ def sage_smooth_quant_k(k: torch.Tensor, block_k: int = 64, k_i8=None, k_scale=N
 def sage_quant_qk(q: torch.Tensor, k: torch.Tensor, sm_scale: float, block_q: int = 128, block_k: int = 64,
                   q_i8=None, q_scale=None, k_i8=None, k_scale=None, k_mean=None, workspace=None, stream=None):
     """sage_quant_q(q) and sage_smooth_quant_k(k) in one launch less -> (q_i8, q_scale, k_i8, k_scale, k_mean)."""
+    r = _fast().quant_qk(q, k, sm_scale, block_q, block_k, q_i8, q_scale, k_i8, k_scale, k_mean, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_quant_qk")
     B, H, Nq, D = q.shape
     Nkv = k.shape[2]
     if k.shape[0] != B or k.shape[1] != H or k.shape[3] != D:
@@ -290,6 +356,9 @@ def sage_attn_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_scale: float
     """Algorithm 1's loop on pre-quantized Q^, K^ and fp16 V -> O [B,H,N,D] fp16.
 
     block_q / block_k are the tokens per scale the tensors were quantized with (1 = per token)."""
+    r = _fast().attn(0, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_fwd")
     B, H, N, D = v.shape
     if out is None:
         out = torch.empty((B, H, N, D), dtype=torch.float16, device=v.device)
@@ -307,6 +376,9 @@ def sage_attn_cross_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_scale:
                         block_q: int = 128, block_k: int = 64, out=None, stream=None):
     """sage_attn_fwd with Nq queries (q_i8 [B,H,Nq,D]) against Nkv keys and values ([B,H,Nkv,D]) -> O [B,H,Nq,D];
     the causal mask is aligned at the end (needs Nq <= Nkv)."""
+    r = _fast().attn(1, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_cross_fwd")
     B, H, Nkv, D = v.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(k_i8.shape) != (B, H, Nkv, D):
@@ -338,6 +410,9 @@ def sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_
     """sage_attn_cross_fwd with the keys cut into n_splits chunks (0 = chosen from the shape) and a merge:
     for few queries against many keys.  workspace: uint8 device tensor of at least
     sage_attn_split_workspace(...) bytes (allocated here if not given)."""
+    r = _fast().attn(2, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_cross_split_fwd")
     B, H, Nkv, D = v.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(k_i8.shape) != (B, H, Nkv, D):
@@ -364,6 +439,9 @@ def sage_attn_pv_int8_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_sca
                                       out=None, workspace=None, stream=None):
     """sage_attn_pv_int8_cross_fwd with the keys cut into n_splits chunks (0 = chosen from the shape) and a merge.
     workspace: uint8 device tensor of at least sage_attn_split_workspace(...) bytes (allocated here if not given)."""
+    r = _fast().attn(2, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_pv_int8_cross_split_fwd")
     B, H, Nkv, D = k_i8.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(Nkv)):
@@ -396,6 +474,9 @@ def sage_quant_v_pitch(N: int) -> int:
 
 def sage_quant_v(v: torch.Tensor, v_i8t=None, v_scale=None, workspace=None, stream=None):
     """psi_V(V), per channel -> (v_i8t int8 [B,H,D,Np] (transposed, Np = sage_quant_v_pitch(N)), v_scale [B,H,D] fp32)."""
+    r = _fast().quant_v(v, v_i8t, v_scale, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_quant_v")
     B, H, N, D = v.shape
     Np = sage_quant_v_pitch(N)
     if v_i8t is None:
@@ -420,6 +501,9 @@ def sage_attn_pv_int8_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal: 
                           block_q: int = 128, block_k: int = 64, out=None, stream=None):
     """Algorithm 1's loop with the INT8 second product of Section 4.3 (SAGEAttn-vB; block sizes 1: -vT)
     on pre-quantized Q^, K^ and V^^T -> O [B,H,N,D] fp16."""
+    r = _fast().attn(0, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_pv_int8_fwd")
     B, H, N, D = q_i8.shape
     if tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(N)):
         raise TypeError(f"v_i8t: expected shape {(B, H, D, sage_quant_v_pitch(N))}")
@@ -440,6 +524,9 @@ def sage_attn_pv_int8_cross_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, ca
                                 block_q: int = 128, block_k: int = 64, out=None, stream=None):
     """sage_attn_pv_int8_fwd with Nq queries (q_i8 [B,H,Nq,D]) against Nkv keys (k_i8 [B,H,Nkv,D], v_i8t from
     sage_quant_v of the Nkv values) -> O [B,H,Nq,D]; end-aligned causal mask (needs Nq <= Nkv)."""
+    r = _fast().attn(1, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attn_pv_int8_cross_fwd")
     B, H, Nq, D = q_i8.shape
     Nkv = k_i8.shape[2]
     if tuple(k_i8.shape) != (B, H, Nkv, D) or tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(Nkv)):
@@ -514,6 +601,9 @@ def sage_attention_fwd(q, k, v, causal: bool, sm_scale: float, block_q: int = 12
                        out=None, workspace=None, stream=None):
     """The whole pass on fp16 q [B,H,Nq,D], k, v [B,H,Nkv,D] in one library call -> O [B,H,Nq,D] fp16.
     workspace: uint8 device tensor of at least sage_attention_workspace(...) bytes (allocated here if not given)."""
+    r = _fast().attention(q, k, v, causal, sm_scale, block_q, block_k, pv_int8, out, workspace, _handle(stream))
+    if r is not None:
+        return _answer(r, "sage_attention_fwd")
     B, H, Nq, D = q.shape
     kv_shape = k.shape
     Nkv = kv_shape[2]

@@ -49,24 +49,68 @@ def source_hash() -> str:
     return h.hexdigest()
 
 
-def built_hash(path: str = LIB):
+def built_hash(path: str = LIB, marker: bytes = HASH_MARKER):
     """The source hash a built library carries (read from the file, nothing is loaded), or None."""
     if not os.path.exists(path):
         return None
     with open(path, "rb") as f:
         blob = f.read()
-    at = blob.find(HASH_MARKER)
+    at = blob.find(marker)
     if at < 0:
         return None
-    digest = blob[at + len(HASH_MARKER): at + len(HASH_MARKER) + 64]
+    digest = blob[at + len(marker): at + len(marker) + 64]
     try:
         return digest.decode("ascii")
     except UnicodeDecodeError:
         return None
 
 
+NATIVE = os.path.join(HERE, "_sage_native.so")
+NATIVE_SOURCE = os.path.join(CSRC, "binding.cpp")
+NATIVE_MARKER = b"SAGE_NATIVE_HASH="
+
+
+def native_hash() -> str:
+    """SHA-256 over what the extension module is compiled from and against: its source, the public header, and
+    the versions of torch and Python."""
+    import hashlib
+    import torch
+    h = hashlib.sha256(f"{torch.__version__} {sys.version}".encode())
+    for path in (NATIVE_SOURCE, os.path.join(HERE, "..", "include", "sage.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
+def native_is_stale() -> bool:
+    return built_hash(NATIVE, NATIVE_MARKER) != native_hash()
+
+
+def build_native() -> str:
+    """Compile the Python extension module (host code only) and return its path."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", f'-DSAGE_NATIVE_HASH="{native_hash()}"',
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-o", tmp, NATIVE_SOURCE,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed:\n" + res.stderr)
+        os.replace(tmp, NATIVE)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+    return NATIVE
+
+
 def build(verbose: bool = False, extra=()) -> str:
-    """Compile every kernel for gfx950 (cross-compiles without a GPU) and return the library path."""
+    """Compile every kernel for gfx950 (cross-compiles without a GPU) and the extension module, and return the
+    library's path."""
+    build_native()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [hipcc(), *HIPCC_FLAGS, *extra, f'-DSAGE_SOURCE_HASH="{source_hash()}"', "-o", tmp,
            *[os.path.join(CSRC, s) for s in SOURCES]]

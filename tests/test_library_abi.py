@@ -224,3 +224,18 @@ def test_whole_pass_call_validates_and_sizes_its_workspace(lib):
     assert call(good, good, good, good, good, sz(need - 1), *shape, f(0.125), 128, 64, 0, None) == 4
     assert call(good, good, good, good, ctypes.c_void_p(0x1010), sz(need), *shape, f(0.125), 128, 64, 0, None) == 5
     assert call(good, good, good, good, good, sz(need), *shape, f(0.0), 128, 64, 0, None) == 7
+
+
+def test_extension_module_belongs_to_the_sources_and_leaves_errors_to_python(lib):
+    """The native half of the wrappers: built from the sources beside it; whatever it does not take (here: host
+    tensors) reaches the Python path and its error."""
+    import torch
+    import paper_2410_02367_amd as sage
+    from paper_2410_02367_amd import binding, build
+    assert not build.native_is_stale() and binding._native.source_hash == build.native_hash()
+    x = torch.zeros(1, 2, 64, 64, dtype=torch.float16)
+    assert binding._native.quant_q(x, None, None, 0.125, 128, None, None, None) is None
+    assert binding._native.attention(x, x, x, 0, 0.125, 128, 64, 0, None, None, None) is None
+    for call in (lambda: sage.sage_quant_q(x, 0.125), lambda: sage.sage_smooth_quant_k(x), lambda: sage.sageattn(x, x, x)):
+        with pytest.raises(TypeError):
+            call()
