@@ -313,7 +313,7 @@ AttentionPlan plan_attention(int B, int H, int Nq, int Nkv, int D, int causal, i
     p.parts = take(sage_smooth_quant_k_workspace(B, H, Nkv, D));
     p.v_i8t = take(pv_int8 ? BH * D * (size_t)sage_quant_v_pitch(Nkv) : 0);
     p.v_scale = take(pv_int8 ? BH * D * sizeof(float) : 0);
-    p.v_amax = take(pv_int8 ? sage_quant_v_workspace(B, H, Nkv, D) : 0);
+    p.v_amax = take(pv_int8 ? BH * sage::plan_colsum((int)BH, Nkv).parts * D * sizeof(unsigned) : 0);
     p.split_bytes = Nq != Nkv ? sage_attn_split_workspace(B, H, Nq, Nkv, D, causal, 0) : 0;
     p.split = take(p.split_bytes);
     p.total = at;
@@ -354,17 +354,14 @@ int sage_attention_fwd(const void* q_f16, const void* k_f16, const void* v_f16, 
     int8_t* k_i8 = (int8_t*)(w + p.k_i8);
     float* k_scale = (float*)(w + p.k_scale);
     // Q is quantized by the attention kernel itself (see Queries)
-    hipError_t e = sage::launch_smooth_quant_k(k_f16, k_i8, k_scale, nullptr, (long long*)(w + p.parts), B * H, Nkv, D, block_k,
-                                               nullptr, nullptr, (hipStream_t)stream);
+    const void* v = pv_int8 ? (const void*)(w + p.v_i8t) : v_f16;
+    float* v_scale = pv_int8 ? (float*)(w + p.v_scale) : nullptr;
+    hipError_t e = pv_int8
+        ? sage::launch_quant_kv(k_f16, k_i8, k_scale, (long long*)(w + p.parts), v_f16, (int8_t*)(w + p.v_i8t), v_scale,
+                                (unsigned*)(w + p.v_amax), B * H, Nkv, D, block_k, (hipStream_t)stream)
+        : sage::launch_smooth_quant_k(k_f16, k_i8, k_scale, nullptr, (long long*)(w + p.parts), B * H, Nkv, D, block_k,
+                                      nullptr, nullptr, (hipStream_t)stream);
     if (e != hipSuccess) return SAGE_ERR_LAUNCH;
-    const void* v = v_f16;
-    float* v_scale = nullptr;
-    if (pv_int8) {
-        v = w + p.v_i8t;
-        v_scale = (float*)(w + p.v_scale);
-        e = sage::launch_quant_v(v_f16, (int8_t*)(w + p.v_i8t), v_scale, (unsigned*)(w + p.v_amax), B * H, Nkv, D, (hipStream_t)stream);
-        if (e != hipSuccess) return SAGE_ERR_LAUNCH;
-    }
     return attn_impl(pv_int8 != 0, Nq != Nkv, {nullptr, nullptr, q_f16, sm_scale}, k_i8, k_scale, v, v_scale, o_f16, w + p.split, p.split_bytes,
                      B, H, Nq, Nkv, D, causal, sm_scale, block_q, block_k, 0, stream);
 }

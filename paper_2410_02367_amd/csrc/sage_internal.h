@@ -25,6 +25,13 @@ hipError_t launch_quant_qk(const void* q, const void* k, int8_t* qq, float* qsca
                            float* kmean, long long* parts, int BH, int Nq, int Nkv, int D, float sm_scale,
                            int block_q, int block_k, hipStream_t st);
 
+// workgroups per slab of a quantizer launch
+int quant_groups(int BH, int units);
+// Both pre-passes of K and V (INT8 second product) in two launches, one for short sequences; vmax: plan_colsum().parts *
+// BH * D words.  block_k 1, 64 or 128.
+hipError_t launch_quant_kv(const void* k, int8_t* kq, float* kscale, long long* parts, const void* v, int8_t* vt, float* vscale,
+                           unsigned* vmax, int BH, int N, int D, int block_k, hipStream_t st);
+
 // The queries of an attention launch: quantized (i8, scale), or fp16 rows that the attention kernel quantizes
 // itself (f16 != nullptr; then i8 and scale are not read).
 struct Queries {

@@ -14,6 +14,7 @@
 // workgroups add the partial sums of their slab (no clearing pass, no atomics).
 #include "sage_internal.h"
 #include "sage_device.h"
+#include "sage_prepass_v.h"
 
 namespace sage {
 
@@ -574,7 +575,7 @@ __global__ void __launch_bounds__(SMALL_NT) k_small_kernel(const _Float16* __res
 
 // Workgroups per slab of the quantizer kernels: enough to fill the chip a few times over, few
 // enough that a workgroup of the K side walks several blocks per read of the partial sums.
-static int quant_groups(int BH, int units) {
+int quant_groups(int BH, int units) {
     const int want = (2048 + BH - 1) / BH;
     return units < want ? units : want;
 }
@@ -756,6 +757,76 @@ hipError_t launch_quant_qk(const void* q, const void* k, int8_t* qq, float* qsca
                            int block_q, int block_k, hipStream_t st) {
     if (D == 64) return quant_qk_d<64>(q, k, qq, qscale, kq, kscale, kmean, parts, BH, Nq, Nkv, sm_scale, block_q, block_k, st);
     return quant_qk_d<128>(q, k, qq, qscale, kq, kscale, kmean, parts, BH, Nq, Nkv, sm_scale, block_q, block_k, st);
+}
+
+// ---- K and V together (the whole-pass call with an INT8 second product) -------------------------
+// Two launches for both pre-passes instead of five: column sums of K | maxima of V (a set per chunk of tokens, nothing to
+// clear and nothing atomic), then codes of K | transposed codes of V; for short sequences one launch, a workgroup per
+// slab and tensor.
+template <int D>
+__global__ void __launch_bounds__(256) kv_first_kernel(const _Float16* __restrict__ k, long long* __restrict__ parts,
+                                                       const _Float16* __restrict__ v, unsigned* __restrict__ vmax, int N, int chunk) {
+    const int P = gridDim.x / 2, bx = blockIdx.x, bh = blockIdx.y;
+    if (bx < P) {
+        k_colsum_body<D, false>(k, parts, N, chunk, nullptr, nullptr, bx, P, bh);
+    } else {
+        __shared__ unsigned short s_part[4][D];
+        const int p = bx - P, begin = p * chunk;
+        const unsigned short m = v_absmax_rows<D, 256>(v + ((size_t)bh * N) * D, begin, begin + chunk < N ? begin + chunk : N, s_part);
+        if (threadIdx.x < D) vmax[((size_t)bh * P + p) * D + threadIdx.x] = __float_as_uint(f16_pattern(m));
+    }
+}
+template <int D, int LPT, bool TOKEN>
+__global__ void __launch_bounds__(256) kv_second_kernel(const _Float16* __restrict__ k, int8_t* __restrict__ kq, float* __restrict__ kscale,
+                                                        const long long* __restrict__ parts, int P, int block_k, int n_k,
+                                                        const _Float16* __restrict__ v, const unsigned* __restrict__ vmax,
+                                                        int8_t* __restrict__ vt, float* __restrict__ vscale, int N, int Np) {
+    const int bx = blockIdx.x, bh = blockIdx.y;
+    if (bx < n_k) {
+        if constexpr (TOKEN) quant_token_body<D, true, false>(k, kq, kscale, nullptr, parts, P, N, 1.0f, nullptr, nullptr, bx, n_k, bh);
+        else quant_block_body<D, LPT, true, false, 256>(k, kq, kscale, nullptr, parts, P, N, block_k, 1.0f, nullptr, nullptr, bx, n_k, bh);
+    } else {
+        v_transpose_body<D, 256>(v, vmax, P, vt, vscale, N, Np, bx - n_k, (int)gridDim.x - n_k, bh);
+    }
+}
+template <int D>
+__global__ void __launch_bounds__(1024) kv_small_kernel(const _Float16* __restrict__ k, int8_t* __restrict__ kq, float* __restrict__ kscale,
+                                                        int block_k, const _Float16* __restrict__ v, int8_t* __restrict__ vt,
+                                                        float* __restrict__ vscale, int N, int Np) {
+    if (blockIdx.y == 0) k_small_body<D, false, 1024>(k, kq, kscale, nullptr, N, block_k, nullptr, nullptr, blockIdx.x);
+    else v_small_body<D>(v, vt, vscale, N, Np, blockIdx.x);
+}
+
+template <int D>
+static hipError_t quant_kv_d(const _Float16* k, int8_t* kq, float* kscale, long long* parts, const _Float16* v, int8_t* vt, float* vscale,
+                             unsigned* vmax, int BH, int N, int block_k, hipStream_t st) {
+    const int Np = 64 * ((N + 63) / 64);
+    if (N <= SMALL_N) {
+        kv_small_kernel<D><<<dim3(BH, 2), 1024, 0, st>>>(k, kq, kscale, block_k, v, vt, vscale, N, Np);
+        return hipGetLastError();
+    }
+    const ColsumPlan cp = plan_colsum(BH, N);
+    kv_first_kernel<D><<<dim3(2 * cp.parts, BH), 256, 0, st>>>(k, parts, v, vmax, N, cp.chunk);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int units = block_k == 1 ? (N + TOK_ROWS<D, false> - 1) / TOK_ROWS<D, false> : (N + block_k - 1) / block_k;
+    const int n_k = quant_groups(BH, units), n_v = quant_groups(BH, (Np + 127) / 128);
+    const dim3 grid(n_k + n_v, BH);
+#define SAGE_KV(LPT, TOK) kv_second_kernel<D, LPT, TOK><<<grid, 256, 0, st>>>(k, kq, kscale, parts, cp.parts, block_k, n_k, v, vmax, vt, vscale, N, Np)
+    if (block_k == 1) { SAGE_KV(1, true); return hipGetLastError(); }
+    switch (block_k * D / 2048) {
+        case 2: SAGE_KV(2, false); break;
+        case 4: SAGE_KV(4, false); break;
+        case 8: SAGE_KV(8, false); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef SAGE_KV
+    return hipGetLastError();
+}
+hipError_t launch_quant_kv(const void* k, int8_t* kq, float* kscale, long long* parts, const void* v, int8_t* vt, float* vscale,
+                           unsigned* vmax, int BH, int N, int D, int block_k, hipStream_t st) {
+    return D == 64 ? quant_kv_d<64>((const _Float16*)k, kq, kscale, parts, (const _Float16*)v, vt, vscale, vmax, BH, N, block_k, st)
+                   : quant_kv_d<128>((const _Float16*)k, kq, kscale, parts, (const _Float16*)v, vt, vscale, vmax, BH, N, block_k, st);
 }
 
 }  // namespace sage
