@@ -82,6 +82,11 @@ __device__ __forceinline__ unsigned quantize4_k(float x0, float x1, float x2, fl
 }
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+// max(m, |x|) of two fp16 values at once, x as a word; the other operand where one is NaN
+__device__ __forceinline__ half2v max_abs(half2v m, unsigned x) {
+    return __builtin_elementwise_max(m, __builtin_bit_cast(half2v, x & 0x7fff7fffu));
+}
 
 // The fp16 rows of a wavefront's 32 queries quantized where they are used (Section 4.6: the quantizer fused
 // into the operator's neighbour): lane l holds half of row l % 32, the channels 32 ks + 16 (l / 32) .. + 15, as the
@@ -104,20 +109,19 @@ struct QueryRows {
     // red: one float of LDS per wavefront, not used for anything else before the next barrier.
     __device__ __forceinline__ float block_amax(float sm_scale, int shift_q, int wave, float* red) const {
         // max |x * sm_scale| = max |x| * sm_scale, rounded once either way (rounding is monotonic): the maximum is
-        // taken on the fp16 patterns without their signs, two per instruction
-        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+        // taken on fp16 pairs.  It passes over NaN, as fmaxf does (a maximum of the bit patterns would not): a row that
+        // holds one leaves the other rows of its block as they are.
+        half2v top = {};
         typedef unsigned u4 __attribute__((ext_vector_type(4)));
-        us2 top = {0, 0};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const u4 w = __builtin_bit_cast(u4, raw[ks][j]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, w[e] & 0x7fff7fffu));
+                for (int e = 0; e < 4; ++e) top = max_abs(top, w[e]);
             }
-        const unsigned short most = top[0] > top[1] ? top[0] : top[1];
-        float m = (float)__builtin_bit_cast(_Float16, most) * sm_scale;
+        float m = __builtin_fmaxf((float)top[0], (float)top[1]) * sm_scale;
         m = __builtin_fmaxf(m, __shfl_xor(m, 32, 64));
         if (shift_q == 0) return m;
 #pragma unroll

@@ -8,32 +8,32 @@
 //
 // Channel-major is what the attention kernel wants: the A operand of the INT8 matrix instruction
 // of O^T = V^^T P^^T is 16 consecutive TOKENS of one channel, i.e. one 16-byte read of a row of V^^T.
-// Maxima are taken on the fp16 bit patterns without the sign, two per instruction (non-negative floats order like
-// their bits), so they do not depend on how the tokens are split.
+// Maxima are taken on fp16 pairs and pass over NaN, so that a token that holds one leaves the other tokens' codes as
+// they are; they do not depend on how the tokens are split.
 #pragma once
 #include "sage_device.h"
 
 namespace sage {
 
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 struct Max8 {          // maxima of 8 channels
-    us2 m[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+    half2v m[4] = {};
     __device__ __forceinline__ void take(const half8& x) {
         typedef unsigned u4 __attribute__((ext_vector_type(4)));
         const u4 w = __builtin_bit_cast(u4, x);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) m[e] = __builtin_elementwise_max(m[e], __builtin_bit_cast(us2, w[e] & 0x7fff7fffu));
+        for (int e = 0; e < 4; ++e) m[e] = max_abs(m[e], w[e]);
     }
     // over the lanes VPR, 2 VPR, ... apart, which hold the same channels of other rows
     template <int VPR> __device__ __forceinline__ void fold() {
 #pragma unroll
         for (int off = VPR; off < 64; off <<= 1)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) m[e] = __builtin_elementwise_max(m[e], __builtin_bit_cast(us2, __shfl_xor(__builtin_bit_cast(int, m[e]), off, 64)));
+            for (int e = 0; e < 4; ++e) m[e] = max_abs(m[e], (unsigned)__shfl_xor(__builtin_bit_cast(int, m[e]), off, 64));
     }
 };
 
-// Per-channel maxima of the rows row_begin .. row_end - 1 of a slab, as fp16 patterns; thread c < D returns channel c's.
+// Per-channel maxima of the rows row_begin .. row_end - 1 of a slab, as fp16 patterns (no NaN among them: they order like
+// their bits); thread c < D returns channel c's.
 // s_part: NT / 64 rows of D patterns.
 template <int D, int NT>
 __device__ __forceinline__ unsigned short v_absmax_rows(const _Float16* __restrict__ base, int row_begin, int row_end,
@@ -57,7 +57,7 @@ __device__ __forceinline__ unsigned short v_absmax_rows(const _Float16* __restri
     m.fold<VPR>();
     if ((t & 63) < VPR) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) *(us2*)&s_part[t >> 6][c8 * 8 + 2 * e] = m.m[e];
+        for (int e = 0; e < 4; ++e) *(half2v*)&s_part[t >> 6][c8 * 8 + 2 * e] = m.m[e];
     }
     __syncthreads();
     unsigned short most = 0;
@@ -178,7 +178,7 @@ __device__ __forceinline__ void v_small_body(const _Float16* __restrict__ v, int
     m.fold<VPR>();
     if ((t & 63) < VPR) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) *(us2*)&s_part[t >> 6][c8 * 8 + 2 * e] = m.m[e];
+        for (int e = 0; e < 4; ++e) *(half2v*)&s_part[t >> 6][c8 * 8 + 2 * e] = m.m[e];
     }
     __syncthreads();
     if (t < D) {
