@@ -208,8 +208,9 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             for (int e = 0; e < 4; ++e) {
                 const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[8 * u + 2 * e], sc, -m_sub));
                 const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(y[8 * u + 2 * e + 1], sc, -m_sub));
-                l += p0 + p1;
-                p[e] = __builtin_bit_cast(int, __builtin_convertvector((d2f){p0, p1}, d2h));
+                const d2h h = __builtin_convertvector((d2f){p0, p1}, d2h);
+                p[e] = __builtin_bit_cast(int, h);
+                l += (float)h[0] + (float)h[1];         // of the weights as the product takes them: their rounding cancels in O / l
             }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
