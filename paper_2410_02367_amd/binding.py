@@ -204,7 +204,7 @@ def _rope_tables(cos, sin, N: int, D: int):
 def sage_rope_quant_q(q: torch.Tensor, rope_cos, rope_sin, sm_scale: float, block_q: int = 128,
                       q_i8=None, q_scale=None, stream=None):
     """sage_quant_q on RoPE(Q), the rotation applied on the fly (tables [N, D/2] fp32)."""
-    r = _fast().quant_q(q, rope_cos, rope_sin, sm_scale, block_q, q_i8, q_scale, _handle(stream))
+    r = _fast().rope_quant_q(q, rope_cos, rope_sin, sm_scale, block_q, q_i8, q_scale, _handle(stream))
     if r is not None:
         return _answer(r, "sage_rope_quant_q")
     B, H, N, D = q.shape
@@ -224,7 +224,7 @@ def sage_rope_quant_q(q: torch.Tensor, rope_cos, rope_sin, sm_scale: float, bloc
 def sage_rope_smooth_quant_k(k: torch.Tensor, rope_cos, rope_sin, block_k: int = 64, k_i8=None, k_scale=None,
                              k_mean=None, workspace=None, stream=None):
     """sage_smooth_quant_k on RoPE(K), the rotation applied on the fly (tables [N, D/2] fp32)."""
-    r = _fast().smooth_quant_k(k, rope_cos, rope_sin, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
+    r = _fast().rope_smooth_quant_k(k, rope_cos, rope_sin, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_rope_smooth_quant_k")
     B, H, N, D = k.shape

@@ -153,8 +153,9 @@ bool fits(const at::Tensor& t) {
     return true;
 }
 
-// (q, cos | None, sin | None, sm_scale, block_q, q_i8 | None, q_scale | None, stream | None)
-PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+// (q, cos, sin, sm_scale, block_q, q_i8 | None, q_scale | None, stream | None); the tables both None unless ROPE: the call is
+// named by its entry, so that a missing table does not turn it into the other one
+template <bool ROPE> PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     if (n != 8) return none();
     Args a(argv);
     const at::Tensor* q = a.in(F16, 4);
@@ -163,7 +164,7 @@ PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     const int block = a.integer();
     PyObject *gi = a.given(I8), *gs = a.given(F32);
     void* st = a.stream();
-    if (!a.ok || block < 1 || !fits(*q) || !cs != !sn) return none();
+    if (!a.ok || block < 1 || !fits(*q) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
     const int64_t B = q->size(0), H = q->size(1), N = q->size(2), D = q->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
@@ -174,15 +175,15 @@ PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_ssize_t n) {
         void *pq = q->data_ptr(), *pi = i8.p(), *ps = sc.p();
         const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
         const int e = call([&] {
-            return c ? api.rope_quant_q(pq, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st)
-                     : api.quant_q(pq, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st);
+            return ROPE ? api.rope_quant_q(pq, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st)
+                        : api.quant_q(pq, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st);
         });
         return result(e, {&i8, &sc});
     });
 }
 
-// (k, cos | None, sin | None, block_k, k_i8 | None, k_scale | None, k_mean | None, workspace | None, stream | None)
-PyObject* py_smooth_quant_k(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+// (k, cos, sin, block_k, k_i8 | None, k_scale | None, k_mean | None, workspace | None, stream | None); tables as above
+template <bool ROPE> PyObject* py_smooth_quant_k(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     if (n != 9) return none();
     Args a(argv);
     const at::Tensor* k = a.in(F16, 4);
@@ -190,7 +191,7 @@ PyObject* py_smooth_quant_k(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     const int block = a.integer();
     PyObject *gi = a.given(I8), *gs = a.given(F32), *gm = a.given(F32), *gw = a.scratch();
     void* st = a.stream();
-    if (!a.ok || block < 1 || !fits(*k) || !cs != !sn) return none();
+    if (!a.ok || block < 1 || !fits(*k) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
     const int64_t B = k->size(0), H = k->size(1), N = k->size(2), D = k->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
@@ -204,8 +205,8 @@ PyObject* py_smooth_quant_k(PyObject*, PyObject* const* argv, Py_ssize_t n) {
         const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
         const size_t wb = ws.size();
         const int e = call([&] {
-            return c ? api.rope_smooth_quant_k(pk, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st)
-                     : api.smooth_quant_k(pk, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st);
+            return ROPE ? api.rope_smooth_quant_k(pk, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st)
+                        : api.smooth_quant_k(pk, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st);
         });
         return result(e, {&i8, &sc, &mean});
     });
@@ -351,8 +352,10 @@ PyObject* py_init(PyObject*, PyObject* const* argv, Py_ssize_t n) {
 
 PyMethodDef methods[] = {
     {"init", (PyCFunction)(void (*)(void))py_init, METH_FASTCALL, nullptr},
-    {"quant_q", (PyCFunction)(void (*)(void))py_quant_q, METH_FASTCALL, nullptr},
-    {"smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k, METH_FASTCALL, nullptr},
+    {"quant_q", (PyCFunction)(void (*)(void))py_quant_q<false>, METH_FASTCALL, nullptr},
+    {"rope_quant_q", (PyCFunction)(void (*)(void))py_quant_q<true>, METH_FASTCALL, nullptr},
+    {"smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k<false>, METH_FASTCALL, nullptr},
+    {"rope_smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k<true>, METH_FASTCALL, nullptr},
     {"quant_qk", (PyCFunction)(void (*)(void))py_quant_qk, METH_FASTCALL, nullptr},
     {"quant_v", (PyCFunction)(void (*)(void))py_quant_v, METH_FASTCALL, nullptr},
     {"attn", (PyCFunction)(void (*)(void))py_attn, METH_FASTCALL, nullptr},
