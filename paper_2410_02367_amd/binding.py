@@ -439,7 +439,7 @@ def sage_attn_pv_int8_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_sca
                                       out=None, workspace=None, stream=None):
     """sage_attn_pv_int8_cross_fwd with the keys cut into n_splits chunks (0 = chosen from the shape) and a merge.
     workspace: uint8 device tensor of at least sage_attn_split_workspace(...) bytes (allocated here if not given)."""
-    r = _fast().attn(2, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
+    r = _fast().attn_pv_int8(2, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_cross_split_fwd")
     B, H, Nkv, D = k_i8.shape
@@ -501,7 +501,7 @@ def sage_attn_pv_int8_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal: 
                           block_q: int = 128, block_k: int = 64, out=None, stream=None):
     """Algorithm 1's loop with the INT8 second product of Section 4.3 (SAGEAttn-vB; block sizes 1: -vT)
     on pre-quantized Q^, K^ and V^^T -> O [B,H,N,D] fp16."""
-    r = _fast().attn(0, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    r = _fast().attn_pv_int8(0, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_fwd")
     B, H, N, D = q_i8.shape
@@ -524,7 +524,7 @@ def sage_attn_pv_int8_cross_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, ca
                                 block_q: int = 128, block_k: int = 64, out=None, stream=None):
     """sage_attn_pv_int8_fwd with Nq queries (q_i8 [B,H,Nq,D]) against Nkv keys (k_i8 [B,H,Nkv,D], v_i8t from
     sage_quant_v of the Nkv values) -> O [B,H,Nq,D]; end-aligned causal mask (needs Nq <= Nkv)."""
-    r = _fast().attn(1, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
+    r = _fast().attn_pv_int8(1, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_cross_fwd")
     B, H, Nq, D = q_i8.shape

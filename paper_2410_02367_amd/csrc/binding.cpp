@@ -265,25 +265,25 @@ PyObject* py_quant_v(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     });
 }
 
-// (kind, q_i8, q_scale, k_i8, k_scale, v, v_scale | None, causal, sm_scale, block_q, block_k, n_splits, out | None, workspace | None,
-// stream | None); v fp16 with v_scale None, or the INT8 codes; kind: 0 equal lengths, 1 any lengths, 2 keys split
-PyObject* py_attn(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+// (kind, q_i8, q_scale, k_i8, k_scale, v, v_scale, causal, sm_scale, block_q, block_k, n_splits, out | None, workspace | None,
+// stream | None); PV8: v the INT8 codes, with their scales, else v fp16 and v_scale None; kind: 0 equal lengths, 1 any lengths,
+// 2 keys split
+template <bool PV8> PyObject* py_attn(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     if (n != 15) return none();
     Args a(argv);
     const int kind = a.integer();
-    const bool pv8 = argv[6] != Py_None;
-    const at::Tensor *qi = a.in(I8, 4), *qs = a.in(F32, 0), *ki = a.in(I8, 4), *ks = a.in(F32, 0), *v = a.in(pv8 ? I8 : F16, 4);
+    const at::Tensor *qi = a.in(I8, 4), *qs = a.in(F32, 0), *ki = a.in(I8, 4), *ks = a.in(F32, 0), *v = a.in(PV8 ? I8 : F16, 4);
     PyObject* gvs = a.given(F32);
     const int causal = a.integer();
     const float sm = a.real();
     const int bq = a.integer(), bk = a.integer(), splits = a.integer();
     PyObject *go = a.given(F16), *gw = a.given(U8);
     void* st = a.stream();
-    if (!a.ok || !fits(*qi) || !fits(*ki) || !fits(*v)) return none();
+    if (!a.ok || PV8 != (gvs != nullptr) || !fits(*qi) || !fits(*ki) || !fits(*v)) return none();
     const int64_t B = ki->size(0), H = ki->size(1), Nkv = ki->size(2), D = ki->size(3), Nq = qi->size(2);
     if (qi->size(0) != B || qi->size(1) != H || qi->size(3) != D || v->size(0) != B || v->size(1) != H) return none();
     if (kind == 0 && Nq != Nkv) return none();
-    if (pv8 ? v->size(2) != D || v->size(3) != blocks(Nkv, 64) * 64 : v->size(2) != Nkv || v->size(3) != D) return none();
+    if (PV8 ? v->size(2) != D || v->size(3) != blocks(Nkv, 64) * 64 : v->size(2) != Nkv || v->size(3) != D) return none();
     return guarded([&] {
         Buffer o, ws;
         o.take(go, *v, {B, H, Nq, D}, F16);
@@ -295,7 +295,7 @@ PyObject* py_attn(PyObject*, PyObject* const* argv, Py_ssize_t n) {
         const int e = call([&] {
             const int8_t *q8 = (const int8_t*)p0, *k8 = (const int8_t*)p2, *v8 = (const int8_t*)p4;
             const float *qsc = (const float*)p1, *ksc = (const float*)p3, *vsc = (const float*)pvs;
-            if (pv8)
+            if (PV8)
                 return kind != 2 ? api.pv8_cross(q8, qsc, k8, ksc, v8, vsc, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
                                   : api.pv8_split(q8, qsc, k8, ksc, v8, vsc, po, pw, wb, B, H, Nq, Nkv, D, c, sm, bq, bk, splits, st);
             return kind != 2 ? api.attn_cross(q8, qsc, k8, ksc, p4, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
@@ -358,7 +358,8 @@ PyMethodDef methods[] = {
     {"rope_smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k<true>, METH_FASTCALL, nullptr},
     {"quant_qk", (PyCFunction)(void (*)(void))py_quant_qk, METH_FASTCALL, nullptr},
     {"quant_v", (PyCFunction)(void (*)(void))py_quant_v, METH_FASTCALL, nullptr},
-    {"attn", (PyCFunction)(void (*)(void))py_attn, METH_FASTCALL, nullptr},
+    {"attn", (PyCFunction)(void (*)(void))py_attn<false>, METH_FASTCALL, nullptr},
+    {"attn_pv_int8", (PyCFunction)(void (*)(void))py_attn<true>, METH_FASTCALL, nullptr},
     {"attention", (PyCFunction)(void (*)(void))py_attention, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sage_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
