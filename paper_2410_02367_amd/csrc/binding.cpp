@@ -90,8 +90,9 @@ struct Args {
     void* stream() {
         PyObject* o = *a++;
         if (o != Py_None) {
-            if (!PyLong_Check(o)) { ok = false; return nullptr; }
-            return PyLong_AsVoidPtr(o);
+            void* p = PyLong_Check(o) ? PyLong_AsVoidPtr(o) : nullptr;
+            if (!PyLong_Check(o) || PyErr_Occurred()) { PyErr_Clear(); ok = false; }
+            return p;
         }
         if (!ok) return nullptr;
         PyObject* dev = PyObject_CallNoArgs(get_device);
@@ -131,10 +132,14 @@ template <class F> int call(F&& f) {
     Py_END_ALLOW_THREADS
     return st;
 }
-template <class F> PyObject* guarded(F&& f) {
+// What the interpreter calls.  No C++ exception may pass through it: what throws here -- an allocation that fails, the
+// sizes of a tensor that has none in numbers (symbolic, nested) -- the Python path meets again and reports.
+using Entry = PyObject* (*)(PyObject* const*, Py_ssize_t);
+template <Entry F> PyObject* guarded(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     try {
-        return f();
-    } catch (const std::exception& e) {          // an allocation that failed: the Python path meets it again and reports it
+        return F(argv, n);
+    } catch (const std::exception&) {
+        PyErr_Clear();
         return none();
     }
 }
@@ -155,7 +160,7 @@ bool fits(const at::Tensor& t) {
 
 // (q, cos, sin, sm_scale, block_q, q_i8 | None, q_scale | None, stream | None); the tables both None unless ROPE: the call is
 // named by its entry, so that a missing table does not turn it into the other one
-template <bool ROPE> PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+template <bool ROPE> PyObject* py_quant_q(PyObject* const* argv, Py_ssize_t n) {
     if (n != 8) return none();
     Args a(argv);
     const at::Tensor* q = a.in(F16, 4);
@@ -168,22 +173,20 @@ template <bool ROPE> PyObject* py_quant_q(PyObject*, PyObject* const* argv, Py_s
     const int64_t B = q->size(0), H = q->size(1), N = q->size(2), D = q->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
-    return guarded([&] {
-        Buffer i8, sc;
-        i8.take(gi, *q, {B, H, N, D}, I8);
-        sc.take(gs, *q, {B, H, blocks(N, block)}, F32);
-        void *pq = q->data_ptr(), *pi = i8.p(), *ps = sc.p();
-        const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
-        const int e = call([&] {
-            return ROPE ? api.rope_quant_q(pq, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st)
-                        : api.quant_q(pq, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st);
-        });
-        return result(e, {&i8, &sc});
+    Buffer i8, sc;
+    i8.take(gi, *q, {B, H, N, D}, I8);
+    sc.take(gs, *q, {B, H, blocks(N, block)}, F32);
+    void *pq = q->data_ptr(), *pi = i8.p(), *ps = sc.p();
+    const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
+    const int e = call([&] {
+        return ROPE ? api.rope_quant_q(pq, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st)
+                    : api.quant_q(pq, (int8_t*)pi, (float*)ps, B, H, N, D, sm, block, st);
     });
+    return result(e, {&i8, &sc});
 }
 
 // (k, cos, sin, block_k, k_i8 | None, k_scale | None, k_mean | None, workspace | None, stream | None); tables as above
-template <bool ROPE> PyObject* py_smooth_quant_k(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+template <bool ROPE> PyObject* py_smooth_quant_k(PyObject* const* argv, Py_ssize_t n) {
     if (n != 9) return none();
     Args a(argv);
     const at::Tensor* k = a.in(F16, 4);
@@ -195,25 +198,23 @@ template <bool ROPE> PyObject* py_smooth_quant_k(PyObject*, PyObject* const* arg
     const int64_t B = k->size(0), H = k->size(1), N = k->size(2), D = k->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
-    return guarded([&] {
-        Buffer i8, sc, mean, ws;
-        i8.take(gi, *k, {B, H, N, D}, I8);
-        sc.take(gs, *k, {B, H, blocks(N, block)}, F32);
-        mean.take(gm, *k, {B, H, D}, F32);
-        ws.bytes(gw, *k, api.k_workspace(B, H, N, D));
-        void *pk = k->data_ptr(), *pi = i8.p(), *ps = sc.p(), *pm = mean.p(), *pw = ws.p();
-        const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
-        const size_t wb = ws.size();
-        const int e = call([&] {
-            return ROPE ? api.rope_smooth_quant_k(pk, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st)
-                        : api.smooth_quant_k(pk, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st);
-        });
-        return result(e, {&i8, &sc, &mean});
+    Buffer i8, sc, mean, ws;
+    i8.take(gi, *k, {B, H, N, D}, I8);
+    sc.take(gs, *k, {B, H, blocks(N, block)}, F32);
+    mean.take(gm, *k, {B, H, D}, F32);
+    ws.bytes(gw, *k, api.k_workspace(B, H, N, D));
+    void *pk = k->data_ptr(), *pi = i8.p(), *ps = sc.p(), *pm = mean.p(), *pw = ws.p();
+    const void *pc = c ? c->data_ptr() : nullptr, *pn = s ? s->data_ptr() : nullptr;
+    const size_t wb = ws.size();
+    const int e = call([&] {
+        return ROPE ? api.rope_smooth_quant_k(pk, (const float*)pc, (const float*)pn, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st)
+                    : api.smooth_quant_k(pk, (int8_t*)pi, (float*)ps, (float*)pm, pw, wb, B, H, N, D, block, st);
     });
+    return result(e, {&i8, &sc, &mean});
 }
 
 // (q, k, sm_scale, block_q, block_k, q_i8, q_scale, k_i8, k_scale, k_mean, workspace, stream), the last seven | None
-PyObject* py_quant_qk(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+PyObject* py_quant_qk(PyObject* const* argv, Py_ssize_t n) {
     if (n != 12) return none();
     Args a(argv);
     const at::Tensor *q = a.in(F16, 4), *k = a.in(F16, 4);
@@ -224,25 +225,23 @@ PyObject* py_quant_qk(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     if (!a.ok || bq < 1 || bk < 1 || !fits(*q) || !fits(*k)) return none();
     const int64_t B = q->size(0), H = q->size(1), Nq = q->size(2), D = q->size(3), Nkv = k->size(2);
     if (k->size(0) != B || k->size(1) != H || k->size(3) != D) return none();
-    return guarded([&] {
-        Buffer qi, qs, ki, ks, mean, ws;
-        qi.take(gqi, *q, {B, H, Nq, D}, I8);
-        qs.take(gqs, *q, {B, H, blocks(Nq, bq)}, F32);
-        ki.take(gki, *q, {B, H, Nkv, D}, I8);
-        ks.take(gks, *q, {B, H, blocks(Nkv, bk)}, F32);
-        mean.take(gm, *q, {B, H, D}, F32);
-        ws.bytes(gw, *q, api.k_workspace(B, H, Nkv, D));
-        void *pq = q->data_ptr(), *pk = k->data_ptr(), *p0 = qi.p(), *p1 = qs.p(), *p2 = ki.p(), *p3 = ks.p(), *p4 = mean.p(), *pw = ws.p();
-        const size_t wb = ws.size();
-        const int e = call([&] {
-            return api.quant_qk(pq, pk, (int8_t*)p0, (float*)p1, (int8_t*)p2, (float*)p3, (float*)p4, pw, wb, B, H, Nq, Nkv, D, sm, bq, bk, st);
-        });
-        return result(e, {&qi, &qs, &ki, &ks, &mean});
+    Buffer qi, qs, ki, ks, mean, ws;
+    qi.take(gqi, *q, {B, H, Nq, D}, I8);
+    qs.take(gqs, *q, {B, H, blocks(Nq, bq)}, F32);
+    ki.take(gki, *q, {B, H, Nkv, D}, I8);
+    ks.take(gks, *q, {B, H, blocks(Nkv, bk)}, F32);
+    mean.take(gm, *q, {B, H, D}, F32);
+    ws.bytes(gw, *q, api.k_workspace(B, H, Nkv, D));
+    void *pq = q->data_ptr(), *pk = k->data_ptr(), *p0 = qi.p(), *p1 = qs.p(), *p2 = ki.p(), *p3 = ks.p(), *p4 = mean.p(), *pw = ws.p();
+    const size_t wb = ws.size();
+    const int e = call([&] {
+        return api.quant_qk(pq, pk, (int8_t*)p0, (float*)p1, (int8_t*)p2, (float*)p3, (float*)p4, pw, wb, B, H, Nq, Nkv, D, sm, bq, bk, st);
     });
+    return result(e, {&qi, &qs, &ki, &ks, &mean});
 }
 
 // (v, v_i8t | None, v_scale | None, workspace | None, stream | None)
-PyObject* py_quant_v(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+PyObject* py_quant_v(PyObject* const* argv, Py_ssize_t n) {
     if (n != 5) return none();
     Args a(argv);
     const at::Tensor* v = a.in(F16, 4);
@@ -254,21 +253,19 @@ PyObject* py_quant_v(PyObject*, PyObject* const* argv, Py_ssize_t n) {
         const at::Tensor& t = *tensor(gi);
         if (t.dim() != 4 || t.size(0) != B || t.size(1) != H || t.size(2) != D || t.size(3) != Np) return none();
     }
-    return guarded([&] {
-        Buffer i8, sc, ws;
-        i8.take(gi, *v, {B, H, D, Np}, I8);
-        sc.take(gs, *v, {B, H, D}, F32);
-        ws.bytes(gw, *v, api.v_workspace(B, H, N, D));
-        void *pv = v->data_ptr(), *pi = i8.p(), *ps = sc.p(), *pw = ws.p();
-        const size_t wb = ws.size();
-        return result(call([&] { return api.quant_v(pv, (int8_t*)pi, (float*)ps, pw, wb, B, H, N, D, st); }), {&i8, &sc});
-    });
+    Buffer i8, sc, ws;
+    i8.take(gi, *v, {B, H, D, Np}, I8);
+    sc.take(gs, *v, {B, H, D}, F32);
+    ws.bytes(gw, *v, api.v_workspace(B, H, N, D));
+    void *pv = v->data_ptr(), *pi = i8.p(), *ps = sc.p(), *pw = ws.p();
+    const size_t wb = ws.size();
+    return result(call([&] { return api.quant_v(pv, (int8_t*)pi, (float*)ps, pw, wb, B, H, N, D, st); }), {&i8, &sc});
 }
 
 // (kind, q_i8, q_scale, k_i8, k_scale, v, v_scale, causal, sm_scale, block_q, block_k, n_splits, out | None, workspace | None,
 // stream | None); PV8: v the INT8 codes, with their scales, else v fp16 and v_scale None; kind: 0 equal lengths, 1 any lengths,
 // 2 keys split
-template <bool PV8> PyObject* py_attn(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+template <bool PV8> PyObject* py_attn(PyObject* const* argv, Py_ssize_t n) {
     if (n != 15) return none();
     Args a(argv);
     const int kind = a.integer();
@@ -284,29 +281,27 @@ template <bool PV8> PyObject* py_attn(PyObject*, PyObject* const* argv, Py_ssize
     if (qi->size(0) != B || qi->size(1) != H || qi->size(3) != D || v->size(0) != B || v->size(1) != H) return none();
     if (kind == 0 && Nq != Nkv) return none();
     if (PV8 ? v->size(2) != D || v->size(3) != blocks(Nkv, 64) * 64 : v->size(2) != Nkv || v->size(3) != D) return none();
-    return guarded([&] {
-        Buffer o, ws;
-        o.take(go, *v, {B, H, Nq, D}, F16);
-        if (kind == 2) ws.bytes(gw, *v, api.split_workspace(B, H, Nq, Nkv, D, causal != 0, splits));
-        void *p0 = qi->data_ptr(), *p1 = qs->data_ptr(), *p2 = ki->data_ptr(), *p3 = ks->data_ptr(), *p4 = v->data_ptr(), *po = o.p(), *pw = ws.p();
-        void* pvs = gvs ? tensor(gvs)->data_ptr() : nullptr;
-        const size_t wb = ws.size();
-        const int c = causal != 0;
-        const int e = call([&] {
-            const int8_t *q8 = (const int8_t*)p0, *k8 = (const int8_t*)p2, *v8 = (const int8_t*)p4;
-            const float *qsc = (const float*)p1, *ksc = (const float*)p3, *vsc = (const float*)pvs;
-            if (PV8)
-                return kind != 2 ? api.pv8_cross(q8, qsc, k8, ksc, v8, vsc, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
-                                  : api.pv8_split(q8, qsc, k8, ksc, v8, vsc, po, pw, wb, B, H, Nq, Nkv, D, c, sm, bq, bk, splits, st);
-            return kind != 2 ? api.attn_cross(q8, qsc, k8, ksc, p4, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
-                              : api.attn_split(q8, qsc, k8, ksc, p4, po, pw, wb, B, H, Nq, Nkv, D, c, sm, bq, bk, splits, st);
-        });
-        return result(e, {&o});
+    Buffer o, ws;
+    o.take(go, *v, {B, H, Nq, D}, F16);
+    if (kind == 2) ws.bytes(gw, *v, api.split_workspace(B, H, Nq, Nkv, D, causal != 0, splits));
+    void *p0 = qi->data_ptr(), *p1 = qs->data_ptr(), *p2 = ki->data_ptr(), *p3 = ks->data_ptr(), *p4 = v->data_ptr(), *po = o.p(), *pw = ws.p();
+    void* pvs = gvs ? tensor(gvs)->data_ptr() : nullptr;
+    const size_t wb = ws.size();
+    const int c = causal != 0;
+    const int e = call([&] {
+        const int8_t *q8 = (const int8_t*)p0, *k8 = (const int8_t*)p2, *v8 = (const int8_t*)p4;
+        const float *qsc = (const float*)p1, *ksc = (const float*)p3, *vsc = (const float*)pvs;
+        if (PV8)
+            return kind != 2 ? api.pv8_cross(q8, qsc, k8, ksc, v8, vsc, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
+                              : api.pv8_split(q8, qsc, k8, ksc, v8, vsc, po, pw, wb, B, H, Nq, Nkv, D, c, sm, bq, bk, splits, st);
+        return kind != 2 ? api.attn_cross(q8, qsc, k8, ksc, p4, po, B, H, Nq, Nkv, D, c, sm, bq, bk, st)
+                          : api.attn_split(q8, qsc, k8, ksc, p4, po, pw, wb, B, H, Nq, Nkv, D, c, sm, bq, bk, splits, st);
     });
+    return result(e, {&o});
 }
 
 // (q, k, v, causal, sm_scale, block_q, block_k, pv_int8, out | None, workspace | None, stream | None)
-PyObject* py_attention(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+PyObject* py_attention(PyObject* const* argv, Py_ssize_t n) {
     if (n != 11) return none();
     Args a(argv);
     const at::Tensor *q = a.in(F16, 4), *k = a.in(F16, 4), *v = a.in(F16, 4);
@@ -319,18 +314,16 @@ PyObject* py_attention(PyObject*, PyObject* const* argv, Py_ssize_t n) {
     const int64_t B = q->size(0), H = q->size(1), Nq = q->size(2), D = q->size(3), Nkv = k->size(2);
     if (k->size(0) != B || k->size(1) != H || k->size(3) != D) return none();
     if (go && tensor(go)->sizes() != q->sizes()) return none();
-    return guarded([&] {
-        Buffer o, ws;
-        o.take(go, *q, {B, H, Nq, D}, F16);
-        ws.bytes(gw, *q, api.attention_workspace(B, H, Nq, Nkv, D, causal != 0, bq, bk, pv8 != 0));
-        void *pq = q->data_ptr(), *pk = k->data_ptr(), *pv = v->data_ptr(), *po = o.p(), *pw = ws.p();
-        const size_t wb = ws.size();
-        return result(call([&] { return api.attention(pq, pk, pv, po, pw, wb, B, H, Nq, Nkv, D, causal != 0, sm, bq, bk, pv8 != 0, st); }), {&o});
-    });
+    Buffer o, ws;
+    o.take(go, *q, {B, H, Nq, D}, F16);
+    ws.bytes(gw, *q, api.attention_workspace(B, H, Nq, Nkv, D, causal != 0, bq, bk, pv8 != 0));
+    void *pq = q->data_ptr(), *pk = k->data_ptr(), *pv = v->data_ptr(), *po = o.p(), *pw = ws.p();
+    const size_t wb = ws.size();
+    return result(call([&] { return api.attention(pq, pk, pv, po, pw, wb, B, H, Nq, Nkv, D, causal != 0, sm, bq, bk, pv8 != 0, st); }), {&o});
 }
 
 // (torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, 15 addresses in Api's order)
-PyObject* py_init(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+PyObject* py_init(PyObject* const* argv, Py_ssize_t n) {
     constexpr int COUNT = sizeof(Api) / sizeof(void*);
     if (n != 2 + COUNT) {
         PyErr_SetString(PyExc_ValueError, "init: wrong number of addresses");
@@ -351,16 +344,16 @@ PyObject* py_init(PyObject*, PyObject* const* argv, Py_ssize_t n) {
 }
 
 PyMethodDef methods[] = {
-    {"init", (PyCFunction)(void (*)(void))py_init, METH_FASTCALL, nullptr},
-    {"quant_q", (PyCFunction)(void (*)(void))py_quant_q<false>, METH_FASTCALL, nullptr},
-    {"rope_quant_q", (PyCFunction)(void (*)(void))py_quant_q<true>, METH_FASTCALL, nullptr},
-    {"smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k<false>, METH_FASTCALL, nullptr},
-    {"rope_smooth_quant_k", (PyCFunction)(void (*)(void))py_smooth_quant_k<true>, METH_FASTCALL, nullptr},
-    {"quant_qk", (PyCFunction)(void (*)(void))py_quant_qk, METH_FASTCALL, nullptr},
-    {"quant_v", (PyCFunction)(void (*)(void))py_quant_v, METH_FASTCALL, nullptr},
-    {"attn", (PyCFunction)(void (*)(void))py_attn<false>, METH_FASTCALL, nullptr},
-    {"attn_pv_int8", (PyCFunction)(void (*)(void))py_attn<true>, METH_FASTCALL, nullptr},
-    {"attention", (PyCFunction)(void (*)(void))py_attention, METH_FASTCALL, nullptr},
+    {"init", (PyCFunction)(void (*)(void))guarded<py_init>, METH_FASTCALL, nullptr},
+    {"quant_q", (PyCFunction)(void (*)(void))guarded<py_quant_q<false>>, METH_FASTCALL, nullptr},
+    {"rope_quant_q", (PyCFunction)(void (*)(void))guarded<py_quant_q<true>>, METH_FASTCALL, nullptr},
+    {"smooth_quant_k", (PyCFunction)(void (*)(void))guarded<py_smooth_quant_k<false>>, METH_FASTCALL, nullptr},
+    {"rope_smooth_quant_k", (PyCFunction)(void (*)(void))guarded<py_smooth_quant_k<true>>, METH_FASTCALL, nullptr},
+    {"quant_qk", (PyCFunction)(void (*)(void))guarded<py_quant_qk>, METH_FASTCALL, nullptr},
+    {"quant_v", (PyCFunction)(void (*)(void))guarded<py_quant_v>, METH_FASTCALL, nullptr},
+    {"attn", (PyCFunction)(void (*)(void))guarded<py_attn<false>>, METH_FASTCALL, nullptr},
+    {"attn_pv_int8", (PyCFunction)(void (*)(void))guarded<py_attn<true>>, METH_FASTCALL, nullptr},
+    {"attention", (PyCFunction)(void (*)(void))guarded<py_attention>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sage_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
