@@ -184,6 +184,29 @@ def _stream(stream) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _elsewhere(stream) -> bool:
+    """A stream was named and it is not the current one.  (Where the GPU was never used no tensor is in its memory, and
+    the call ends in an error either way.)"""
+    return torch.cuda.is_initialized() and _stream(stream) != _stream(None)
+
+
+def _on_stream(stream, call, *args):
+    """call(*args) with `stream` as the current stream.  The allocator hands memory out in the order of the stream it was
+    asked on: what a call allocates (scratch above all, which is free again when the wrapper returns) is written while
+    `stream` runs, so it has to come from there.  The caller's own stream is noted on the outputs, which it will read."""
+    caller = torch.cuda.current_stream()
+    if not isinstance(stream, torch.cuda.Stream):
+        handle = _stream(stream)
+        # (0 and 1 name the default stream)
+        stream = torch.cuda.ExternalStream(handle) if handle not in (0, 1) else torch.cuda.default_stream()
+    with torch.cuda.stream(stream):
+        r = call(*args)
+    for t in r if isinstance(r, tuple) else (r,):
+        if not any(t is a for a in args):
+            t.record_stream(caller)
+    return r
+
+
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError(f"{name}: expected a contiguous {dtype} tensor in device memory")
@@ -207,6 +230,8 @@ def sage_rope_quant_q(q: torch.Tensor, rope_cos, rope_sin, sm_scale: float, bloc
     r = _fast().rope_quant_q(q, rope_cos, rope_sin, sm_scale, block_q, q_i8, q_scale, _handle(stream))
     if r is not None:
         return _answer(r, "sage_rope_quant_q")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_rope_quant_q, q, rope_cos, rope_sin, sm_scale, block_q, q_i8, q_scale)
     B, H, N, D = q.shape
     pc, ps = _rope_tables(rope_cos, rope_sin, N, D)
     if q_i8 is None:
@@ -227,6 +252,8 @@ def sage_rope_smooth_quant_k(k: torch.Tensor, rope_cos, rope_sin, block_k: int =
     r = _fast().rope_smooth_quant_k(k, rope_cos, rope_sin, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_rope_smooth_quant_k")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_rope_smooth_quant_k, k, rope_cos, rope_sin, block_k, k_i8, k_scale, k_mean, workspace)
     B, H, N, D = k.shape
     pc, ps = _rope_tables(rope_cos, rope_sin, N, D)
     if k_i8 is None:
@@ -253,6 +280,8 @@ def sage_quant_q(q: torch.Tensor, sm_scale: float, block_q: int = 128, q_i8=None
     r = _fast().quant_q(q, None, None, sm_scale, block_q, q_i8, q_scale, _handle(stream))
     if r is not None:
         return _answer(r, "sage_quant_q")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_quant_q, q, sm_scale, block_q, q_i8, q_scale)
     B, H, N, D = q.shape
     if q_i8 is None:
         q_i8 = torch.empty((B, H, N, D), dtype=torch.int8, device=q.device)
@@ -276,6 +305,8 @@ def sage_smooth_quant_k(k: torch.Tensor, block_k: int = 64, k_i8=None, k_scale=N
     r = _fast().smooth_quant_k(k, None, None, block_k, k_i8, k_scale, k_mean, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_smooth_quant_k")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_smooth_quant_k, k, block_k, k_i8, k_scale, k_mean, workspace)
     B, H, N, D = k.shape
     if k_i8 is None:
         k_i8 = torch.empty((B, H, N, D), dtype=torch.int8, device=k.device)
@@ -301,6 +332,9 @@ def sage_quant_qk(q: torch.Tensor, k: torch.Tensor, sm_scale: float, block_q: in
     r = _fast().quant_qk(q, k, sm_scale, block_q, block_k, q_i8, q_scale, k_i8, k_scale, k_mean, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_quant_qk")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_quant_qk, q, k, sm_scale, block_q, block_k, q_i8, q_scale, k_i8, k_scale,
+                          k_mean, workspace)
     B, H, Nq, D = q.shape
     Nkv = k.shape[2]
     if k.shape[0] != B or k.shape[1] != H or k.shape[3] != D:
@@ -336,6 +370,8 @@ NOALLOC_SCRATCH_BYTES = 4 << 20     # SAGE_NOALLOC_SCRATCH_BYTES of include/sage
 def sage_smooth_quant_k_noalloc(k: torch.Tensor, block_k: int = 64, k_i8=None, k_scale=None, k_mean=None, stream=None):
     """sage_smooth_quant_k without a workspace argument: the library call allocates nothing (its scratch is a
     static device array); pass k_i8 / k_scale / k_mean as well and neither does this wrapper."""
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_smooth_quant_k_noalloc, k, block_k, k_i8, k_scale, k_mean)
     B, H, N, D = k.shape
     if k_i8 is None:
         k_i8 = torch.empty((B, H, N, D), dtype=torch.int8, device=k.device)
@@ -359,6 +395,8 @@ def sage_attn_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_scale: float
     r = _fast().attn(0, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_fwd, q_i8, q_scale, k_i8, k_scale, v, causal, sm_scale, block_q, block_k, out)
     B, H, N, D = v.shape
     if out is None:
         out = torch.empty((B, H, N, D), dtype=torch.float16, device=v.device)
@@ -379,6 +417,9 @@ def sage_attn_cross_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_scale:
     r = _fast().attn(1, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_cross_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_cross_fwd, q_i8, q_scale, k_i8, k_scale, v, causal, sm_scale, block_q,
+                          block_k, out)
     B, H, Nkv, D = v.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(k_i8.shape) != (B, H, Nkv, D):
@@ -413,6 +454,9 @@ def sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, causal: bool, sm_
     r = _fast().attn(2, q_i8, q_scale, k_i8, k_scale, v, None, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_cross_split_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_cross_split_fwd, q_i8, q_scale, k_i8, k_scale, v, causal, sm_scale,
+                          block_q, block_k, n_splits, out, workspace)
     B, H, Nkv, D = v.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(k_i8.shape) != (B, H, Nkv, D):
@@ -442,6 +486,9 @@ def sage_attn_pv_int8_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_sca
     r = _fast().attn_pv_int8(2, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, n_splits, out, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_cross_split_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_pv_int8_cross_split_fwd, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale,
+                          causal, sm_scale, block_q, block_k, n_splits, out, workspace)
     B, H, Nkv, D = k_i8.shape
     Nq = q_i8.shape[2]
     if tuple(q_i8.shape) != (B, H, Nq, D) or tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(Nkv)):
@@ -477,6 +524,8 @@ def sage_quant_v(v: torch.Tensor, v_i8t=None, v_scale=None, workspace=None, stre
     r = _fast().quant_v(v, v_i8t, v_scale, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_quant_v")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_quant_v, v, v_i8t, v_scale, workspace)
     B, H, N, D = v.shape
     Np = sage_quant_v_pitch(N)
     if v_i8t is None:
@@ -504,6 +553,9 @@ def sage_attn_pv_int8_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal: 
     r = _fast().attn_pv_int8(0, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_pv_int8_fwd, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal,
+                          sm_scale, block_q, block_k, out)
     B, H, N, D = q_i8.shape
     if tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(N)):
         raise TypeError(f"v_i8t: expected shape {(B, H, D, sage_quant_v_pitch(N))}")
@@ -527,6 +579,9 @@ def sage_attn_pv_int8_cross_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, ca
     r = _fast().attn_pv_int8(1, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal, sm_scale, block_q, block_k, 0, out, None, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attn_pv_int8_cross_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_pv_int8_cross_fwd, q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, causal,
+                          sm_scale, block_q, block_k, out)
     B, H, Nq, D = q_i8.shape
     Nkv = k_i8.shape[2]
     if tuple(k_i8.shape) != (B, H, Nkv, D) or tuple(v_i8t.shape) != (B, H, D, sage_quant_v_pitch(Nkv)):
@@ -547,6 +602,8 @@ def sage_attn_pv_int8_cross_fwd(q_i8, q_scale, k_i8, k_scale, v_i8t, v_scale, ca
 def sage_attn_qk_i32_debug(q_i8, k_i8, s_i32=None, block_q: int = 128, block_k: int = 64, wg_rows: int = 0, stream=None):
     """Raw int32 scores Q^ K^^T [B,H,N,N] through the attention kernel's MFMA path (test hook);
     wg_rows = 128 / 256 names the workgroup shape, 0 leaves it to the launcher."""
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_qk_i32_debug, q_i8, k_i8, s_i32, block_q, block_k, wg_rows)
     B, H, N, D = q_i8.shape
     if s_i32 is None:
         s_i32 = torch.empty((B, H, N, N), dtype=torch.int32, device=q_i8.device)
@@ -563,6 +620,8 @@ def sage_attn_clock_debug(q_i8, q_scale, k_i8, k_scale, v, out=None, causal: boo
     """sage_attn_fwd's kernel at D = 128 in its 256-row shape, built with counters (measurement hook) ->
     (out, clocks): clocks [B*H*ceil(N/256)*8, 4] int64, per wavefront shader-clock ticks, 100 MHz ticks, raises
     of the running maximum, key tiles visited."""
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attn_clock_debug, q_i8, q_scale, k_i8, k_scale, v, out, causal, block_q, block_k)
     B, H, N, D = q_i8.shape
     if out is None:
         out = torch.empty((B, H, N, D), dtype=torch.float16, device=q_i8.device)
@@ -580,6 +639,8 @@ def sage_attn_clock_debug(q_i8, q_scale, k_i8, k_scale, v, out=None, causal: boo
 def sage_microbench(kind: int, waves_per_simd: int, workgroups: int, iters: int, data, out=None, stream=None):
     """One launch of an instruction-stream probe (see include/sage.h) -> out [wavefronts, 4] uint64 as int64:
     shader-clock ticks, constant-rate ticks, checksum, 0.  data: 1024 int32 of random bits on the device."""
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_microbench, kind, waves_per_simd, workgroups, iters, data, out)
     waves = workgroups * 4 * waves_per_simd
     if out is None:
         out = torch.empty((waves, 4), dtype=torch.int64, device=data.device)
@@ -604,6 +665,8 @@ def sage_attention_fwd(q, k, v, causal: bool, sm_scale: float, block_q: int = 12
     r = _fast().attention(q, k, v, causal, sm_scale, block_q, block_k, pv_int8, out, workspace, _handle(stream))
     if r is not None:
         return _answer(r, "sage_attention_fwd")
+    if stream is not None and _elsewhere(stream):
+        return _on_stream(stream, sage_attention_fwd, q, k, v, causal, sm_scale, block_q, block_k, pv_int8, out, workspace)
     B, H, Nq, D = q.shape
     kv_shape = k.shape
     Nkv = kv_shape[2]

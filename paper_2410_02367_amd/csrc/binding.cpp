@@ -50,7 +50,7 @@ bool on_device(const at::Tensor& t) { return t.is_cuda() && t.is_contiguous(); }
 // Arguments of one call, read in order; ok turns false where one is not what the fast path handles.
 struct Args {
     PyObject* const* a;
-    bool ok = true;
+    bool ok = true, elsewhere = false;       // elsewhere: a stream was named that is not the current one
     explicit Args(PyObject* const* args) : a(args) {}
     // a contiguous device tensor of this type
     const at::Tensor* in(at::ScalarType type, int dims) {
@@ -87,22 +87,32 @@ struct Args {
         if (!PyFloat_Check(o)) { ok = false; return 0.0f; }
         return (float)PyFloat_AS_DOUBLE(o);
     }
-    void* stream() {
-        PyObject* o = *a++;
-        if (o != Py_None) {
-            void* p = PyLong_Check(o) ? PyLong_AsVoidPtr(o) : nullptr;
-            if (!PyLong_Check(o) || PyErr_Occurred()) { PyErr_Clear(); ok = false; }
-            return p;
-        }
-        if (!ok) return nullptr;
+    // the current stream's handle, or null and false where it cannot be told
+    static bool current(void*& p) {
         PyObject* dev = PyObject_CallNoArgs(get_device);
         PyObject* s = dev ? PyObject_CallOneArg(get_stream, dev) : nullptr;
         Py_XDECREF(dev);
-        void* p = s ? PyLong_AsVoidPtr(s) : nullptr;
+        p = s ? PyLong_AsVoidPtr(s) : nullptr;
         Py_XDECREF(s);
-        if (PyErr_Occurred()) { PyErr_Clear(); ok = false; }
+        const bool told = !PyErr_Occurred();
+        PyErr_Clear();
+        return told;
+    }
+    void* stream() {
+        PyObject* o = *a++;
+        if (!ok) return nullptr;
+        void *p = nullptr, *now = nullptr;
+        if (o == Py_None) {
+            ok = current(p);
+            return p;
+        }
+        p = PyLong_Check(o) ? PyLong_AsVoidPtr(o) : nullptr;
+        if (!PyLong_Check(o) || PyErr_Occurred()) { PyErr_Clear(); ok = false; }
+        elsewhere = ok && current(now) && p != now;
         return p;
     }
+    // Memory allocated here is the current stream's: a call on another one is taken only with every buffer given.
+    bool take(bool all_given) const { return ok && (all_given || !elsewhere); }
 };
 
 // An output or scratch tensor: the caller's, or a new one on the device of `like`.
@@ -169,7 +179,7 @@ template <bool ROPE> PyObject* py_quant_q(PyObject* const* argv, Py_ssize_t n) {
     const int block = a.integer();
     PyObject *gi = a.given(I8), *gs = a.given(F32);
     void* st = a.stream();
-    if (!a.ok || block < 1 || !fits(*q) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
+    if (!a.take(gi && gs) || block < 1 || !fits(*q) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
     const int64_t B = q->size(0), H = q->size(1), N = q->size(2), D = q->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
@@ -194,7 +204,7 @@ template <bool ROPE> PyObject* py_smooth_quant_k(PyObject* const* argv, Py_ssize
     const int block = a.integer();
     PyObject *gi = a.given(I8), *gs = a.given(F32), *gm = a.given(F32), *gw = a.scratch();
     void* st = a.stream();
-    if (!a.ok || block < 1 || !fits(*k) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
+    if (!a.take(gi && gs && gm && gw) || block < 1 || !fits(*k) || ROPE != (cs != nullptr) || ROPE != (sn != nullptr)) return none();
     const int64_t B = k->size(0), H = k->size(1), N = k->size(2), D = k->size(3);
     const at::Tensor *c = cs ? tensor(cs) : nullptr, *s = sn ? tensor(sn) : nullptr;
     if (c && (c->dim() != 2 || c->size(0) != N || c->size(1) != D / 2 || s->dim() != 2 || s->size(0) != N || s->size(1) != D / 2)) return none();
@@ -222,7 +232,7 @@ PyObject* py_quant_qk(PyObject* const* argv, Py_ssize_t n) {
     const int bq = a.integer(), bk = a.integer();
     PyObject *gqi = a.given(I8), *gqs = a.given(F32), *gki = a.given(I8), *gks = a.given(F32), *gm = a.given(F32), *gw = a.scratch();
     void* st = a.stream();
-    if (!a.ok || bq < 1 || bk < 1 || !fits(*q) || !fits(*k)) return none();
+    if (!a.take(gqi && gqs && gki && gks && gm && gw) || bq < 1 || bk < 1 || !fits(*q) || !fits(*k)) return none();
     const int64_t B = q->size(0), H = q->size(1), Nq = q->size(2), D = q->size(3), Nkv = k->size(2);
     if (k->size(0) != B || k->size(1) != H || k->size(3) != D) return none();
     Buffer qi, qs, ki, ks, mean, ws;
@@ -247,7 +257,7 @@ PyObject* py_quant_v(PyObject* const* argv, Py_ssize_t n) {
     const at::Tensor* v = a.in(F16, 4);
     PyObject *gi = a.given(I8), *gs = a.given(F32), *gw = a.scratch();
     void* st = a.stream();
-    if (!a.ok || !fits(*v)) return none();
+    if (!a.take(gi && gs && gw) || !fits(*v)) return none();
     const int64_t B = v->size(0), H = v->size(1), N = v->size(2), D = v->size(3), Np = blocks(N, 64) * 64;
     if (gi) {
         const at::Tensor& t = *tensor(gi);
@@ -276,7 +286,7 @@ template <bool PV8> PyObject* py_attn(PyObject* const* argv, Py_ssize_t n) {
     const int bq = a.integer(), bk = a.integer(), splits = a.integer();
     PyObject *go = a.given(F16), *gw = a.given(U8);
     void* st = a.stream();
-    if (!a.ok || PV8 != (gvs != nullptr) || !fits(*qi) || !fits(*ki) || !fits(*v)) return none();
+    if (!a.take(go && (gw || kind != 2)) || PV8 != (gvs != nullptr) || !fits(*qi) || !fits(*ki) || !fits(*v)) return none();
     const int64_t B = ki->size(0), H = ki->size(1), Nkv = ki->size(2), D = ki->size(3), Nq = qi->size(2);
     if (qi->size(0) != B || qi->size(1) != H || qi->size(3) != D || v->size(0) != B || v->size(1) != H) return none();
     if (kind == 0 && Nq != Nkv) return none();
@@ -310,7 +320,7 @@ PyObject* py_attention(PyObject* const* argv, Py_ssize_t n) {
     const int bq = a.integer(), bk = a.integer(), pv8 = a.integer();
     PyObject *go = a.given(F16), *gw = a.given(U8);
     void* st = a.stream();
-    if (!a.ok || !fits(*q) || !fits(*k) || v->sizes() != k->sizes()) return none();
+    if (!a.take(go && gw) || !fits(*q) || !fits(*k) || v->sizes() != k->sizes()) return none();
     const int64_t B = q->size(0), H = q->size(1), Nq = q->size(2), D = q->size(3), Nkv = k->size(2);
     if (k->size(0) != B || k->size(1) != H || k->size(3) != D) return none();
     if (go && tensor(go)->sizes() != q->sizes()) return none();

@@ -34,3 +34,44 @@ def test_int8_second_product_refuses_calls_without_its_scales(v_given):
     for call in (sage.sage_attn_pv_int8_fwd, sage.sage_attn_pv_int8_cross_fwd, sage.sage_attn_pv_int8_cross_split_fwd):
         with pytest.raises(TypeError):
             call(q_i8, q_scale, k_i8, k_scale, v, None, False, 0.125)
+
+
+def flat(r):
+    return r if isinstance(r, tuple) else (r,)
+
+
+@pytest.mark.parametrize("handle", [False, True])
+@pytest.mark.parametrize("what", ["attention", "attention_int8", "quant_qk", "quant_v", "rope_k", "split"])
+def test_a_named_streams_scratch_is_not_handed_out_while_it_runs(what, handle):
+    """The named stream is kept busy, so the call's kernels run after later work of the current stream has taken and
+    filled memory of the same sizes: scratch and outputs must not be among it."""
+    q, k = tensor(1, 4, 1500, 64), tensor(1, 4, 1500, 64)
+    table = torch.ones(1500, 32, device="cuda")
+    q_i8, q_scale, k_i8, k_scale, _ = sage.sage_quant_qk(q[:, :, :40].contiguous(), k, 0.125)
+    calls = {
+        "attention": lambda s: sage.sage_attention_fwd(q, k, q, True, 0.125, stream=s),
+        "attention_int8": lambda s: sage.sage_attention_fwd(q, k, q, True, 0.125, pv_int8=True, stream=s),
+        "quant_qk": lambda s: sage.sage_quant_qk(q, k, 0.125, stream=s),
+        "quant_v": lambda s: sage.sage_quant_v(q, stream=s),
+        "rope_k": lambda s: sage.sage_rope_smooth_quant_k(k, table, table, stream=s),
+        "split": lambda s: sage.sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, k, True, 0.125, n_splits=4, stream=s),
+    }
+    expected = [t.cpu() for t in flat(calls[what](None))]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(5_000_000)
+    got = flat(calls[what](side.cuda_stream if handle else side))
+    junk = [torch.full((1 << n,), 0x55, dtype=torch.uint8, device="cuda") for n in range(9, 24) for _ in range(4)]
+    torch.cuda.current_stream().wait_stream(side)
+    for a, b in zip(got, expected):
+        assert torch.equal(a.cpu(), b)
+    assert all(int(x[-1]) == 0x55 for x in junk)
+    # with every buffer given nothing is allocated, whatever the stream
+    if what == "quant_v":
+        ws = torch.empty(max(sage.sage_quant_v_workspace(1, 4, 1500, 64), 4) // 4, dtype=torch.int32, device="cuda")
+        given = [torch.zeros_like(t) for t in got]
+        torch.cuda.synchronize()
+        back = sage.sage_quant_v(q, given[0], given[1], ws, stream=side)
+        torch.cuda.synchronize()
+        assert back[0] is given[0] and all(torch.equal(a.cpu(), b) for a, b in zip(given, expected))
