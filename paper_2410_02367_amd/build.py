@@ -257,16 +257,15 @@ def check_attention_asm(text: str, expected: int = 20) -> list:
     return problems
 
 
-def check_pv8_asm(text: str) -> list:
-    """Checks the assembly text of the INT8-P~V attention kernels (sage_attn_pv8.hip).  Their matrix
-    instructions are compiler builtins, so the compiler places the waits itself; what the source
-    relies on is only that nothing spills to scratch memory and that the compiler never touches m0,
-    which the hand-written global->LDS loads set."""
+def check_loads_asm(text: str, kernel: str, expected: int) -> list:
+    """Checks the assembly text of `kernel`'s instantiations, whose matrix instructions are compiler builtins: the compiler
+    places the waits itself, and what the source relies on is only that nothing spills to scratch memory and that the
+    compiler never touches m0, which the hand-written global->LDS loads set."""
     import re
-    bodies = re.findall(r"^(_ZN4sage20sage_attn_pv8_kernel\w+):(.*?)^\.Lfunc_end\d+:", text, re.S | re.M)
+    bodies = re.findall(rf"^(_ZN4sage{len(kernel)}{kernel}\w+):(.*?)^\.Lfunc_end\d+:", text, re.S | re.M)
     problems = []
-    if len(bodies) != 16:     # head dimension {64, 128} x {causal, full} x {per-block, per-token key scales} x {whole, key chunks}
-        problems.append(f"expected 16 INT8-P~V attention kernels in the assembly, found {len(bodies)}")
+    if len(bodies) != expected:
+        problems.append(f"expected {expected} instantiations of {kernel} in the assembly, found {len(bodies)}")
     for name, body in bodies:
         in_asm = False
         for line in body.split("\n"):
@@ -284,6 +283,24 @@ def check_pv8_asm(text: str) -> list:
             if re.search(r"\bm0\b", code):
                 problems.append(f"{name}: compiler-generated use of m0: {code}")
     return problems
+
+
+def check_pv8_asm(text: str) -> list:
+    """The INT8-P~V attention kernels: head dimension {64, 128} x {causal, full} x {per-block, per-token key scales} x {whole,
+    key chunks}."""
+    return check_loads_asm(text, "sage_attn_pv8_kernel", 16)
+
+
+def check_short_asm(text: str) -> list:
+    """The whole-pass kernels for short sequences: {128, 256, 512 keys at D = 64, 128, 256 at D = 128} x {per-block, per-token
+    key scales}."""
+    return check_loads_asm(text, "sage_short_kernel", 10)
+
+
+def check_decode_asm(text: str) -> list:
+    """The kernels for few queries: head dimension {64, 128} x {per-block, per-token key scales} x {2, 4 wavefronts}; and the
+    merge of key chunks beside them, which has no loads of that kind."""
+    return check_loads_asm(text, "sage_decode_kernel", 8) + check_no_spills(text)
 
 
 def check_no_spills(text: str) -> list:
@@ -305,14 +322,14 @@ ATTENTION_KERNELS = 4 + 4 * 3 + 2
 
 def verify_attention_isa(extra=()) -> None:
     """Compiles the kernel sources to assembly and raises RuntimeError if check_attention_asm(),
-    check_pv8_asm() or check_no_spills() objects."""
+    check_loads_asm() or check_no_spills() objects."""
     import tempfile
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     problems = []
     with tempfile.TemporaryDirectory() as tmp:
         for src, check in (("sage_attn.hip", lambda text: check_attention_asm(text, ATTENTION_KERNELS)), ("sage_attn_pv8.hip", check_pv8_asm),
                            ("sage_prepass.hip", check_no_spills), ("sage_prepass_v.hip", check_no_spills),
-                           ("sage_short.hip", check_no_spills), ("sage_decode.hip", check_no_spills)):
+                           ("sage_short.hip", check_short_asm), ("sage_decode.hip", check_decode_asm)):
             out = os.path.join(tmp, src + ".s")
             cmd = [hipcc(), *flags, *extra, "-S", "--cuda-device-only", "-o", out, os.path.join(CSRC, src)]
             res = subprocess.run(cmd, capture_output=True, text=True)

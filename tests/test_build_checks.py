@@ -1,6 +1,8 @@
 """The build inspects the assembly of the attention kernels (their matrix instructions are inline
 assembly that updates accumulator registers behind the compiler's back).  These tests plant each
 kind of violation in a small fake assembly text and make sure the checker objects; no GPU needed."""
+import pytest
+
 from paper_2410_02367_amd.build import check_attention_asm
 
 KERNELS = ["_ZN4sage16sage_attn_kernelILi%dELi%dELb%dELb%dELb%dEEEvPKa" % (d, nw, c, dump, ktok)
@@ -96,7 +98,7 @@ def test_matrix_instruction_reading_a_fresh_valu_result_is_reported():
 
 # ------------------------------------------------------------------ INT8-P~V kernels (compiler-scheduled)
 
-from paper_2410_02367_amd.build import check_pv8_asm  # noqa: E402
+from paper_2410_02367_amd.build import check_decode_asm, check_pv8_asm, check_short_asm  # noqa: E402
 
 PV8_KERNELS = ["_ZN4sage20sage_attn_pv8_kernelILi%dELb%dELb%dELb%dEEEvPKa" % (d, c, k, sp)
                for d in (64, 128) for c in (0, 1) for k in (0, 1) for sp in (0, 1)]
@@ -125,6 +127,19 @@ def test_pv8_clean_text_passes_and_a_missing_kernel_is_reported():
 def test_pv8_scratch_and_compiler_use_of_m0_are_reported():
     bad = PV8_CLEAN.replace("\ts_endpgm\n", "\tscratch_load_dword v1, off, off\n\ts_mov_b32 m0, s9\n\ts_endpgm\n")
     problems = check_pv8_asm(fake_pv8(bad))
+    assert any("scratch access" in p for p in problems) and any("use of m0" in p for p in problems)
+
+
+@pytest.mark.parametrize("check, names", [
+    (check_short_asm, ["_ZN4sage17sage_short_kernelILi%dELi%dELi%dELb%dEEEvPKDF16_" % (d, n, nw, k)
+                       for d, n, nw in ((64, 2, 4), (64, 4, 4), (64, 8, 8), (128, 2, 4), (128, 4, 8)) for k in (0, 1)]),
+    (check_decode_asm, ["_ZN4sage18sage_decode_kernelILi%dELb%dELi2ELi%dEEEvPKa" % (d, k, nw)
+                        for d in (64, 128) for k in (0, 1) for nw in (2, 4)])])
+def test_short_and_few_query_kernels_are_held_to_the_same_rule(check, names):
+    assert check(fake_pv8(PV8_CLEAN, names)) == []
+    assert any("expected" in p for p in check(fake_pv8(PV8_CLEAN, names[:-1])))
+    bad = PV8_CLEAN.replace("\ts_endpgm\n", "\tscratch_load_dword v1, off, off\n\ts_mov_b32 m0, s9\n\ts_endpgm\n")
+    problems = check(fake_pv8(bad, names))
     assert any("scratch access" in p for p in problems) and any("use of m0" in p for p in problems)
 
 
