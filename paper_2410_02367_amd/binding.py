@@ -56,7 +56,7 @@ def load() -> ctypes.CDLL:
             raise RuntimeError(f"{_LIB_PATH} is missing or was not built from the present sources "
                                f"(embedded hash {_build.built_hash()}, sources {_build.source_hash()}), "
                                "and there is no hipcc to rebuild it")
-        _build.build()
+        _build.build_library()
     lib = ctypes.CDLL(_LIB_PATH)
     lib.sage_source_hash.restype = ctypes.c_char_p
     lib.sage_source_hash.argtypes = []
@@ -126,20 +126,31 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+class _PythonOnly:
+    """In the extension module's place where it cannot be had: takes no call, so that every wrapper goes on in Python."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _open_native(lib) -> None:
     """Load the extension module (rebuilt first if it does not belong to the sources beside it, as the library is) and
-    hand it the library's entry points."""
+    hand it the library's entry points.  It saves host time and computes nothing: without it, where it is stale and no
+    g++ can rebuild it for this torch and Python, the wrappers make the same library calls through ctypes."""
     global _native
     import importlib.util
     from . import build as _build
-    if _build.native_is_stale():
-        try:
+    try:
+        if _build.native_is_stale():
             _build.build_native()
-        except FileNotFoundError:
-            raise RuntimeError(f"{_build.NATIVE} is missing or was not built from the present sources, and there is no g++ to rebuild it")
-    spec = importlib.util.spec_from_file_location("_sage_native", _build.NATIVE)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
+        spec = importlib.util.spec_from_file_location("_sage_native", _build.NATIVE)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except (OSError, ImportError, RuntimeError) as e:
+        import warnings
+        warnings.warn(f"{_build.NATIVE} is missing or not of the present sources, torch and Python, and could not be "
+                      f"rebuilt; calls take 2 to 15 us more of host time each: {e}", RuntimeWarning, stacklevel=2)
+        _native = _PythonOnly()
+        return
     # (torch._C has these two in builds with a GPU back end only; without one no tensor passes the module's checks)
     module.init(getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None),
                 *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))

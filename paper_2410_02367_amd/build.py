@@ -108,9 +108,15 @@ def build_native() -> str:
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    """Compile every kernel for gfx950 (cross-compiles without a GPU) and the extension module, and return the
+    """Compile every kernel for gfx950 (cross-compiles without a GPU), then the extension module, and return the
     library's path."""
+    build_library(verbose, extra)
     build_native()
+    return LIB
+
+
+def build_library(verbose: bool = False, extra=()) -> str:
+    """Compile every kernel and return the library's path."""
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [hipcc(), *HIPCC_FLAGS, *extra, f'-DSAGE_SOURCE_HASH="{source_hash()}"', "-o", tmp,
            *[os.path.join(CSRC, s) for s in SOURCES]]

@@ -271,3 +271,45 @@ def test_tensors_without_sizes_in_numbers_are_left_to_python(lib):
     import sys
     run = subprocess.run([sys.executable, "-c", SYMBOLIC], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert run.returncode == 0 and "all left to Python" in run.stdout, (run.returncode, run.stderr[-500:])
+
+
+NO_COMPILER = """
+import os, tempfile, warnings
+import torch
+from paper_2410_02367_amd import binding, build
+build.NATIVE = os.path.join(tempfile.mkdtemp(), "_sage_native.so")      # not there, and no g++ on the path
+os.environ["PATH"] = os.path.dirname(build.NATIVE)
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    lib = binding.load()
+assert any(w.category is RuntimeWarning and "_sage_native" in str(w.message) for w in seen)
+assert lib.sage_source_hash().decode() == build.source_hash() and binding.sage_default_sm_scale(64) == 0.125
+try:
+    binding.sageattn(*[torch.zeros(1, 2, 64, 64, dtype=torch.float16)] * 3)
+except TypeError as e:
+    assert "device memory" in str(e)
+    print("the Python path")
+"""
+
+
+def test_without_the_extension_module_the_wrappers_go_through_python(lib):
+    """The module only saves host time: where it is stale and cannot be rebuilt, loading warns and every call is made
+    through ctypes.  (In a process of its own: this one has loaded it.)"""
+    import subprocess
+    import sys
+    run = subprocess.run([sys.executable, "-c", NO_COMPILER], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0 and "the Python path" in run.stdout, (run.returncode, run.stderr[-500:])
+
+
+def test_the_kernels_are_built_before_the_extension_module(monkeypatch):
+    from paper_2410_02367_amd import build
+    done = []
+
+    def fail():
+        raise RuntimeError("g++ failed")
+
+    monkeypatch.setattr(build, "build_library", lambda *a: done.append("kernels"))
+    monkeypatch.setattr(build, "build_native", fail)
+    with pytest.raises(RuntimeError):
+        build.build()
+    assert done == ["kernels"]
