@@ -85,7 +85,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -1077,7 +1076,7 @@ hipError_t launch_attn_clocks(const Queries& q, const int8_t* kq, const float* k
 // With few query rows per slab a launch has too few workgroups for the chip and each walks every
 // key tile.  The keys are cut into n_splits chunks, a workgroup per (slab, chunk, query tile) leaves
 // the attention of its rows over its chunk -- O_s normalized by the chunk's own denominator, fp16,
-// and lse_s = m_s + log2 l_s -- and the merge below forms
+// and lse_s = m_s + log2 l_s -- and the merge (sage_decode.hip) forms
 //     O = sum_s w_s O_s / sum_s w_s,   w_s = 2^(lse_s - max_s lse_s),
 // which is the attention over all keys: w_s is the chunk's share of the softmax denominator.
 SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested) {

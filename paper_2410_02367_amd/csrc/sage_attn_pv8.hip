@@ -42,7 +42,6 @@ namespace sage {
 typedef int p4i __attribute__((ext_vector_type(4)));
 typedef int p16i __attribute__((ext_vector_type(16)));
 typedef float p16f __attribute__((ext_vector_type(16)));
-typedef _Float16 p4h __attribute__((ext_vector_type(4)));
 
 namespace {
 constexpr float PV8_LOG2E = 1.4426950408889634f;

@@ -282,8 +282,13 @@ static hipError_t launch_decode_d(const Queries& q, const int8_t* kq, const floa
     const dim3 grid((unsigned)(BH * sp.n_splits));
 #define SAGE_DECODE(KT, NW) sage_decode_kernel<D, KT, 2, NW><<<grid, NW * 64, 0, st>>>(q.i8, q.scale, kq, kscale, (const _Float16*)v, \
         (_Float16*)o, sp.lse, Nq, N, shift_q, shift_k, causal, BH, sp.n_splits, sp.chunk, (const _Float16*)q.f16, q.sm_scale)
-    if (D == 128 && grid.x > 256) { if (block_k == 1) SAGE_DECODE(true, 2); else SAGE_DECODE(false, 2); }
-    else { if (block_k == 1) SAGE_DECODE(true, 4); else SAGE_DECODE(false, 4); }
+    if constexpr (D == 128) {
+        if (grid.x > 256) {
+            if (block_k == 1) SAGE_DECODE(true, 2); else SAGE_DECODE(false, 2);
+            return hipGetLastError();
+        }
+    }
+    if (block_k == 1) SAGE_DECODE(true, 4); else SAGE_DECODE(false, 4);
 #undef SAGE_DECODE
     return hipGetLastError();
 }

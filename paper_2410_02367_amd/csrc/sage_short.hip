@@ -25,7 +25,6 @@ typedef float s16f __attribute__((ext_vector_type(16)));
 typedef short s4s __attribute__((ext_vector_type(4)));
 typedef float s2f __attribute__((ext_vector_type(2)));
 typedef _Float16 s2h __attribute__((ext_vector_type(2)));
-typedef _Float16 s4h __attribute__((ext_vector_type(4)));
 
 namespace {
 constexpr float SHORT_LOG2E = 1.4426950408889634f;
