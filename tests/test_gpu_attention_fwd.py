@@ -82,3 +82,72 @@ def test_mismatched_tensors_are_refused_before_any_launch():
         sage.sageattn(q.transpose(1, 2), q.transpose(1, 2), q.transpose(1, 2))
     with pytest.raises(sage.SageError):
         sage.sageattn(q, q, q, block_k=32)
+
+
+# ------------------------------------------------------------------ launches that fill the chip
+
+def on_device(seed, slabs, Nq, Nkv, D):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+
+    def normal(n):
+        return torch.randn((1, slabs, n, D), generator=g, device="cuda")
+
+    return normal(Nq).half(), (normal(Nkv) + 3.0 * normal(1)).half(), normal(Nkv).half()
+
+
+def oracle_slab(q, k, v, slab, causal, bq, bk):
+    q, k, v = (np.ascontiguousarray(x[:, slab:slab + 1].cpu().numpy()) for x in (q, k, v))
+    kq, ks, _ = oracle.smooth_quant_k(k, bk)
+    qq, qs = oracle.quant_q(q, sage.sage_default_sm_scale(q.shape[3]), bq)
+    lq, lk = max(bq, 64) if bq != 1 else 128, max(bk, 64) if bk != 1 else 64
+    return oracle.attn_l2_cross(qq, qs, kq, ks, v, causal, lq, lk, gran_q=bq, gran_k=bk)
+
+
+# Launches of 256-row workgroups: D = 128, at least 512 of them, more than 2048 keys (4096 with a mask), and without a mask
+# no poorly filled last round: 128 x 17 of them are 8.5 rounds of the 256 compute units.
+LARGE = [(128, 4100, False, 128, 64), (128, 4100, False, 64, 128), (128, 4100, False, 1, 64), (32, 16384, True, 128, 64),
+         (128, 4100, False, 1, 1), (128, 4100, False, 32, 1), (32, 4200, True, 1, 1)]
+
+
+@pytest.mark.parametrize("slabs,N,causal,bq,bk", LARGE)
+def test_whole_pass_in_256_row_workgroups(slabs, N, causal, bq, bk):
+    """Queries quantized inside the kernel (two 128-row scale blocks, four of 64 or one per row in a workgroup) give bit for
+    bit what the separate calls give, on every row; the oracle's rows on one slab, where that is quick."""
+    D = 128
+    assert slabs * -(-N // 256) >= 512
+    print(f"[case] {slabs} x {N} x {D} causal={causal} scales {bq}x{bk}", flush=True)
+    q, k, v = on_device(N + bq, slabs, N, N, D)
+    sm = sage.sage_default_sm_scale(D)
+    o = sage.sageattn(q, k, v, causal, sm, bq, bk)
+    q_i8, q_scale, k_i8, k_scale, _ = sage.sage_quant_qk(q, k, sm, bq, bk)
+    chain = sage.sage_attn_fwd(q_i8, q_scale, k_i8, k_scale, v, causal, sm, bq, bk)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), chain.view(torch.int16))
+    if N < 5000:
+        assert_output_close(o[:, slabs - 1:].cpu().numpy(), oracle_slab(q, k, v, slabs - 1, causal, bq, bk))
+
+
+# The one-launch path with fewer workgroups than query tiles: each makes several turns (the next rows requested
+# during the present ones, the scale words alternating).  Slabs x turns: 128-row workgroups, three (D = 64) or two per CU;
+# 256-row ones, one per CU.
+TURNS = [(768, 197, 197, 64, False, 128, 64, 2), (800, 400, 120, 64, False, 64, 1, 4), (520, 300, 100, 128, False, 128, 64, 3),
+         (520, 128, 128, 128, True, 32, 64, 1), (300, 700, 500, 64, False, 128, 128, 3), (300, 512, 512, 64, True, 128, 64, 2),
+         (260, 600, 256, 128, False, 1, 1, 3), (140, 1000, 256, 128, False, 128, 64, 4)]
+
+
+@pytest.mark.parametrize("slabs,Nq,Nkv,D,causal,bq,bk,turns", TURNS)
+def test_short_sequences_in_several_turns(slabs, Nq, Nkv, D, causal, bq, bk, turns):
+    rows, per_cu = (256, 1) if Nkv * D > 16384 else (128, 3 if D == 64 else 2)
+    groups = min(max(256 * per_cu // slabs, 1), -(-Nq // rows))
+    assert sage.sage_attention_workspace(1, slabs, Nq, Nkv, D, causal, bq, bk) == 0 and -(-(-(-Nq // rows)) // groups) == turns
+    print(f"[case] {slabs} x {Nq} x {Nkv} x {D} causal={causal} scales {bq}x{bk}", flush=True)
+    q, k, v = on_device(Nq + Nkv, slabs, Nq, Nkv, D)
+    sm = sage.sage_default_sm_scale(D)
+    o = sage.sageattn(q, k, v, causal, sm, bq, bk)
+    q_i8, q_scale, k_i8, k_scale, _ = sage.sage_quant_qk(q, k, sm, bq, bk)
+    chain = sage.sage_attn_cross_fwd(q_i8, q_scale, k_i8, k_scale, v, causal, sm, bq, bk)
+    torch.cuda.synchronize()
+    # the separate calls add in another order: every row within the tolerance of either against the oracle
+    assert bool(torch.isfinite(o).all()) and float((o.float() - chain.float()).abs().max()) <= ABS_TOL
+    for slab in (0, slabs // 2, slabs - 1):
+        assert_output_close(o[:, slab:slab + 1].cpu().numpy(), oracle_slab(q, k, v, slab, causal, bq, bk), f"slab {slab}")

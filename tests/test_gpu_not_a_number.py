@@ -21,6 +21,7 @@ CASES = [
     (1, 2, 200, 200, 128, True, 128, True),
     (1, 2, 700, 700, 64, True, 128, True),
     (2, 2, 1300, 1300, 128, True, 1, True),
+    (1, 32, 3900, 3900, 128, False, 128, False),
 ]
 
 

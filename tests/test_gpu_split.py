@@ -211,7 +211,8 @@ def test_int8_second_product_decode_at_the_headline_shape_sampled_slabs():
 
 
 def test_convenience_wrapper_routes_by_lengths_and_second_product():
-    """sageattn() only chains the library calls: its output is bit for bit that of the explicit chain."""
+    """sageattn() is one library call, and beyond the short sequences that have a kernel of their own it makes the launches of
+    the separate calls: its output is bit for bit that of the explicit chain."""
     q, k, v, sm = make("wrap", 1, 4, 7, 4000, 128, 3)
     qd, kd, vd = to_dev(q), to_dev(k), to_dev(v)
     k_i8, k_scale, _ = sage.sage_smooth_quant_k(kd, 64)
