@@ -1060,7 +1060,7 @@ hipError_t launch_attn(const Queries& q, const int8_t* kq, const float* kscale,
                        const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int D, int causal,
                        int block_q, int block_k, hipStream_t st, int wg_rows) {
     const SplitPlan whole = {1, 0, nullptr};
-    if (!sdump && decode_fits(Nq)) return launch_decode(q, kq, kscale, v, o, BH, Nq, N, D, causal, block_q, block_k, whole, st);
+    if (!sdump && decode_takes(BH, Nq, N, D, block_k)) return launch_decode(q, kq, kscale, v, o, BH, Nq, N, D, causal, block_q, block_k, whole, st);
     if (D == 64) return launch_d<64>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
     return launch_d<128>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, whole, st, wg_rows);
 }
@@ -1117,7 +1117,7 @@ hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* ks
     // workspace: partial O [n_splits, BH, Nq, D] fp16, then lse [n_splits, BH, Nq] fp32
     _Float16* part = (_Float16*)workspace;
     sp.lse = (float*)((char*)workspace + (size_t)sp.n_splits * rows * D * sizeof(_Float16));
-    hipError_t e = decode_fits(Nq)
+    hipError_t e = decode_takes((long)BH * sp.n_splits, Nq, sp.chunk, D, block_k)
         ? launch_decode(q, kq, kscale, v, part, BH, Nq, N, D, causal, block_q, block_k, sp, st)
         : D == 64
         ? launch_d<64>(q, kq, kscale, v, part, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st)

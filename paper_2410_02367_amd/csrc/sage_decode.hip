@@ -44,7 +44,7 @@ __device__ __forceinline__ void dec_load4(const d4i& rsrc, unsigned goff, unsign
 
 // grid: one workgroup per (slab, key chunk), chunk fastest.  lse != nullptr: a partial result per chunk, as in sage_attn.hip.
 // NW wavefronts: 4 while every workgroup has a compute unit to itself; with more workgroups than that and 24 KB of LDS per
-// wavefront (D = 128), 2, so that three fit (420 slabs of 1436 keys: 51 us with 4, the start of a second round).
+// wavefront (D = 128), 2, so that three fit, unless the workgroups are long: see launch_decode_d().
 template <int D, bool KTOK, int NBUF, int NW>
 __global__ void __launch_bounds__(NW * 64, 1)
 sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc, const int8_t* __restrict__ ki,
@@ -273,7 +273,17 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     }
 }
 
-bool decode_fits(int Nq) { return Nq <= 32; }
+// At D = 128 this kernel has one or three workgroups on a CU, the general one (sage_attn.hip) three of one 64-key tile at a
+// time.  Where the workgroups do not go evenly into the 256 CUs -- more than one each, fewer than one and a half -- and are
+// long, three small ones in flight read the memory better: us here / there, each pass on other inputs, 100 slabs of 5000
+// keys (3 chunks) 50 / 47, of 16384 133 / 123; 130 of 8192 (2 chunks) 100 / 86; 300 of 1436 40 / 38, of 4096 101 / 92; 350 of
+// 4096 105 / 100; 380 of 4096 108 / 107; from there on this one (400: 110 / 111, 600: 170 / 204); short ones too (130 of
+// 1436, 718 a workgroup: 24.0 / 24.1; 300 of 700 21.7 / 22.6).  With one scale per key there is no such case (300 of
+// 4096 102 / 105).
+bool decode_takes(long workgroups, int Nq, int keys, int D, int block_k) {
+    if (Nq > 32) return false;
+    return !(D == 128 && block_k != 1 && workgroups > 256 && workgroups < 384 && keys >= 1280);
+}
 
 template <int D>
 static hipError_t launch_decode_d(const Queries& q, const int8_t* kq, const float* kscale, const void* v, void* o, int BH, int Nq,
@@ -282,8 +292,11 @@ static hipError_t launch_decode_d(const Queries& q, const int8_t* kq, const floa
     const dim3 grid((unsigned)(BH * sp.n_splits));
 #define SAGE_DECODE(KT, NW) sage_decode_kernel<D, KT, 2, NW><<<grid, NW * 64, 0, st>>>(q.i8, q.scale, kq, kscale, (const _Float16*)v, \
         (_Float16*)o, sp.lse, Nq, N, shift_q, shift_k, causal, BH, sp.n_splits, sp.chunk, (const _Float16*)q.f16, q.sm_scale)
+    // D = 128: 2 wavefronts while the second round of workgroups would be what counts (us with 2 / 4, each pass on other inputs: 600
+    // slabs of 1436 keys 66 / 70, 800 of 700 46 / 53); for long ones the deeper queue of 4 (400 of 4096: 115 / 110, 200 of
+    // 12000 in 2 chunks 169 / 162; 700 of 2000 97 / 96)
     if constexpr (D == 128) {
-        if (grid.x > 256) {
+        if (grid.x > 256 && (sp.lse != nullptr ? sp.chunk : N) <= 2048) {
             if (block_k == 1) SAGE_DECODE(true, 2); else SAGE_DECODE(false, 2);
             return hipGetLastError();
         }

@@ -73,8 +73,9 @@ hipError_t launch_attn_split(const Queries& q, const int8_t* kq, const float* ks
                              const void* v, void* o, void* workspace, int BH, int Nq, int N, int D, int causal,
                              int block_q, int block_k, int requested, hipStream_t st);
 
-// The same for at most 32 query rows per slab (sage_decode.hip): sp.lse == nullptr writes o, else partial results
-bool decode_fits(int Nq);
+// The same for at most 32 query rows per slab (sage_decode.hip): sp.lse == nullptr writes o, else partial results.
+// decode_takes: whether it is the faster one for that many (slab, chunk) pairs of that many keys.
+bool decode_takes(long workgroups, int Nq, int keys, int D, int block_k);
 hipError_t launch_decode(const Queries& q, const int8_t* kq, const float* kscale, const void* v, void* o, int BH, int Nq, int N,
                          int D, int causal, int block_q, int block_k, const SplitPlan& sp, hipStream_t st);
 

@@ -47,3 +47,32 @@ def test_few_queries(i):
     lq, lk = max(bq, 64) if bq != 1 else 128, max(bk, 64) if bk != 1 else 64
     ref = oracle.attn_l2_cross(qq, qs, kq, ks, v, causal, lq, lk, gran_q=bq, gran_k=bk)
     assert_output_close(o.cpu().numpy(), ref, f"case {i}")
+
+
+# More workgroups than compute units at D = 128: two wavefronts each (short ones), four (more than 2048 keys), or the
+# general kernel (fewer than 384 workgroups of at least 1280 keys, one scale per block).
+MANY = [(300, 1279, 128, 64), (300, 1280, 128, 64), (383, 1300, 128, 64), (384, 1300, 128, 64), (300, 1300, 1, 1),
+        (400, 2048, 128, 64), (400, 2049, 128, 64), (257, 2100, 1, 1), (90, 4000, 128, 64)]
+
+
+@pytest.mark.parametrize("slabs,Nkv,bq,bk", MANY)
+def test_few_queries_of_many_slabs(slabs, Nkv, bq, bk):
+    D, Nq = 128, 3
+    n = sage.sage_attn_split_count(1, slabs, Nq, Nkv, True, 0)
+    print(f"[case] {slabs} x ({Nq}, {Nkv}) x {D} scales {bq}x{bk} chunks {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(slabs + Nkv)
+    q, v = (torch.randn((1, slabs, m, D), generator=g, device="cuda").half() for m in (Nq, Nkv))
+    k = (torch.randn((1, slabs, Nkv, D), generator=g, device="cuda") + 3.0 * torch.randn((1, slabs, 1, D), generator=g, device="cuda")).half()
+    sm = sage.sage_default_sm_scale(D)
+    q_i8, q_scale, k_i8, k_scale, _ = sage.sage_quant_qk(q, k, sm, bq, bk)
+    outs = [sage.sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, True, sm, bq, bk),
+            sage.sage_attn_cross_fwd(q_i8, q_scale, k_i8, k_scale, v, True, sm, bq, bk),
+            sage.sageattn(q, k, v, True, sm, bq, bk)]
+    torch.cuda.synchronize()
+    for slab in (0, 131 % slabs, slabs - 1):
+        a, b, c = (np.ascontiguousarray(x[:, slab:slab + 1].cpu().numpy()) for x in (q, k, v))
+        qq, qs = oracle.quant_q(a, sm, bq)
+        kq, ks, _ = oracle.smooth_quant_k(b, bk)
+        ref = oracle.attn_l2_cross(qq, qs, kq, ks, c, True, 128, 64, gran_q=bq, gran_k=bk)
+        for o in outs:
+            assert_output_close(o[:, slab:slab + 1].cpu().numpy(), ref, f"slab {slab}")
