@@ -228,8 +228,8 @@ template <class T> __device__ __forceinline__ void pin_a(T& x) { asm volatile(""
 // constant-rate (100 MHz) counter ticks it ran for, how often it raised a running maximum and how
 // many key tiles it visited -- from which the clock the chip held and the clocks per tile follow.
 template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false>
-// Workgroups of 4 wavefronts per CU that the register budget is cut for: 3 at D = 64 (168 registers
-// per lane; measured 4 % faster than 2; the per-token variant needs more), else 2.
+// Workgroups of 4 wavefronts per CU that the register budget is cut for: 2.  At D = 64 the compiler stays within
+// the 168 registers of three on its own (152, with one scale per key 160), which is 4 % faster than two.
 __global__ void __launch_bounds__(NW * 64, NW == 4 && SAGE_QS == 1 ? 2 : 1)
 sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const int8_t* __restrict__ ki, const float* __restrict__ ksc,
@@ -1037,18 +1037,28 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
                            const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                            int block_q, int block_k, const SplitPlan& sp, hipStream_t st, int wg_rows = 0,
                            unsigned long long* clocks = nullptr) {
-    // 256-row workgroups (8 wavefronts sharing one set of LDS tiles) for long sequences at D = 128;
-    // 128-row workgroups, two or three per CU, for D = 64, for short sequences, where a workgroup visits few tiles and
-    // the finer causal staircase and the independent progress of the small workgroups matter more than the sharing (at
-    // D = 128: 1536 keys causal 80 us instead of 91; equal from 4K causal and 1K non-causal on), and where a launch of
-    // the larger ones would end on a round that leaves many CUs idle: 30 slabs of 3000 rows are 1.4 rounds, 115 us
-    // with small workgroups instead of 132.  (A causal launch fills its tail with light tiles: only below two rounds.)
-    const long big_tiles = (long)BH * sp.n_splits * ((Nq + 8 * WROWS - 1) / (8 * WROWS));
-    const long rounds = (big_tiles + 255) / 256;
+    // D = 64: 128-row workgroups, three per CU.  D = 128: 128-row ones, two per CU, or 256-row ones (8 wavefronts sharing one
+    // set of LDS tiles), one per CU; a row's bits do not depend on which.  us below are with 128 / 256 rows.
+    // Short sequences, to 2048 keys, 4096 with a mask: 128 rows.  A workgroup visits few tiles, and the independent progress of
+    // the small ones and the finer causal staircase matter more than the sharing.  No mask: 4096 queries of 128 slabs against
+    // 200 keys 83 / 98, against 800 196 / 208; 90 slabs of 1000 47 / 56, 60 of 2000 106 / 103.  Causal: 128 slabs of 1536 keys
+    // 77 / 81, of 3000 259 / 264, of 4096 441 / 449, 64 of 4096 219 / 217; with one scale per key 83 / 88, 287 / 288,
+    // 494 / 499, 244 / 243.
+    // Longer, causal: 256 rows where there are two of them per CU; with fewer the launch is the chain of its heaviest tile (16
+    // slabs of 5000 93 / 104).
+    // Longer, no mask: a 256-row workgroup takes 3-5 % less than two 128-row ones side by side, but a 128-row one that has its
+    // CU to itself 0.74 of that time.  So the smaller ones where their last round over the 512 places is at most half full
+    // and no more than five full ones are before it (12 slabs of 6000, 564 of them: 207 / 245; 30 of 3000, 720: 115 / 132;
+    // 86 of 4096, 2752: 567 / 579), the larger ones elsewhere (12 of 3000, 288: 64 / 58; 46 of 3800, 1380: 281 / 268; one
+    // scale per key, 20 of 6000, 940: 328 / 315).
+    const int small_tiles = (Nq + 4 * WROWS - 1) / (4 * WROWS), large_tiles = (Nq + 8 * WROWS - 1) / (8 * WROWS);
+    const long units = (long)BH * sp.n_splits;
     const int n_seen = sp.n_splits > 1 ? sp.chunk : N;           // keys a workgroup walks
-    const bool short_seq = n_seen <= 2048 || (causal && n_seen <= 4096);
-    const bool idle_cus = big_tiles < 2 * 256 || (!causal && 10 * big_tiles < 9 * 256 * rounds);
-    bool small = QS == 1 && (D == 64 || ((idle_cus || short_seq) && !sdump));
+    bool small = QS == 1 && !(sdump && D == 128);
+    if (small && D == 128 && n_seen > (causal ? 4096 : 2048)) {
+        const long rounds = (units * small_tiles + 511) / 512, last = units * small_tiles - 512 * (rounds - 1);
+        small = causal ? units * large_tiles < 2 * 256 : last <= 256 && rounds <= 6;
+    }
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only

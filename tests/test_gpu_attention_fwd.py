@@ -127,6 +127,22 @@ def test_whole_pass_in_256_row_workgroups(slabs, N, causal, bq, bk):
         assert_output_close(o[:, slabs - 1:].cpu().numpy(), oracle_slab(q, k, v, slabs - 1, causal, bq, bk))
 
 
+# No mask, D = 128, more than 2048 keys: 128-row workgroups where their last round over 512 places is at most half full
+# and they need at most six, else 256-row ones.  Slabs and rows on both sides of either line.
+ROUNDS = [(8, 4096, False), (9, 3700, True), (3, 2049, True), (27, 2400, False), (40, 2432, True), (150, 2300, True), (171, 2300, False)]
+
+
+@pytest.mark.parametrize("slabs,N,per_token", ROUNDS)
+def test_workgroup_shape_by_its_last_round(slabs, N, per_token):
+    D, (bq, bk) = 128, (1, 1) if per_token else (128, 64)
+    tiles = slabs * -(-N // 128)
+    print(f"[case] {slabs} x {N} x {D} scales {bq}x{bk}: {tiles} tiles, last round {(tiles - 1) % 512 + 1}", flush=True)
+    q, k, v = on_device(slabs + N, slabs, N, N, D)
+    o = sage.sageattn(q, k, v, False, sage.sage_default_sm_scale(D), bq, bk)
+    torch.cuda.synchronize()
+    assert_output_close(o[:, slabs - 1:].cpu().numpy(), oracle_slab(q, k, v, slabs - 1, False, bq, bk))
+
+
 # The one-launch path with fewer workgroups than query tiles: each makes several turns (the next rows requested
 # during the present ones, the scale words alternating).  Slabs x turns: 128-row workgroups, three (D = 64) or two per CU;
 # 256-row ones, one per CU.
