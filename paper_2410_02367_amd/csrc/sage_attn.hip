@@ -123,11 +123,6 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 #define IDX(x) (std::remove_reference_t<decltype(x)>::value)
 
-// LDS tiles are unpadded; 16-byte chunks are XOR-swizzled inside each row so that the operand
-// reads of 16 consecutive rows touch every bank once.
-template <int D> __device__ __forceinline__ int k_swz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
-template <int D> __device__ __forceinline__ int v_swz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
-
 __device__ __forceinline__ int swap32i(int v) {
     // value held by the lane 32 away
     auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
@@ -177,24 +172,6 @@ __device__ __forceinline__ void pv_mfma(const v16f& acc, const v8h& a, const v8h
 __device__ __forceinline__ void l_mfma(const v4f& acc, const v4i& sel, const v4i& b) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : : "a"(acc), "a"(sel), "v"(b));
 }
-// One 16-byte-per-lane load from global memory straight into LDS: lane l lands at LDS byte address
-// lds_addr + 16*l (lds_addr wave-uniform).  Written as assembly because the compiler, which cannot
-// tell which LDS bytes such a load writes, makes every later LDS read wait for it (vmcnt(0)) and
-// so turns the asynchronous load into a synchronous one.  Completion is tracked by hand: the
-// issuing wavefront waits with s_waitcnt vmcnt before the barrier that publishes the tile.
-//
-// The load is a raw-buffer load: the descriptor (four scalar registers) carries the base address
-// and the byte size of the (batch, head) slab, the per-lane offset is checked against that size by
-// the hardware and a lane beyond it reads zero instead of memory.  The ragged last tile therefore
-// needs no clamping code at all (its rows are masked or multiplied by P~ = 0 anyway).
-__device__ __forceinline__ v4i slab_descriptor(const void* base, unsigned bytes) {
-    const unsigned long long p = (unsigned long long)base;
-    // dword 0-1: 48-bit base, stride 0 (raw buffer); dword 2: size in bytes; dword 3: 32-bit data format
-    // (readfirstlane: the values are wave-uniform, this pins them to scalar registers)
-    return (v4i){__builtin_amdgcn_readfirstlane((int)(unsigned)p),
-                 __builtin_amdgcn_readfirstlane((int)((unsigned)(p >> 32) & 0xffffu)),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
 // The descriptor of a slab moved forward to one of its tiles: base + tile bytes, size - tile bytes
 // (scalar arithmetic).  The per-lane offset inside the tile then goes into the load as it is, and
 // the range check still ends at the end of the slab.  (Adding the tile offset to the per-lane
@@ -204,10 +181,6 @@ __device__ __forceinline__ v4i tile_descriptor(const v4i& slab, unsigned tile) {
     const unsigned lo = (unsigned)slab[0] + tile;
     const unsigned hi = (unsigned)slab[1] + (lo < tile ? 1u : 0u);
     return (v4i){(int)lo, (int)hi, (int)((unsigned)slab[2] - tile), slab[3]};
-}
-__device__ __forceinline__ void load_to_lds16(const v4i& rsrc, unsigned goff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 : : "v"(goff), "s"(rsrc), "s"(lds_addr) : "memory");
 }
 // Tells the compiler that an accumulator changed, 12 wait states after the last matrix instruction
 // that wrote it (all of these statements are volatile, so their order is kept).
@@ -344,8 +317,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         int vidx = t + NTHREADS * i, row = vidx / VCH, c = (vidx % VCH) ^ v_swz<D>(row);
         v_goff[i] = row * 2 * D + c * 16;
     }
-    const v4i k_rsrc = slab_descriptor(ki + slab * D, (unsigned)N * D);
-    const v4i v_rsrc = slab_descriptor(vg + slab * D, (unsigned)N * 2 * D);
+    const v4i k_rsrc = buffer_descriptor(ki + slab * D, (unsigned)N * D);
+    const v4i v_rsrc = buffer_descriptor(vg + slab * D, (unsigned)N * 2 * D);
     const unsigned lds_base = (unsigned)(size_t)LDS_PTR(unsigned char, lds);     // LDS byte address of the tile area
     auto load_k = [&](int j, int buf) {
         const v4i rsrc = tile_descriptor(k_rsrc, (unsigned)j * (KTILE * D));

@@ -50,27 +50,10 @@ constexpr float PV8_HIDDEN = -3.0e38f;            // stands for a masked score: 
 constexpr int PV8_FLUSH_TILES = 1024;
 
 __device__ __forceinline__ float lane32_partner(float v) { return __shfl_xor(v, 32, 64); }
-// Raw-buffer descriptor of `bytes` bytes at `base` (wave-uniform, pinned to scalar registers): loads
-// through it are range-checked by the hardware, lanes past the end read zero.
-__device__ __forceinline__ p4i pv8_descriptor(const void* base, unsigned bytes) {
-    const unsigned long long a = (unsigned long long)base;
-    return (p4i){__builtin_amdgcn_readfirstlane((int)(unsigned)a),
-                 __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
-// 16 bytes per lane from global memory straight into LDS (no staging registers): lane l lands at
-// LDS byte lds_addr + 16 * l (lds_addr wave-uniform).  Asynchronous: the issuing wavefront waits
-// with s_waitcnt vmcnt(0) before the barrier that publishes the tile.
-__device__ __forceinline__ void pv8_load_to_lds16(const p4i& rsrc, unsigned goff, unsigned lds_addr) {
-    const unsigned uniform_addr = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr);      // pins it to a scalar register
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 : : "v"(goff), "s"(rsrc), "s"(uniform_addr) : "memory");
-}
 __device__ __forceinline__ int k_unperm(int p) {
     // key of a tile held by LDS row p: row 32kb + 8g + 4h + b holds key 32kb + 16h + 4g + b
     return (p & 32) | ((p & 4) << 2) | ((p & 24) >> 1) | (p & 3);
 }
-template <int D> __device__ __forceinline__ int k_swz8(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
 __device__ __forceinline__ int vt_swz(int ch) { return (ch >> 2) & 3; }
 }  // namespace
 
@@ -147,7 +130,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
 #pragma unroll
             for (int i = 0; i < 4; ++i) code[i] = (int)rows.word(ks, i, sm_scale, rcp);
             if (ks < QREG) qreg[ks] = code;
-            else *(p4i*)(lds + QOFF + wave * (32 * D) + ql * D + (((2 * ks + h) ^ k_swz8<D>(ql)) * 16)) = code;
+            else *(p4i*)(lds + QOFF + wave * (32 * D) + ql * D + (((2 * ks + h) ^ k_swz<D>(ql)) * 16)) = code;
         }
     } else {
 #pragma unroll
@@ -172,32 +155,32 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     // (instruction i of a tensor is instruction 0 plus a constant: NT / KCH further K^ rows -- a
     // multiple of 32, which neither the permutation nor the swizzle sees -- or 64 further channels)
     static_assert((NT / KCH) % 32 == 0, "K^ rows of consecutive load instructions differ by whole 32-key blocks");
-    const unsigned k_goff0 = (unsigned)(k_unperm(t / KCH) * D + (((t % KCH) ^ k_swz8<D>(t / KCH)) * 16));
+    const unsigned k_goff0 = (unsigned)(k_unperm(t / KCH) * D + (((t % KCH) ^ k_swz<D>(t / KCH)) * 16));
     const unsigned v_goff0 = (unsigned)((t >> 2) * Np + (((t & 3) ^ vt_swz(t >> 2)) * 16));
-    const p4i k_desc = pv8_descriptor(ki + slab * D, (unsigned)N * D);
-    const p4i v_desc = pv8_descriptor(vt + (size_t)bh * D * Np + k0, (unsigned)D * Np - (unsigned)k0);
-    const p4i ks_desc = pv8_descriptor(ksc_bh, (unsigned)N * 4u);      // per-token variant: N scales; past the end reads 0
+    const p4i k_desc = buffer_descriptor(ki + slab * D, (unsigned)N * D);
+    const p4i v_desc = buffer_descriptor(vt + (size_t)bh * D * Np + k0, (unsigned)D * Np - (unsigned)k0);
+    const p4i ks_desc = buffer_descriptor(ksc_bh, (unsigned)N * 4u);      // per-token variant: N scales; past the end reads 0
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
     if (QREG < KS && qf == nullptr) {
         // same row pitch and chunk swizzle as a K^ tile (no key permutation); rows past Nq read as zero
-        const p4i q_desc = pv8_descriptor(qi + slab_q * D, (unsigned)Nq * D);
+        const p4i q_desc = buffer_descriptor(qi + slab_q * D, (unsigned)Nq * D);
 #pragma unroll
         for (int i = 0; i < QB / 16 / NT; ++i) {
             const int vidx = t + NT * i, p = vidx / KCH, slot = vidx % KCH;
-            pv8_load_to_lds16(q_desc, (unsigned)((qt * QTILE + p) * D + ((slot ^ k_swz8<D>(p)) * 16)),
-                              lds_base + QOFF + wave * 1024 + i * (NT * 16));
+            load_to_lds16(q_desc, (unsigned)((qt * QTILE + p) * D + ((slot ^ k_swz<D>(p)) * 16)),
+                          uniform(lds_base + QOFF + wave * 1024 + i * (NT * 16)));
         }
     }
     auto fetch = [&](int j, int buf) {
         if (KTOK && wave == 0 && lane < KT / 4)          // the tile's 64 key scales, 16 bytes per lane
-            pv8_load_to_lds16(ks_desc, (unsigned)lane * 16u + (unsigned)j * (KT * 4), lds_base + 3 * (KB + VB) + buf * KSL);
+            load_to_lds16(ks_desc, (unsigned)lane * 16u + (unsigned)j * (KT * 4), uniform(lds_base + 3 * (KB + VB) + buf * KSL));
         const unsigned kb_addr = lds_base + buf * (KB + VB) + wave * 1024;
 #pragma unroll
         for (int i = 0; i < KL; ++i)
-            pv8_load_to_lds16(k_desc, k_goff0 + (unsigned)(i * (NT / KCH) * D) + (unsigned)j * (KT * D), kb_addr + i * (NT * 16));
+            load_to_lds16(k_desc, k_goff0 + (unsigned)(i * (NT / KCH) * D) + (unsigned)j * (KT * D), uniform(kb_addr + i * (NT * 16)));
 #pragma unroll
         for (int i = 0; i < VL; ++i)
-            pv8_load_to_lds16(v_desc, v_goff0 + (unsigned)(i * (NT / 4)) * (unsigned)Np + (unsigned)j * KT, kb_addr + KB + i * (NT * 16));
+            load_to_lds16(v_desc, v_goff0 + (unsigned)(i * (NT / 4)) * (unsigned)Np + (unsigned)j * KT, uniform(kb_addr + KB + i * (NT * 16)));
     };
 
     // ---- operand read offsets (per lane, inside a buffer).  The swizzle of a row depends on the
@@ -205,7 +188,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     // V^^T are the first ones plus a constant: KS + 2 registers, the rest immediates.
     int k_rd0[KS], v_rd0[2];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_rd0[ks] = ql * D + (((2 * ks + h) ^ k_swz8<D>(ql)) * 16);
+    for (int ks = 0; ks < KS; ++ks) k_rd0[ks] = ql * D + (((2 * ks + h) ^ k_swz<D>(ql)) * 16);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) v_rd0[kb] = KB + ql * KT + (((2 * kb + h) ^ vt_swz(ql)) * 16);
     auto k_rd = [&](int kb, int ks) { return k_rd0[ks] + kb * (32 * D); };

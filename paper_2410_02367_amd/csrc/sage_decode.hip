@@ -24,22 +24,6 @@ typedef _Float16 d4h __attribute__((ext_vector_type(4)));
 namespace {
 constexpr float DEC_LOG2E = 1.4426950408889634f;
 constexpr float DEC_SLACK = 8.0f;           // log2 of the largest P~ tolerated before the running maximum is raised
-
-template <int D> __device__ __forceinline__ int dec_kswz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
-template <int D> __device__ __forceinline__ int dec_vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
-
-__device__ __forceinline__ d4i dec_descriptor(const void* base, unsigned bytes) {
-    const unsigned long long a = (unsigned long long)base;
-    return (d4i){__builtin_amdgcn_readfirstlane((int)(unsigned)a), __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
-// 16 (4) bytes per lane from global memory to LDS, lane l to lds_addr + 16 l (4 l); asynchronous (vmcnt)
-__device__ __forceinline__ void dec_load16(const d4i& rsrc, unsigned goff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(goff), "s"(rsrc), "s"(lds_addr) : "memory");
-}
-__device__ __forceinline__ void dec_load4(const d4i& rsrc, unsigned goff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds" : : "v"(goff), "s"(rsrc), "s"(lds_addr) : "memory");
-}
 }  // namespace
 
 // grid: one workgroup per (slab, key chunk), chunk fastest.  lse != nullptr: a partial result per chunk, as in sage_attn.hip.
@@ -74,27 +58,27 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // ---- tile loads of this wavefront.  Rows past the end lie beyond the descriptors: their K^ is masked, their V must
     // be finite, so the V buffers start as zeros (a load may leave them untouched).
     const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds + wave * WBUF;
-    const d4i k_rsrc = dec_descriptor(ki + slab * D, (unsigned)N * D);
-    const d4i v_rsrc = dec_descriptor(vg + slab * D, (unsigned)N * VROW);
-    const d4i s_rsrc = dec_descriptor(ksc_bh, (unsigned)N * 4u);
+    const d4i k_rsrc = buffer_descriptor(ki + slab * D, (unsigned)N * D);
+    const d4i v_rsrc = buffer_descriptor(vg + slab * D, (unsigned)N * VROW);
+    const d4i s_rsrc = buffer_descriptor(ksc_bh, (unsigned)N * 4u);
     unsigned k_goff[KL], v_goff[VL];
 #pragma unroll
     for (int i = 0; i < KL; ++i) {
         const int vi = 64 * i + lane, row = vi / KCH;
-        k_goff[i] = (unsigned)(row * D + ((vi % KCH) ^ dec_kswz<D>(row)) * 16);
+        k_goff[i] = (unsigned)(row * D + ((vi % KCH) ^ k_swz<D>(row)) * 16);
     }
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
         const int vi = 64 * i + lane, row = vi / VCH;
-        v_goff[i] = (unsigned)(row * VROW + ((vi % VCH) ^ dec_vswz<D>(row)) * 16);
+        v_goff[i] = (unsigned)(row * VROW + ((vi % VCH) ^ v_swz<D>(row)) * 16);
     }
     auto request = [&](int j, int buf) {
         const unsigned at = __builtin_amdgcn_readfirstlane((int)(base + buf * BUF));
 #pragma unroll
-        for (int i = 0; i < KL; ++i) dec_load16(k_rsrc, k_goff[i] + (unsigned)j * KB, at + 1024 * i);
+        for (int i = 0; i < KL; ++i) load_to_lds16(k_rsrc, k_goff[i] + (unsigned)j * KB, at + 1024 * i);
 #pragma unroll
-        for (int i = 0; i < VL; ++i) dec_load16(v_rsrc, v_goff[i] + (unsigned)j * VB, at + KB + 1024 * i);
-        if (KTOK) dec_load4(s_rsrc, (unsigned)(j * 32 + lane) * 4u, at + KB + VB);
+        for (int i = 0; i < VL; ++i) load_to_lds16(v_rsrc, v_goff[i] + (unsigned)j * VB, at + KB + 1024 * i);
+        if (KTOK) load_to_lds4(s_rsrc, (unsigned)(j * 32 + lane) * 4u, at + KB + VB);
     };
     unsigned char* const mine = lds + wave * WBUF;
     if (tiles * 32 > N) {
@@ -136,11 +120,11 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // ---- operand read offsets, as in sage_attn.hip
     int k_off[KS], v_off[DT];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * D + (((2 * ks + g) ^ dec_kswz<D>(ql)) * 16);
+    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * D + (((2 * ks + g) ^ k_swz<D>(ql)) * 16);
     const int grp = lane >> 4, li = lane & 15, v_row = 4 * (grp >> 1) + (li >> 2);
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-        v_off[dt] = KB + v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ dec_vswz<D>(v_row)) * 16) + (li & 1) * 8;
+        v_off[dt] = KB + v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ v_swz<D>(v_row)) * 16) + (li & 1) * 8;
 
     d16f o[DT];
 #pragma unroll

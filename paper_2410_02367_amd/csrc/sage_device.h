@@ -1,4 +1,4 @@
-// Device code shared by the kernels that quantize.
+// Device code shared by the kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,6 +32,40 @@ __device__ __forceinline__ double fold16(double a, double b) {
     auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
     return __builtin_bit_cast(double, (u2){lo[0], hi[0]}) + __builtin_bit_cast(double, (u2){lo[1], hi[1]});
 }
+
+// ---- tiles of K^ and V in LDS (the attention kernels)
+// Rows are unpadded (K^ of D bytes, V of 2 D); their 16-byte chunks are XOR-swizzled so that the operand reads of 16
+// consecutive rows touch every bank once.
+template <int D> __device__ __forceinline__ int k_swz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
+template <int D> __device__ __forceinline__ int v_swz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+
+// Raw-buffer descriptor of `bytes` bytes at `base` (wave-uniform; readfirstlane pins it to scalar registers): the hardware
+// checks every lane's offset against the size, and a lane beyond it does not touch memory.  The ragged last tile
+// needs no clamping code: its rows are masked or multiplied by P~ = 0 anyway.
+typedef int buffer4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ buffer4 buffer_descriptor(const void* base, unsigned bytes) {
+    const unsigned long long p = (unsigned long long)base;
+    // dword 0-1: 48-bit base, stride 0 (raw buffer); dword 2: size in bytes; dword 3: 32-bit data format
+    return (buffer4){__builtin_amdgcn_readfirstlane((int)(unsigned)p),
+                     __builtin_amdgcn_readfirstlane((int)((unsigned)(p >> 32) & 0xffffu)),
+                     __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+// 16 (4) bytes per lane from global memory straight into LDS: lane l lands at LDS byte address lds_addr + 16 l (4 l), with
+// lds_addr in a scalar register.  Written as assembly because the compiler, which cannot tell which LDS bytes such a
+// load writes, makes every later LDS read wait for it (vmcnt(0)) and so turns the asynchronous load into a synchronous
+// one.  Completion is tracked by hand: the issuing wavefront waits with s_waitcnt vmcnt before it reads the bytes, or
+// before the barrier that publishes them.  m0 is set without being declared; the build checks that the compiler does not
+// use it itself.
+__device__ __forceinline__ void load_to_lds16(const buffer4& rsrc, unsigned goff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 : : "v"(goff), "s"(rsrc), "s"(lds_addr) : "memory");
+}
+__device__ __forceinline__ void load_to_lds4(const buffer4& rsrc, unsigned goff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
+                 : : "v"(goff), "s"(rsrc), "s"(lds_addr) : "memory");
+}
+// an address that is the same in every lane, pinned to a scalar register
+__device__ __forceinline__ unsigned uniform(unsigned addr) { return (unsigned)__builtin_amdgcn_readfirstlane((int)addr); }
 
 // Causal launches: item `slot` of an XCD -> (unit, query tile).  A unit is a (batch, head) slab or a key chunk of one; a
 // tile's weight grows with qt, so the order is heaviest tile first over `group` units of the XCD at a time (one pass),

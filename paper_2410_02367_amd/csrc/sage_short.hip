@@ -34,20 +34,6 @@ constexpr float SHORT_MAGIC = 12582912.0f;
 typedef float s4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float as_f(unsigned v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ unsigned as_u(float v) { return __builtin_bit_cast(unsigned, v); }
-
-template <int D> __device__ __forceinline__ int short_kswz(int row) { return D == 128 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
-template <int D> __device__ __forceinline__ int short_vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
-
-__device__ __forceinline__ s4i short_descriptor(const void* base, unsigned bytes) {
-    const unsigned long long a = (unsigned long long)base;
-    return (s4i){__builtin_amdgcn_readfirstlane((int)(unsigned)a), __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
-// 16 bytes per lane from global memory to LDS, lane l to lds_addr + 16 l; asynchronous (vmcnt)
-__device__ __forceinline__ void short_load_to_lds16(const s4i& rsrc, unsigned goff, unsigned lds_addr) {
-    const unsigned addr = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr);
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(goff), "s"(rsrc), "s"(addr) : "memory");
-}
 }  // namespace
 
 // D channels, NTILE tiles of 64 keys at most, NW wavefronts; KTOK: one scale per key.  grid: groups workgroups per
@@ -101,16 +87,16 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     // ---- values into LDS, asynchronously.  Chunks of rows past the end are zeroed first (P~ is 0 there, but 0 * NaN
     // would not be); their loads lie beyond the descriptor.
     {
-        const s4i rsrc = short_descriptor(vf + slab * D, (unsigned)N * VROW);
+        const s4i rsrc = buffer_descriptor(vf + slab * D, (unsigned)N * VROW);
         const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)vl;
         const int vecs = tiles * (64 * VCH);
         for (int i = wave * 64; i < vecs; i += NT) {
-            const int vi = i + lane, row = vi / VCH, c = (vi % VCH) ^ short_vswz<D>(row);
+            const int vi = i + lane, row = vi / VCH, c = (vi % VCH) ^ v_swz<D>(row);
             if (i / VCH + 64 / VCH > N) {
                 *(s4i*)(vl + vi * 16) = (s4i){0, 0, 0, 0};
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
-            short_load_to_lds16(rsrc, (unsigned)(row * VROW + c * 16), base + i * 16);
+            load_to_lds16(rsrc, (unsigned)(row * VROW + c * 16), uniform(base + i * 16));
         }
     }
     const int rtiles = (Nq + 31) / 32;
@@ -179,7 +165,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     }
     auto store_codes = [&](const float (&f)[8], int r, float rcp) {
         const uint2 w = make_uint2(quantize4_k(f[0], f[1], f[2], f[3], rcp), quantize4_k(f[4], f[5], f[6], f[7], rcp));
-        *(uint2*)(kl + r * D + (((c8 >> 1) ^ short_kswz<D>(r)) * 16) + (c8 & 1) * 8) = w;
+        *(uint2*)(kl + r * D + (((c8 >> 1) ^ k_swz<D>(r)) * 16) + (c8 & 1) * 8) = w;
     };
     auto row_max = [&](float m, const float (&f)[8]) {
 #pragma unroll
@@ -240,11 +226,11 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     // ---- operand read offsets, as in sage_attn.hip
     int k_off[KS], v_off[DT];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * D + (((2 * ks + g) ^ short_kswz<D>(ql)) * 16);
+    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * D + (((2 * ks + g) ^ k_swz<D>(ql)) * 16);
     const int grp = lane >> 4, li = lane & 15, v_row = 4 * (grp >> 1) + (li >> 2);
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-        v_off[dt] = v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ short_vswz<D>(v_row)) * 16) + (li & 1) * 8;
+        v_off[dt] = v_row * VROW + (((4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ v_swz<D>(v_row)) * 16) + (li & 1) * 8;
 
     // seed of the scores and selector of the row sums, as in sage_attn.hip
     s16i magic;
