@@ -9,9 +9,9 @@
 // Several workgroups can share a slab (each takes its part of the query tiles and makes K^ for itself); see
 // short_groups() for how many, and short_fits() for which launches come here.
 //
-// Measured against the two launches before it (K pre-pass, attention kernel), us for the whole call: 12 x 64 slabs of
-// 197 keys at D = 64: 40 -> 30; 1 x 2 of 256: 16.5 -> 9.5; 256 of 256 at D = 128: 40 -> 23; 128 x (4096 queries against
-// 77 keys): 128 -> 87.  Bounds: launch latency for few slabs; for many, a memory phase (Q, K, V in, at the copy rate)
+// Measured against the launches of the separate calls, us for the whole call: 12 x 64 slabs of 197 keys at D = 64: 44 ->
+// 26.5; 1 x 2 of 256: 32 -> 8.6; 129 of 512: 36 -> 25; 256 of 256 at D = 128: 39 -> 17.5; 128 x (4096 queries against 77
+// keys): 133 -> 67.  Bounds: launch latency for few slabs; for many, a memory phase (Q, K, V in, at the copy rate)
 // and a VALU phase (codes of K^ and Q^, softmax) of about equal length, which overlap only between workgroups.
 #include "sage_internal.h"
 #include "sage_device.h"
@@ -380,7 +380,9 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
 // Key sequences whose K^ and V fit the LDS beside a second workgroup's, or nearly: 512 keys of 64 channels, 256 of 128.
 bool short_fits(int N, int D) { return N <= (D == 64 ? 512 : 256); }
 
-// Workgroups per slab: up to one per round of the wavefronts while the chip has room for more workgroups.
+// Workgroups per slab: up to one per round of the wavefronts while the chip has room for more workgroups.  (Rounded down:
+// 129 to 255 slabs of 256-row workgroups get one each, and leave the CUs between; 129 of 512 keys at D = 64 take 25 us,
+// 256 of them 28.)
 static int short_groups(int BH, int Nq, int rows, int per_cu) {
     const int most = (Nq + rows - 1) / rows;
     const int room = 256 * per_cu / BH;
