@@ -1022,15 +1022,16 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
     // Longer, no mask: a 256-row workgroup takes 3-5 % less than two 128-row ones side by side, but a 128-row one that has its
     // CU to itself 0.74 of that time.  So the smaller ones where their last round over the 512 places is at most half full
     // and no more than five full ones are before it (12 slabs of 6000, 564 of them: 207 / 245; 30 of 3000, 720: 115 / 132;
-    // 86 of 4096, 2752: 567 / 579), the larger ones elsewhere (12 of 3000, 288: 64 / 58; 46 of 3800, 1380: 281 / 268; one
-    // scale per key, 20 of 6000, 940: 328 / 315).
+    // 86 of 4096, 2752: 567 / 579) and where rows that are no multiple of 256 cost the larger ones a round more (480 against
+    // 288 for 96 chunks of 2816 keys and 640 queries: 92 / 117), the larger ones elsewhere (12 of 3000, 288: 64 / 58; 46 of
+    // 3800, 1380: 281 / 268; one scale per key, 20 of 6000, 940: 328 / 315).
     const int small_tiles = (Nq + 4 * WROWS - 1) / (4 * WROWS), large_tiles = (Nq + 8 * WROWS - 1) / (8 * WROWS);
     const long units = (long)BH * sp.n_splits;
     const int n_seen = sp.n_splits > 1 ? sp.chunk : N;           // keys a workgroup walks
     bool small = QS == 1 && !(sdump && D == 128);
     if (small && D == 128 && n_seen > (causal ? 4096 : 2048)) {
         const long rounds = (units * small_tiles + 511) / 512, last = units * small_tiles - 512 * (rounds - 1);
-        small = causal ? units * large_tiles < 2 * 256 : last <= 256 && rounds <= 6;
+        small = causal ? units * large_tiles < 2 * 256 : (last <= 256 && rounds <= 6) || (units * large_tiles + 255) / 256 > rounds;
     }
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
