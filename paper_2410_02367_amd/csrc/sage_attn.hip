@@ -1069,8 +1069,11 @@ SplitPlan plan_split(int BH, int Nq, int N, int causal, int requested) {
         // chunks only add partial results to write and merge.  With more rows it is bound by the matrix pipe, which
         // wants two workgroups on every CU, and no more: 32 slabs of 512 rows against 16K keys, us at 2 / 4 / 6 / 8
         // chunks: 129 / 115 / 123 / 122; of 256 rows at 4 / 8 / 12: 74 / 68 / 76.  Chunks of at least 8 key tiles.
+        // A launch that has a workgroup for every CU is left whole: at 128 slabs of 256 rows two chunks gain 6 % against
+        // 4096 keys at D = 64, nothing at D = 128, and lose 20 % against 1024 (15.0 / 18.9, 22.4 / 26.6); and a result that
+        // did not pass through fp16 partial results is 2.9e-4 instead of 3.6e-4 from the 64-bit one.
         const long wg = (long)BH * ((Nq + 127) / 128);
-        const long want = Nq <= 128 ? (256 + wg - 1) / wg : 512 / wg;
+        const long want = wg >= 256 ? 1 : Nq <= 128 ? (256 + wg - 1) / wg : 512 / wg;
         const long most = N / 512 < 64 ? N / 512 : 64;
         requested = (int)(want < most ? want : most);
     }

@@ -167,6 +167,11 @@ def test_split_call_validates_and_its_chunk_plan_keeps_its_promises(lib):
     # 65535 slabs x 32768 chunks of 128 keys: more (slab, chunk) pairs than the kernels count
     assert lib.sage_attn_cross_split_fwd(*head, good, sz(1 << 62), 255, 257, 1, 1 << 22, 64, 0, f(0.125), 128, 64, 1 << 15, None) == 2
     assert lib.sage_attn_split_count(1, 1, 4097, 4096, 1, 4) == 0
+    # a launch with a workgroup of 128 rows for each of the 256 compute units is not cut; one with fewer is
+    for Nq in (130, 200, 256):
+        assert lib.sage_attn_split_count(4, 32, Nq, 1024, 0, 0) == lib.sage_attn_split_count(8, 32, Nq, 8192, 1, 0) == 1
+        assert lib.sage_attn_split_workspace(4, 32, Nq, 4096, 128, 1, 0) == 0
+        assert lib.sage_attn_split_count(1, 127, Nq, 4096, 0, 0) == 2
     assert lib.sage_attn_split_count(1, 1, 4, 4096, 1, 1) == 1 and lib.sage_attn_split_workspace(1, 1, 4, 4096, 64, 1, 1) == 0
     assert lib.sage_attn_split_workspace(2, 3, 4, 4096, 64, 1, 4) == 4 * 2 * 3 * 4 * (2 * 64 + 4)
     # a request far beyond the number of 128-key groups is the plan of that number (and must not
