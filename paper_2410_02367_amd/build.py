@@ -309,6 +309,11 @@ def check_short_asm(text: str) -> list:
     return check_loads_asm(text, "sage_short_kernel", 10)
 
 
+def check_short_pair_asm(text: str) -> list:
+    """The same with two wavefronts per query tile: {256, 512 keys at D = 64} x {per-block, per-token key scales}."""
+    return check_loads_asm(text, "sage_short_pair_kernel", 4)
+
+
 def check_decode_asm(text: str) -> list:
     """The kernels for few queries: {4 wavefronts at D = 64, 2 and 4 at D = 128} x {per-block, per-token key scales}; and the
     merge of key chunks beside them, which has no loads of that kind."""
@@ -335,7 +340,7 @@ def verify_attention_isa(extra=()) -> None:
     with tempfile.TemporaryDirectory() as tmp:
         for src, check in (("sage_attn.hip", check_attention_asm), ("sage_attn_pv8.hip", check_pv8_asm),
                            ("sage_prepass.hip", check_no_spills), ("sage_prepass_v.hip", check_no_spills),
-                           ("sage_short.hip", check_short_asm), ("sage_decode.hip", check_decode_asm)):
+                           ("sage_short.hip", check_short_asm), ("sage_short.hip", check_short_pair_asm), ("sage_decode.hip", check_decode_asm)):
             out = os.path.join(tmp, src + ".s")
             cmd = [hipcc(), *flags, *extra, "-S", "--cuda-device-only", "-o", out, os.path.join(CSRC, src)]
             res = subprocess.run(cmd, capture_output=True, text=True)

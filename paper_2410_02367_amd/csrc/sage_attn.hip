@@ -503,15 +503,15 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 off_grid[qs] = __builtin_fmaf(-MAGIC_F, sc[qs], sum) != m_run[qs];
             }
             if (need_mask) {
-                const int q_row = qrow0 + 32 * qs + ql;
+                // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
+                int seen = N - kv0;
+                if (CAUSAL && seen > qrow0 + 32 * qs + ql + coff + 1 - kv0) seen = qrow0 + 32 * qs + ql + coff + 1 - kv0;
+                seen -= 4 * g;
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        int key = kv0 + 32 * s + 8 * (r >> 2) + 4 * g + (r & 3);
-                        bool hide = (key >= N) || (CAUSAL && key > q_row + coff);
-                        acc_s[qs][s][r] = hide ? (int)0xFF800000 : acc_s[qs][s][r];
-                    }
+                    for (int r = 0; r < 16; ++r)
+                        acc_s[qs][s][r] = 32 * s + 8 * (r >> 2) + (r & 3) < seen ? acc_s[qs][s][r] : (int)0xFF800000;
             }
         }
     };

@@ -49,7 +49,6 @@ constexpr float PV8_LOG2_127 = 6.988684686772166f;
 constexpr float PV8_HIDDEN = -3.0e38f;            // stands for a masked score: finite, so that 0 * it is not NaN
 constexpr int PV8_FLUSH_TILES = 1024;
 
-__device__ __forceinline__ float lane32_partner(float v) { return __shfl_xor(v, 32, 64); }
 __device__ __forceinline__ int k_unperm(int p) {
     // key of a tile held by LDS row p: row 32kb + 8g + 4h + b holds key 32kb + 16h + 4g + b
     return (p & 32) | ((p & 4) << 2) | ((p & 24) >> 1) | (p & 3);
@@ -309,13 +308,14 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         }
         if (edge) {          // wave-uniform: interior tiles skip the mask arithmetic
             asm volatile("" ::: "memory");      // keeps this a branch (not 64 compare-and-select pairs on every tile)
+            // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
+            int seen = N - j * KT;
+            if (CAUSAL && seen > q_row + coff + 1 - j * KT) seen = q_row + coff + 1 - j * KT;
+            seen -= 16 * h;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int kidx = j * KT + 32 * kb + 16 * h + r;
-                    if (kidx >= N || (CAUSAL && kidx > q_row + coff)) y[kb][r] = PV8_HIDDEN;
-                }
+                for (int r = 0; r < 16; ++r) y[kb][r] = 32 * kb + r < seen ? y[kb][r] : PV8_HIDDEN;
         }
         float tmax = PV8_HIDDEN;
 #pragma unroll
@@ -323,7 +323,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
 #pragma unroll
             for (int r = 0; r < 16; ++r) tmax = __builtin_fmaxf(tmax, y[kb][r]);
         tmax *= sc;
-        tmax = __builtin_fmaxf(tmax, lane32_partner(tmax));
+        tmax = pair32_max(tmax);
         const float m_new = __builtin_fmaxf(m_run, tmax);
         ++since;
         if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0ull || since >= PV8_FLUSH_TILES) {
@@ -385,7 +385,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     if (pending) finish_previous();
 
     // ---- epilogue: O = (O_fp32 + A) * delta_V[c] / sum(127 P~)
-    const float lt = l127 + lane32_partner(l127);
+    const float lt = pair32_sum(l127);
     const float inv = 1.0f / lt, g_run = 1.0f / ginv;
     int q_out = qrow0;
     if (SPLIT) asm volatile("" : "+s"(q_out));       // the output addresses are formed here, not carried through the loop

@@ -172,7 +172,7 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         float top = y[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, y[r]);
-        top = __builtin_fmaxf(top, __shfl_xor(top, 32, 64)) * sc;
+        top = pair32_max(top) * sc;
         if (__builtin_amdgcn_ballot_w64(top > m_run + DEC_SLACK) != 0ull) {
             const float m_new = __builtin_fmaxf(m_run, top);
             // (a row that has seen no key yet: nothing to rescale, and no difference of infinities)
@@ -213,7 +213,7 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     }
 
     // ---- the wavefronts' results: O = sum_w f_w O_w / sum_w f_w l_w, f_w = 2^(m_w - max m)
-    l += __shfl_xor(l, 32, 64);
+    l = pair32_sum(l);
     if (g == 0) {
         s_m[wave][ql] = m_run;
         s_l[wave][ql] = l;

@@ -18,6 +18,40 @@ __device__ __forceinline__ unsigned quantize4(float x0, float x1, float x2, floa
     return lo | hi;
 }
 
+// a word as a float, by value (a bit_cast of a vector's element in place takes element 0 whatever its index)
+__device__ __forceinline__ float word_f32(unsigned v) { return __builtin_bit_cast(float, v); }
+// max / sum of a lane's value and that of the lane 32 away
+__device__ __forceinline__ float pair32_max(float m) {
+    const unsigned v = __builtin_bit_cast(unsigned, m);
+    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return __builtin_fmaxf(word_f32(r[0]), word_f32(r[1]));
+}
+__device__ __forceinline__ float pair32_sum(float x) {
+    const unsigned v = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return word_f32(r[0]) + word_f32(r[1]);
+}
+
+// Maximum over groups of LANES adjacent lanes (4, 8, 16, 32 or 64), in every lane; passes over NaN as fmaxf does.  Lane
+// permutations of the vector unit, about 8 clocks a step: __shfl_xor goes through the LDS, 60 or more, and the steps are a chain.
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float m) {
+    const int v = __builtin_bit_cast(int, m);
+    return __builtin_fmaxf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false)));
+}
+template <int LANES>
+__device__ __forceinline__ float lanes_max(float m) {
+    m = dpp_max<0xB1>(m);                        // lane ^ 1
+    m = dpp_max<0x4E>(m);                        // lane ^ 2
+    if (LANES >= 8) m = dpp_max<0x141>(m);       // the other half of 8, mirrored
+    if (LANES >= 16) m = dpp_max<0x140>(m);      // the other half of 16, mirrored
+    if (LANES >= 32) {
+        const unsigned v = __builtin_bit_cast(unsigned, m);
+        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        m = __builtin_fmaxf(word_f32(r[0]), word_f32(r[1]));
+    }
+    return LANES >= 64 ? pair32_max(m) : m;
+}
 // x + the value of the lane 32 (16) away, of two values at once: lanes of the lower half (even rows of 16) end with
 // the sum of a, the others with the sum of b
 __device__ __forceinline__ double fold32(double a, double b) {
@@ -156,10 +190,9 @@ struct QueryRows {
                 for (int e = 0; e < 4; ++e) top = max_abs(top, w[e]);
             }
         float m = __builtin_fmaxf((float)top[0], (float)top[1]) * sm_scale;
-        m = __builtin_fmaxf(m, __shfl_xor(m, 32, 64));
+        m = pair32_max(m);
         if (shift_q == 0) return m;
-#pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+        m = lanes_max<32>(m);
         if (shift_q == 5) return m;
         if ((threadIdx.x & 63) == 0) red[wave] = m;
         __syncthreads();

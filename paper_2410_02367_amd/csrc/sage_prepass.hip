@@ -209,8 +209,7 @@ __device__ __forceinline__ float slab_mean(const long long* __restrict__ parts, 
 
 template <int NT = 256>
 __device__ __forceinline__ float wg_max(float v, float* red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off, 64));
+    v = lanes_max<64>(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     float m = red[0];
@@ -382,8 +381,7 @@ __device__ __forceinline__ void quant_token_body(const _Float16* __restrict__ x,
             float amax = 0.0f;
 #pragma unroll
             for (int j = 0; j < CH; ++j) amax = __builtin_fmaxf(amax, amax8<IS_K>(raw[i].x[j], mean[j], sm_scale));
-#pragma unroll
-            for (int off = VPR / 2; off >= 1; off >>= 1) amax = __builtin_fmaxf(amax, __shfl_xor(amax, off, 64));
+            amax = lanes_max<VPR>(amax);
             const float delta = amax / 127.0f;
             const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
             if (r < N) {
@@ -518,8 +516,7 @@ __device__ __forceinline__ void k_small_body(const _Float16* __restrict__ k,
             if (i < nset) {
                 const int r = rg + i * RG;
                 float amax = row_amax(x[i]);
-#pragma unroll
-                for (int off = VPR / 2; off >= 1; off >>= 1) amax = __builtin_fmaxf(amax, __shfl_xor(amax, off, 64));
+                amax = lanes_max<VPR>(amax);
                 if (r < N) {
                     if (c8 == 0) scale[(size_t)bh * N + r] = amax / 127.0f;
                     quantize_row(x[i], amax > 0.0f ? 127.0f / amax : 0.0f, r);
@@ -537,8 +534,7 @@ __device__ __forceinline__ void k_small_body(const _Float16* __restrict__ k,
     for (int i = 0; i < MAXR; ++i) {
         if (i < nset) {
             float m = row_amax(x[i]);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+            m = lanes_max<64>(m);
             if (lane == 0) s_red[i * NW + wave] = rg + i * RG < N ? m : 0.0f;
         }
     }

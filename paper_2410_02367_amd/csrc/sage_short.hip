@@ -10,8 +10,10 @@
 // short_groups() for how many, and short_fits() for which launches come here.
 //
 // Measured against the launches of the separate calls, us for the whole call: 12 x 64 slabs of 197 keys at D = 64: 44 ->
-// 26.5; 1 x 2 of 256: 32 -> 8.6; 129 of 512: 36 -> 25; 256 of 256 at D = 128: 39 -> 17.5; 128 x (4096 queries against 77
-// keys): 133 -> 67.  Bounds: launch latency for few slabs; for many, a memory phase (Q, K, V in, at the copy rate)
+// 24.4; 1 x 2 of 256: 32 -> 7.8; 129 of 512: 36 -> 25; 256 of 256 at D = 128: 39 -> 17.5; 128 x (4096 queries against 77
+// keys): 133 -> 67.  (26.5 and 8.6 before maxima went through lane permutations instead of the LDS, masks took one comparison
+// per score and the first tile's rescaling of an empty accumulator was left out; 667 x 468, causal: 66.1 -> 60.5, 616 x 84 x
+// 128, causal: 18.0 -> 15.9.)  Bounds: launch latency for few slabs; for many, a memory phase (Q, K, V in, at the copy rate)
 // and a VALU phase (codes of K^ and Q^, softmax) of about equal length, which overlap only between workgroups.
 #include "sage_internal.h"
 #include "sage_device.h"
@@ -38,10 +40,12 @@ __device__ __forceinline__ unsigned as_u(float v) { return __builtin_bit_cast(un
 
 // D channels, NTILE tiles of 64 keys at most, NW wavefronts; KTOK: one scale per key.  grid: groups workgroups per
 // slab.  48 KB of K^ and V (NTILE * D = 256): 4 wavefronts, two or three workgroups per CU; 96 KB: 8 wavefronts, one.
-template <int D, int NTILE, int NW, bool KTOK>
-__global__ void __launch_bounds__(NW * 64, NW == 8 || D == 128 ? 2 : 3)
-sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ kf, const _Float16* __restrict__ vf,
-                  _Float16* __restrict__ og, int Nq, int N, int shift_q, int shift_k, int causal, float sm_scale, int groups) {
+// KSP = 2: launches that leave CUs empty, where a workgroup's chain is all there is.  Two wavefronts share a query tile, each
+// takes every other key tile, and their results are added up in LDS; a workgroup makes one round (NW / 2 query tiles).
+template <int D, int NTILE, int NW, int KSP, bool KTOK>
+__device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, const _Float16* __restrict__ kf,
+                                           const _Float16* __restrict__ vf, _Float16* __restrict__ og, int Nq, int N,
+                                           int shift_q, int shift_k, int causal, float sm_scale, int groups) {
     constexpr int KMAX = NTILE * 64;            // keys that fit
     constexpr int VPR = D / 8;                  // 16-byte vectors (8 channels) of a K row
     constexpr int RPI = 64 / VPR;               // K rows per load instruction of a wavefront
@@ -52,19 +56,25 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     constexpr int VROW = 2 * D;
     constexpr int VCH = VROW / 16;              // 16-byte chunks of a V row
     static_assert(GPW >= 1, "every wavefront owns at least one group of 32 keys");
-    __shared__ __attribute__((aligned(1024))) unsigned char kl[KMAX * D];
-    __shared__ __attribute__((aligned(1024))) unsigned char vl[KMAX * VROW];
+    constexpr int RT = NW / KSP;                // query tiles of a round
+    static_assert(KSP == 1 || RT == 4, "a round is a multiple of every block_q");
+    constexpr int MERGE = KSP == 1 ? 0 : RT * 32 * D * 4, TILES = KMAX * D + KMAX * VROW;      // bytes
+    __shared__ __attribute__((aligned(1024))) unsigned char pool[TILES > MERGE ? TILES : MERGE];
+    unsigned char* const kl = pool;
+    unsigned char* const vl = pool + KMAX * D;
     __shared__ __attribute__((aligned(16))) float s_mean[D];
     __shared__ float s_max[KMAX / 32];
     __shared__ __attribute__((aligned(16))) float s_scale[KTOK ? KMAX : KMAX / 64];
     __shared__ __attribute__((aligned(16))) float s_bias[KTOK ? KMAX : 4];       // -12582912 * s_scale
-    __shared__ float s_q[2][NW];
+    __shared__ float s_q[2][RT];
+    __shared__ float s_ml[KSP == 1 ? 1 : 2 * RT][64];
     static_assert(NW * D * 8 <= KMAX * D, "the partial column sums fit where K^ will be");
     double (*const s_part)[D] = (double (*)[D])kl;       // [wavefront][channel]; read before the codes are written
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int ql = lane & 31, g = lane >> 5;
+    const int own = KSP == 1 ? wave : wave % RT, kpart = KSP == 1 ? 0 : wave / RT;      // query tile of a round; share of the key tiles
     const int bh = blockIdx.x / groups, part = blockIdx.x - bh * groups;
     const size_t slab = (size_t)bh * N, slab_q = (size_t)bh * Nq;
     const int tiles = (N + 63) / 64;
@@ -100,10 +110,10 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         }
     }
     const int rtiles = (Nq + 31) / 32;
-    // the workgroup's query tiles: NW at a time (128 or 256 rows, a multiple of every block_q), one per wavefront
+    // the workgroup's query tiles: RT at a time (128 or 256 rows, a multiple of every block_q)
     QueryRows<KS> rows;
     {
-        const int row = (part * NW + wave) * 32 + ql;
+        const int row = (part * RT + own) * 32 + ql;
         rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
     }
 
@@ -180,8 +190,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
             for (int i = 0; i < LPG; ++i) {
                 const int r = r0 + gr * 32 + i * RPI;
                 float m = row_max(0.0f, xs[gr][i]);
-#pragma unroll
-                for (int off = VPR / 2; off >= 1; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+                m = lanes_max<VPR>(m);
                 if (c8 == 0) {
                     // 22 significant bits, so that 12582912 * a is exact; not 0, so that -inf * a is not NaN
                     const float a = as_f(as_u(__builtin_fmaxf(m / 127.0f, 1e-30f)) & ~3u);
@@ -202,8 +211,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         }
 #pragma unroll
         for (int gr = 0; gr < GPW; ++gr) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) gm[gr] = __builtin_fmaxf(gm[gr], __shfl_xor(gm[gr], off, 64));
+            gm[gr] = lanes_max<64>(gm[gr]);
             if (lane == 0) s_max[wave * GPW + gr] = gm[gr];
         }
         __syncthreads();
@@ -239,9 +247,9 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
     const int sel_word = (((lane >> 4) ^ lane) & 1) ? 0 : 0x3C003C00;
     const s4i sel = {sel_word, sel_word, sel_word, sel_word};
 
-    for (int set = part, turn = 0; set * NW < rtiles; set += groups, turn ^= 1) {
-        const int row0 = (set * NW + wave) * 32, q_row = row0 + ql;
-        const float qmax = rows.block_amax(sm_scale, shift_q, wave, s_q[turn]);
+    for (int set = part, turn = 0; set * RT < rtiles; set += groups, turn ^= 1) {
+        const int row0 = (set * RT + own) * 32;
+        const float qmax = rows.block_amax(sm_scale, shift_q, own, s_q[turn]);
         const float qrcp = qmax > 0.0f ? 127.0f / qmax : 0.0f;
         const float dq = qmax / 127.0f * SHORT_LOG2E;
         s4i q[KS];
@@ -249,11 +257,11 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int i = 0; i < 4; ++i) q[ks][i] = (int)rows.word(ks, i, sm_scale, qrcp);
-        if ((set + groups) * NW < rtiles) {          // the next rows are requested before this tile's loop
-            const int row = ((set + groups) * NW + wave) * 32 + ql;
+        if (KSP == 1 && (set + groups) * RT < rtiles) {          // the next rows are requested before this tile's loop
+            const int row = ((set + groups) * RT + own) * 32 + ql;
             rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
         }
-        if (row0 >= Nq) continue;
+        if (KSP == 1 && row0 >= Nq) continue;
 
         s16f o[DT];
 #pragma unroll
@@ -261,7 +269,10 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
         s4f lsum = {0.0f, 0.0f, 0.0f, 0.0f};       // registers 0, 1: sums of the queries lane % 16, 16 + lane % 16
-        float m_run = -__builtin_inff();
+        // Below every score, and finite: with KSP = 2 a row may see none of its wavefront's keys; its weights are then
+        // exp2(-inf + 1e30) = 0, where an infinity would make them NaN.
+        float m_run = -1e30f;
+        bool fresh = true;                           // O and l are 0
         // keys this wavefront sees; a tile of which it sees only the first half is done by halves
         int seen = causal ? row0 + 32 + coff : N;
         seen = seen < N ? seen : N;
@@ -278,13 +289,18 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
             // register r of half h: key 64 j + 32 h + 8 (r / 4) + 4 g + r % 4
             const float sc = KTOK ? __builtin_fmaxf(dq, 1e-30f) : as_f(as_u(__builtin_fmaxf(dq * s_scale[j], 1e-30f)) & ~3u);
             if (j * 64 + 32 * NH > N || (causal && j * 64 + 32 * NH - 1 > row0 + coff)) {
+                // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
+                // (formed here and not ahead of the loop, where it would cost a register of the 168)
+                int ln = t & 63;
+                asm volatile("" : "+v"(ln));
+                int last = N;
+                if (causal && last > row0 + (ln & 31) + coff + 1) last = row0 + (ln & 31) + coff + 1;
+                last -= 64 * j + 4 * (ln >> 5);
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = 64 * j + 32 * h + 8 * (r >> 2) + 4 * g + (r & 3);
-                        if (key >= N || (causal && key > q_row + coff)) s[h][r] = (int)0xFF800000;       // -inf, and below every score
-                    }
+                    for (int r = 0; r < 16; ++r)        // -inf, and below every score
+                        s[h][r] = 32 * h + 8 * (r >> 2) + (r & 3) < last ? (int)s[h][r] : (int)0xFF800000;
             }
             // the argument of exp2 is y * sc + bias, y the seeded score (KTOK: the score times delta_K); see sage_attn.hip
             // for why it is rounded once, and why that needs the running maximum on the grid of 12582912 * sc
@@ -324,7 +340,7 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
                 want = off_grid || __builtin_fmaf(as_f((unsigned)mi), sc, bias) > SHORT_SLACK;
             }
             if (__builtin_amdgcn_ballot_w64(want) != 0ull) {
-                // (on the first tile m_run is -inf and every row that sees a key is here)
+                // (on the first tile every row that sees a key is here)
                 float top;
                 if (KTOK) {
                     auto x = __builtin_amdgcn_permlane32_swap(as_u(mf), as_u(mf), false, false);
@@ -338,12 +354,15 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
                 const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
                 bias = KTOK ? -m_run : -__builtin_fmaf(SHORT_MAGIC, sc, m_run);
-                lsum *= alpha;
+                if (!fresh) {
+                    lsum *= alpha;
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+                    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+                        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+                }
             }
+            fresh = false;
             const unsigned char* vt = vl + j * (64 * VROW);
 #pragma unroll
             for (int h = 0; h < NH; ++h)
@@ -370,11 +389,50 @@ sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ 
                 }
         };
         const int whole = (seen + 31) / 64;
-        for (int j = 0; j < whole; ++j) tile(j, std::integral_constant<int, 2>{});
-        if (whole * 64 < seen) tile(whole, std::integral_constant<int, 1>{});
-        const float inv = 1.0f / ((lane & 16) ? lsum[1] : lsum[0]);
+        if (KSP == 1 || row0 < Nq) {
+            for (int j = kpart; j < whole; j += KSP) tile(j, std::integral_constant<int, 2>{});
+            if (whole * 64 < seen && (KSP == 1 || whole % KSP == kpart)) tile(whole, std::integral_constant<int, 1>{});
+        }
+        float l = (lane & 16) ? lsum[1] : lsum[0];
+        if constexpr (KSP == 2) {
+            // the other wavefront's result, relative to its own maximum, through the LDS that held the key tiles
+            float* const other = (float*)pool + own * (32 * D) + lane;
+            __syncthreads();
+            if (kpart == 1) {
+                s_ml[own][lane] = m_run;
+                s_ml[RT + own][lane] = l;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) other[(16 * dt + r) * 64] = o[dt][r];
+            }
+            __syncthreads();
+            if (kpart == 1 || row0 >= Nq) return;
+            const float m1 = s_ml[own][lane], top = __builtin_fmaxf(m_run, m1);
+            const float f0 = __builtin_amdgcn_exp2f(m_run - top), f1 = __builtin_amdgcn_exp2f(m1 - top);
+            l = __builtin_fmaf(l, f0, s_ml[RT + own][lane] * f1);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[dt][r] = __builtin_fmaf(o[dt][r], f0, other[(16 * dt + r) * 64] * f1);
+        }
+        const float inv = 1.0f / l;
         store_rows<D>(og + (slab_q + row0) * D, Nq - row0, lane, true, [&](int dt, int r) { return o[dt][r] * inv; });
+        if (KSP == 2) return;
     }
+}
+
+template <int D, int NTILE, int NW, bool KTOK>
+__global__ void __launch_bounds__(NW * 64, NW == 8 || D == 128 ? 2 : 3)
+sage_short_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ kf, const _Float16* __restrict__ vf,
+                  _Float16* __restrict__ og, int Nq, int N, int shift_q, int shift_k, int causal, float sm_scale, int groups) {
+    short_pass<D, NTILE, NW, 1, KTOK>(qf, kf, vf, og, Nq, N, shift_q, shift_k, causal, sm_scale, groups);
+}
+template <int D, int NTILE, int NW, bool KTOK>
+__global__ void __launch_bounds__(NW * 64, 2)
+sage_short_pair_kernel(const _Float16* __restrict__ qf, const _Float16* __restrict__ kf, const _Float16* __restrict__ vf,
+                       _Float16* __restrict__ og, int Nq, int N, int shift_q, int shift_k, int causal, float sm_scale, int groups) {
+    short_pass<D, NTILE, NW, 2, KTOK>(qf, kf, vf, og, Nq, N, shift_q, shift_k, causal, sm_scale, groups);
 }
 
 // Key sequences whose K^ and V fit the LDS beside a second workgroup's, or nearly: 512 keys of 64 channels, 256 of 128.
@@ -389,15 +447,19 @@ static int short_groups(int BH, int Nq, int rows, int per_cu) {
     return room < 1 ? 1 : (room < most ? room : most);
 }
 
-template <int D, int NTILE, int NW>
+template <int D, int NTILE, int NW, int KSP = 1>
 static hipError_t launch_short_t(const void* q, const void* k, const void* v, void* o, int BH, int Nq, int N, int causal,
                                  float sm_scale, int block_q, int block_k, hipStream_t st) {
-    const int groups = short_groups(BH, Nq, NW * 32, NW == 8 ? 1 : D == 64 ? 3 : 2);
+    const int groups = KSP == 2 ? (Nq + 127) / 128 : short_groups(BH, Nq, NW * 32, NW == 8 ? 1 : D == 64 ? 3 : 2);
     const int shift_q = __builtin_ctz((unsigned)block_q), shift_k = __builtin_ctz((unsigned)block_k);
     const dim3 grid((unsigned)(BH * groups));
-#define SAGE_SHORT(KT) sage_short_kernel<D, NTILE, NW, KT><<<grid, NW * 64, 0, st>>>((const _Float16*)q, (const _Float16*)k, (const _Float16*)v, \
+#define SAGE_SHORT(NAME, KT) NAME<D, NTILE, NW, KT><<<grid, NW * 64, 0, st>>>((const _Float16*)q, (const _Float16*)k, (const _Float16*)v, \
         (_Float16*)o, Nq, N, shift_q, shift_k, causal, sm_scale, groups)
-    if (block_k == 1) SAGE_SHORT(true); else SAGE_SHORT(false);
+    if constexpr (KSP == 2) {
+        if (block_k == 1) SAGE_SHORT(sage_short_pair_kernel, true); else SAGE_SHORT(sage_short_pair_kernel, false);
+    } else {
+        if (block_k == 1) SAGE_SHORT(sage_short_kernel, true); else SAGE_SHORT(sage_short_kernel, false);
+    }
 #undef SAGE_SHORT
     return hipGetLastError();
 }
@@ -406,6 +468,15 @@ hipError_t launch_short(const void* q, const void* k, const void* v, void* o, in
                         float sm_scale, int block_q, int block_k, hipStream_t st) {
 #define SAGE_SHORT_N(DD, NT, NW) return launch_short_t<DD, NT, NW>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st)
     if (D == 64) {
+        // Two wavefronts per query tile (KSP = 2) where there is a CU for every 128 rows and the chain of key tiles is long
+        // enough.  us with one / two: 2 slabs of 300 keys 11.4 / 9.2, 85 of 330 12.6 / 10.7, 60 of 500 14.9 / 13.0, 40 of 230,
+        // per token, 9.5 / 8.6, 2 of 256 7.9 / 7.8; with a mask, where half the tiles are left out anyway, 2 of 488 13.2 / 11.0,
+        // but 64 of 512 (256 workgroups) 14.0 / 14.5 and 128 of 256 8.2 / 8.7.  Not at D = 128, at most 4 tiles and twice the
+        // results to exchange: 64 of 126 8.7 / 10.0, 128 of 256 13.9 / 15.3.
+        if (N > 192 && (long)BH * ((Nq + 127) / 128) <= (causal ? 128 : 256)) {
+            if (N <= 256) return launch_short_t<64, 4, 8, 2>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st);
+            return launch_short_t<64, 8, 8, 2>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st);
+        }
         if (N <= 128) SAGE_SHORT_N(64, 2, 4);
         if (N <= 256) SAGE_SHORT_N(64, 4, 4);
         SAGE_SHORT_N(64, 8, 8);

@@ -167,3 +167,22 @@ def test_short_sequences_in_several_turns(slabs, Nq, Nkv, D, causal, bq, bk, tur
     assert bool(torch.isfinite(o).all()) and float((o.float() - chain.float()).abs().max()) <= ABS_TOL
     for slab in (0, slabs // 2, slabs - 1):
         assert_output_close(o[:, slab:slab + 1].cpu().numpy(), oracle_slab(q, k, v, slab, causal, bq, bk), f"slab {slab}")
+
+
+# Two wavefronts per query tile, each with every other key tile: D = 64, 193 .. 512 keys and no more 128-row workgroups than
+# CUs (half as many with a mask).  Odd and even numbers of tiles, a last half tile, rows that see no key of the second
+# wavefront (causal rows 0 .. 63), fewer and more queries than keys, both sides of the line.
+PAIRS = [(1, 193, 193, False, 64, 64), (3, 256, 256, True, 128, 128), (2, 257, 257, True, 1, 1), (5, 1, 500, True, 128, 64),
+         (2, 200, 512, True, 32, 1), (2, 1000, 225, False, 128, 64), (64, 512, 512, False, 128, 64), (65, 512, 512, False, 64, 64),
+         (64, 250, 250, True, 128, 64), (65, 250, 250, True, 1, 64)]
+
+
+@pytest.mark.parametrize("slabs,Nq,Nkv,causal,bq,bk", PAIRS)
+def test_short_sequences_with_two_wavefronts_per_query_tile(slabs, Nq, Nkv, causal, bq, bk):
+    print(f"[case] {slabs} x {Nq} x {Nkv} x 64 causal={causal} scales {bq}x{bk}", flush=True)
+    q, k, v = on_device(Nq + Nkv + bq, slabs, Nq, Nkv, 64)
+    out = torch.full_like(q, float("nan"))
+    sage.sage_attention_fwd(q, k, v, causal, sage.sage_default_sm_scale(64), bq, bk, out=out)
+    torch.cuda.synchronize()
+    for slab in (0, slabs - 1):
+        assert_output_close(out[:, slab:slab + 1].cpu().numpy(), oracle_slab(q, k, v, slab, causal, bq, bk), f"slab {slab}")
