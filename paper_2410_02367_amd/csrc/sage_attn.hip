@@ -33,7 +33,7 @@
 //   The running maximum is only raised when a row's tile maximum exceeds it by more than 2^8
 //   (P~ <= 256 fits FP16 comfortably); the rescale of O is then a rare branch between slots A and B.
 //   Inside a softmax slot the order is: matrix instruction, the LDS reads of the operand three
-//   instructions ahead, the chunk's VALU work.  At D = 128 two steps share one loop body, so that the
+//   instructions ahead, the chunk's VALU work.  Two steps share one loop body, so that the
 //   buffer parity is a constant and every LDS address is a register plus an immediate.
 //
 // Register files
@@ -493,13 +493,13 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             //   off_grid  whether the running maximum is off the grid on which this tile's bias is
             //             exact (then it is re-rounded in the rare path as well).
             if constexpr (KTOK) {
-                bias[qs] = -m_run[qs];
+                bias[qs] = m_run[qs];
                 off_grid[qs] = false;
             } else {
                 // 12582912 * sc is exact (22 bits), so both FMAs round their sum only: the first gives
                 // the bias, the second what the bias really subtracts besides the seed
                 const float sum = __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
-                bias[qs] = -sum;
+                bias[qs] = sum;
                 off_grid[qs] = __builtin_fmaf(-MAGIC_F, sc[qs], sum) != m_run[qs];
             }
             if (need_mask) {
@@ -565,7 +565,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             // the exp2 argument of the own maximum; on the first tile the bias is +inf and so is this
-            const float top = __builtin_fmaf(KTOK ? pmaxf[qs][0] : as_f32(pmax[qs][0]), sc[qs], bias[qs]);
+            const float top = __builtin_fmaf(KTOK ? pmaxf[qs][0] : as_f32(pmax[qs][0]), sc[qs], -bias[qs]);
             want = want || off_grid[qs] || (top > MAX_SLACK);
         }
         return __builtin_amdgcn_ballot_w64(want) != 0ull;
@@ -628,8 +628,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     };
     auto set_bias = [&]() {
 #pragma unroll
-        for (int qs = 0; qs < QS; ++qs)       // exp2 argument = acc*sc + bias
-            bias[qs] = KTOK ? -m_run[qs] : -__builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
+        for (int qs = 0; qs < QS; ++qs)       // exp2 argument = acc*sc - bias
+            bias[qs] = KTOK ? m_run[qs] : __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
     };
 
     // ---- one pipeline step: softmax of tile j (scores in acc_s), P~V of tile j-1, K^Q^^T of tile
@@ -692,8 +692,8 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     auto chunk_fma = [&](int ch) {
         const int grp_su = ch / CHUNKS, cc = ch % CHUNKS, qs = cc / 4, pair = cc % 4;
         const int s_ = grp_su >> 1, r = 8 * (grp_su & 1) + 2 * pair;
-        xs[ch % 3][0] = __builtin_fmaf(as_f32(acc_s[qs][s_][r]), sc[qs], bias[qs]);
-        xs[ch % 3][1] = __builtin_fmaf(as_f32(acc_s[qs][s_][r + 1]), sc[qs], bias[qs]);
+        xs[ch % 3][0] = __builtin_fmaf(as_f32(acc_s[qs][s_][r]), sc[qs], -bias[qs]);
+        xs[ch % 3][1] = __builtin_fmaf(as_f32(acc_s[qs][s_][r + 1]), sc[qs], -bias[qs]);
     };
     auto chunk_exp = [&](int ch) {
         xs[ch % 3][0] = __builtin_amdgcn_exp2f(xs[ch % 3][0]);
@@ -709,7 +709,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         // Pinned to this place in the instruction stream: otherwise the compiler is free to sink the
         // whole softmax of the step down to its first use in the next step (it does, once two steps
         // share a loop body), out of the shadow of this step's matrix instructions.
-        if constexpr (D == 128) asm volatile("" : "+v"(packed));     // (only the unrolled loop needs it)
+        asm volatile("" : "+v"(packed));
         pk[qs][grp_su >> 1][grp_su & 1][pair] = packed;
     };
     // Schedule of a step (QS = 1 in the formulas):
@@ -883,19 +883,17 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         step_b(par);
         asm volatile("" : "+s"(opaque));
     };
-    if constexpr (D == 128) {
-        // two tiles per trip, so that the buffer parity is a compile-time constant inside the body
-        // (12 address computations less per step; measured +2..4 % at D = 128, -3 % at D = 64)
-        for (; j + 1 < Tw; j += 2) {
-            iteration(j, 0);
-            iteration(j + 1, 1);
-        }
-        if (j < Tw) {
-            iteration(j, 0);
-            ++j;
-        }
-    } else {
-        for (; j < Tw; ++j) iteration(j, j & 1);
+    // Two tiles per trip, so that the buffer parity is a compile-time constant inside the body: 12 address computations
+    // less per step at D = 128 (+2..4 %), 8 at D = 64: 60 slabs of 17776 keys 4310 -> 4240 us, 40 of 4096, causal, 87.1 ->
+    // 85.4, with one scale per key 104.3 -> 103.  (D = 64 gains only with the packed weights pinned, see chunk_pack: that
+    // keeps it at 152 registers; 164 without, and no faster.)
+    for (; j + 1 < Tw; j += 2) {
+        iteration(j, 0);
+        iteration(j + 1, 1);
+    }
+    if (j < Tw) {
+        iteration(j, 0);
+        ++j;
     }
     // The scores of tile Tw that the last step produced are never read: keep their registers
     // untouched until the matrix instructions have written them (the compiler would hand them out
