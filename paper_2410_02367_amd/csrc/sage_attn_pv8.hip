@@ -46,9 +46,22 @@ typedef float p16f __attribute__((ext_vector_type(16)));
 namespace {
 constexpr float PV8_LOG2E = 1.4426950408889634f;
 constexpr float PV8_LOG2_127 = 6.988684686772166f;
-constexpr float PV8_HIDDEN = -3.0e38f;            // stands for a masked score: finite, so that 0 * it is not NaN
+// The scores' accumulators start at the bit pattern of the inline constant 1 / (2 pi) = 0x3E22F983 (an operand that takes no
+// register): read as fp32 they are c0 + S^ 2^-26 exactly, since the mantissa 0x22F983 +- 127 * 127 * 128 stays within its
+// binade, and subtracting c0 leaves S^ 2^-26 exactly.  One addition per score where a conversion from int32 was, which
+// takes the vector unit twice as long; the factor 2^26 goes into the scale.
+constexpr int PV8_SEED = 0x3E22F983;
+constexpr float PV8_UNIT = 0x1p26f;
+constexpr float PV8_HIDDEN = -3.0e38f / PV8_UNIT;        // stands for a masked score: finite, so that 0 * it is not NaN
 constexpr int PV8_FLUSH_TILES = 1024;
 
+// The first matrix instruction of a block of scores.  (Written out because the compiler would keep the constant in 16
+// registers.  It is followed by the next of its chain, which takes its result without a wait.)
+__device__ __forceinline__ p16i seeded_mfma(const p4i& a, const p4i& b) {
+    p16i d;
+    asm("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494" : "=&v"(d) : "v"(a), "v"(b));
+    return d;
+}
 __device__ __forceinline__ int k_unperm(int p) {
     // key of a tile held by LDS row p: row 32kb + 8g + 4h + b holds key 32kb + 16h + 4g + b
     return (p & 32) | ((p & 4) << 2) | ((p & 24) >> 1) | (p & 3);
@@ -270,14 +283,13 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[kb][r] = 0;
-#pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 const p4i a = *(const p4i*)(tb + k_rd(kb, ks));
                 p4i b;
                 if (ks < QREG) b = qreg[ks];
                 else b = *(const p4i*)(lds + QOFF + wave * (32 * D) + k_rd0[ks]);      // this wavefront's Q^ rows
-                s[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, s[kb], 0, 0, 0);
+                if (ks == 0) s[kb] = seeded_mfma(a, b);
+                else s[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, s[kb], 0, 0, 0);
             }
         }
         if (HAS_PREV) {
@@ -286,18 +298,18 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         }
         // mask: keys past N, and keys after the lane's query when causal (edge tiles only)
         const bool edge = (j * KT + KT > N) || (CAUSAL && j * KT + KT - 1 > qrow0 + coff);
-        // Per-block key scale: y = (float)S^ and sc = delta_Q log2(e) delta_K[tile]; per-token key
-        // scales: y = (float)S^ * delta_K[key] and sc = delta_Q log2(e).  Either way the maximum is
+        // Per-block key scale: y = S^ 2^-26 and sc = delta_Q log2(e) delta_K[tile] 2^26; per-token key
+        // scales: y = S^ 2^-26 delta_K[key] and sc = delta_Q log2(e) 2^26.  Either way the maximum is
         // taken on y and scaled once (sc > 0), and the softmax argument is one FMA, y * sc - m'.
         // Hidden scores become a huge negative number whose exponential is 0 (sc >= 1e-30 keeps the
         // product far below any maximum).
-        const float sc = __builtin_fmaxf(KTOK ? dq : dq * ksc_bh[(j * KT) >> shift_k], 1e-30f);
+        const float sc = __builtin_fmaxf(KTOK ? dq : dq * ksc_bh[(j * KT) >> shift_k], 1e-30f) * PV8_UNIT;
         float y[2][16];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                y[kb][r] = (float)s[kb][r];
+                y[kb][r] = __builtin_bit_cast(float, (int)s[kb][r]) - __builtin_bit_cast(float, PV8_SEED);
                 if (KTOK) {
                     const float* kl = (const float*)(lds + 3 * (KB + VB) + buf * KSL);
                     y[kb][r] *= kl[32 * kb + 16 * h + r];
