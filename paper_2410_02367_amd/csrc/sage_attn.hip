@@ -633,8 +633,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     };
 
     // ---- one pipeline step: softmax of tile j (scores in acc_s), P~V of tile j-1, K^Q^^T of tile
-    // j+1.  For j = 0 the P~ registers are zero and the V buffer that is read is zero-filled, so
-    // that P~V adds nothing.
+    // j+1.  (Tile 0 has no P~V before it: first_tile(); the last one no K^Q^^T after it.)
     //
     // Flat operand sequence o = 0 .. 4*DT + 2*KS - 1: four P~V groups (DT operands each), then
     // the two K^Q^^T halves (KS operands each).  Operand o+PD is read from LDS before the matrix
@@ -723,12 +722,17 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     static_assert(QS == 1 || SA == 1, "the generalized schedule is written for one query sub-tile");
     constexpr int MB = ((4 - SA) * DT + KS) * QS;
     constexpr int NB = (NOPS - NA) * QS;                // matrix instructions of step_b
+    constexpr int LAST_TICKS = NCH - 2 * QS, MB_LAST = (4 - SA) * DT * QS;
     using Plan = TickPlan<NCH, MB>;
+    using LastPlan = TickPlan<LAST_TICKS, MB_LAST>;
     static_assert(KS * QS >= 2, "two drain ticks need two matrix instructions after the last fma");
     // a P~ group is packed only after its P~V of tile j-1 has been issued ...
     static_assert(SA >= 2 || Plan::slot_of(CHUNKS * 1 + 2) >= (2 - SA) * DT * QS - 1, "group 1 packed after its matrix instructions");
     static_assert(SA >= 3 || Plan::slot_of(CHUNKS * 2 + 2) >= (3 - SA) * DT * QS - 1, "group 2 packed after its matrix instructions");
     static_assert(SA >= 4 || Plan::slot_of(CHUNKS * 3 + 2) >= (4 - SA) * DT * QS - 1, "group 3 packed after its matrix instructions");
+    static_assert(SA >= 2 || LastPlan::slot_of(CHUNKS * 1 + 2) >= (2 - SA) * DT * QS - 1, "last tile: group 1 packed after its matrix instructions");
+    static_assert(SA >= 3 || LastPlan::slot_of(CHUNKS * 2 + 2) >= (3 - SA) * DT * QS - 1, "last tile: group 2 packed after its matrix instructions");
+    static_assert(CHUNKS * 3 + 2 >= LAST_TICKS, "last tile: group 3 packed after its matrix instructions");
     // ... and each half of S_j is consumed before the K^Q^^T of that half is issued
     static_assert(Plan::slot_of(NCH / 2 - 1) < (4 - SA) * DT * QS, "first half of S consumed before it is overwritten");
     static_assert(Plan::slot_of(NCH - 1) < MB, "second half of S consumed before it is overwritten");
@@ -749,28 +753,64 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             if constexpr (o % DT == DT - 1) row_sums(std::integral_constant<int, o / DT>{});
         });
     };
-    auto step_b = [&](int par) {
+    // Chunk-pipeline ticks first .. end - 1.
+    auto ticks = [&](auto FIRST, auto END) {
+        static_for<IDX(END) - IDX(FIRST)>([&](auto I) {
+            constexpr int n = IDX(FIRST) + IDX(I);
+            if constexpr (n - 2 >= 0 && n - 2 < NCH) chunk_pack(n - 2);
+            if constexpr (n - 1 >= 0 && n - 1 < NCH) chunk_exp(n - 1);
+            if constexpr (n < NCH) chunk_fma(n);
+        });
+    };
+    // LAST: the wavefront's last tile has no K^Q^^T after it.  The chunks go behind the P~V instructions alone, the last ones
+    // behind none (14 ticks in 12 or 6 slots: the fourth P~ group is packed after its last matrix instruction).
+    auto step_b = [&](int par, auto LAST) {
+        constexpr bool last = IDX(LAST) != 0;
+        constexpr int ops = last ? 4 * DT : NOPS;
+        using Plan = TickPlan<last ? LAST_TICKS : NCH, last ? MB_LAST : MB>;
         const int vbuf = par ^ 1, kbuf = par ^ 1;
-        static_for<NOPS - NA>([&](auto OO) {
+        static_for<ops - NA>([&](auto OO) {
             constexpr int o = IDX(OO) + NA;
             static_for<QS>([&](auto QSI) {
                 constexpr int qs = IDX(QSI);
                 issue_mfma(std::integral_constant<int, o>{}, QSI);
-                if constexpr (qs == 0 && o + PD < NOPS) {
+                if constexpr (qs == 0 && o + PD < ops) {
                     // the next operand read goes out in the shadow of the matrix instruction
                     load_operand(std::integral_constant<int, o + PD>{}, vbuf, kbuf);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 constexpr int i = (o - NA) * QS + qs;       // index of the matrix instruction in step_b
-#pragma unroll
-                for (int n = Plan::first(i); n < Plan::end(i); ++n) {
-                    if (n - 2 >= 0 && n - 2 < NCH) chunk_pack(n - 2);
-                    if (n - 1 >= 0 && n - 1 < NCH) chunk_exp(n - 1);
-                    if (n >= 0 && n < NCH) chunk_fma(n);
-                }
+                ticks(std::integral_constant<int, Plan::first(i)>{}, std::integral_constant<int, Plan::end(i)>{});
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (o < 4 * DT && o % DT == DT - 1) row_sums(std::integral_constant<int, o / DT>{});
+        });
+        if constexpr (last) ticks(std::integral_constant<int, LAST_TICKS>{}, std::integral_constant<int, NCH + 2>{});
+    };
+    // The first tile: no P~V before it, and nothing to rescale when its maximum is taken.  K^Q^^T of tile 1 starts when the
+    // softmax has consumed the first half of the scores.  The step above with zeros in the place of P~, which did this before,
+    // cost 24 matrix instructions and a rescale per workgroup together with the last tile's unused K^Q^^T: 128 slabs of 1536
+    // keys at D = 128, causal, 79.0 -> 74.4 us, 96 of 1105 at D = 64 39.6 -> 38.1, 128 of 4096 at D = 128 799 -> 775.
+    auto first_tile = [&]() {
+        static_for<QS>([&](auto QSI) {
+            static_for<NA>([&](auto P) { partial_max(QSI, P, 0); });
+        });
+        finish_max();
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs)
+            m_run[qs] = KTOK ? m_cand[qs] : __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_cand[qs]));
+        set_bias();
+        static_for<PD>([&](auto O) { load_operand(std::integral_constant<int, 4 * DT + IDX(O)>{}, 1, 1); });
+        ticks(std::integral_constant<int, 0>{}, std::integral_constant<int, NCH / 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<2 * KS>([&](auto I) {
+            constexpr int o = 4 * DT + IDX(I), i = IDX(I);
+            static_for<QS>([&](auto QSI) { issue_mfma(std::integral_constant<int, o>{}, QSI); });
+            if constexpr (o + PD < NOPS) load_operand(std::integral_constant<int, o + PD>{}, 1, 1);
+            constexpr int per = NCH / 2 / KS;
+            if constexpr (i < KS) ticks(std::integral_constant<int, NCH / 2 + i * per>{}, std::integral_constant<int, NCH / 2 + (i + 1) * per>{});
+            else if constexpr (i == KS) ticks(std::integral_constant<int, NCH>{}, std::integral_constant<int, NCH + 2>{});
+            __builtin_amdgcn_sched_barrier(0);
         });
     };
 
@@ -790,10 +830,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         }
     };
 
-    // ---- prologue: K^(0), K^(1) into LDS; S_0.  Both V buffers start zero-filled: step 0 reads
-    // buffer 1 before any tile has arrived (its P~ is zero, but 0 * NaN would not be), and rows of a
-    // ragged last tile that lie beyond the slab must hold finite values whatever the load leaves there.
-    if (!DUMP) {
+    // ---- prologue: K^(0), K^(1) into LDS; S_0.  Where the last tile is ragged both V buffers start zero-filled: its rows
+    // beyond the slab must hold finite values whatever the load leaves there (their P~ is zero, but 0 * NaN would not be).
+    if (!DUMP && N % KTILE != 0) {
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -868,7 +907,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // assembly statements carry a value around the loop that the compiler cannot see through; they
     // keep it from restructuring the loop nest, which made it spill registers.)
     unsigned opaque = 0;
-    auto iteration = [&](int j, int par) {
+    auto iteration = [&](int j, int par, auto LAST) {
         asm volatile("" : "+s"(opaque));
         turn(j, par);
         begin_tile(j);
@@ -880,19 +919,29 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             set_bias();
         }
         asm volatile("" : "+s"(opaque));
-        step_b(par);
+        step_b(par, LAST);
         asm volatile("" : "+s"(opaque));
     };
     // Two tiles per trip, so that the buffer parity is a compile-time constant inside the body: 12 address computations
     // less per step at D = 128 (+2..4 %), 8 at D = 64: 60 slabs of 17776 keys 4310 -> 4240 us, 40 of 4096, causal, 87.1 ->
     // 85.4, with one scale per key 104.3 -> 103.  (D = 64 gains only with the packed weights pinned, see chunk_pack: that
     // keeps it at 152 registers; 164 without, and no faster.)
-    for (; j + 1 < Tw; j += 2) {
-        iteration(j, 0);
-        iteration(j + 1, 1);
+    constexpr std::integral_constant<int, 0> inner{};
+    constexpr std::integral_constant<int, 1> last{};
+    turn(0, 0);
+    begin_tile(0);
+    first_tile();
+    if constexpr (CLOCKS) ++n_raised;
+    for (j = 1; j + 2 < Tw; j += 2) {
+        iteration(j, 1, inner);
+        iteration(j + 1, 0, inner);
+    }
+    if (j + 1 < Tw) {
+        iteration(j, 1, inner);
+        ++j;
     }
     if (j < Tw) {
-        iteration(j, 0);
+        iteration(j, j & 1, last);
         ++j;
     }
     // The scores of tile Tw that the last step produced are never read: keep their registers
