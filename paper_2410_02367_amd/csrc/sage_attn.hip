@@ -839,6 +839,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             for (int i = 0; i < VL; ++i)
                 if (NTHREADS * i + wave * 64 < VVEC) *(v4i*)(lds + 2 * KB + b * VB + (t + NTHREADS * i) * 16) = (v4i){0, 0, 0, 0};
     }
+    // fp16 queries are requested before the tiles: their way from memory (2400 .. 3900 clocks) and their quantization are the
+    // longest chain of the prologue.
+    QueryRows<KS> rows;
+    if (!DUMP && QS == 1 && qf != nullptr) rows.fetch(qf + (slab_q + (qrow0 + ql < Nq ? qrow0 + ql : Nq - 1)) * D, g);
     load_k(0, 0);
     if (T > 1) load_k(1, 1);
     request_key_scales(0);
@@ -848,16 +852,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // little power, where a real row in the place of each cost a launch of few rows 2-4 % (420 slabs of 33 rows, 1436 keys,
     // D = 64: 26.8 / 27.8 us).
     if (!DUMP && QS == 1 && qf != nullptr) {
-        QueryRows<KS> rows;
-        const int q_row = qrow0 + ql < Nq ? qrow0 + ql : Nq - 1;
-        rows.fetch(qf + (slab_q + q_row) * D, g);
         const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
         const float rcp = amax > 0.0f && qrow0 + ql < Nq ? 127.0f / amax : 0.0f;
         dq[0] = amax / 127.0f * LOG2E;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) qreg[0][ks][i] = (int)rows.word(ks, i, sm_scale, rcp);
+        rows.codes(sm_scale, rcp, [&](int ks, int i, unsigned w) { qreg[0][ks][i] = (int)w; });
     } else {
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {

@@ -70,7 +70,7 @@ __device__ __forceinline__ int vt_swz(int ch) { return (ch >> 2) & 3; }
 }  // namespace
 
 template <int D, bool CAUSAL, bool KTOK, bool SPLIT>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, D == 64 ? 3 : 2)
 sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                      const int8_t* __restrict__ ki, const float* __restrict__ ksc,
                      const int8_t* __restrict__ vt, const float* __restrict__ vsc,
@@ -127,28 +127,9 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     const int coff = Nkv - Nq - k0;
     const int nbq = (Nq + (1 << shift_q) - 1) >> shift_q, nbk = (Nkv + (1 << shift_k) - 1) >> shift_k;
 
-    p4i qreg[QREG > 0 ? QREG : 1];
-    float dq;
-    if (qf != nullptr) {
-        // fp16 rows, quantized here: steps below QREG to registers, the others to the wavefront's own rows of the LDS copy
-        QueryRows<KS> rows;
-        rows.fetch(qf + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D, h);
-        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + QOFF + QB));
-        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
-        dq = amax / 127.0f * PV8_LOG2E;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            p4i code;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) code[i] = (int)rows.word(ks, i, sm_scale, rcp);
-            if (ks < QREG) qreg[ks] = code;
-            else *(p4i*)(lds + QOFF + wave * (32 * D) + ql * D + (((2 * ks + h) ^ k_swz<D>(ql)) * 16)) = code;
-        }
-    } else {
-#pragma unroll
-        for (int ks = 0; ks < QREG; ++ks) qreg[ks] = *(const p4i*)(qi + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D + ks * 32 + h * 16);
-        dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
-    }
+    // fp16 queries are requested first, then the first tile, so that their quantization runs while that is on its way
+    QueryRows<KS> rows;
+    if (qf != nullptr) rows.fetch(qf + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D, h);
     const float* __restrict__ ksc_bh = ksc + (size_t)bh * nbk + (k0 >> shift_k);
 
     const int kv_tiles_all = (N + KT - 1) / KT;
@@ -194,6 +175,26 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         for (int i = 0; i < VL; ++i)
             load_to_lds16(v_desc, v_goff0 + (unsigned)(i * (NT / 4)) * (unsigned)Np + (unsigned)j * KT, uniform(kb_addr + KB + i * (NT * 16)));
     };
+
+    fetch(0, 0);
+    p4i qreg[QREG > 0 ? QREG : 1];
+    float dq;
+    if (qf != nullptr) {
+        // fp16 rows, quantized here: steps below QREG to registers, the others to the wavefront's own rows of the LDS copy
+        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + QOFF + QB));
+        const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
+        dq = amax / 127.0f * PV8_LOG2E;
+        p4i code;
+        rows.codes(sm_scale, rcp, [&](int ks, int i, unsigned w) {
+            code[i] = (int)w;
+            if (ks < QREG) qreg[ks] = code;
+            else if (i == 3) *(p4i*)(lds + QOFF + wave * (32 * D) + ql * D + (((2 * ks + h) ^ k_swz<D>(ql)) * 16)) = code;
+        });
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < QREG; ++ks) qreg[ks] = *(const p4i*)(qi + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D + ks * 32 + h * 16);
+        dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
+    }
 
     // ---- operand read offsets (per lane, inside a buffer).  The swizzle of a row depends on the
     // row's low bits only, so the second 32-key block of K^ and the further 32-channel blocks of
@@ -342,24 +343,25 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
             // O relative to the running maximum is g * of + A with a per-lane factor g that takes
             // the rescaling: (g of + A) alpha = (g alpha) (of + A / g), so a flush is one conversion and
             // one FMA per element, of += A * (1 / g), and then g *= alpha.  1 / g = 2^(rise of the
-            // maximum since the row began) is carried instead of g; the first tile (m_run = -inf,
-            // of = A = 0) leaves it at 1.
-#pragma unroll
-            for (int cb = 0; cb < DT; ++cb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) of[cb][r] = __builtin_fmaf((float)acc[cb][r], ginv, of[cb][r]);
-            const bool first = m_run == -__builtin_inff();
-            l127 *= __builtin_amdgcn_exp2f(m_run - m_new);          // 0 on the first tile; l127 is 0 there
-            // (a rise of more than 60 is taken as 60: what was accumulated before is then below 2^-60
-            // of the new terms either way, and 1 / g stays finite: <= 2^60 * 2^60)
-            ginv = first ? 1.0f : ginv * __builtin_amdgcn_exp2f(__builtin_fminf(m_new - m_run, 60.0f));
-            if (__builtin_amdgcn_ballot_w64(ginv > 0x1p60f) != 0ull) {      // rare: fold g into of before 1 / g overflows
-                const float g = ginv > 0x1p60f ? 1.0f / ginv : 1.0f;
+            // maximum since the row began) is carried instead of g.  On the first tile of = A = 0, and nothing is
+            // to be done but to take the maximum.
+            if (HAS_PREV) {
 #pragma unroll
                 for (int cb = 0; cb < DT; ++cb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) of[cb][r] *= g;
-                ginv = ginv > 0x1p60f ? 1.0f : ginv;
+                    for (int r = 0; r < 16; ++r) of[cb][r] = __builtin_fmaf((float)acc[cb][r], ginv, of[cb][r]);
+                l127 *= __builtin_amdgcn_exp2f(m_run - m_new);
+                // (a rise of more than 60 is taken as 60: what was accumulated before is then below 2^-60
+                // of the new terms either way, and 1 / g stays finite: <= 2^60 * 2^60)
+                ginv *= __builtin_amdgcn_exp2f(__builtin_fminf(m_new - m_run, 60.0f));
+                if (__builtin_amdgcn_ballot_w64(ginv > 0x1p60f) != 0ull) {      // rare: fold g into of before 1 / g overflows
+                    const float g = ginv > 0x1p60f ? 1.0f / ginv : 1.0f;
+#pragma unroll
+                    for (int cb = 0; cb < DT; ++cb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) of[cb][r] *= g;
+                    ginv = ginv > 0x1p60f ? 1.0f : ginv;
+                }
             }
             m_run = m_new;
             since = 0;
@@ -378,7 +380,6 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         pending = true;
     };
 
-    fetch(0, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 

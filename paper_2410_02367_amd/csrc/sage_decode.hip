@@ -104,10 +104,7 @@ sage_decode_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         const float amax = rows.block_amax(sm_scale, shift_q == 0 ? 0 : 5, wave, nullptr);
         const float rcp = amax > 0.0f ? 127.0f / amax : 0.0f;
         dq = amax / 127.0f * DEC_LOG2E;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) q[ks][i] = (int)rows.word(ks, i, sm_scale, rcp);
+        rows.codes(sm_scale, rcp, [&](int ks, int i, unsigned w) { q[ks][i] = (int)w; });
     } else {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) q[ks] = *(const d4i*)(qi + (slab_q + qc) * D + ks * 32 + g * 16);

@@ -253,10 +253,7 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
         const float qrcp = qmax > 0.0f ? 127.0f / qmax : 0.0f;
         const float dq = qmax / 127.0f * SHORT_LOG2E;
         s4i q[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) q[ks][i] = (int)rows.word(ks, i, sm_scale, qrcp);
+        rows.codes(sm_scale, qrcp, [&](int ks, int i, unsigned w) { q[ks][i] = (int)w; });
         if (KSP == 1 && (set + groups) * RT < rtiles) {          // the next rows are requested before this tile's loop
             const int row = ((set + groups) * RT + own) * 32 + ql;
             rows.fetch(qf + (slab_q + (row < Nq ? row : Nq - 1)) * D, g);
