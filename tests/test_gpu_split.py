@@ -278,3 +278,29 @@ def test_random_split_shape(i, B, H, Nq, Nkv, D, causal, bq, bk, req):
     o8_ref, big_l = oracle.attn_pv8_cross_split(qq, qs, kq, ks, vq, vs, causal, 128, 64, starts, gran_q=bq, gran_k=bk,
                                                 return_l=True)
     assert_pv8_close(o8.cpu().numpy(), o8_ref, big_l, vs, f"split sweep {i} INT8 PV")
+
+
+# Chunks of more than 2048 keys under a mask, D = 128: 256-row workgroups where the 128-row ones fill more than half of 512
+# places and the rows are whole pairs of 128-row tiles (13 of 130: 468 -> 234; 20 of 250 and 65 of 129), 128-row ones where they
+# are not (40 of 300, 3 tiles or 2) or where half the places would do (12 of 500, asked for 4 chunks).
+SHAPES_OF_CHUNKS = [(13, 130, 40000, 128, 64, 0), (20, 250, 30000, 1, 1, 0), (65, 129, 5200, 64, 128, 2), (40, 300, 16500, 128, 64, 0),
+                    (12, 500, 10000, 128, 64, 4)]
+
+
+@pytest.mark.parametrize("slabs,Nq,Nkv,bq,bk,req", SHAPES_OF_CHUNKS)
+def test_workgroup_shape_of_chunks_under_a_mask(slabs, Nq, Nkv, bq, bk, req):
+    D, sm = 128, sage.sage_default_sm_scale(128)
+    n = sage.sage_attn_split_count(1, slabs, Nq, Nkv, True, req)
+    print(f"[case] {slabs} x {Nq} x {Nkv} scales {bq}x{bk}: {n} chunks", flush=True)
+    assert n > 1
+    g = torch.Generator(device="cuda").manual_seed(Nq + Nkv)
+    q, k, v = (torch.randn((1, slabs, m, D), generator=g, device="cuda").half() for m in (Nq, Nkv, Nkv))
+    k_i8, k_scale, _ = sage.sage_smooth_quant_k(k, bk)
+    q_i8, q_scale = sage.sage_quant_q(q, sm, bq)
+    o = sage.sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, True, sm, bq, bk, n_splits=req)
+    torch.cuda.synchronize()
+    lq, lk = (128, 64) if bq == 1 else (max(bq, 64), max(bk, 64))
+    for slab in (0, slabs - 1):
+        ref = oracle.attn_l2_cross(*(x[:, slab:slab + 1].contiguous().cpu().numpy() for x in (q_i8, q_scale, k_i8, k_scale, v)),
+                                   True, lq, lk, gran_q=bq, gran_k=bk)
+        assert_output_close(o[:, slab:slab + 1].cpu().numpy(), ref, f"slab {slab}")
