@@ -1075,13 +1075,19 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
     // 86 of 4096, 2752: 567 / 579) and where rows that are no multiple of 256 cost the larger ones a round more (480 against
     // 288 for 96 chunks of 2816 keys and 640 queries: 92 / 117), the larger ones elsewhere (12 of 3000, 288: 64 / 58; 46 of
     // 3800, 1380: 281 / 268; one scale per key, 20 of 6000, 940: 328 / 315).
+    // Chunks of the keys under a mask (a chunk of a prompt, where the mask takes little of any workgroup): as without one, if the
+    // rows fill as many halves of 256-row tiles as 128-row ones: 32 slabs of 512 rows against 16384 keys 111.9 / 107.6, 20 of
+    // 1000 against 20000 167 / 159, 13 of 130 against 40000 56.5 / 53.7, with one scale per key 50 of 500 against 6000 84.1 / 78.0;
+    // 40 of 640 against 12000 (5 tiles or 3) 137 / 139.
     const int small_tiles = (Nq + 4 * WROWS - 1) / (4 * WROWS), large_tiles = (Nq + 8 * WROWS - 1) / (8 * WROWS);
     const long units = (long)BH * sp.n_splits;
     const int n_seen = sp.n_splits > 1 ? sp.chunk : N;           // keys a workgroup walks
     bool small = QS == 1 && !(sdump && D == 128);
-    if (small && D == 128 && n_seen > (causal ? 4096 : 2048)) {
+    const bool staircase = causal && sp.n_splits == 1;
+    if (small && D == 128 && n_seen > (staircase ? 4096 : 2048)) {
         const long rounds = (units * small_tiles + 511) / 512, last = units * small_tiles - 512 * (rounds - 1);
-        small = causal ? units * large_tiles < 2 * 256 : (last <= 256 && rounds <= 6) || (units * large_tiles + 255) / 256 > rounds;
+        small = staircase ? units * large_tiles < 2 * 256 : (last <= 256 && rounds <= 6) || (units * large_tiles + 255) / 256 > rounds;
+        if (causal && !staircase && 2 * large_tiles != small_tiles) small = true;
     }
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
