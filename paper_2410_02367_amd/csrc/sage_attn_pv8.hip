@@ -2,7 +2,7 @@
 // per block with the static scale 1/127, V per channel; the SAGEAttn-vB / -vT kernels of Section 4.5).
 //
 // Same decomposition as the FP16-P~V kernel, in its plain form: a workgroup of 4 wavefronts owns 128
-// query rows (32 per wavefront), K^ and V^^T tiles of 64 keys are double-buffered in LDS, scores are
+// query rows (32 per wavefront), K^ and V^^T tiles of 64 keys pass through three buffers in LDS, scores are
 // computed transposed (S^T = K^ Q^^T) so that a lane owns one query, and O^T = V^^T P^^T.  Both
 // products use the 32x32x32 INT8 matrix instruction.  What is specific to this variant:
 //
@@ -29,9 +29,9 @@
 //     into a register with one instruction per code.
 //
 // This variant is written with compiler builtins and compiler scheduling; it trades the second
-// product's instruction count (half) for more VALU work per score (conversion, rounding, packing,
-// flushes).  Measured on MI355X against the FP16-second-product kernel: 0-5 % faster at 16K keys,
-// 8-15 % from 32K up (flushes are rare there), 3-6 % slower below 8K; it is bound by VALU issue
+// product's instruction count (half) for more VALU work per score (subtraction of the seed, rounding,
+// packing, flushes).  Measured on MI355X against the FP16-second-product kernel: 2 % faster at 16K keys,
+// 11 % at 128K (flushes are rare there), 3-12 % slower below 8K; it is bound by VALU issue
 // (about 264 VALU instructions against 16 matrix instructions per 32 x 64 step).
 #include "sage_internal.h"
 #include "sage_device.h"
