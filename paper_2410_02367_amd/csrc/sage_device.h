@@ -141,8 +141,8 @@ __device__ __forceinline__ bool causal_item(int xcd, int slot, int tiles_q, cons
     return false;
 }
 
-// The same without the clamp: where 127 / amax is finite, and for K, where no product exceeds 127 (1 + 2^-22) and none overflows -- the smallest
-// non-zero |K - mean| is far above 2^-121 (K is a multiple of 2^-24, the mean at least 2^-47).
+// The same without the clamp: where 127 / amax and every value are finite, and for K, where no product exceeds 127 (1 + 2^-22)
+// and none overflows -- the smallest non-zero |K - mean| is far above 2^-121 (K is a multiple of 2^-24, the mean at least 2^-47).
 __device__ __forceinline__ unsigned quantize4_k(float x0, float x1, float x2, float x3, float rcp) {
     auto code = [rcp](float x) { return __builtin_bit_cast(unsigned, x * rcp + 12582912.0f); };
     const unsigned lo = __builtin_amdgcn_perm(code(x1), code(x0), 0x0c0c0400u);
@@ -152,9 +152,12 @@ __device__ __forceinline__ unsigned quantize4_k(float x0, float x1, float x2, fl
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-// max(m, |x|) of two fp16 values at once, x as a word; the other operand where one is NaN
-__device__ __forceinline__ half2v max_abs(half2v m, unsigned x) {
-    return __builtin_elementwise_max(m, __builtin_bit_cast(half2v, x & 0x7fff7fffu));
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+// max(m, |x|) of two fp16 values at once, x as a word; of half2v the other operand where one is NaN, of ushort2v the larger
+// bit pattern: the order of the numbers, infinity and then NaN above them
+template <class T>
+__device__ __forceinline__ T max_abs(T m, unsigned x) {
+    return __builtin_elementwise_max(m, __builtin_bit_cast(T, x & 0x7fff7fffu));
 }
 
 // The fp16 rows of a wavefront's 32 queries quantized where they are used (Section 4.6: the quantizer fused
@@ -165,6 +168,7 @@ __device__ __forceinline__ half2v max_abs(half2v m, unsigned x) {
 template <int KS>
 struct QueryRows {
     half8 raw[KS][2];
+    bool special;           // wave-uniform, set by block_amax(): some query of the wavefront is NaN or infinite
     // row: the lane's row; lanes past the last row fetch that row again, which changes no maximum they share with a
     // row that exists (a condition around the loads would make them wait for each other)
     __device__ __forceinline__ void fetch(const _Float16* row, int half) {
@@ -176,20 +180,27 @@ struct QueryRows {
     }
     // largest |x * sm_scale| of the lane's quantization block; every wavefront of the workgroup calls it.
     // red: one float of LDS per wavefront, not used for anything else before the next barrier.
-    __device__ __forceinline__ float block_amax(float sm_scale, int shift_q, int wave, float* red) const {
+    __device__ __forceinline__ float block_amax(float sm_scale, int shift_q, int wave, float* red) {
         // max |x * sm_scale| = max |x| * sm_scale, rounded once either way (rounding is monotonic): the maximum is
-        // taken on fp16 pairs.  It passes over NaN, as fmaxf does (a maximum of the bit patterns would not): a row that
-        // holds one leaves the other rows of its block as they are.
-        half2v top = {};
-        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        // taken on fp16 pairs, of the bit patterns, which shows a NaN at no cost.  Where there is one it is taken again and
+        // passes over NaN, as fmaxf does: a row that holds one leaves the other rows of its block as they are.
+        auto over_all = [&](auto start) {
+            typedef unsigned u4 __attribute__((ext_vector_type(4)));
+            auto m = start;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const u4 w = __builtin_bit_cast(u4, raw[ks][j]);
+                for (int j = 0; j < 2; ++j) {
+                    const u4 w = __builtin_bit_cast(u4, raw[ks][j]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) top = max_abs(top, w[e]);
-            }
+                    for (int e = 0; e < 4; ++e) m = max_abs(m, w[e]);
+                }
+            return m;
+        };
+        const ushort2v pattern = over_all(ushort2v{});
+        special = __builtin_amdgcn_ballot_w64(pattern[0] >= 0x7C00 || pattern[1] >= 0x7C00) != 0ull;
+        half2v top = __builtin_bit_cast(half2v, pattern);
+        if (__builtin_expect(special, 0)) top = over_all(half2v{});
         float m = __builtin_fmaxf((float)top[0], (float)top[1]) * sm_scale;
         m = pair32_max(m);
         if (shift_q == 0) return m;
@@ -203,8 +214,8 @@ struct QueryRows {
         return m;
     }
     // put(ks, i, word): word i of contraction step ks, channels 4 i .. 4 i + 3 of the lane's 16.  rcp = 127 / amax, or 0.
-    // The clamp matters only where 127 / amax overflows (amax below 2^-121): elsewhere no product exceeds 127 (1 + 2^-22).
-    // Without it a code is 3.75 vector instructions instead of 4.75.
+    // The clamp matters only where 127 / amax overflows (amax below 2^-121), elsewhere no product exceeds 127 (1 + 2^-22), and
+    // for a product that is not a number, whose code is -127.  Without it a code is 3.75 vector instructions instead of 4.75.
     template <class F>
     __device__ __forceinline__ void codes(float sm_scale, float rcp, F&& put) const {
         auto all = [&](auto clamp) {
@@ -213,7 +224,7 @@ struct QueryRows {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) put(ks, i, word<decltype(clamp)::value>(ks, i, sm_scale, rcp));
         };
-        if (__builtin_amdgcn_ballot_w64(rcp == __builtin_inff()) != 0ull) all(std::true_type{});
+        if (__builtin_expect(special || __builtin_amdgcn_ballot_w64(rcp == __builtin_inff()) != 0ull, 0)) all(std::true_type{});
         else all(std::false_type{});
     }
     template <bool CLAMP>

@@ -49,3 +49,24 @@ def test_a_nan_stays_in_its_row(i):
         first = token - (Nkv - Nq) if causal else 0
         fine[:, :, max(first, 0):, channel] = True
     assert fine.all(), np.argwhere(~fine)[:5]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_a_nan_gets_the_code_that_the_separate_calls_give_it(i):
+    """A query that is no number has the code -127 wherever it is quantized: its row, whose other channels are finite, comes
+    out of the whole pass as it does of the pre-pass calls and the attention call."""
+    B, H, Nq, Nkv, D, causal, bq, pv8 = CASES[i]
+    print(f"[case] B{B} H{H} Nq{Nq} Nkv{Nkv} D{D} causal={causal} block_q {bq} pv_int8={pv8}", flush=True)
+    w = si.custom(f"nancode{i}", B, H, max(Nq, Nkv), D, False, seed=si.BASE_SEED + 1600 + i)
+    q, k, v = (to_dev(np.ascontiguousarray(x[:, :, :n])) for x, n in zip(si.full(w), (Nq, Nkv, Nkv)))
+    q[:, :, 3, 7] = float("nan")            # the lane's first channels and its last, in rows of either half of a wavefront's
+    q[:, :, Nq - 1, D - 1] = float("nan")
+    o = sage.sageattn(q, k, v, causal, w.sm_scale, bq, 64, pv_int8=pv8)
+    q_i8, q_scale, k_i8, k_scale, _ = sage.sage_quant_qk(q, k, w.sm_scale, bq, 64)
+    assert bool((q_i8[:, :, 3, 7] == -127).all()) and bool((q_i8[:, :, Nq - 1, D - 1] == -127).all())
+    if pv8:
+        chain = sage.sage_attn_pv_int8_cross_fwd(q_i8, q_scale, k_i8, k_scale, *sage.sage_quant_v(v), causal, w.sm_scale, bq, 64)
+    else:
+        chain = sage.sage_attn_cross_fwd(q_i8, q_scale, k_i8, k_scale, v, causal, w.sm_scale, bq, 64)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(o).all()) and float((o.float() - chain.float()).abs().max()) <= ABS_TOL
