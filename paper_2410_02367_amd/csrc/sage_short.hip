@@ -266,9 +266,10 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
         s4f lsum = {0.0f, 0.0f, 0.0f, 0.0f};       // registers 0, 1: sums of the queries lane % 16, 16 + lane % 16
-        // Below every score, and finite: with KSP = 2 a row may see none of its wavefront's keys; its weights are then
-        // exp2(-inf + 1e30) = 0, where an infinity would make them NaN.
-        float m_run = -1e30f;
+        // Below every score.  With KSP = 2 a row may see none of its wavefront's keys, and the start is finite: the row's weights
+        // are then exp2(-inf + 3.4e38) = 0, where an infinity would make them NaN.  (The second lowest number, since rounding
+        // the lowest to the grid of a huge scale could leave the range.)
+        float m_run = KSP == 1 ? -__builtin_inff() : -0x1.fffffcp127f;
         bool fresh = true;                           // O and l are 0
         // keys this wavefront sees; a tile of which it sees only the first half is done by halves
         int seen = causal ? row0 + 32 + coff : N;
