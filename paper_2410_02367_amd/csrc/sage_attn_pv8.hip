@@ -49,11 +49,19 @@ constexpr float PV8_LOG2_127 = 6.988684686772166f;
 // The scores' accumulators start at the bit pattern of the inline constant 1 / (2 pi) = 0x3E22F983 (an operand that takes no
 // register): read as fp32 they are c0 + S^ 2^-26 exactly, since the mantissa 0x22F983 +- 127 * 127 * 128 stays within its
 // binade, and subtracting c0 leaves S^ 2^-26 exactly.  One addition per score where a conversion from int32 was, which
-// takes the vector unit twice as long; the factor 2^26 goes into the scale.
+// takes the vector unit twice as long; the factor 2^26 goes into the scale.  (One FMA that leaves S^ itself is 8 bytes of code
+// where the subtraction is 4, and cost 1-2 % at D = 64: 128 slabs of 4096 keys 509 / 519 us.)
 constexpr int PV8_SEED = 0x3E22F983;
 constexpr float PV8_UNIT = 0x1p26f;
 constexpr float PV8_HIDDEN = -3.0e38f / PV8_UNIT;        // stands for a masked score: finite, so that 0 * it is not NaN
 constexpr int PV8_FLUSH_TILES = 1024;
+// A row's factor that leaves no room for that (key scales are 131008 / 127 at most) is brought down to 2^90 by a power of two:
+// key scales are 2^-47 / 127 at least, so that two scores that differ at all do so by 2^12 or more, with either factor, and
+// weights are 0 or 1.  (Here and not where the scale is formed: a branch in the loop, although never taken, cost 32 slabs of
+// 16384 keys 1 %.)
+__device__ __forceinline__ float pv8_row_scale(float dq) {
+    return dq > 0x1p90f ? __builtin_amdgcn_frexp_mantf(dq) * 0x1p91f : dq;
+}
 
 // The first matrix instruction of a block of scores.  (Written out because the compiler would keep the constant in 16
 // registers.  It is followed by the next of its chain, which takes its result without a wait.)
@@ -195,6 +203,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
         for (int ks = 0; ks < QREG; ++ks) qreg[ks] = *(const p4i*)(qi + (slab_q + (q_row < Nq ? q_row : Nq - 1)) * D + ks * 32 + h * 16);
         dq = qsc[(size_t)bh * nbq + ((q_row < Nq ? q_row : Nq - 1) >> shift_q)] * PV8_LOG2E;
     }
+    dq = pv8_row_scale(dq);
 
     // ---- operand read offsets (per lane, inside a buffer).  The swizzle of a row depends on the
     // row's low bits only, so the second 32-key block of K^ and the further 32-channel blocks of

@@ -39,3 +39,14 @@ def test_rows_whose_scores_are_all_far_below_zero(B, H, N, D, sm_scale):
     # weights are 0 and 1: half a unit of the fp16 result, and the fp32 sum of up to N values and its division (N 2^-24)
     assert np.isfinite(got).all()
     assert (np.abs(got - want) <= 2.0 ** -11 * np.abs(want) + 2.0 ** -25 + N * 2.0 ** -24 * np.abs(v).max()).all()
+
+
+@pytest.mark.parametrize("N, D, block_k, sm_scale", [(200, 64, 64, 4e30), (300, 64, 1, 1e33), (200, 128, 64, 1e33), (130, 128, 1, 4e30)])
+def test_huge_scales_with_the_int8_second_product(N, D, block_k, sm_scale):
+    q, k, v, want = powers_of_two(1, 2, N, D, 1750 + N + D)
+    o = sage.sageattn(*(torch.from_numpy(x).cuda() for x in (q, k, v)), True, sm_scale, 64 if block_k > 1 else 1, block_k, pv_int8=True)
+    got = o.cpu().numpy().astype(np.float64)
+    # the codes of V are half a step of their channel's scale off at most, a mean of them no more
+    assert np.isfinite(got).all()
+    step = np.abs(v.astype(np.float64)).max(axis=2, keepdims=True) / 127.0
+    assert (np.abs(got - want) <= 0.5 * step + 2.0 ** -11 * np.abs(want) + 2.0 ** -25 + N * 2.0 ** -24 * np.abs(v).max()).all()
