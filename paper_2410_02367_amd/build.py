@@ -142,6 +142,70 @@ def build_library(verbose: bool = False, extra=()) -> str:
 ATTENTION_KERNELS = 4 + 4 * 3 + 2
 
 
+def _registers(operand: str, file: str) -> set:
+    """Numbers of the registers of a file ("v" or "a") that an operand such as v12 or a[12:15] names."""
+    import re
+    m = re.fullmatch(file + r"(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    if not m:
+        return set()
+    return {int(m.group(1))} if m.group(1) else set(range(int(m.group(2)), int(m.group(3)) + 1))
+
+
+def _operands(code: str) -> list:
+    parts = code.split(None, 1)
+    return [o.strip() for o in parts[1].split(",")] if len(parts) > 1 else []
+
+
+class MatrixHazards:
+    """The waits that the compiler would insert if it knew that inline assembly holds matrix instructions, checked over a
+    kernel's instructions in the order of the text:
+      - no instruction touches a VGPR within 12 wait states of a matrix instruction writing it (except the next matrix
+        instruction of the same accumulation chain), where either of the two is the source's own,
+      - none of the source's own matrix instructions reads a VGPR that one of the two preceding instructions wrote.
+    Between instructions that it placed itself the compiler sees to the waits."""
+
+    def __init__(self, kernel: str, problems: list):
+        self.kernel, self.problems = kernel, problems
+        self.pending = []         # [registers written by a matrix instruction, wait states since, its text, source's own]
+        self.recent = []          # VGPRs written by the last two non-matrix instructions
+
+    def branch(self, code: str) -> None:
+        """A label ("") or a branch."""
+        if code.startswith("s_branch"):
+            self.pending, self.recent = [], []          # nothing falls through an unconditional branch
+        elif code:
+            for p in self.pending:
+                p[1] += 1
+
+    def instruction(self, code: str, own: bool) -> None:
+        """own: a matrix instruction that the source wrote."""
+        import re
+        ops = _operands(code)
+        touched = set().union(*[_registers(o, "v") for o in ops]) if ops else set()
+        is_mfma = code.startswith("v_mfma")
+        own = own and is_mfma
+        for written, waited, text, theirs in self.pending:
+            same_chain = is_mfma and _registers(ops[0], "v") == written and _registers(ops[-1], "v") == written
+            if touched & written and not same_chain and (own or theirs):
+                self.problems.append(f"{self.kernel}: '{code}' touches the result of '{text}' after {waited} wait states")
+        if own and any(_registers(o, "v") & w for o in ops[1:] for w in self.recent):
+            self.problems.append(f"{self.kernel}: '{code}' reads a register written less than 2 wait states before")
+        m = re.match(r"s_nop\s+(\d+)", code)
+        step = int(m.group(1)) + 1 if m else 1
+        for p in self.pending:
+            p[1] += step
+        dst = _registers(ops[0], "v") if is_mfma else set()
+        # (a result that the chain's next instruction has taken over is that one's)
+        self.pending = [p for p in self.pending if p[1] < 12 and p[0] != dst]
+        if is_mfma:
+            if dst:
+                self.pending.append([dst, 0, code, own])
+            self.recent = []
+        else:
+            wrote = _registers(ops[0], "v") if ops and code.startswith("v_") else set()      # VALU results only: loads are covered by s_waitcnt
+            self.recent = ([wrote] + self.recent)[:2] if step == 1 else []
+
+
 def check_attention_asm(text: str) -> list:
     """Checks the assembly text of the attention kernels for what their hand-placed register use
     relies on (see "Register files" at the top of sage_attn.hip) and returns the list of problems
@@ -153,11 +217,8 @@ def check_attention_asm(text: str) -> list:
         rare rescale and the epilogue), i.e. never inside a block that issues matrix instructions
         (AGPRs that no matrix instruction names are the compiler's own parking space and exempt),
       - nothing spills to scratch memory,
-      - and it never touches m0, which the hand-written global->LDS loads set.
-      - no instruction touches a VGPR within 12 wait states of a matrix instruction writing it
-        (except the next matrix instruction of the same accumulation chain), and no matrix
-        instruction reads a VGPR that one of the two preceding instructions wrote -- the waits the
-        compiler would insert if it knew these were matrix instructions.
+      - it never touches m0, which the hand-written global->LDS loads set,
+      - and the waits are there that the compiler does not know of (MatrixHazards).
     Instructions between ";;#ASMSTART" and ";;#ASMEND" are the source's own assembly."""
     import re
     kernels = re.findall(r"^(_ZN4sage16sage_attn_kernel\w+):.*?^\.Lfunc_end\d+:", text, re.S | re.M)
@@ -166,26 +227,6 @@ def check_attention_asm(text: str) -> list:
     if len(bodies) != ATTENTION_KERNELS:
         problems.append(f"expected {ATTENTION_KERNELS} attention kernels in the assembly, found {len(bodies)}")
 
-    def vregs(operand: str) -> set:
-        """VGPR numbers named by one operand such as v12 or v[12:15]."""
-        m = re.fullmatch(r"v\[(\d+):(\d+)\]", operand)
-        if m:
-            return set(range(int(m.group(1)), int(m.group(2)) + 1))
-        m = re.fullmatch(r"v(\d+)", operand)
-        return {int(m.group(1))} if m else set()
-
-    def aregs(operand: str) -> set:
-        """AGPR numbers named by one operand such as a12 or a[12:15]."""
-        m = re.fullmatch(r"a\[(\d+):(\d+)\]", operand)
-        if m:
-            return set(range(int(m.group(1)), int(m.group(2)) + 1))
-        m = re.fullmatch(r"a(\d+)", operand)
-        return {int(m.group(1))} if m else set()
-
-    def operands(code: str) -> list:
-        parts = code.split(None, 1)
-        return [o.strip() for o in parts[1].split(",")] if len(parts) > 1 else []
-
     for name, body in zip(kernels, bodies):
         # AGPRs that matrix instructions name (accumulators, resident operands).  The compiler may
         # park unrelated values in the remaining AGPRs; moving those around is harmless.
@@ -193,13 +234,12 @@ def check_attention_asm(text: str) -> list:
         for line in body.split("\n"):
             code = line.split(";")[0].strip()
             if code.startswith("v_mfma"):
-                for o in operands(code):
-                    matrix_agprs |= aregs(o)
+                for o in _operands(code):
+                    matrix_agprs |= _registers(o, "a")
         state = {"mfma": False, "reads": []}
         in_asm = False
         seen_mfma = False
-        pending = []          # [registers written by a matrix instruction, wait states since, its text]
-        recent = []           # VGPRs written by the last two non-matrix instructions
+        hazards = MatrixHazards(name, problems)
 
         def close_block():
             if state["mfma"] and state["reads"]:
@@ -216,47 +256,19 @@ def check_attention_asm(text: str) -> list:
                 continue
             if re.match(r"^\.LBB\d+_\d+:", line) or code.startswith("s_cbranch") or code.startswith("s_branch"):
                 close_block()
-                if code.startswith("s_branch"):
-                    pending, recent = [], []          # nothing falls through an unconditional branch
-                elif code:
-                    for p_ in pending:
-                        p_[1] += 1
+                hazards.branch("" if code.startswith(".") else code)
                 continue
             if not code or code.startswith("."):
                 continue
-            ops = operands(code)
-            touched = set().union(*[vregs(o) for o in ops]) if ops else set()
-            is_mfma = code.startswith("v_mfma")
-            # --- hazard windows
-            for p_ in pending:
-                same_chain = is_mfma and ops and vregs(ops[0]) == p_[0] and vregs(ops[-1]) == p_[0]
-                if touched & p_[0] and not same_chain:
-                    problems.append(f"{name}: '{code}' touches the result of '{p_[2]}' after {p_[1]} wait states")
-            if is_mfma:
-                for o in ops[1:]:
-                    for w in recent:
-                        if vregs(o) & w:
-                            problems.append(f"{name}: '{code}' reads a register written less than 2 wait states before")
-            m = re.match(r"s_nop\s+(\d+)", code)
-            step = int(m.group(1)) + 1 if m else 1
-            for p_ in pending:
-                p_[1] += step
-            pending = [p_ for p_ in pending if p_[1] < 12]
-            if is_mfma:
-                dst = vregs(ops[0]) if ops else set()
-                if dst:
-                    pending.append([dst, 0, code])
-                recent = []
-            else:
-                wrote = vregs(ops[0]) if ops and code.startswith("v_") else set()      # VALU results only: loads are covered by s_waitcnt
-                recent = ([wrote] + recent)[:2] if step == 1 else []
+            hazards.instruction(code, True)
+            is_mfma, ops = code.startswith("v_mfma"), _operands(code)
             # --- register-file rules
             if in_asm:
                 if is_mfma:
                     state["mfma"] = True
                     seen_mfma = True
                 continue
-            named = set().union(*[aregs(o) for o in ops]) if ops else set()
+            named = set().union(*[_registers(o, "a") for o in ops]) if ops else set()
             if code.startswith("v_accvgpr_mov") and seen_mfma and named & matrix_agprs:
                 problems.append(f"{name}: accumulator-to-accumulator copy: {code}")
             if code.startswith("v_accvgpr_read") and named & matrix_agprs:
@@ -270,9 +282,9 @@ def check_attention_asm(text: str) -> list:
 
 
 def check_loads_asm(text: str, kernel: str, expected: int) -> list:
-    """Checks the assembly text of `kernel`'s instantiations, whose matrix instructions are compiler builtins: the compiler
-    places the waits itself, and what the source relies on is only that nothing spills to scratch memory and that the
-    compiler never touches m0, which the hand-written global->LDS loads set."""
+    """Checks the assembly text of `kernel`'s instantiations, whose matrix instructions are compiler builtins but for the
+    seeded ones of the INT8 second product: that nothing spills to scratch memory, that the compiler never touches m0, which
+    the hand-written global->LDS loads set, and that the waits around hand-written matrix instructions are there."""
     import re
     bodies = re.findall(rf"^(_ZN4sage{len(kernel)}{kernel}\w+):(.*?)^\.Lfunc_end\d+:", text, re.S | re.M)
     problems = []
@@ -280,6 +292,7 @@ def check_loads_asm(text: str, kernel: str, expected: int) -> list:
         problems.append(f"expected {expected} instantiations of {kernel} in the assembly, found {len(bodies)}")
     for name, body in bodies:
         in_asm = False
+        hazards = MatrixHazards(name, problems)
         for line in body.split("\n"):
             if "#ASMSTART" in line:
                 in_asm = True
@@ -288,7 +301,13 @@ def check_loads_asm(text: str, kernel: str, expected: int) -> list:
                 in_asm = False
                 continue
             code = line.split(";")[0].strip()
-            if in_asm or not code:
+            if re.match(r"^\.LBB\d+_\d+:", line) or code.startswith("s_cbranch") or code.startswith("s_branch"):
+                hazards.branch("" if code.startswith(".") else code)
+                continue
+            if not code or code.startswith("."):
+                continue
+            hazards.instruction(code, in_asm)
+            if in_asm:
                 continue
             if code.startswith("scratch_"):
                 problems.append(f"{name}: scratch access: {code}")

@@ -99,7 +99,7 @@ def test_matrix_instruction_reading_a_fresh_valu_result_is_reported():
 
 # ------------------------------------------------------------------ INT8-P~V kernels (compiler-scheduled)
 
-from paper_2410_02367_amd.build import check_decode_asm, check_pv8_asm, check_short_asm  # noqa: E402
+from paper_2410_02367_amd.build import check_decode_asm, check_pv8_asm, check_short_asm, check_short_pair_asm  # noqa: E402
 
 PV8_KERNELS = ["_ZN4sage20sage_attn_pv8_kernelILi%dELb%dELb%dELb%dEEEvPKa" % (d, c, k, sp)
                for d in (64, 128) for c in (0, 1) for k in (0, 1) for sp in (0, 1)]
@@ -131,7 +131,42 @@ def test_pv8_scratch_and_compiler_use_of_m0_are_reported():
     assert any("scratch access" in p for p in problems) and any("use of m0" in p for p in problems)
 
 
+SEEDED = """\t;;#ASMSTART
+\tv_mfma_i32_32x32x32_i8 v[0:15], v[16:19], v[20:23], 0.15915494
+\t;;#ASMEND
+"""
+CHAINED = "\tv_mfma_i32_32x32x32_i8 v[0:15], v[24:27], v[28:31], v[0:15]\n"
+
+
+def test_pv8_waits_around_the_seeded_matrix_instruction():
+    """The compiler places no waits around the matrix instruction that the source wrote; around its own it does."""
+    def found(body):
+        return check_pv8_asm(fake_pv8(body + "\ts_endpgm\n"))
+    assert found(SEEDED + CHAINED) == []
+    # the result read, overwritten or copied before the chain's next instruction, or by it as another operand
+    for early in ("\tv_sub_f32_e32 v40, v3, v41\n", "\tv_mov_b32_e32 v15, v41\n", "\tds_write_b128 v50, v[4:7]\n",
+                  "\tv_mfma_i32_32x32x32_i8 v[60:75], v[24:27], v[28:31], v[0:15]\n",
+                  "\tv_mfma_i32_32x32x32_i8 v[60:75], v[12:15], v[28:31], v[60:75]\n"):
+        assert any("touches the result" in p for p in found(SEEDED + early + CHAINED)), early
+        # ... nor across a branch that may fall through, nor past a label
+        assert any("touches the result" in p for p in found(SEEDED + "\ts_cbranch_scc1 .LBB0_1\n.LBB0_9:\n" + early + CHAINED)), early
+    assert found(SEEDED + "\ts_nop 11\n\tv_mov_b32_e32 v15, v41\n") == []
+    # an operand written by one of the two instructions before it
+    for write in ("\tv_mov_b32_e32 v18, v40\n", "\tv_lshlrev_b32_e32 v23, 6, v40\n"):
+        for gap in ("", "\tv_mov_b32_e32 v90, v91\n"):
+            assert any("less than 2 wait states" in p for p in found(write + gap + SEEDED + CHAINED))
+        assert found(write + 2 * "\tv_mov_b32_e32 v90, v91\n" + SEEDED + CHAINED) == []
+    # an operand, or its own registers, still being written by one of the compiler's matrix instructions
+    for dst in ("v[16:31]", "v[8:23]", "v[0:15]"):
+        before = f"\tv_mfma_i32_32x32x32_i8 {dst}, v[60:63], v[64:67], 0\n"
+        assert any("touches the result" in p for p in found(before + SEEDED + CHAINED)), dst
+        assert found(before + "\ts_nop 11\n" + SEEDED + CHAINED) == []
+    # what the compiler placed itself is its own to time
+    assert found(CHAINED + "\ts_nop 7\n\tv_sub_f32_e32 v40, v3, v41\n") == []
+
+
 @pytest.mark.parametrize("check, names", [
+    (check_short_pair_asm, ["_ZN4sage22sage_short_pair_kernelILi64ELi%dELi8ELb%dEEEvPKDF16_" % (n, k) for n in (4, 8) for k in (0, 1)]),
     (check_short_asm, ["_ZN4sage17sage_short_kernelILi%dELi%dELi%dELb%dEEEvPKDF16_" % (d, n, nw, k)
                        for d, n, nw in ((64, 2, 4), (64, 4, 4), (64, 8, 8), (128, 2, 4), (128, 4, 8)) for k in (0, 1)]),
     (check_decode_asm, ["_ZN4sage18sage_decode_kernelILi%dELb%dELi2ELi%dEEEvPKa" % (d, k, nw)
