@@ -281,6 +281,22 @@ def check_attention_asm(text: str) -> list:
     return problems
 
 
+# Registers (VGPRs and AGPRs together) with which three workgroups of 4 wavefronts fit on a CU: 512 / 3, in steps of 8.
+THREE_WORKGROUPS_VGPRS = 168
+
+
+def check_attention_registers(text: str) -> list:
+    """The attention kernels of D = 64 run three workgroups on a CU; their launch bounds ask for two, so nothing but this keeps
+    the compiler within the registers of three."""
+    import re
+    used = re.findall(r"^\s*\.amdhsa_kernel (_ZN4sage16sage_attn_kernelILi64ELi4ELb[01]ELb0E\w+).*?^\s*\.amdhsa_next_free_vgpr (\d+)", text, re.S | re.M)
+    problems = [f"{name}: {n} registers, with which two workgroups fit on a CU instead of three" for name, n in used
+                if int(n) > THREE_WORKGROUPS_VGPRS]
+    if len(used) != 4:
+        problems.append(f"expected the register counts of 4 attention kernels with D = 64, found {len(used)}")
+    return problems
+
+
 def check_loads_asm(text: str, kernel: str, expected: int) -> list:
     """Checks the assembly text of `kernel`'s instantiations, whose matrix instructions are compiler builtins but for the
     seeded ones of the INT8 second product: that nothing spills to scratch memory, that the compiler never touches m0, which
@@ -357,7 +373,7 @@ def verify_attention_isa(extra=()) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     problems = []
     with tempfile.TemporaryDirectory() as tmp:
-        for src, check in (("sage_attn.hip", check_attention_asm), ("sage_attn_pv8.hip", check_pv8_asm),
+        for src, check in (("sage_attn.hip", lambda s: check_attention_asm(s) + check_attention_registers(s)), ("sage_attn_pv8.hip", check_pv8_asm),
                            ("sage_prepass.hip", check_no_spills), ("sage_prepass_v.hip", check_no_spills),
                            ("sage_short.hip", check_short_asm), ("sage_short.hip", check_short_pair_asm), ("sage_decode.hip", check_decode_asm)):
             out = os.path.join(tmp, src + ".s")

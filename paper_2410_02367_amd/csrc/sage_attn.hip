@@ -202,7 +202,7 @@ template <class T> __device__ __forceinline__ void pin_a(T& x) { asm volatile(""
 // many key tiles it visited -- from which the clock the chip held and the clocks per tile follow.
 template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false>
 // Workgroups of 4 wavefronts per CU that the register budget is cut for: 2.  At D = 64 the compiler stays within
-// the 168 registers of three on its own (152, with one scale per key 160), which is 4 % faster than two.
+// the 168 registers of three on its own (152, with one scale per key 164), which is 4 % faster than two; the build checks it.
 __global__ void __launch_bounds__(NW * 64, NW == 4 && SAGE_QS == 1 ? 2 : 1)
 sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const int8_t* __restrict__ ki, const float* __restrict__ ksc,

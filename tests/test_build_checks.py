@@ -97,6 +97,15 @@ def test_matrix_instruction_reading_a_fresh_valu_result_is_reported():
     assert check_attention_asm(fake(ok)) == []
 
 
+def test_registers_that_cost_the_third_workgroup_are_reported():
+    from paper_2410_02367_amd.build import check_attention_registers
+    text = "\n".join(f"\t.amdhsa_kernel {k}\n\t\t.amdhsa_next_free_vgpr {168 if 'ILi64E' in k else 216}\n\t.end_amdhsa_kernel" for k in KERNELS)
+    assert check_attention_registers(text) == []
+    problems = check_attention_registers(text.replace(" 168", " 169", 3))      # (the first of the three is the score dump)
+    assert len(problems) == 2 and all("169 registers" in p for p in problems)
+    assert any("expected" in p for p in check_attention_registers(text.replace(KERNELS[1], "other")))
+
+
 # ------------------------------------------------------------------ INT8-P~V kernels (compiler-scheduled)
 
 from paper_2410_02367_amd.build import check_decode_asm, check_pv8_asm, check_short_asm, check_short_pair_asm  # noqa: E402
