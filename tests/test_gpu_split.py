@@ -281,14 +281,15 @@ def test_random_split_shape(i, B, H, Nq, Nkv, D, causal, bq, bk, req):
 
 
 # Chunks of more than 2048 keys under a mask, D = 128: 256-row workgroups where the 128-row ones fill more than half of 512
-# places and the rows are whole pairs of 128-row tiles (13 of 130: 468 -> 234; 20 of 250 and 65 of 129), 128-row ones where they
-# are not (40 of 300, 3 tiles or 2) or where half the places would do (12 of 500, asked for 4 chunks).
+# places and the rows are whole pairs of 128-row tiles (13 of 130 in 19 chunks: 494 -> 247; 20 of 250 and 65 of 129), 128-row
+# ones where they are not (40 of 300, 3 tiles or 2) or where half the places would do (12 of 500, asked for 4 chunks).
+# test_workgroup_shape.py holds the rule to that.
 SHAPES_OF_CHUNKS = [(13, 130, 40000, 128, 64, 0), (20, 250, 30000, 1, 1, 0), (65, 129, 5200, 64, 128, 2), (40, 300, 16500, 128, 64, 0),
                     (12, 500, 10000, 128, 64, 4)]
 
 
 @pytest.mark.parametrize("slabs,Nq,Nkv,bq,bk,req", SHAPES_OF_CHUNKS)
-def test_workgroup_shape_of_chunks_under_a_mask(slabs, Nq, Nkv, bq, bk, req):
+def test_chunks_under_a_mask_in_either_workgroup_shape(slabs, Nq, Nkv, bq, bk, req):
     D, sm = 128, sage.sage_default_sm_scale(128)
     n = sage.sage_attn_split_count(1, slabs, Nq, Nkv, True, req)
     print(f"[case] {slabs} x {Nq} x {Nkv} scales {bq}x{bk}: {n} chunks", flush=True)
