@@ -65,7 +65,7 @@
 //   - the int32 accumulators start at 0x4B400000; reinterpreted as fp32 the result is exactly
 //     12582912 + S^ (|S^| <= 127*127*128 < 2^22), so no int->float conversion is issued and the
 //     dequantization, the log2(e) factor and the subtraction of the running maximum are one FMA;
-//     that FMA rounds once only if its bias -(12582912 * sc + m) is exact, which holds because sc
+//     that FMA rounds once only if what it subtracts, 12582912 * sc + m, is exact, which holds because sc
 //     carries 22 significant bits and m is kept on the grid of 12582912 * sc (see begin_tile(),
 //     finish_max(), raise_maximum());
 //   - the row maximum is taken on the raw accumulators with integer max;
@@ -96,7 +96,7 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 //   8 wavefronts, one workgroup per CU  -- two wavefronts per SIMD share one set of LDS tiles;
 //   4 wavefronts, two or three workgroups per CU -- chosen by the launcher for D = 64, for short
 //                                          sequences and whenever the larger tile would leave CUs
-//                                          without work (see launch_d()).
+//                                          without work (see sage_shape.h).
 // QS = 2 (64 rows per wavefront, every LDS operand feeding two matrix instructions, one wavefront
 // per SIMD) is what the QS loops in the kernel are for; an earlier version measured it 2-3 % slower
 // than QS = 1, and the build and the tests cover QS = 1 only.
@@ -372,10 +372,6 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     constexpr int NA = SA * DT;
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) pk[qs][a][b] = (v4i){0, 0, 0, 0};
         m_run[qs] = -__builtin_inff();
         sc[qs] = 0.0f; bias[qs] = 0.0f; m_cand[qs] = 0.0f; off_grid[qs] = false;
     }
@@ -478,7 +474,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             // a zero scale (all-zero quantization block) would turn -inf * scale into NaN
             sc[qs] = __builtin_fmaxf(dq[qs] * dk, 1e-30f);
             if constexpr (!KTOK) {
-                // The exp2 argument is fma(seeded score, sc, bias) with bias = -(12582912 * sc + m):
+                // The exp2 argument is fma(seeded score, sc, -bias) with bias = 12582912 * sc + m:
                 // it equals S^ * sc - m rounded ONCE only if that bias is exact.  The product is
                 // exact once sc is cut to 22 significant bits (a relative change of 2^-22 in the
                 // scale); the sum is exact when m is a multiple of the product's ulp, which
@@ -565,7 +561,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         bool want = false;
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
-            // the exp2 argument of the own maximum; on the first tile the bias is +inf and so is this
+            // the exp2 argument of the own maximum
             const float top = __builtin_fmaf(KTOK ? pmaxf[qs][0] : as_f32(pmax[qs][0]), sc[qs], -bias[qs]);
             want = want || off_grid[qs] || (top > MAX_SLACK);
         }
@@ -791,7 +787,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // The first tile: no P~V before it, and nothing to rescale when its maximum is taken.  K^Q^^T of tile 1 starts when the
     // softmax has consumed the first half of the scores.  The step above with zeros in the place of P~, which did this before,
     // cost 24 matrix instructions and a rescale per workgroup together with the last tile's unused K^Q^^T: 128 slabs of 1536
-    // keys at D = 128, causal, 79.0 -> 74.4 us, 96 of 1105 at D = 64 39.6 -> 38.1, 128 of 4096 at D = 128 799 -> 775.
+    // keys at D = 128, causal, 82.9 -> 79.1 us, of 4096 436 -> 420, without a mask 775 -> 765; 96 of 1105 at D = 64 39.7 -> 38.7.
     auto first_tile = [&]() {
         static_for<QS>([&](auto QSI) {
             static_for<NA>([&](auto P) { partial_max(QSI, P, 0); });
@@ -943,9 +939,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         iteration(j, j & 1, last);
         ++j;
     }
-    // The scores of tile Tw that the last step produced are never read: keep their registers
-    // untouched until the matrix instructions have written them (the compiler would hand them out
-    // as temporaries at once).
+    // A wavefront with one tile has scores of a tile that it does not visit (first_tile()), which are never read: keep their
+    // registers untouched until the matrix instructions have written them (the compiler would hand them out as temporaries
+    // at once).
     score_fence();
     // the P~V of the wavefront's last tile ...
     turn(j, j & 1);

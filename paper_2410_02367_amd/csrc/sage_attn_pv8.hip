@@ -30,9 +30,11 @@
 //
 // This variant is written with compiler builtins and compiler scheduling; it trades the second
 // product's instruction count (half) for more VALU work per score (subtraction of the seed, rounding,
-// packing, flushes).  Measured on MI355X against the FP16-second-product kernel: 2 % faster at 16K keys,
-// 11 % at 128K (flushes are rare there), 3-12 % slower below 8K; it is bound by VALU issue
-// (about 264 VALU instructions against 16 matrix instructions per 32 x 64 step).
+// packing, flushes).  Measured on MI355X against the FP16-second-product kernel, D = 128: 0-3 % faster at
+// 16K keys, 3-6 % at 32K, 9-11 % at 128K (flushes are rare there), as fast at 8K, 3-7 % slower at 4K, 13 %
+// for 128 slabs of 1536, causal; D = 64: 7-11 % slower from 2K to 8K, as fast at 16K, 2-3 % faster at 32K.
+// It is bound by VALU issue (about 194 VALU instructions per 32 x 64 step and 136 more per flush, 245 at 16K
+// keys, against 16 matrix instructions).
 #include "sage_internal.h"
 #include "sage_device.h"
 #include <type_traits>
@@ -230,7 +232,7 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
     // iteration late, so that every group of matrix instructions but one has independent VALU work
     // next to it in the instruction stream:
     //     K^Q^^T of tile j (8 matrix instructions)            | codes of tile j-1, second half
-    //     V^^T P^^T of tile j-1, second half (4)              | int -> float conversion of tile j's scores
+    //     V^^T P^^T of tile j-1, second half (4)              | the seed subtracted from tile j's scores
     //     maximum, flush if a row's maximum rose (rare), codes of tile j, first half
     //     V^^T P^^T of tile j, first half (4)
     // State carried to the next iteration: the second half's 16 dequantizable scores per lane, the

@@ -471,6 +471,9 @@ hipError_t launch_short(const void* q, const void* k, const void* v, void* o, in
         // per token, 9.5 / 8.6, 2 of 256 7.9 / 7.8; with a mask, where half the tiles are left out anyway, 2 of 488 13.2 / 11.0,
         // but 64 of 512 (256 workgroups) 14.0 / 14.5 and 128 of 256 8.2 / 8.7.  Not at D = 128, at most 4 tiles and twice the
         // results to exchange: 64 of 126 8.7 / 10.0, 128 of 256 13.9 / 15.3.
+        // The sums are made in another order, each half's weights relative to its own maximum.  Relative error against 64 bits
+        // over the same codes, 1e-4, with one / two: 2 slabs of 256 2.78 / 2.71, 60 of 500 2.80 / 2.76, 20 of 400 causal, per
+        // token, 2.44 / 2.41; smaller in all of 17 shapes from 197 to 512 keys, six inputs each.
         if (N > 192 && (long)BH * ((Nq + 127) / 128) <= (causal ? 128 : 256)) {
             if (N <= 256) return launch_short_t<64, 4, 8, 2>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st);
             return launch_short_t<64, 8, 8, 2>(q, k, v, o, BH, Nq, N, causal, sm_scale, block_q, block_k, st);
