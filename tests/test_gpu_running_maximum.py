@@ -1,0 +1,57 @@
+"""Scores that leave the range of the running maximum: weights of FP16 end at 2^16, and the maximum of the first key tile is kept
+until one of them does.  Keys that grow along the sequence (every block with another scale, so that the grid of the maximum
+changes too) or one far larger key in the middle or at the end, in every shape of the attention kernel, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2410_02367_amd as sage
+import sage_inputs as si
+from gpu_util import assert_output_close, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# B, H, Nq, Nkv, D, causal, block_q, block_k
+SHAPES = [
+    (1, 2, 513, 513, 64, False, 128, 64), (1, 2, 700, 700, 64, True, 1, 64), (1, 2, 1105, 1105, 64, True, 32, 128), (1, 2, 600, 600, 64, True, 1, 1),
+    (1, 2, 300, 300, 128, False, 64, 64), (1, 2, 577, 577, 128, True, 128, 128), (1, 2, 640, 640, 128, False, 1, 1),
+    (1, 2, 33, 1500, 128, True, 128, 64), (1, 3, 200, 3000, 64, False, 128, 64),       # keys in chunks
+    (1, 17, 2100, 2100, 128, False, 128, 64), (2, 29, 2300, 4200, 128, True, 128, 64),  # workgroups of 256 rows
+]
+
+
+def keys(kind, k, rng):
+    N = k.shape[2]
+    if kind == "growing":
+        return k * np.geomspace(0.1, 10.0, N)[:, None]
+    at = {"middle": N // 2, "last": N - 1, "second tile": 64}[kind]
+    k = k.copy()
+    k[:, :, at] *= 14.0
+    return k
+
+
+@pytest.mark.parametrize("kind", ["growing", "middle", "last", "second tile"])
+@pytest.mark.parametrize("B, H, Nq, Nkv, D, causal, bq, bk", SHAPES)
+def test_scores_far_above_those_of_the_first_tile(kind, B, H, Nq, Nkv, D, causal, bq, bk):
+    if H > 3 and kind != "growing":
+        pytest.skip("the large shapes run once")
+    print(f"[case] {kind} B{B} H{H} Nq{Nq} Nkv{Nkv} D{D} causal={causal} scales {bq}x{bk}", flush=True)
+    rng = np.random.default_rng(si.BASE_SEED + Nkv + D)
+    q = (3.0 * rng.standard_normal((B, H, Nq, D))).astype(np.float16)
+    k = keys(kind, rng.standard_normal((B, H, Nkv, D)), rng).astype(np.float16)
+    # rows are all but a single value here: below 2, where one unit of the fp16 result is half of the tolerance
+    v = np.clip(rng.standard_normal((B, H, Nkv, D)), -1.99, 1.99).astype(np.float16)
+    sm = D ** -0.5
+    out = sage.sageattn(to_dev(q), to_dev(k), to_dev(v), causal, sm, bq, bk).cpu().numpy()
+    kq, ks, _ = oracle.smooth_quant_k(k, bk)
+    qq, qs = oracle.quant_q(q, sm, bq)
+    # the last row of the first head sees every key: its scores do leave the range after the first tile
+    row = (qq[0, 0, -1].astype(np.float64) @ kq[0, 0].astype(np.float64).T) * qs[0, 0, -1] * np.repeat(ks[0, 0], bk)[:Nkv] * np.log2(np.e)
+    assert row.max() > row[:64].max() + 16 or kind != "growing"
+    lq, lk = max(bq, 64) if bq != 1 else 128, max(bk, 64) if bk != 1 else 64
+    heads = [(0, 0), (B - 1, H - 1)]
+    for b, h in heads:
+        one = lambda x: np.ascontiguousarray(x[b:b + 1, h:h + 1])
+        ref = oracle.attn_l2_cross(one(qq), one(qs), one(kq), one(ks), one(v), causal, lq, lk, gran_q=bq, gran_k=bk)
+        assert_output_close(one(out), ref, f"{kind}, head {b} {h}")
