@@ -105,6 +105,11 @@ constexpr int KTILE = 64;                  // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int MAGIC_I = 0x4B400000;        // bit pattern of 12582912.0f = 1.5 * 2^23
 constexpr float MAGIC_F = 12582912.0f;
+// A tile that is redone leaves its weights at 2^-8 and below: where the scores of a wavefront rise by 2^16 once they do so again,
+// and each time costs a step (128 key tiles, scores with a standard deviation of 6 in the exponent of e: 1.1 times per wavefront
+// instead of 2.6).  Such rows rest on few weights; one of them is as exact at 2^-8 as at 1, and one 2^-6 times as large
+// loses less than the largest does by being rounded.
+constexpr float HEADROOM = 8.0f;
 constexpr float MAX_SLACK = 8.0f;          // one scale per key: log2 of the largest P~ tolerated before the maximum is raised
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
@@ -464,13 +469,15 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         const float x = __builtin_fmaxf(dq[qs] * dk, 1e-30f);
         return KTOK ? x : as_f32(as_i32(x) & ~3);          // KTOK: the 22 bits are the key's factor's
     };
-    // a maximum rounded to the grid on which the bias of a tile with factor x is exact, or one four times as coarse, on which it
-    // stays exact when the factors of later tiles are larger (rounding moves every weight of a row by the same factor, below
-    // 2^(4 x); hence not for a large x)
-    auto on_grid = [&](float m, float x) {
-        if constexpr (KTOK) return m;
-        const float y = x < 0.0625f ? 4.0f * x : x;
-        return __builtin_fmaf(-MAGIC_F, y, __builtin_fmaf(MAGIC_F, y, m));
+    // A maximum rounded to the grid on which the bias of the tile with the largest factor of all is exact, and with it that of
+    // every other (but for sums that pass into the next binade, see begin_tile()).  With the grid of the tile at hand every 4th
+    // to 9th wavefront met a coarser one later, and redo_tile(): 128 slabs of 1536 x 128, causal, 105.0 / 101.6.  (A grid
+    // four times as coarse does without the largest factor, but the largest weight of a row is then further from 1, which FP16
+    // represents: 1 % more error.)
+    float dk_top = 0.0f;               // largest key scale
+    auto on_grid = [&](float m, int qs) {
+        const float x = tile_scale(qs, dk_top);
+        return KTOK ? m : __builtin_fmaf(-MAGIC_F, x, __builtin_fmaf(MAGIC_F, x, m));
     };
 
     // ---- begin_tile: what the softmax of the tile whose scores sit in acc_s (tile j) needs
@@ -585,7 +592,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             for (int qs = 0; qs < QS; ++qs) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) refresh(acc_o[qs][dt]);
-                const float m_new = on_grid(on_grid(__builtin_fmaxf(m_run[qs], top[qs]), scp[qs]), sc[qs]);
+                float m_new = on_grid(__builtin_fmaxf(m_run[qs], top[qs] + HEADROOM), qs);
+                // (where the bias of tile j passes into the next binade, its own grid)
+                m_new = __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_new));
                 const float alpha = __builtin_amdgcn_exp2f(m_run[qs] - m_new);
                 m_run[qs] = m_new;
                 acc_l[qs] = before_l[qs] * alpha;        // the register of the lane's own query is the one that counts
@@ -859,7 +868,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 static_for<DT>([&](auto P) { partial_max(QSI, P, 0); });
                 m_run[qs] = pair32_max(pmax[qs]) * sc[qs];          // -inf stays -inf: sc > 0
             } else {
-                m_run[qs] = on_grid(row_maximum(QSI, sc[qs]), sc[qs]);
+                m_run[qs] = on_grid(row_maximum(QSI, sc[qs]), qs);
             }
         });
         set_bias();
@@ -911,6 +920,17 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     load_k(0, 0);
     if (T > 1) load_k(1, 1);
     request_key_scales(0);
+    // every lane a share of the chunk's key scales, the first of them on their way with the tiles
+    const int scales = (N + (1 << shift_k) - 1) >> shift_k;
+    auto some_scales = [&](int i, float (&x)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = ksc_bh[i + 64 * e < scales ? i + 64 * e : scales - 1];
+    };
+    float some[4];
+    if constexpr (!DUMP && !KTOK) {
+        some_scales(lane, some);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // The queries, while the key tiles are on their way.  They are read as codes, or made here from fp16 rows (qf):
     // a query is read once by the launch either way, and the quantizer's own pass over Q (2 bytes read and 1 written
     // per element, 1 read again) is saved.  Lanes past the last row get codes of 0: their scores raise no maximum and cost
@@ -938,6 +958,14 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     for (int qs = 0; qs < QS; ++qs)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) pin_a(qreg[qs][ks]);
+    if constexpr (!DUMP && !KTOK) {
+        for (int i = lane;; some_scales(i, some)) {
+            dk_top = __builtin_fmaxf(__builtin_fmaxf(dk_top, some[0]), __builtin_fmaxf(__builtin_fmaxf(some[1], some[2]), some[3]));
+            i += 256;
+            if (i - lane >= scales) break;
+        }
+        dk_top = as_f32(__builtin_amdgcn_readfirstlane(as_i32(lanes_max<64>(dk_top))));
+    }
     tiles_ready_barrier();
     qk_half(0, std::integral_constant<int, 0>{});
     qk_half(0, std::integral_constant<int, 1>{});
