@@ -105,11 +105,11 @@ constexpr int KTILE = 64;                  // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int MAGIC_I = 0x4B400000;        // bit pattern of 12582912.0f = 1.5 * 2^23
 constexpr float MAGIC_F = 12582912.0f;
-// A tile that is redone leaves its weights at 2^-8 and below: where the scores of a wavefront rise by 2^16 once they do so again,
-// and each time costs a step (128 key tiles, scores with a standard deviation of 6 in the exponent of e: 1.1 times per wavefront
-// instead of 2.6).  Such rows rest on few weights; one of them is as exact at 2^-8 as at 1, and one 2^-6 times as large
-// loses less than the largest does by being rounded.
-constexpr float HEADROOM = 8.0f;
+// log2 of the room above the weights of a tile that is redone: where the scores of a wavefront rise by 2^16 once they do so
+// again, and each time costs a step.  The largest weight of a row is then at 2^-2, and what FP16 cannot hold are weights 2^-22
+// times as large.  More room is felt: relative error against 64 bits of 2 slabs of 900 x 64 with some tokens 12 times as large,
+// 1e-5: 6.98 with none, 6.97 with 2, 7.08 with 4, 7.94 with 6, 16.2 with 8 (7.20 with the maximum of every tile).
+constexpr float HEADROOM = 2.0f;
 constexpr float MAX_SLACK = 8.0f;          // one scale per key: log2 of the largest P~ tolerated before the maximum is raised
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
