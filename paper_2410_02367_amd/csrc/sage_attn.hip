@@ -105,11 +105,14 @@ constexpr int KTILE = 64;                  // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int MAGIC_I = 0x4B400000;        // bit pattern of 12582912.0f = 1.5 * 2^23
 constexpr float MAGIC_F = 12582912.0f;
-// log2 of the room above the weights of a tile that is redone: where the scores of a wavefront rise by 2^16 once they do so
-// again, and each time costs a step.  The largest weight of a row is then at 2^-2, and what FP16 cannot hold are weights 2^-22
-// times as large.  More room is felt: relative error against 64 bits of 2 slabs of 900 x 64 with some tokens 12 times as large,
-// 1e-5: 6.98 with none, 6.97 with 2, 7.08 with 4, 7.94 with 6, 16.2 with 8 (7.20 with the maximum of every tile).
-constexpr float HEADROOM = 2.0f;
+// log2 of the room above the weights of the first tile and of one that is redone: the scores of a wavefront have to rise by so
+// much more before a tile is redone, which costs the workgroup about three steps (the others wait at its barrier).  The
+// largest weight of a row may then be 2^-4 or 2^-2, and what FP16 cannot hold are weights 2^-20 times as large.  More room is
+// felt where few keys carry a row: relative error against 64 bits of 2 slabs of 900 x 64 with some tokens 12 times as large,
+// 1e-5, 6.98 with HEADROOM 0, 6.97 with 2, 7.08 with 4, 7.94 with 6, 16.2 with 8 (7.20 with the maximum of every tile); with 2
+// and FIRST_ROOM 0 / 2 / 4: 6.97 / 7.06 / 7.03.  Scores with a standard deviation of 3.7 in the exponent of e (rotated keys
+// whose bias the smoothing leaves), 64 key tiles: 1.2 / 0.9 / 0.5 redone per wavefront with FIRST_ROOM 0 / 2 / 4.
+constexpr float FIRST_ROOM = 4.0f, HEADROOM = 2.0f;
 constexpr float MAX_SLACK = 8.0f;          // one scale per key: log2 of the largest P~ tolerated before the maximum is raised
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
@@ -408,10 +411,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 
     // 12 wait states between the matrix instructions that wrote the scores and the first VALU or
     // memory instruction that touches them; the operands tie every later use to the fence.
-    auto score_fence = [&]() {
+    auto score_fence = [](v16i (&s)[QS][2]) {
         static_assert(QS == 1 || QS == 2, "the fence lists the score registers explicitly");
-        if constexpr (QS == 2) asm volatile("s_nop 11" : "+v"(acc_s[0][0]), "+v"(acc_s[0][1]), "+v"(acc_s[QS - 1][0]), "+v"(acc_s[QS - 1][1]));
-        else asm volatile("s_nop 11" : "+v"(acc_s[0][0]), "+v"(acc_s[0][1]));
+        if constexpr (QS == 2) asm volatile("s_nop 11" : "+v"(s[0][0]), "+v"(s[0][1]), "+v"(s[QS - 1][0]), "+v"(s[QS - 1][1]));
+        else asm volatile("s_nop 11" : "+v"(s[0][0]), "+v"(s[0][1]));
     };
     // The same tie without the pause, for the main loop: there the barrier and the tile requests of
     // turn() already stand between the matrix instructions and the first use (the build's assembly
@@ -512,11 +515,11 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             }
         }
     };
-    // the rows' maxima over the tile in acc_s in the exp2 domain, x: its factor.  A row whose keys are all hidden holds -inf,
+    // the rows' maxima over a tile's scores in the exp2 domain, x: its factor.  A row whose keys are all hidden holds -inf,
     // and stays there: x > 0.
-    auto row_maximum = [&](auto QSI, float x) {
+    auto row_maximum = [&](auto QSI, const v16i (&s)[QS][2], float x) {
         constexpr int qs = IDX(QSI);
-        auto val = [&](int f) { return acc_s[qs][f >> 4][f & 15]; };
+        auto val = [&](int f) { return s[qs][f >> 4][f & 15]; };
         int m = val(0);
 #pragma unroll
         for (int f = 1; f + 1 < 32; f += 2) m = imax3(m, val(f), val(f + 1));
@@ -548,7 +551,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // from restructuring the loop nest, which made it spill registers.
     unsigned opaque = 0;
     // scores of tile jt from K^ in memory (its LDS buffer is another tile's by now)
-    auto score_again = [&](int jt) __attribute__((always_inline)) {
+    auto score_again = [&](int jt, v16i (&s_)[QS][2]) __attribute__((always_inline)) {
         const int kv0 = jt * KTILE;
         static_for<2>([&](auto S) {
             constexpr int s = IDX(S);
@@ -559,31 +562,34 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 const v4i a = *(const v4i*)(row + ks * 32);
                 static_for<QS>([&](auto QSI) {
                     constexpr int qs = IDX(QSI);
-                    if constexpr (ks == 0) qk_mfma_first(acc_s[qs][s], a, qreg[qs][ks], magic);
-                    else qk_mfma_next(acc_s[qs][s], a, qreg[qs][ks]);
+                    if constexpr (ks == 0) qk_mfma_first(s_[qs][s], a, qreg[qs][ks], magic);
+                    else qk_mfma_next(s_[qs][s], a, qreg[qs][ks]);
                 });
             });
         });
-        score_fence();
+        score_fence(s_);
         if (need_mask(kv0)) {
 #pragma unroll
             for (int qs = 0; qs < QS; ++qs)
 #pragma unroll
-                for (int s = 0; s < 2; ++s) mask_half(acc_s[qs][s], qs, s, kv0);
+                for (int s = 0; s < 2; ++s) mask_half(s_[qs][s], qs, s, kv0);
         }
     };
     // redo_tile (rare): raises the running maximum to what tile j - 1 holds, rounds it to the grids of that tile and of tile j,
-    // rescales O and l, and makes the weights of tile j - 1 again.  Its scores are gone and are computed a second time, then
-    // those of tile j: nothing has to be kept, and the loop needs no registers for this path.
+    // rescales O and l, and makes the weights of tile j - 1 again.  Its scores are gone and are computed a second time; at D =
+    // 64, where the registers of the scores are all there are, those of tile j after them.
+    constexpr bool SPARE = D == 128;
     auto redo_tile = [&](int j) __attribute__((always_inline)) {
+        v16i spare[QS][2];
+        v16i (&s_)[QS][2] = SPARE ? spare : acc_s;
         const int kv0 = (j - 1) * KTILE;
         const float dk = ksc_bh[kv0 >> shift_k];
-        score_again(j - 1);
+        score_again(j - 1, s_);
         float top[QS], scp[QS];
         static_for<QS>([&](auto QSI) {
             constexpr int qs = IDX(QSI);
             scp[qs] = tile_scale(qs, dk);
-            top[qs] = row_maximum(QSI, scp[qs]);
+            top[qs] = row_maximum(QSI, s_, scp[qs]);
         });
         int apart;
         asm volatile("s_mov_b32 %0, 0" : "=s"(apart));
@@ -613,7 +619,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             for (int i = 0; i < 8; ++i) {
                 float p[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(as_f32(acc_s[qs][i >> 2][4 * (i & 3) + e]), scp[qs], -b));
+                for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(as_f32(s_[qs][i >> 2][4 * (i & 3) + e]), scp[qs], -b));
                 pk[qs][i >> 2][(i >> 1) & 1][2 * (i & 1)] = pack2(p[0], p[1]);
                 pk[qs][i >> 2][(i >> 1) & 1][2 * (i & 1) + 1] = pack2(p[2], p[3]);
             }
@@ -622,7 +628,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             for (int i = 0; i < 3; ++i) l_mfma_next(acc_l[qs], sel, pk[qs][i >> 1][i & 1]);
             l_mfma_last(acc_l[qs], sel, pk[qs][1][1]);
         });
-        score_again(j);
+        if constexpr (!SPARE) score_again(j, acc_s);
         set_bias();
         asm volatile("s_nop 1");
     };
@@ -868,7 +874,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 static_for<DT>([&](auto P) { partial_max(QSI, P, 0); });
                 m_run[qs] = pair32_max(pmax[qs]) * sc[qs];          // -inf stays -inf: sc > 0
             } else {
-                m_run[qs] = on_grid(row_maximum(QSI, sc[qs]), qs);
+                m_run[qs] = on_grid(row_maximum(QSI, acc_s, sc[qs]) + FIRST_ROOM, qs);
             }
         });
         set_bias();
@@ -890,7 +896,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 
     auto dump_tile = [&](int j) {
         const int kv0 = j * KTILE;
-        score_fence();
+        score_fence(acc_s);
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             const int q_row = qrow0 + 32 * qs + ql;
@@ -1035,7 +1041,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // A wavefront with one tile has scores of a tile that it does not visit (first_tile()), which are never read: keep their
     // registers untouched until the matrix instructions have written them (the compiler would hand them out as temporaries
     // at once).
-    score_fence();
+    score_fence(acc_s);
     turn(j, j & 1);
     if constexpr (!KTOK) {
 #pragma unroll
