@@ -138,8 +138,11 @@ def build_library(verbose: bool = False, extra=()) -> str:
 
 # The attention kernels that are built: the score dump for head dimension {64, 128} x {4, 8 wavefronts}; {causal, full} x
 # {per-block, per-token key scales} for D = 64 with 4 wavefronts and D = 128 with 4 and 8; the two measurement builds (D =
-# 128, 8 wavefronts, causal / full, with the clock counters).
+# 128, 8 wavefronts, causal / full, with the clock counters).  Beside them TWO_SET_KERNELS: {causal, full} x {per-block,
+# per-token} for D = 64 with two sets of 4 wavefronts, known by their last template argument.
 ATTENTION_KERNELS = 4 + 4 * 3 + 2
+TWO_SET_KERNELS = 4
+TWO_SETS = "ELi1ELi2EEEv"
 
 
 def _registers(operand: str, file: str) -> set:
@@ -224,8 +227,9 @@ def check_attention_asm(text: str) -> list:
     kernels = re.findall(r"^(_ZN4sage16sage_attn_kernel\w+):.*?^\.Lfunc_end\d+:", text, re.S | re.M)
     bodies = re.findall(r"^_ZN4sage16sage_attn_kernel\w+:.*?^\.Lfunc_end\d+:", text, re.S | re.M)
     problems = []
-    if len(bodies) != ATTENTION_KERNELS:
-        problems.append(f"expected {ATTENTION_KERNELS} attention kernels in the assembly, found {len(bodies)}")
+    one_set = sum(TWO_SETS not in name for name in kernels)
+    if one_set != ATTENTION_KERNELS:
+        problems.append(f"expected {ATTENTION_KERNELS} attention kernels in the assembly, found {one_set}")
 
     for name, body in zip(kernels, bodies):
         # AGPRs that matrix instructions name (accumulators, resident operands).  The compiler may
@@ -295,6 +299,13 @@ def check_attention_registers(text: str) -> list:
     if len(used) != 4:
         problems.append(f"expected the register counts of 4 attention kernels with D = 64, found {len(used)}")
     return problems
+
+
+def check_two_sets(text: str) -> list:
+    """All attention kernels with two sets of wavefronts are in the text that check_attention_asm() looks through."""
+    import re
+    found = sum(TWO_SETS in name for name in re.findall(r"^(_ZN4sage16sage_attn_kernel\w+):", text, re.M))
+    return [] if found == TWO_SET_KERNELS else [f"expected {TWO_SET_KERNELS} attention kernels with two sets of wavefronts, found {found}"]
 
 
 def check_loads_asm(text: str, kernel: str, expected: int) -> list:
@@ -373,7 +384,7 @@ def verify_attention_isa(extra=()) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     problems = []
     with tempfile.TemporaryDirectory() as tmp:
-        for src, check in (("sage_attn.hip", lambda s: check_attention_asm(s) + check_attention_registers(s)), ("sage_attn_pv8.hip", check_pv8_asm),
+        for src, check in (("sage_attn.hip", lambda s: check_attention_asm(s) + check_attention_registers(s) + check_two_sets(s)), ("sage_attn_pv8.hip", check_pv8_asm),
                            ("sage_prepass.hip", check_no_spills), ("sage_prepass_v.hip", check_no_spills),
                            ("sage_short.hip", check_short_asm), ("sage_short.hip", check_short_pair_asm), ("sage_decode.hip", check_decode_asm)):
             out = os.path.join(tmp, src + ".s")

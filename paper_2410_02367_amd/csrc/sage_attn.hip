@@ -3,7 +3,8 @@
 // Work decomposition
 //   One workgroup = 8 wavefronts (two per SIMD, 256 registers each) = 256 query rows, 32 per
 //   wavefront; for D = 64, for short sequences and for small problems 4 wavefronts = 128 rows,
-//   two or three workgroups per CU.
+//   two or three workgroups per CU.  Launches that leave CUs empty at D = 64: two sets of 4 wavefronts
+//   on the same 128 rows (HALVES).
 //   Key/value tiles of 64 tokens are double-buffered in LDS and shared by all wavefronts of the
 //   workgroup; they are brought in by asynchronous, range-checked buffer loads that write LDS
 //   directly and bypass the register file.
@@ -96,7 +97,7 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
-// Shape of a workgroup: NW wavefronts (a template parameter of the kernel, 8 or 4) of WROWS rows.
+// Shape of a workgroup: NW wavefronts (a template parameter of the kernel, 8 or 4) of WROWS rows, in one set or two.
 //   8 wavefronts, one workgroup per CU  -- two wavefronts per SIMD share one set of LDS tiles;
 //   4 wavefronts, two or three workgroups per CU -- chosen by the launcher for D = 64, for short
 //                                          sequences and whenever the larger tile would leave CUs
@@ -208,7 +209,12 @@ template <class T> __device__ __forceinline__ void pin_a(T& x) { asm volatile(""
 // CLOCKS (measurement build of the same kernel): every wavefront also leaves the shader-clock and
 // constant-rate (100 MHz) counter ticks it ran for, how often it raised a running maximum and how
 // many key tiles it visited -- from which the clock the chip held and the clocks per tile follow.
-template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false, int QS = 1>
+//
+// HALVES = 2: launches of at most one 128-row workgroup per CU (two_halves() in sage_shape.h), where a wavefront that has its
+// SIMD to itself shows every latency of its chain.  The 8 wavefronts are two sets of 4 on the same rows, each with half of
+// the keys, tiles of its own in LDS and its own m, l and O; the second set's are added to the first's through LDS at the end,
+// in fp32.  What a set does is what a workgroup of a split launch does with its chunk.
+template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false, int QS = 1, int HALVES = 1>
 // Workgroups of 4 wavefronts per CU that the register budget is cut for: 2.  At D = 64 the compiler stays within
 // the 168 registers of three on its own (152, with one scale per key 164), which is 4 % faster than two; the build checks it.
 __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1)
@@ -219,9 +225,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  int Nq, int Nkv, int shift_q, int shift_k, int tiles_q, int per_xcd, long total_tiles,
                  int BH, int n_splits, int chunk, CausalOrder order,
                  const _Float16* __restrict__ qf, float sm_scale) {
-    constexpr int NWAVES = NW, NTHREADS = NW * 64;
+    constexpr int RW = NW / HALVES, NTHREADS = RW * 64;         // wavefronts and threads of a set
     constexpr int WROWS = 32 * QS;      // query rows per wavefront, in 32-row sub-tiles
-    constexpr int QTILE = NW * WROWS;   // query rows per workgroup
+    constexpr int QTILE = RW * WROWS;   // query rows per workgroup
     constexpr int KROW = D;             // bytes per K^ row in LDS
     constexpr int VROW = 2 * D;         // bytes per V row in LDS
     constexpr int KB = KTILE * KROW;    // bytes per K^ tile
@@ -235,7 +241,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     constexpr int KCH = KROW / 16, VCH = VROW / 16;             // chunks per row
     static_assert(!(KTOK && DUMP), "the score dump has no scales");
     constexpr int KSL = KTOK ? 2 * 2 * KTILE * 4 : 0;           // per-key (a, b) factors, two tiles
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * KB + 2 * VB + KSL + NW * 4];      // NW floats: QueryRows
+    constexpr int AREA = 2 * KB + 2 * VB + KSL + RW * 4;        // a set's tiles and RW floats for QueryRows
+    constexpr int SET = HALVES == 1 ? AREA : (AREA + 1023) / 1024 * 1024;
+    static_assert(HALVES == 1 || (!DUMP && !CLOCKS && QS == 1 && HALVES * SET >= RW * 64 * (16 * (D / 32) + 2) * 4), "room for the second set's results");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[HALVES * SET];
 
     // Workgroup -> (slab, query tile).  Consecutive workgroup ids land on the 8 XCDs in turn; give
     // each XCD a contiguous range of the slab-major order so that the workgroups resident on one XCD share
@@ -255,8 +264,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     unsigned long long clock_t0 = 0, clock_r0 = 0;
     int n_raised = 0;
     if constexpr (CLOCKS) { clock_t0 = __builtin_readcyclecounter(); clock_r0 = wall_clock64(); }
-    const int t = threadIdx.x, lane = t & 63;
+    const int t = HALVES == 1 ? threadIdx.x : threadIdx.x & (NTHREADS - 1), lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);     // wave-uniform: keeps control flow scalar
+    const int half = HALVES == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS);
+    const int area = half * SET;                     // the set's part of the LDS
     const int ql = lane & 31, g = lane >> 5;
     const int qrow0 = qt * QTILE + wave * WROWS;     // first row of the wavefront; sub-tile qs starts 32*qs later
     // Nq query rows against N keys per slab (the paper's setting is Nq = N).  With a causal mask the
@@ -266,8 +277,25 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // partial result: its own normalized O and, per row, log2 of its softmax denominator in absolute
     // terms (lse), from which the partial results of a row are merged.  N is the chunk's key count
     // from here on; one chunk is the whole slab.
-    const int k0 = split * chunk;
-    const int N = split == n_splits - 1 ? Nkv - k0 : chunk;
+    int k0 = split * chunk;
+    int N = split == n_splits - 1 ? Nkv - k0 : chunk;
+    // HALVES == 2 (one chunk): the second set starts at `cut`, the middle of the workgroup's key tiles on a boundary of the key
+    // scales' blocks.  Every row of the workgroup has to see a key of either set; where one does not, both walk all keys (in
+    // the time that one would need) and the second set's result is not used.
+    bool alone = false;
+    int T_other = 0;                    // the other set's key tiles
+    if constexpr (HALVES == 2) {
+        const int first = CAUSAL ? qt * QTILE + Nkv - Nq : Nkv - 1;          // last key that every row sees
+        const int end = CAUSAL && first + QTILE < Nkv ? first + QTILE : Nkv;
+        const int unit_k = shift_k > 6 ? 1 << shift_k : KTILE;
+        const int cut = ((end + 1) / 2 + unit_k - 1) / unit_k * unit_k;
+        alone = cut > first;
+        if (!alone) {
+            T_other = half == 0 ? (end - cut + KTILE - 1) / KTILE : cut / KTILE;
+            k0 = half * cut;
+            N = half == 0 ? cut : Nkv - cut;
+        }
+    }
     const size_t slab = (size_t)bh * Nkv + k0, slab_q = (size_t)bh * Nq;
     const size_t slab_o = ((size_t)split * BH + bh) * Nq;
     const int coff = Nkv - Nq - k0;
@@ -329,7 +357,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     }
     const v4i k_rsrc = buffer_descriptor(ki + slab * D, (unsigned)N * D);
     const v4i v_rsrc = buffer_descriptor(vg + slab * D, (unsigned)N * 2 * D);
-    const unsigned lds_base = (unsigned)(size_t)LDS_PTR(unsigned char, lds);     // LDS byte address of the tile area
+    const unsigned lds_base = (unsigned)(size_t)LDS_PTR(unsigned char, lds) + area;     // LDS byte address of the tile area
     auto load_k = [&](int j, int buf) {
         const v4i rsrc = tile_descriptor(k_rsrc, (unsigned)j * (KTILE * D));
 #pragma unroll
@@ -357,7 +385,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // K^ operand: row ql (+32 per sub-tile), chunk 2*ks+g, swizzled
     int k_off[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_off[ks] = ql * KROW + (((2 * ks + g) ^ k_swz<D>(ql)) << 4);
+    for (int ks = 0; ks < KS; ++ks) k_off[ks] = area + ql * KROW + (((2 * ks + g) ^ k_swz<D>(ql)) << 4);
     // V^T operand through the transposing read: source lane li of a 16-lane group addresses key
     // (li/4) and the 4-channel chunk (li%4) of the group's 16 channels
     const int grp = lane >> 4, li = lane & 15;
@@ -366,7 +394,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
         int chunk = (4 * dt + 2 * (grp & 1) + ((li & 3) >> 1)) ^ v_swz<D>(v_row);
-        v_off[dt] = v_row * VROW + chunk * 16 + (li & 1) * 8;
+        v_off[dt] = area + v_row * VROW + chunk * 16 + (li & 1) * 8;
     }
 
     v16i acc_s[QS][2];       // S^T of the current tile, two 32-key halves per sub-tile (raw int32 + seed)
@@ -387,7 +415,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // KTOK: wavefront 0 carries the scale of key (tile j, lane) from the load in slot j-1 to the
     // LDS write before barrier j.
     float dk_tok = 0.0f;
-    float* const ksl = (float*)(lds + 2 * KB + 2 * VB);          // [tile parity][a | b][key]
+    float* const ksl = (float*)(lds + area + 2 * KB + 2 * VB);          // [tile parity][a | b][key]
     auto request_key_scales = [&](int j) {
         if constexpr (KTOK) {
             if (wave == 0) {
@@ -917,7 +945,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int i = 0; i < VL; ++i)
-                if (NTHREADS * i + wave * 64 < VVEC) *(v4i*)(lds + 2 * KB + b * VB + (t + NTHREADS * i) * 16) = (v4i){0, 0, 0, 0};
+                if (NTHREADS * i + wave * 64 < VVEC) *(v4i*)(lds + area + 2 * KB + b * VB + (t + NTHREADS * i) * 16) = (v4i){0, 0, 0, 0};
     }
     // fp16 queries are requested before the tiles: their way from memory (2400 .. 3900 clocks) and their quantization are the
     // longest chain of the prologue.
@@ -943,7 +971,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // little power, where a real row in the place of each cost a launch of few rows 2-4 % (420 slabs of 33 rows, 1436 keys,
     // D = 64: 26.8 / 27.8 us).
     if (!DUMP && QS == 1 && qf != nullptr) {
-        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + 2 * KB + 2 * VB + KSL));
+        const float amax = rows.block_amax(sm_scale, shift_q, wave, (float*)(lds + area + 2 * KB + 2 * VB + KSL));
         const float rcp = amax > 0.0f && qrow0 + ql < Nq ? 127.0f / amax : 0.0f;
         dq[0] = amax / 127.0f * LOG2E;
         rows.codes(sm_scale, rcp, [&](int ks, int i, unsigned w) { qreg[0][ks][i] = (int)w; });
@@ -1056,6 +1084,34 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     }
     // ... and the wavefront keeps feeding the workgroup's tile pipeline until all are done.
     for (++j; j <= T; ++j) turn(j, j & 1);
+    if constexpr (HALVES == 2) {
+        for (; j <= T_other; ++j) __syncthreads();
+        __syncthreads();                             // nobody reads the tiles any more
+        if constexpr (KTOK) refresh(acc_l[0]);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) refresh(acc_o[0][dt]);
+        // the second set's results: [register][row of the set], so that a wavefront's words lie side by side
+        float* const other = (float*)lds + t;
+        if (half == 1) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) other[(16 * dt + r) * NTHREADS] = acc_o[0][dt][r];
+            other[16 * DT * NTHREADS] = m_run[0];
+            other[(16 * DT + 1) * NTHREADS] = (lane & 16) ? acc_l[0][1] : acc_l[0][0];
+        }
+        __syncthreads();
+        if (half == 1) return;
+        if (!alone) {
+            const float m1 = other[16 * DT * NTHREADS], top = __builtin_fmaxf(m_run[0], m1);
+            const float f0 = __builtin_amdgcn_exp2f(m_run[0] - top), f1 = __builtin_amdgcn_exp2f(m1 - top);
+            acc_l[0] = acc_l[0] * f0 + other[(16 * DT + 1) * NTHREADS] * f1;       // (the register of the lane's own query is the one that counts)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[0][dt][r] = __builtin_fmaf(acc_o[0][dt][r], f0, other[(16 * dt + r) * NTHREADS] * f1);
+        }
+    }
 
     // ---- O = diag(l)^-1 O, fp16 store
 #pragma unroll
@@ -1106,12 +1162,12 @@ int causal_items_per_xcd(const CausalOrder& o, int tiles_q) {
     return o.full * o.group * tiles_q + most;
 }
 
-template <int D, int NW, int QS>
+template <int D, int NW, int QS, int HALVES = 1>
 static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* kscale,
                             const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                             int block_q, int block_k, const SplitPlan& sp, hipStream_t st,
                             unsigned long long* clocks = nullptr) {
-    constexpr int QTILE = NW * 32 * QS, NTHREADS = NW * 64;
+    constexpr int QTILE = NW / HALVES * 32 * QS, NTHREADS = NW * 64;
     const int tiles_q = (Nq + QTILE - 1) / QTILE;
     const long total = (long)BH * sp.n_splits * tiles_q;
     CausalOrder order = {0, 0, 0};
@@ -1126,7 +1182,7 @@ static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* ksc
     _Float16* op = (_Float16*)o;
     const bool ktok = block_k == 1;
 #define SAGE_ARGS q.i8, q.scale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, order, (const _Float16*)q.f16, q.sm_scale
-#define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT, false, QS><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
+#define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT, false, QS, HALVES><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
     if (clocks != nullptr) {
         // the measurement build exists for the headline shape only: D = 128, 256-row workgroups, block scales
         if constexpr (D == 128 && NW == 8) {
@@ -1138,9 +1194,11 @@ static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* ksc
             return hipErrorInvalidValue;
         }
     }
-    if (sdump) { SAGE_LAUNCH(false, true, false); return hipGetLastError(); }
+    if constexpr (HALVES == 1) {
+        if (sdump) { SAGE_LAUNCH(false, true, false); return hipGetLastError(); }
+    }
     // (D = 64 comes in 128-row workgroups only; the score dump is built in both shapes of either head dimension)
-    if constexpr (D == 64 && NW == 8) {
+    if constexpr (D == 64 && NW == 8 && HALVES == 1) {
         return hipErrorInvalidValue;
     } else {
         if (ktok) {
@@ -1164,6 +1222,10 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
     if (sdump && wg_rows != 0) small = wg_rows == 128;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only
+    if constexpr (D == 64) {
+        if (!sdump && two_halves(D, BH, Nq, N, causal != 0, sp.n_splits))
+            return launch_dn<64, 8, 1, 2>(q, kq, kscale, v, o, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
+    }
     if (small) return launch_dn<D, 4, 1>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);
     return launch_dn<D, 8, 1>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st, clocks);
 }

@@ -35,4 +35,14 @@ inline bool small_workgroups(int D, int BH, int Nq, int N, bool causal, int n_sp
     return (last <= 256 && rounds <= 6) || (units * large_tiles + 255) / 256 > rounds;
 }
 
+// Whether the 128-row workgroups of a launch are made of two sets of 4 wavefronts, each with half of the keys (HALVES in
+// sage_attn.hip): where a CU has one of them at most, and with it one wavefront per SIMD.  us for the calls of a whole pass
+// with one / two sets, D = 64: 1 slab of 20000 182 / 134, of 32000 causal 287 / 210, 2 of 8192 80.5 / 62.1, 8 of 4096 causal
+// 47.8 / 39.7, 12 of 2600 causal 45.7 / 37.4, 32 of 1024 causal 30.3 / 26.6, 60 of 512 22.7 / 20.8, 40 of 400 20.9 / 19.6, 10 of
+// 300 18.2 / 18.1.  Not with few keys under a mask, where the first tiles of rows have nothing to share: 85 of 384 21.1 / 23.7,
+// 64 of 512 22.8 / 21.6.  Not at D = 128, where the rule above counts on it that a row's bits do not depend on the shape.
+inline bool two_halves(int D, int BH, int Nq, int N, bool causal, int n_splits) {
+    return D == 64 && n_splits == 1 && N >= (causal ? 512 : 257) && (long)BH * ((Nq + 127) / 128) <= 256;
+}
+
 }  // namespace sage
