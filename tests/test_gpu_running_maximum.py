@@ -55,3 +55,21 @@ def test_scores_far_above_those_of_the_first_tile(kind, B, H, Nq, Nkv, D, causal
         one = lambda x: np.ascontiguousarray(x[b:b + 1, h:h + 1])
         ref = oracle.attn_l2_cross(one(qq), one(qs), one(kq), one(ks), one(v), causal, lq, lk, gran_q=bq, gran_k=bk)
         assert_output_close(one(out), ref, f"{kind}, head {b} {h}")
+
+
+@pytest.mark.parametrize("factor", [1e-9, 1e-4, 1e-2, 1.0])
+@pytest.mark.parametrize("causal", [False, True])
+def test_small_scores_redo_no_tile(factor, causal):
+    """A first tile counts as one raise; however small the scores, and with them the constant that their factor is folded
+    with, no other tile is redone, and the result is the oracle's."""
+    print(f"[case] key scales x {factor}, causal={causal}", flush=True)
+    w = si.custom("small", 1, 2, 1500, 128, causal, seed=si.BASE_SEED + 1500)
+    q, k, v = si.full(w)
+    k_i8, k_scale, _ = sage.sage_smooth_quant_k(to_dev(k), 64)
+    q_i8, q_scale = sage.sage_quant_q(to_dev(q), w.sm_scale, 128)
+    k_scale = k_scale * factor
+    o, clocks = sage.sage_attn_clock_debug(q_i8, q_scale, k_i8, k_scale, to_dev(v), causal=causal, block_q=128, block_k=64)
+    torch.cuda.synchronize()
+    assert int(clocks.cpu()[:, 2].max()) == 1
+    ref = oracle.attn_l2(q_i8.cpu().numpy(), q_scale.cpu().numpy(), k_i8.cpu().numpy(), k_scale.cpu().numpy(), v, causal, 128, 64)
+    assert_output_close(o.cpu().numpy(), ref, f"x {factor}")
