@@ -29,10 +29,10 @@
 //   buffers: a 16-key group of P~_{j-1} is consumed by its matrix instructions before the softmax
 //   overwrites it, and each half of S_{j+1} is produced after the softmax has consumed that half
 //   of S_j.
-//   No maximum is taken in the steady state.  Any m cancels in O / l, so a row keeps the maximum of its first tile until a
-//   weight 2^(S - m) leaves the range of FP16 (2^16), which shows in the tile's row sums as infinity or NaN.  They are looked
-//   at before the tile's P~V; such a tile (rare: its scores exceed all of the first tile by 11 in the exponent of e) is redone
-//   with its own maximum, from K^ in memory (redo_tile()).  FP16 is as precise at 2^15 as at 1, and weights far below
+//   No maximum is taken in the steady state.  Any m cancels in O / l, so a row keeps the maximum of its first tile, with room
+//   above it, until a weight 2^(S - m) leaves the range of FP16 (2^16), which shows in the tile's row sums as infinity or NaN.
+//   They are looked at before the tile's P~V; such a tile (rare: its scores exceed all of the first tile by 14 in the exponent
+//   of e) is redone with its own maximum, from K^ in memory (redo_tile()).  FP16 is as precise at 2^15 as at 1, and weights far below
 //   the first tile's were lost next to them either way.  The 16 three-way maxima and the comparison that this saves are 18 of
 //   106 VALU instructions of a step, and the softmax no longer waits for them: us of the call before / now, 60 slabs of 17776
 //   x 64 4280 / 4100, 128 of 4096 x 128 864 / 840, 32 of 16384 x 128, causal, 1652 / 1607, 96 of 1105 x 64 51.5 / 49.3.
