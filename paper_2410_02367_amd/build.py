@@ -142,7 +142,7 @@ def build_library(verbose: bool = False, extra=()) -> str:
 # per-token} for D = 64 with two sets of 4 wavefronts, known by their last template argument.
 ATTENTION_KERNELS = 4 + 4 * 3 + 2
 TWO_SET_KERNELS = 4
-TWO_SETS = "ELi1ELi2EEEv"
+TWO_SETS = "ELb0ELi2EEEv"
 
 
 def _registers(operand: str, file: str) -> set:

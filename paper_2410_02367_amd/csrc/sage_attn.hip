@@ -10,7 +10,7 @@
 //   directly and bypass the register file.
 //   Scores are computed TRANSPOSED, S^T = K^ Q^^T, with the 32x32x32 INT8 matrix instruction: each
 //   lane then owns one query column and 16 keys per 32-key sub-tile, so
-//     - the row maximum needs one cross-lane step (lane <-> lane+32), the row sum none (see l_mfma_first),
+//     - the row maximum needs one cross-lane step (lane <-> lane+32), the row sum none (see l_mfma),
 //     - the exponentiated scores are already in the register layout the FP16 32x32x16 instruction
 //       wants for its B operand (P~^T), and O^T = V^T P~^T accumulates with the rescale factor
 //       being a per-lane scalar.
@@ -24,31 +24,26 @@
 //   tile j (VALU) is spread between the matrix instructions of P~V of tile j-1 and K^Q^^T of tile
 //   j+1.  A step is a flat sequence of LDS operands, each feeding one matrix instruction per query
 //   sub-tile, with VALU work after every matrix instruction, fenced so the order survives:
-//        PV_{j-1}[ 0:16], [16:32], [32:48], [48:64], QK_{j+1}[ 0:32] | softmax_j, evenly    QK_{j+1}[32:64]
+//        slot A  PV_{j-1}[ 0:16] | row maximum of S_j   slot D  PV_{j-1}[48:64] | softmax_j[32:48]
+//        slot B  PV_{j-1}[16:32] | softmax_j[ 0:16]     slot E  QK_{j+1}[ 0:32] | softmax_j[48:64]
+//        slot C  PV_{j-1}[32:48] | softmax_j[16:32]     slot F  QK_{j+1}[32:64]
 //   (a softmax "chunk" = 2 scores: 2 FMA, 2 exp2, 1 pack).  S and P~ live in single register
 //   buffers: a 16-key group of P~_{j-1} is consumed by its matrix instructions before the softmax
 //   overwrites it, and each half of S_{j+1} is produced after the softmax has consumed that half
 //   of S_j.
-//   No maximum is taken in the steady state.  Any m cancels in O / l, so a row keeps the maximum of its first tile, with room
-//   above it, until a weight 2^(S - m) leaves the range of FP16 (2^16), which shows in the tile's row sums as infinity or NaN.
-//   They are looked at before the tile's P~V; such a tile (rare: its scores exceed all of the first tile by 14 in the exponent
-//   of e) is redone with its own maximum, from K^ in memory (redo_tile()).  FP16 is as precise at 2^15 as at 1, and weights far below
-//   the first tile's were lost next to them either way.  The 16 three-way maxima and the comparison that this saves are 18 of
-//   106 VALU instructions of a step, and the softmax no longer waits for them: us of the call before / now, 60 slabs of 17776
-//   x 64 4280 / 4100, 128 of 4096 x 128 864 / 840, 32 of 16384 x 128, causal, 1652 / 1607, 96 of 1105 x 64 51.5 / 49.3.
-//   (With one scale per key the maximum stays: see raise_maximum().)
+//   The running maximum is only raised when a row's tile maximum exceeds it by more than 2^8
+//   (P~ <= 256 fits FP16 comfortably); the rescale of O is then a rare branch between slots A and B.
 //   Inside a softmax slot the order is: matrix instruction, the LDS reads of the operand three
 //   instructions ahead, the chunk's VALU work.  Two steps share one loop body, so that the
-//   buffer parity is a constant and every LDS address is a register plus an immediate.  The first operands of a step are
-//   requested before the row sums are looked at: behind that branch their latency shows (32 slabs of 16384 x 128 1561 / 1547).
+//   buffer parity is a constant and every LDS address is a register plus an immediate.
 //
 // Register files
 //   The matrix instructions are written as inline assembly so that the register file of every
-//   operand is chosen by hand: O^T (QS*DT*16 registers), the resident Q^ operands
+//   operand is chosen by hand: O^T (QS*DT*16 registers), the row sums, the resident Q^ operands
 //   and the row-sum selector operand are pinned in the accumulator file (AGPRs) -- only matrix instructions
-//   touch them in the steady state, so there are no AGPR<->VGPR moves at all -- while scores, P~, row sums,
+//   touch them in the steady state, so there are no AGPR<->VGPR moves at all -- while scores, P~,
 //   LDS operands and staging data are ordinary variables in VGPRs.
-//   The O^T statements name their accumulator as an INPUT and update that register
+//   The O^T / row-sum statements name their accumulator as an INPUT and update that register
 //   behind the compiler's back: to the compiler the accumulators are loop-invariant values, which
 //   it keeps in one place; refresh() ("+a") tells it the truth before C++ code reads them (rare
 //   rescale, epilogue).  This only works while the compiler never copies such a value to a second
@@ -72,11 +67,12 @@
 //     12582912 + S^ (|S^| <= 127*127*128 < 2^22), so no int->float conversion is issued and the
 //     dequantization, the log2(e) factor and the subtraction of the running maximum are one FMA;
 //     that FMA rounds once only if what it subtracts, 12582912 * sc + m, is exact, which holds because sc
-//     carries 22 significant bits and m is kept on the grid of 12582912 * sc (see begin_tile() and on_grid());
-//   - where a maximum is taken, it is taken on the raw accumulators with integer max;
+//     carries 22 significant bits and m is kept on the grid of 12582912 * sc (see begin_tile(),
+//     finish_max(), raise_maximum());
+//   - the row maximum is taken on the raw accumulators with integer max;
 //   - P~ is packed to FP16 with the packed round-to-nearest-even convert; the row sum l comes from
 //     one 16x16x32 FP16 matrix instruction per 16 keys whose A operand selects, for every query, the
-//     contraction blocks that hold its keys (see l_mfma_first): l is exactly the sum of the FP16 P~ that
+//     contraction blocks that hold its keys (see l_mfma): l is exactly the sum of the FP16 P~ that
 //     multiplies V, and costs no VALU issue slot.  (Dot-product instructions such as v_dot2c run on the
 //     matrix pipe as well, but block it for VALU work -- measured.)
 #include "sage_internal.h"
@@ -102,19 +98,25 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 //   4 wavefronts, two or three workgroups per CU -- chosen by the launcher for D = 64, for short
 //                                          sequences and whenever the larger tile would leave CUs
 //                                          without work (see sage_shape.h).
-constexpr int KTILE = 64;                  // keys per LDS tile
+// QS = 2 (64 rows per wavefront, every LDS operand feeding two matrix instructions, one wavefront
+// per SIMD) is what the QS loops in the kernel are for; an earlier version measured it 2-3 % slower
+// than QS = 1, and the build and the tests cover QS = 1 only.
+#ifndef SAGE_QS
+#define SAGE_QS 1
+#endif
+// SAGE_SA: P~V groups issued ahead of the softmax, beside the row maximum (see "Schedule of a step"
+// in the kernel).  2 gives the maximum more matrix instructions to hide behind and packs the softmax
+// chunks denser afterwards; it measured equal at D = 128 and 1 % slower at D = 64.
+#ifndef SAGE_SA
+#define SAGE_SA 1
+#endif
+constexpr int QS = SAGE_QS;            // 32-row query sub-tiles per wavefront
+constexpr int WROWS = 32 * QS;         // query rows per wavefront
+constexpr int KTILE = 64;              // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int MAGIC_I = 0x4B400000;        // bit pattern of 12582912.0f = 1.5 * 2^23
 constexpr float MAGIC_F = 12582912.0f;
-// log2 of the room above the weights of the first tile and of one that is redone: the scores of a wavefront have to rise by so
-// much more before a tile is redone, which costs the workgroup about three steps (the others wait at its barrier).  The
-// largest weight of a row may then be 2^-4 or 2^-2, and what FP16 cannot hold are weights 2^-20 times as large.  More room is
-// felt where few keys carry a row: relative error against 64 bits of 2 slabs of 900 x 64 with some tokens 12 times as large,
-// 1e-5, 6.98 with HEADROOM 0, 6.97 with 2, 7.08 with 4, 7.94 with 6, 16.2 with 8 (7.20 with the maximum of every tile); with 2
-// and FIRST_ROOM 0 / 2 / 4: 6.97 / 7.06 / 7.03.  Scores with a standard deviation of 3.7 in the exponent of e (rotated keys
-// whose bias the smoothing leaves), 64 key tiles: 1.2 / 0.9 / 0.5 redone per wavefront with FIRST_ROOM 0 / 2 / 4.
-constexpr float FIRST_ROOM = 4.0f, HEADROOM = 2.0f;
-constexpr float MAX_SLACK = 8.0f;          // one scale per key: log2 of the largest P~ tolerated before the maximum is raised
+constexpr float MAX_SLACK = 8.0f;          // log2 of the largest P~ tolerated before the maximum is raised
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
 template <class F, int... I>
@@ -133,12 +135,13 @@ __device__ __forceinline__ float as_f32(int v) { return __builtin_bit_cast(float
 __device__ __forceinline__ int as_i32(float v) { return __builtin_bit_cast(int, v); }
 __device__ __forceinline__ int imax3(int a, int b, int c) { return max(max(a, b), c); }
 
-// Which softmax pipeline ticks run behind matrix instruction i of a step: instructions START .. MB - 1 share the NCH
-// chunk entries as evenly as they divide, the two after them take the two ticks that drain the three-stage chunk pipeline.
-template <int NCH, int MB, int START>
+// Which softmax pipeline ticks run behind matrix instruction i of a step's second part: the first
+// MB instructions share the NCH chunk entries as evenly as they divide, the two after them take
+// the two ticks that drain the three-stage chunk pipeline.
+template <int NCH, int MB>
 struct TickPlan {
-    static constexpr int first(int i) { return i < START ? 0 : i < MB ? (i - START) * NCH / (MB - START) : i - MB < 2 ? NCH + (i - MB) : NCH + 2; }
-    static constexpr int end(int i) { return first(i + 1); }
+    static constexpr int first(int i) { return i < MB ? i * NCH / MB : NCH + (i - MB); }
+    static constexpr int end(int i) { return i < MB ? (i + 1) * NCH / MB : (i - MB < 2 ? NCH + (i - MB) + 1 : NCH + (i - MB)); }
     static constexpr int slot_of(int n) { int i = 0; while (end(i) <= n) ++i; return i; }
 };
 
@@ -166,19 +169,9 @@ __device__ __forceinline__ void pv_mfma(const v16f& acc, const v8h& a, const v8h
 // lane's result registers 0 and 1 (rows 4 (l / 16) + 0, + 1 of column l % 16) are the row sums of the
 // queries l % 16 and 16 + l % 16, and the one that is the lane's own query is selected in the epilogue.
 // No VALU slot, no cross-lane step, 18 clocks of the matrix pipe in the stream of 32-clock
-// instructions (measured; two of the 4x4x4 instructions, which did this before, took 27).  acc = before + sums, of the first group of a
-// tile; the others add.
-// l_mfma_parked: the same with the sums in the accumulator file, in place as pv_mfma.
-__device__ __forceinline__ void l_mfma_first(v4f& acc, const v4i& sel, const v4i& b, const v4f& before) {
-    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %3" : "=&v"(acc) : "a"(sel), "v"(b), "v"(before));
-}
-__device__ __forceinline__ void l_mfma_next(v4f& acc, const v4i& sel, const v4i& b) {
-    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "a"(sel), "v"(b));
-}
-__device__ __forceinline__ void l_mfma_last(v4f& acc, const v4i& sel, const v4i& b) {      // and the wait for its result
-    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0\n\ts_nop 11" : "+v"(acc) : "a"(sel), "v"(b));
-}
-__device__ __forceinline__ void l_mfma_parked(const v4f& acc, const v4i& sel, const v4i& b) {
+// instructions (measured; two of the 4x4x4 instructions, which did this before, took 27).  acc += sums;
+// same in-place convention as pv_mfma.
+__device__ __forceinline__ void l_mfma(const v4f& acc, const v4i& sel, const v4i& b) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : : "a"(acc), "a"(sel), "v"(b));
 }
 // The descriptor of a slab moved forward to one of its tiles: base + tile bytes, size - tile bytes
@@ -214,10 +207,10 @@ template <class T> __device__ __forceinline__ void pin_a(T& x) { asm volatile(""
 // SIMD to itself shows every latency of its chain.  The 8 wavefronts are two sets of 4 on the same rows, each with half of
 // the keys, tiles of its own in LDS and its own m, l and O; the second set's are added to the first's through LDS at the end,
 // in fp32.  What a set does is what a workgroup of a split launch does with its chunk.
-template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false, int QS = 1, int HALVES = 1>
+template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false, int HALVES = 1>
 // Workgroups of 4 wavefronts per CU that the register budget is cut for: 2.  At D = 64 the compiler stays within
 // the 168 registers of three on its own (152, with one scale per key 164), which is 4 % faster than two; the build checks it.
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1)
+__global__ void __launch_bounds__(NW * 64, NW == 4 && SAGE_QS == 1 ? 2 : 1)
 sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const int8_t* __restrict__ ki, const float* __restrict__ ksc,
                  const _Float16* __restrict__ vg, _Float16* __restrict__ og,
@@ -226,7 +219,6 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  int BH, int n_splits, int chunk, CausalOrder order,
                  const _Float16* __restrict__ qf, float sm_scale) {
     constexpr int RW = NW / HALVES, NTHREADS = RW * 64;         // wavefronts and threads of a set
-    constexpr int WROWS = 32 * QS;      // query rows per wavefront, in 32-row sub-tiles
     constexpr int QTILE = RW * WROWS;   // query rows per workgroup
     constexpr int KROW = D;             // bytes per K^ row in LDS
     constexpr int VROW = 2 * D;         // bytes per V row in LDS
@@ -305,10 +297,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     v4i qreg[QS][KS];
     float dq[QS];
     v16f acc_o[QS][DT];      // O^T accumulators
-    // Row sums l, accumulated on the matrix pipe (see l_mfma_first): registers 0 and 1 hold the sums of the queries lane % 16 and
-    // 16 + lane % 16 over all keys so far.  before_l: without the last tile, whose weights may have left the range of FP16.
-    // With one scale per key the range cannot be left; the sums are parked in the accumulator file.
-    v4f acc_l[QS], before_l[QS];
+    // Row sums l, accumulated on the matrix pipe (see l_mfma): registers 0 and 1 hold the sums of the
+    // queries lane % 16 and 16 + lane % 16 over all keys so far.
+    v4f acc_l[QS];
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
 #pragma unroll
@@ -318,7 +309,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             pin_a(acc_o[qs][dt]);
         }
         acc_l[qs] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (KTOK) pin_a(acc_l[qs]);
+        pin_a(acc_l[qs]);
     }
     // selector operand of the row-sum instruction: FP16 ones in the contraction blocks of the row's parity
     const int sel_word = (((lane >> 4) ^ lane) & 1) ? 0 : 0x3C003C00;
@@ -399,13 +390,18 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 
     v16i acc_s[QS][2];       // S^T of the current tile, two 32-key halves per sub-tile (raw int32 + seed)
     v4i pk[QS][2][2];        // P~^T as FP16 pairs: [sub-tile][32-key half][16-key group]
-    float m_run[QS], sc[QS], bias[QS];
-    float pmax[QS];          // KTOK: partial maxima of the current tile's scores
+    float m_run[QS], sc[QS], bias[QS], m_cand[QS];
     bool off_grid[QS];       // the running maximum is not on the grid on which this tile's bias is exact
+    int pmax[QS][DT];        // partial integer row maxima of the current tile
+    float pmaxf[QS][DT];     // ... floating-point ones when every key has its own scale
+    // P~V groups (of DT matrix instructions) that a step issues before the softmax starts, i.e.
+    // while the row maximum is being taken
+    constexpr int SA = SAGE_SA;
+    constexpr int NA = SA * DT;
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
         m_run[qs] = -__builtin_inff();
-        sc[qs] = 0.0f; bias[qs] = 0.0f; off_grid[qs] = false;
+        sc[qs] = 0.0f; bias[qs] = 0.0f; m_cand[qs] = 0.0f; off_grid[qs] = false;
     }
     v16i magic;
 #pragma unroll
@@ -439,10 +435,10 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 
     // 12 wait states between the matrix instructions that wrote the scores and the first VALU or
     // memory instruction that touches them; the operands tie every later use to the fence.
-    auto score_fence = [](v16i (&s)[QS][2]) {
+    auto score_fence = [&]() {
         static_assert(QS == 1 || QS == 2, "the fence lists the score registers explicitly");
-        if constexpr (QS == 2) asm volatile("s_nop 11" : "+v"(s[0][0]), "+v"(s[0][1]), "+v"(s[QS - 1][0]), "+v"(s[QS - 1][1]));
-        else asm volatile("s_nop 11" : "+v"(s[0][0]), "+v"(s[0][1]));
+        if constexpr (QS == 2) asm volatile("s_nop 11" : "+v"(acc_s[0][0]), "+v"(acc_s[0][1]), "+v"(acc_s[QS - 1][0]), "+v"(acc_s[QS - 1][1]));
+        else asm volatile("s_nop 11" : "+v"(acc_s[0][0]), "+v"(acc_s[0][1]));
     };
     // The same tie without the pause, for the main loop: there the barrier and the tile requests of
     // turn() already stand between the matrix instructions and the first use (the build's assembly
@@ -467,7 +463,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             });
         });
     };
-    // O^T += V^T P~^T for the 16 keys of group (s, u) of the V tile in buffer vbuf
+    // O^T += V^T P~^T for the 16 keys of group (s, u) of the V tile in buffer vbuf, and their row sums
     auto pv_group = [&](int vbuf, auto S, auto U) {
         constexpr int s = IDX(S), u = IDX(U);
         const unsigned char* vb = lds + 2 * KB + vbuf * VB + (32 * s + 16 * u) * VROW;
@@ -481,37 +477,16 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 pv_mfma(acc_o[qs][dt], a, __builtin_bit_cast(v8h, pk[qs][s][u]));
             });
         });
+        static_for<QS>([&](auto QSI) {
+            constexpr int qs = IDX(QSI);
+            l_mfma(acc_l[qs], sel, pk[qs][s][u]);
+        });
     };
 
-    // hidden keys of tile kv0 / 64 (beyond N, or after the query when causal) get the bit pattern of -inf, which is below every
-    // real score as an integer and exponentiates to 0; s: 32-key half
-    auto mask_half = [&](v16i& acc, int qs, int s, int kv0) {
-        // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
-        int seen = N - kv0;
-        if (CAUSAL && seen > qrow0 + 32 * qs + ql + coff + 1 - kv0) seen = qrow0 + 32 * qs + ql + coff + 1 - kv0;
-        seen -= 4 * g;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 32 * s + 8 * (r >> 2) + (r & 3) < seen ? acc[r] : (int)0xFF800000;
-    };
-    auto need_mask = [&](int kv0) { return (kv0 + KTILE > N) || (CAUSAL && kv0 + KTILE - 1 > qrow0 + coff); };
-    // factor of the tile's scores for a key scale dk (KTOK: 1).  A zero scale (all-zero quantization block) would turn
-    // -inf * scale into NaN.  One scale per block: cut to 22 significant bits, see begin_tile().
-    auto tile_scale = [&](int qs, float dk) {
-        const float x = __builtin_fmaxf(dq[qs] * dk, 1e-30f);
-        return KTOK ? x : as_f32(as_i32(x) & ~3);          // KTOK: the 22 bits are the key's factor's
-    };
-    // A maximum rounded to the grid on which the bias of the tile with the largest factor of all is exact, and with it that of
-    // every other (but for sums that pass into the next binade, see begin_tile()).  With the grid of the tile at hand every 4th
-    // to 9th wavefront met a coarser one later, and redo_tile(): 128 slabs of 1536 x 128, causal, 105.0 / 101.6.  (A grid
-    // four times as coarse does without the largest factor, but the largest weight of a row is then further from 1, which FP16
-    // represents: 1 % more error.)
-    float dk_top = 0.0f;               // largest key scale
-    auto on_grid = [&](float m, int qs) {
-        const float x = tile_scale(qs, dk_top);
-        return KTOK ? m : __builtin_fmaf(-MAGIC_F, x, __builtin_fmaf(MAGIC_F, x, m));
-    };
-
-    // ---- begin_tile: what the softmax of the tile whose scores sit in acc_s (tile j) needs
+    // ---- running-maximum bookkeeping for the tile whose scores sit in acc_s (tile j)
+    // begin_tile: scale of the tile; on diagonal / tail tiles, hidden keys (beyond N, or after the
+    // query when causal) get the bit pattern of -inf, which is below every real score as an
+    // integer and exponentiates to 0.
     auto begin_tile = [&](int j) {
         const int kv0 = j * KTILE;
         score_tie();
@@ -521,185 +496,127 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             const int jn = j + 1 < kv_tiles_all ? j + 1 : j;
             dk_next = ksc_bh[(jn * KTILE) >> shift_k];
         }
-        const bool masked = need_mask(kv0);
+        const bool need_mask = (kv0 + KTILE > N) || (CAUSAL && kv0 + KTILE - 1 > qrow0 + coff);
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
-            sc[qs] = tile_scale(qs, dk);
-            // The exp2 argument is fma(seeded score, sc, -bias) with bias = 12582912 * sc + m: it equals S^ * sc - m rounded
-            // ONCE only if that bias is exact.  The product is exact since sc carries 22 significant bits; the sum is exact
-            // when m is a multiple of the product's ulp, which off_grid tells (then redo_tile() moves m to such a multiple).
+            // a zero scale (all-zero quantization block) would turn -inf * scale into NaN
+            sc[qs] = __builtin_fmaxf(dq[qs] * dk, 1e-30f);
+            if constexpr (!KTOK) {
+                // The exp2 argument is fma(seeded score, sc, -bias) with bias = 12582912 * sc + m:
+                // it equals S^ * sc - m rounded ONCE only if that bias is exact.  The product is
+                // exact once sc is cut to 22 significant bits (a relative change of 2^-22 in the
+                // scale); the sum is exact when m is a multiple of the product's ulp, which
+                // the check below detects and raise_maximum() establishes.
+                sc[qs] = as_f32(as_i32(sc[qs]) & ~3);
+            }
+            // Everything the steady state needs from the running maximum is prepared here, ahead
+            // of the matrix instructions of step_a, so that between the two parts of a step only
+            // one compare and one branch stand (a chain of dependent VALU instructions there stalls
+            // the in-order stream and, with it, the matrix pipe: measured 15 % of the kernel):
+            //   bias      for the softmax FMA, valid as long as the maximum is not raised -- the same
+            //             FMA applied to the own tile maximum tells whether it must be (must_raise());
+            //   off_grid  whether the running maximum is off the grid on which this tile's bias is
+            //             exact (then it is re-rounded in the rare path as well).
             if constexpr (KTOK) {
                 bias[qs] = m_run[qs];
+                off_grid[qs] = false;
             } else {
                 // 12582912 * sc is exact (22 bits), so both FMAs round their sum only: the first gives
-                // the bias, the second what the bias really subtracts besides the seed.  Where the maximum is the larger
-                // part of the sum the two differ by an ulp of it, as the softmax argument of a score far below it does by its
-                // own rounding: that is no reason to redo a tile (small scores had every tile redone: 32 slabs of 16384 x
-                // 128, keys 1e-9 times as large, 4.4 ms instead of 2.7).
+                // the bias, the second what the bias really subtracts besides the seed
                 const float sum = __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
                 bias[qs] = sum;
-                off_grid[qs] = __builtin_fabsf(__builtin_fmaf(-MAGIC_F, sc[qs], sum) - m_run[qs]) > __builtin_fmaf(__builtin_fabsf(m_run[qs]), 0x1p-22f, 0x1p-20f);
+                off_grid[qs] = __builtin_fmaf(-MAGIC_F, sc[qs], sum) != m_run[qs];
             }
-            if (masked) {
+            if (need_mask) {
+                // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
+                int seen = N - kv0;
+                if (CAUSAL && seen > qrow0 + 32 * qs + ql + coff + 1 - kv0) seen = qrow0 + 32 * qs + ql + coff + 1 - kv0;
+                seen -= 4 * g;
 #pragma unroll
-                for (int s = 0; s < 2; ++s) mask_half(acc_s[qs][s], qs, s, kv0);
-            }
-        }
-    };
-    // the rows' maxima over a tile's scores in the exp2 domain, x: its factor.  A row whose keys are all hidden holds -inf,
-    // and stays there: x > 0.
-    auto row_maximum = [&](auto QSI, const v16i (&s)[QS][2], float x) {
-        constexpr int qs = IDX(QSI);
-        auto val = [&](int f) { return s[qs][f >> 4][f & 15]; };
-        int m = val(0);
+                for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int f = 1; f + 1 < 32; f += 2) m = imax3(m, val(f), val(f + 1));
-        m = max(m, val(31));
-        auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-        return (as_f32(max((int)r[0], (int)r[1])) - MAGIC_F) * x;      // signed: the hidden pattern is negative
-    };
-    // must_redo: has a weight of the previous tile left the range of FP16 (its row sum is then infinite, or NaN in the
-    // rows of the matrix instruction's result where it meets a zero of the selector), or is this tile's bias inexact?
-    auto must_redo = [&]() -> bool {
-        bool want = false;
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) want = want || off_grid[qs] || !(acc_l[qs][0] + acc_l[qs][1] < __builtin_inff());
-        return __builtin_amdgcn_ballot_w64(want) != 0ull;
-    };
-    auto set_bias = [&]() {
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs)       // exp2 argument = acc*sc - bias
-            bias[qs] = KTOK ? m_run[qs] : __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
-    };
-    // Two weights of a tile as a packed pair, rounded to FP16 with round-to-nearest-even as Algorithm 1 has it.
-    auto pack2 = [](float a, float b) {
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        const f2 pp = {a, b};
-        return __builtin_bit_cast(int, __builtin_convertvector(pp, h2));
-    };
-    // The empty assembly statements on it carry a value around the loops that the compiler cannot see through; they keep it
-    // from restructuring the loop nest, which made it spill registers.
-    unsigned opaque = 0;
-    // scores of tile jt from K^ in memory (its LDS buffer is another tile's by now)
-    auto score_again = [&](int jt, v16i (&s_)[QS][2]) __attribute__((always_inline)) {
-        const int kv0 = jt * KTILE;
-        static_for<2>([&](auto S) {
-            constexpr int s = IDX(S);
-            const int key = kv0 + 32 * s + ql;
-            const int8_t* row = ki + (slab + (key < N ? key : N - 1)) * D + g * 16;
-            static_for<KS>([&](auto KSI) {
-                constexpr int ks = IDX(KSI);
-                const v4i a = *(const v4i*)(row + ks * 32);
-                static_for<QS>([&](auto QSI) {
-                    constexpr int qs = IDX(QSI);
-                    if constexpr (ks == 0) qk_mfma_first(s_[qs][s], a, qreg[qs][ks], magic);
-                    else qk_mfma_next(s_[qs][s], a, qreg[qs][ks]);
-                });
-            });
-        });
-        score_fence(s_);
-        if (need_mask(kv0)) {
-#pragma unroll
-            for (int qs = 0; qs < QS; ++qs)
-#pragma unroll
-                for (int s = 0; s < 2; ++s) mask_half(s_[qs][s], qs, s, kv0);
-        }
-    };
-    // redo_tile (rare): raises the running maximum to what tile j - 1 holds, rounds it to the grids of that tile and of tile j,
-    // rescales O and l, and makes the weights of tile j - 1 again.  Its scores are gone and are computed a second time; at D =
-    // 64, where the registers of the scores are all there are, those of tile j after them.
-    constexpr bool SPARE = D == 128;
-    auto redo_tile = [&](int j) __attribute__((always_inline)) {
-        v16i spare[QS][2];
-        v16i (&s_)[QS][2] = SPARE ? spare : acc_s;
-        const int kv0 = (j - 1) * KTILE;
-        const float dk = ksc_bh[kv0 >> shift_k];
-        score_again(j - 1, s_);
-        float top[QS], scp[QS];
-        static_for<QS>([&](auto QSI) {
-            constexpr int qs = IDX(QSI);
-            scp[qs] = tile_scale(qs, dk);
-            top[qs] = row_maximum(QSI, s_, scp[qs]);
-        });
-        int apart;
-        asm volatile("s_mov_b32 %0, 0" : "=s"(apart));
-        if (apart == 0) {                // always: a block of its own, away from the matrix instructions
-#pragma unroll
-            for (int qs = 0; qs < QS; ++qs) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) refresh(acc_o[qs][dt]);
-                float m_new = on_grid(__builtin_fmaxf(m_run[qs], top[qs] + HEADROOM), qs);
-                // (where the bias of tile j passes into the next binade, its own grid)
-                m_new = __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_new));
-                const float alpha = __builtin_amdgcn_exp2f(m_run[qs] - m_new);
-                m_run[qs] = m_new;
-                acc_l[qs] = before_l[qs] * alpha;        // the register of the lane's own query is the one that counts
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc_o[qs][dt][r] *= alpha;
-                    pin_a(acc_o[qs][dt]);
-                }
+                    for (int r = 0; r < 16; ++r)
+                        acc_s[qs][s][r] = 32 * s + 8 * (r >> 2) + (r & 3) < seen ? acc_s[qs][s][r] : (int)0xFF800000;
             }
         }
-        static_for<QS>([&](auto QSI) {
-            constexpr int qs = IDX(QSI);
-            const float b = __builtin_fmaf(MAGIC_F, scp[qs], m_run[qs]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float p[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(as_f32(s_[qs][i >> 2][4 * (i & 3) + e]), scp[qs], -b));
-                pk[qs][i >> 2][(i >> 1) & 1][2 * (i & 1)] = pack2(p[0], p[1]);
-                pk[qs][i >> 2][(i >> 1) & 1][2 * (i & 1) + 1] = pack2(p[2], p[3]);
-            }
-            asm volatile("s_nop 1" : "+v"(pk[qs][0][0]), "+v"(pk[qs][0][1]), "+v"(pk[qs][1][0]), "+v"(pk[qs][1][1]));
-#pragma unroll
-            for (int i = 0; i < 3; ++i) l_mfma_next(acc_l[qs], sel, pk[qs][i >> 1][i & 1]);
-            l_mfma_last(acc_l[qs], sel, pk[qs][1][1]);
-        });
-        if constexpr (!SPARE) score_again(j, acc_s);
-        set_bias();
-        asm volatile("s_nop 1");
     };
-
-    // ---- one scale per key: the maximum of a tile is taken before its softmax, and raised when it exceeds the running one by
-    // more than 2^8.  (Without, as above, the kernel does not fit its registers: the second pass over a tile would need the
-    // factors of its keys as well.)
-    // partial_max(qs, p, par): the scores of part p (of DT) replaced by t = S^ * delta_K[key], and their maximum; issued
-    // between the step's first matrix instructions.
+    // partial_max(qs, p): integer maximum over part p (of DT) of sub-tile qs's 32 scores per lane;
+    // issued between the matrix instructions of the step's first slot.
     auto partial_max = [&](auto QSI, auto P, int par) {
         constexpr int qs = IDX(QSI), p = IDX(P);
-        constexpr int CNT = 32 / DT, FIRST = p * CNT;              // flat index = 16*s + r
-        // registers 4*q4 .. +3 of sub-tile s are keys 32*s + 8*q4 + 4*g .. +3: one 16-byte read each of a and b
-        const float* kf = ksl + par * 2 * KTILE + 4 * g;
-        float mf = p == 0 ? -__builtin_inff() : pmax[qs];          // the maximum is carried from part to part
+        constexpr int CNT = 32 / NA, FIRST = p * CNT;              // flat index = 16*s + r
+        static_assert(CNT % 4 == 0, "whole groups of four registers per part");
+        if constexpr (KTOK) {
+            // registers 4*q4 .. +3 of sub-tile s are keys 32*s + 8*q4 + 4*g .. +3: one 16-byte
+            // read each of a and b; the scores are replaced by t = S^ * delta_K[key]
+            const float* kf = ksl + par * 2 * KTILE + 4 * g;
+            float mf = p == 0 ? -__builtin_inff() : pmaxf[qs][0];       // the maximum is carried from part to part
 #pragma unroll
-        for (int f = FIRST; f < FIRST + CNT; f += 4) {
-            const int s_ = f >> 4, r = f & 15;
-            const v4f a = *(const v4f*)(kf + 32 * s_ + 2 * r), b = *(const v4f*)(kf + KTILE + 32 * s_ + 2 * r);
-            float tv[4];
+            for (int f = FIRST; f < FIRST + CNT; f += 4) {
+                const int s_ = f >> 4, r = f & 15;
+                const v4f a = *(const v4f*)(kf + 32 * s_ + 2 * r), b = *(const v4f*)(kf + KTILE + 32 * s_ + 2 * r);
+                float tv[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                tv[e] = __builtin_fmaf(as_f32(acc_s[qs][s_][r + e]), a[e], b[e]);
-                acc_s[qs][s_][r + e] = as_i32(tv[e]);
+                for (int e = 0; e < 4; ++e) {
+                    tv[e] = __builtin_fmaf(as_f32(acc_s[qs][s_][r + e]), a[e], b[e]);
+                    acc_s[qs][s_][r + e] = as_i32(tv[e]);
+                }
+                mf = __builtin_fmaxf(__builtin_fmaxf(mf, tv[0]), tv[1]);
+                mf = __builtin_fmaxf(__builtin_fmaxf(mf, tv[2]), tv[3]);
             }
-            mf = __builtin_fmaxf(__builtin_fmaxf(mf, tv[0]), tv[1]);
-            mf = __builtin_fmaxf(__builtin_fmaxf(mf, tv[2]), tv[3]);
+            pmaxf[qs][0] = mf;
+            return;
         }
-        pmax[qs] = mf;
+        // the maximum is carried from part to part: CNT new values and the carry are CNT/2
+        // three-way maxima (the first part, without a carry, ends on a two-way one)
+        auto val = [&](int f) { return acc_s[qs][f >> 4][f & 15]; };
+        if constexpr (p == 0) {
+            int mi = val(FIRST);
+#pragma unroll
+            for (int f = FIRST + 1; f + 1 < FIRST + CNT; f += 2) mi = imax3(mi, val(f), val(f + 1));
+            pmax[qs][0] = max(mi, val(FIRST + CNT - 1));
+        } else {
+            int mi = pmax[qs][0];
+#pragma unroll
+            for (int f = FIRST; f < FIRST + CNT; f += 2) mi = imax3(mi, val(f), val(f + 1));
+            pmax[qs][0] = mi;
+        }
     };
-    // A lane looks at the maximum over its own 32 keys only; the query's other 32 keys are with the lane 32 away, which takes
-    // part in the same vote.
+    // must_raise: does some row of the wavefront need a higher running maximum?  A lane looks at
+    // the maximum over its own 32 keys only; the query's other 32 keys are with the lane 32 away,
+    // which takes part in the same vote.
     auto must_raise = [&]() -> bool {
         bool want = false;
 #pragma unroll
-        for (int qs = 0; qs < QS; ++qs) want = want || __builtin_fmaf(pmax[qs], sc[qs], -bias[qs]) > MAX_SLACK;
+        for (int qs = 0; qs < QS; ++qs) {
+            // the exp2 argument of the own maximum
+            const float top = __builtin_fmaf(KTOK ? pmaxf[qs][0] : as_f32(pmax[qs][0]), sc[qs], -bias[qs]);
+            want = want || off_grid[qs] || (top > MAX_SLACK);
+        }
         return __builtin_amdgcn_ballot_w64(want) != 0ull;
     };
-    // The rare path: new running maximum; O^T, l and the P~ still waiting for its matrix instructions are rescaled.
+    // finish_max (rare path only): the row maximum of the tile in the exp2 domain.
+    auto finish_max = [&]() {
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) {
+            // after the swap one result holds the own value and the other the partner's, in
+            // either half of the wavefront
+            if constexpr (KTOK) {
+                const int mb = as_i32(pmaxf[qs][0]);
+                auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
+                m_cand[qs] = __builtin_fmaxf(as_f32(r[0]), as_f32(r[1])) * sc[qs];     // -inf stays -inf: sc > 0
+            } else {
+                auto r = __builtin_amdgcn_permlane32_swap(pmax[qs][0], pmax[qs][0], false, false);
+                const int mi = max((int)r[0], (int)r[1]);      // signed: the hidden pattern is negative
+                // a row whose keys are all hidden holds the pattern of -inf, and stays -inf here
+                m_cand[qs] = (as_f32(mi) - MAGIC_F) * sc[qs];
+            }
+        }
+    };
+    // The rare path: new running maximum; O^T, l and the P~ still waiting for its matrix
+    // instructions are rescaled.
     auto raise_maximum = [&]() {
+        finish_max();
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             refresh(acc_l[qs]);
@@ -708,7 +625,9 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         }
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
-            const float m_new = __builtin_fmaxf(m_run[qs], pair32_max(pmax[qs]) * sc[qs]);
+            float m_new = __builtin_fmaxf(m_run[qs], m_cand[qs]);
+            if constexpr (!KTOK)        // onto the grid on which the bias is exact
+                m_new = __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_new));
             const float alpha = __builtin_amdgcn_exp2f(m_run[qs] - m_new);
             m_run[qs] = m_new;
             acc_l[qs] *= alpha;        // the register of the lane's own query is the one that counts
@@ -731,15 +650,23 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                         pk[qs][s][u][e] = __builtin_bit_cast(int, __builtin_bit_cast(h2, w) * a2);
                     }
         }
-        set_bias();
+    };
+    auto set_bias = [&]() {
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs)       // exp2 argument = acc*sc - bias
+            bias[qs] = KTOK ? m_run[qs] : __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
     };
 
-    // ---- one pipeline step: softmax of tile j (scores in acc_s), P~V of tile j-1, K^Q^^T of tile j+1, row sums of tile j.
-    // (Tile 0 has no P~V before it: first_tile(); the last one no K^Q^^T after it.)
+    // ---- one pipeline step: softmax of tile j (scores in acc_s), P~V of tile j-1, K^Q^^T of tile
+    // j+1.  (Tile 0 has no P~V before it: first_tile(); the last one no K^Q^^T after it.)
     //
     // Flat operand sequence o = 0 .. 4*DT + 2*KS - 1: four P~V groups (DT operands each), then
     // the two K^Q^^T halves (KS operands each).  Operand o+PD is read from LDS before the matrix
-    // instructions of operand o are issued.
+    // instructions of operand o are issued.  The step comes in two parts:
+    //   step_a  the first P~V group, with the row maximum of tile j computed between its matrix
+    //           instructions (nothing of tile j's softmax can start before the maximum is known);
+    //   step_b  everything else, with the softmax chunks between the matrix instructions.
+    // Between the two the (rare) raise of the running maximum takes place.
     constexpr int NOPS = 4 * DT + 2 * KS;
     // LDS operands are read PD operands ahead of their matrix instructions.  The depth does not show
     // in the timing, but at D = 64 the four registers of a ring slot decide whether a third
@@ -770,22 +697,12 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             else qk_mfma_next(acc_s[qs][half], opnd[o % (PD + 1)], qreg[qs][ks]);
         }
     };
-    // row sums of a 16-key group just packed: l += 1^T P~^T on the matrix pipe.  WAIT: for the last group's result, where the
-    // compiler may copy the sums next.
-    auto row_sums = [&](auto G, auto WAIT) {
+    auto row_sums = [&](auto G) {
+        // row sums of a 16-key group just consumed: l += 1^T P~^T on the matrix pipe
         constexpr int grp_su = IDX(G);
         static_for<QS>([&](auto QSI) {
             constexpr int qs = IDX(QSI);
-            if constexpr (KTOK) {
-                l_mfma_parked(acc_l[qs], sel, pk[qs][grp_su >> 1][grp_su & 1]);
-            } else if constexpr (grp_su == 0) {
-                before_l[qs] = acc_l[qs];
-                l_mfma_first(acc_l[qs], sel, pk[qs][0][0], before_l[qs]);
-            } else if constexpr (grp_su == 3 && IDX(WAIT) != 0) {
-                l_mfma_last(acc_l[qs], sel, pk[qs][1][1]);
-            } else {
-                l_mfma_next(acc_l[qs], sel, pk[qs][grp_su >> 1][grp_su & 1]);
-            }
+            l_mfma(acc_l[qs], sel, pk[qs][grp_su >> 1][grp_su & 1]);
         });
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -807,92 +724,93 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         xs[ch % 3][1] = __builtin_amdgcn_exp2f(xs[ch % 3][1]);
     };
     auto chunk_pack = [&](int ch) {
+        // P~ is rounded to FP16 with round-to-nearest-even (one packed convert), as Algorithm 1 has it.
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
         const int grp_su = ch / CHUNKS, cc = ch % CHUNKS, qs = cc / 4, pair = cc % 4;
-        int packed = pack2(xs[ch % 3][0], xs[ch % 3][1]);
+        const f2 pp = {xs[ch % 3][0], xs[ch % 3][1]};
+        int packed = __builtin_bit_cast(int, __builtin_convertvector(pp, h2));
         // Pinned to this place in the instruction stream: otherwise the compiler is free to sink the
         // whole softmax of the step down to its first use in the next step (it does, once two steps
         // share a loop body), out of the shadow of this step's matrix instructions.
         asm volatile("" : "+v"(packed));
         pk[qs][grp_su >> 1][grp_su & 1][pair] = packed;
     };
-    // Schedule of a step: the P~V groups and the first half of K^Q^^T (MB matrix instructions) carry the NCH softmax chunks, as
-    // evenly as they divide; the second half of K^Q^^T follows (it overwrites the half of S that the last chunks read) and takes
-    // the two ticks that drain the chunk pipeline.  Chunk c enters at tick c (fma), is exponentiated at tick c+1 and packed
-    // at tick c+2.  The row sums of a group follow one matrix instruction after the group is packed.
-    constexpr int MB = (4 * DT + KS) * QS;
-    // One scale per key: the first P~V group carries the row maximum.  Two sub-tiles: a group's P~V takes twice the instructions.
-    constexpr int START = KTOK ? DT * QS : QS == 1 ? 0 : 2;
-    constexpr int LAST_TICKS = NCH - 2 * QS, MB_LAST = 4 * DT * QS;
-    using Plan = TickPlan<NCH, MB, START>;
-    using LastPlan = TickPlan<LAST_TICKS, MB_LAST, START>;
+    // Schedule of a step (QS = 1 in the formulas):
+    //   step_a  the first SA P~V groups (NA matrix instructions); the row maximum of tile j is
+    //           taken between them -- nothing of tile j's softmax can start before it is known;
+    //   step_b  the other P~V groups and the first half of K^Q^^T (MB matrix instructions) carry
+    //           the NCH softmax chunks, as evenly as they divide; the second half of K^Q^^T
+    //           follows (it overwrites the half of S that the last chunks read) and takes the two
+    //           ticks that drain the chunk pipeline.
+    // Chunk c enters at tick c (fma), is exponentiated at tick c+1 and packed at tick c+2.
+    static_assert(QS == 1 || SA == 1, "the generalized schedule is written for one query sub-tile");
+    constexpr int MB = ((4 - SA) * DT + KS) * QS;
+    constexpr int NB = (NOPS - NA) * QS;                // matrix instructions of step_b
+    constexpr int LAST_TICKS = NCH - 2 * QS, MB_LAST = (4 - SA) * DT * QS;
+    using Plan = TickPlan<NCH, MB>;
+    using LastPlan = TickPlan<LAST_TICKS, MB_LAST>;
     static_assert(KS * QS >= 2, "two drain ticks need two matrix instructions after the last fma");
     // a P~ group is packed only after its P~V of tile j-1 has been issued ...
-    static_assert(Plan::slot_of(CHUNKS * 0 + 2) >= 1 * DT * QS - 1, "group 0 packed after its matrix instructions");
-    static_assert(Plan::slot_of(CHUNKS * 1 + 2) >= 2 * DT * QS - 1, "group 1 packed after its matrix instructions");
-    static_assert(Plan::slot_of(CHUNKS * 2 + 2) >= 3 * DT * QS - 1, "group 2 packed after its matrix instructions");
-    static_assert(Plan::slot_of(CHUNKS * 3 + 2) >= 4 * DT * QS - 1, "group 3 packed after its matrix instructions");
-    static_assert(LastPlan::slot_of(CHUNKS * 0 + 2) >= 1 * DT * QS - 1, "last tile: group 0 packed after its matrix instructions");
-    static_assert(LastPlan::slot_of(CHUNKS * 1 + 2) >= 2 * DT * QS - 1, "last tile: group 1 packed after its matrix instructions");
-    static_assert(LastPlan::slot_of(CHUNKS * 2 + 2) >= 3 * DT * QS - 1, "last tile: group 2 packed after its matrix instructions");
+    static_assert(SA >= 2 || Plan::slot_of(CHUNKS * 1 + 2) >= (2 - SA) * DT * QS - 1, "group 1 packed after its matrix instructions");
+    static_assert(SA >= 3 || Plan::slot_of(CHUNKS * 2 + 2) >= (3 - SA) * DT * QS - 1, "group 2 packed after its matrix instructions");
+    static_assert(SA >= 4 || Plan::slot_of(CHUNKS * 3 + 2) >= (4 - SA) * DT * QS - 1, "group 3 packed after its matrix instructions");
+    static_assert(SA >= 2 || LastPlan::slot_of(CHUNKS * 1 + 2) >= (2 - SA) * DT * QS - 1, "last tile: group 1 packed after its matrix instructions");
+    static_assert(SA >= 3 || LastPlan::slot_of(CHUNKS * 2 + 2) >= (3 - SA) * DT * QS - 1, "last tile: group 2 packed after its matrix instructions");
     static_assert(CHUNKS * 3 + 2 >= LAST_TICKS, "last tile: group 3 packed after its matrix instructions");
     // ... and each half of S_j is consumed before the K^Q^^T of that half is issued
-    static_assert(Plan::slot_of(NCH / 2 - 1) < 4 * DT * QS, "first half of S consumed before it is overwritten");
+    static_assert(Plan::slot_of(NCH / 2 - 1) < (4 - SA) * DT * QS, "first half of S consumed before it is overwritten");
     static_assert(Plan::slot_of(NCH - 1) < MB, "second half of S consumed before it is overwritten");
+    // par = j & 1, passed separately so that the unrolled main loop can give it as a constant: every
+    // LDS address of the step is then a per-lane register plus an immediate.
+    auto step_a = [&](int par) {
+        const int vbuf = par ^ 1, kbuf = par ^ 1;       // V(j-1) and K^(j+1) sit in the other buffer
+        static_for<PD>([&](auto O) { load_operand(O, vbuf, kbuf); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NA>([&](auto O) {
+            constexpr int o = IDX(O);
+            load_operand(std::integral_constant<int, o + PD>{}, vbuf, kbuf);
+            static_for<QS>([&](auto QSI) {
+                issue_mfma(O, QSI);
+                partial_max(QSI, O, par);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (o % DT == DT - 1) row_sums(std::integral_constant<int, o / DT>{});
+        });
+    };
     // Chunk-pipeline ticks first .. end - 1.
     auto ticks = [&](auto FIRST, auto END) {
-        static_for<(IDX(END) > IDX(FIRST) ? IDX(END) - IDX(FIRST) : 0)>([&](auto I) {
+        static_for<IDX(END) - IDX(FIRST)>([&](auto I) {
             constexpr int n = IDX(FIRST) + IDX(I);
             if constexpr (n - 2 >= 0 && n - 2 < NCH) chunk_pack(n - 2);
             if constexpr (n - 1 >= 0 && n - 1 < NCH) chunk_exp(n - 1);
             if constexpr (n < NCH) chunk_fma(n);
         });
     };
-    // par = j & 1, passed separately so that the unrolled main loop can give it as a constant: every
-    // LDS address of the step is then a per-lane register plus an immediate.
     // LAST: the wavefront's last tile has no K^Q^^T after it.  The chunks go behind the P~V instructions alone, the last ones
-    // behind none: the fourth P~ group is packed after its last matrix instruction.
-    // TAIL: not in the loop of the steady state.
-    auto step = [&](int par, auto LAST, auto TAIL) __attribute__((always_inline)) {
+    // behind none (14 ticks in 12 or 6 slots: the fourth P~ group is packed after its last matrix instruction).
+    auto step_b = [&](int par, auto LAST) {
         constexpr bool last = IDX(LAST) != 0;
         constexpr int ops = last ? 4 * DT : NOPS;
-        using Plan = TickPlan<last ? LAST_TICKS : NCH, last ? MB_LAST : MB, START>;
-        const int vbuf = par ^ 1, kbuf = par ^ 1;       // V(j-1) and K^(j+1) sit in the other buffer
-        static_for<ops>([&](auto O) {
-            constexpr int o = IDX(O);
+        using Plan = TickPlan<last ? LAST_TICKS : NCH, last ? MB_LAST : MB>;
+        const int vbuf = par ^ 1, kbuf = par ^ 1;
+        static_for<ops - NA>([&](auto OO) {
+            constexpr int o = IDX(OO) + NA;
             static_for<QS>([&](auto QSI) {
                 constexpr int qs = IDX(QSI);
-                issue_mfma(O, QSI);
+                issue_mfma(std::integral_constant<int, o>{}, QSI);
                 if constexpr (qs == 0 && o + PD < ops) {
                     // the next operand read goes out in the shadow of the matrix instruction
                     load_operand(std::integral_constant<int, o + PD>{}, vbuf, kbuf);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                constexpr int i = o * QS + qs;          // index of the matrix instruction
-                if constexpr (KTOK && o < DT) {
-                    partial_max(QSI, O, par);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if constexpr (KTOK && i == START - 1) {
-                    if (must_raise()) {
-                        if constexpr (CLOCKS) ++n_raised;
-                        raise_maximum();
-                    }
-                    asm volatile("" : "+s"(opaque));
-                }
+                constexpr int i = (o - NA) * QS + qs;       // index of the matrix instruction in step_b
                 ticks(std::integral_constant<int, Plan::first(i)>{}, std::integral_constant<int, Plan::end(i)>{});
                 __builtin_amdgcn_sched_barrier(0);
-                // groups whose last chunk was packed before this instruction and not before the one ahead of it
-                static_for<4>([&](auto G) {
-                    constexpr int packed = CHUNKS * (IDX(G) + 1) + 2;       // ticks that are through by then
-                    if constexpr (i > 0 && Plan::first(i) >= packed && Plan::first(i - 1) < packed) row_sums(G, TAIL);
-                });
             });
+            if constexpr (o < 4 * DT && o % DT == DT - 1) row_sums(std::integral_constant<int, o / DT>{});
         });
-        constexpr int through = Plan::first(ops * QS), before = Plan::first(ops * QS - 1);
-        ticks(std::integral_constant<int, through>{}, std::integral_constant<int, NCH + 2>{});
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 1");
-        static_for<4>([&](auto G) { if constexpr (before < CHUNKS * (IDX(G) + 1) + 2) row_sums(G, TAIL); });
+        if constexpr (last) ticks(std::integral_constant<int, LAST_TICKS>{}, std::integral_constant<int, NCH + 2>{});
     };
     // The first tile: no P~V before it, and nothing to rescale when its maximum is taken.  K^Q^^T of tile 1 starts when the
     // softmax has consumed the first half of the scores.  The step above with zeros in the place of P~, which did this before,
@@ -900,14 +818,12 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     // keys at D = 128, causal, 82.9 -> 79.1 us, of 4096 436 -> 420, without a mask 775 -> 765; 96 of 1105 at D = 64 39.7 -> 38.7.
     auto first_tile = [&]() {
         static_for<QS>([&](auto QSI) {
-            constexpr int qs = IDX(QSI);
-            if constexpr (KTOK) {
-                static_for<DT>([&](auto P) { partial_max(QSI, P, 0); });
-                m_run[qs] = pair32_max(pmax[qs]) * sc[qs];          // -inf stays -inf: sc > 0
-            } else {
-                m_run[qs] = on_grid(row_maximum(QSI, acc_s, sc[qs]) + FIRST_ROOM, qs);
-            }
+            static_for<NA>([&](auto P) { partial_max(QSI, P, 0); });
         });
+        finish_max();
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs)
+            m_run[qs] = KTOK ? m_cand[qs] : __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_cand[qs]));
         set_bias();
         static_for<PD>([&](auto O) { load_operand(std::integral_constant<int, 4 * DT + IDX(O)>{}, 1, 1); });
         ticks(std::integral_constant<int, 0>{}, std::integral_constant<int, NCH / 2>{});
@@ -921,13 +837,11 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             else if constexpr (i == KS) ticks(std::integral_constant<int, NCH>{}, std::integral_constant<int, NCH + 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
-        asm volatile("s_nop 1");
-        static_for<4>([&](auto G) { row_sums(G, std::integral_constant<int, 1>{}); });
     };
 
     auto dump_tile = [&](int j) {
         const int kv0 = j * KTILE;
-        score_fence(acc_s);
+        score_fence();
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             const int q_row = qrow0 + 32 * qs + ql;
@@ -957,17 +871,6 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     load_k(0, 0);
     if (T > 1) load_k(1, 1);
     request_key_scales(0);
-    // every lane a share of the chunk's key scales, the first of them on their way with the tiles
-    const int scales = (N + (1 << shift_k) - 1) >> shift_k;
-    auto some_scales = [&](int i, float (&x)[4]) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = ksc_bh[i + 64 * e < scales ? i + 64 * e : scales - 1];
-    };
-    float some[4];
-    if constexpr (!DUMP && !KTOK) {
-        some_scales(lane, some);
-        __builtin_amdgcn_sched_barrier(0);
-    }
     // The queries, while the key tiles are on their way.  They are read as codes, or made here from fp16 rows (qf):
     // a query is read once by the launch either way, and the quantizer's own pass over Q (2 bytes read and 1 written
     // per element, 1 read again) is saved.  Lanes past the last row get codes of 0: their scores raise no maximum and cost
@@ -995,14 +898,6 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     for (int qs = 0; qs < QS; ++qs)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) pin_a(qreg[qs][ks]);
-    if constexpr (!DUMP && !KTOK) {
-        for (int i = lane;; some_scales(i, some)) {
-            dk_top = __builtin_fmaxf(__builtin_fmaxf(dk_top, some[0]), __builtin_fmaxf(__builtin_fmaxf(some[1], some[2]), some[3]));
-            i += 256;
-            if (i - lane >= scales) break;
-        }
-        dk_top = as_f32(__builtin_amdgcn_readfirstlane(as_i32(lanes_max<64>(dk_top))));
-    }
     tiles_ready_barrier();
     qk_half(0, std::integral_constant<int, 0>{});
     qk_half(0, std::integral_constant<int, 1>{});
@@ -1030,21 +925,24 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         }
         return;
     }
-    // (A tile whose weights left the range of FP16 is redone when the next one has begun, before its P~V.)
-    auto iteration = [&](int j, int par, auto LAST, auto TAIL) __attribute__((always_inline)) {
+    // The inner loop holds nothing but the steady state: a tile whose maximum forces a rescale
+    // leaves it, is finished on the slow path, and the inner loop is entered again.  (The empty
+    // assembly statements carry a value around the loop that the compiler cannot see through; they
+    // keep it from restructuring the loop nest, which made it spill registers.)
+    unsigned opaque = 0;
+    auto iteration = [&](int j, int par, auto LAST) {
         asm volatile("" : "+s"(opaque));
         turn(j, par);
-        static_for<PD>([&](auto O) { load_operand(O, par ^ 1, par ^ 1); });
         begin_tile(j);
-        if constexpr (!KTOK) {
-            if (__builtin_expect(must_redo(), 0)) {
-                if constexpr (CLOCKS) ++n_raised;
-                redo_tile(j);
-                static_for<PD>([&](auto O) { load_operand(O, par ^ 1, par ^ 1); });
-            }
+        asm volatile("" : "+s"(opaque));
+        step_a(par);
+        if (must_raise()) {
+            if constexpr (CLOCKS) ++n_raised;
+            raise_maximum();
+            set_bias();
         }
         asm volatile("" : "+s"(opaque));
-        step(par, LAST, TAIL);
+        step_b(par, LAST);
         asm volatile("" : "+s"(opaque));
     };
     // Two tiles per trip, so that the buffer parity is a compile-time constant inside the body: 12 address computations
@@ -1058,27 +956,23 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     first_tile();
     if constexpr (CLOCKS) ++n_raised;
     for (j = 1; j + 2 < Tw; j += 2) {
-        iteration(j, 1, inner, inner);
-        iteration(j + 1, 0, inner, inner);
+        iteration(j, 1, inner);
+        iteration(j + 1, 0, inner);
     }
     if (j + 1 < Tw) {
-        iteration(j, 1, inner, last);
+        iteration(j, 1, inner);
         ++j;
     }
     if (j < Tw) {
-        iteration(j, j & 1, last, last);
+        iteration(j, j & 1, last);
         ++j;
     }
     // A wavefront with one tile has scores of a tile that it does not visit (first_tile()), which are never read: keep their
     // registers untouched until the matrix instructions have written them (the compiler would hand them out as temporaries
     // at once).
-    score_fence(acc_s);
+    score_fence();
+    // the P~V of the wavefront's last tile ...
     turn(j, j & 1);
-    if constexpr (!KTOK) {
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) { off_grid[qs] = false; asm volatile("s_nop 11" : "+v"(acc_l[qs])); }
-        if (__builtin_expect(must_redo(), 0)) redo_tile(j);
-    }
     {
         const int vbuf = (j - 1) & 1;
         static_for<4>([&](auto G) {
@@ -1090,7 +984,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     if constexpr (HALVES == 2) {
         for (; j <= T_other; ++j) __syncthreads();
         __syncthreads();                             // nobody reads the tiles any more
-        if constexpr (KTOK) refresh(acc_l[0]);
+        refresh(acc_l[0]);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) refresh(acc_o[0][dt]);
         // the second set's results: [register][row of the set], so that a wavefront's words lie side by side
@@ -1120,7 +1014,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
         const int q_row = qrow0 + 32 * qs + ql;
-        if constexpr (KTOK) refresh(acc_l[qs]);
+        refresh(acc_l[qs]);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) refresh(acc_o[qs][dt]);
         const float l_row = (lane & 16) ? acc_l[qs][1] : acc_l[qs][0];       // the lane's own query, all keys
@@ -1165,12 +1059,12 @@ int causal_items_per_xcd(const CausalOrder& o, int tiles_q) {
     return o.full * o.group * tiles_q + most;
 }
 
-template <int D, int NW, int QS, int HALVES = 1>
+template <int D, int NW, int HALVES = 1>
 static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* kscale,
                             const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                             int block_q, int block_k, const SplitPlan& sp, hipStream_t st,
                             unsigned long long* clocks = nullptr) {
-    constexpr int QTILE = NW / HALVES * 32 * QS, NTHREADS = NW * 64;
+    constexpr int QTILE = NW / HALVES * WROWS, NTHREADS = NW * 64;
     const int tiles_q = (Nq + QTILE - 1) / QTILE;
     const long total = (long)BH * sp.n_splits * tiles_q;
     CausalOrder order = {0, 0, 0};
@@ -1185,7 +1079,7 @@ static hipError_t launch_dn(const Queries& q, const int8_t* kq, const float* ksc
     _Float16* op = (_Float16*)o;
     const bool ktok = block_k == 1;
 #define SAGE_ARGS q.i8, q.scale, kq, kscale, vp, op, sdump, sp.lse, clocks, Nq, N, shift_q, shift_k, tiles_q, per_xcd, total, BH, sp.n_splits, sp.chunk, order, (const _Float16*)q.f16, q.sm_scale
-#define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT, false, QS, HALVES><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
+#define SAGE_LAUNCH(C, DMP, KT) sage_attn_kernel<D, NW, C, DMP, KT, false, HALVES><<<grid, NTHREADS, 0, st>>>(SAGE_ARGS)
     if (clocks != nullptr) {
         // the measurement build exists for the headline shape only: D = 128, 256-row workgroups, block scales
         if constexpr (D == 128 && NW == 8) {
@@ -1221,16 +1115,16 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
                            const void* v, void* o, int32_t* sdump, int BH, int Nq, int N, int causal,
                            int block_q, int block_k, const SplitPlan& sp, hipStream_t st, int wg_rows = 0,
                            unsigned long long* clocks = nullptr) {
-    bool small = !(sdump && D == 128) && small_workgroups(D, BH, Nq, N, causal != 0, sp.n_splits, sp.chunk);
+    bool small = QS == 1 && !(sdump && D == 128) && small_workgroups(D, BH, Nq, N, causal != 0, sp.n_splits, sp.chunk);
     // the score dump may name the workgroup shape, so that a test reaches every instantiation
-    if (sdump && wg_rows != 0) small = wg_rows == 128;
+    if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only
-    if constexpr (D == 64) {
+    if constexpr (D == 64 && QS == 1) {
         if (!sdump && two_halves(D, BH, Nq, N, causal != 0, sp.n_splits))
-            return launch_dn<64, 8, 1, 2>(q, kq, kscale, v, o, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
+            return launch_dn<64, 8, 2>(q, kq, kscale, v, o, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
     }
-    if (small) return launch_dn<D, 4, 1>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);
-    return launch_dn<D, 8, 1>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st, clocks);
+    if (small) return launch_dn<D, 4>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);
+    return launch_dn<D, 8>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st, clocks);
 }
 
 hipError_t launch_attn(const Queries& q, const int8_t* kq, const float* kscale,
