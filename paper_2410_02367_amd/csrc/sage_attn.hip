@@ -68,7 +68,7 @@
 //     dequantization, the log2(e) factor and the subtraction of the running maximum are one FMA;
 //     that FMA rounds once only if what it subtracts, 12582912 * sc + m, is exact, which holds because sc
 //     carries 22 significant bits and m is kept on the grid of 12582912 * sc (see begin_tile(),
-//     finish_max(), raise_maximum());
+//     finish_max(), raise_maximum(); for scales that make that grid coarse, coarse_dk);
 //   - the row maximum is taken on the raw accumulators with integer max;
 //   - P~ is packed to FP16 with the packed round-to-nearest-even convert; the row sum l comes from
 //     one 16x16x32 FP16 matrix instruction per 16 keys whose A operand selects, for every query, the
@@ -209,7 +209,7 @@ template <class T> __device__ __forceinline__ void pin_a(T& x) { asm volatile(""
 // in fp32.  What a set does is what a workgroup of a split launch does with its chunk.
 template <int D, int NW, bool CAUSAL, bool DUMP, bool KTOK, bool CLOCKS = false, int HALVES = 1>
 // Workgroups of 4 wavefronts per CU that the register budget is cut for: 2.  At D = 64 the compiler stays within
-// the 168 registers of three on its own (152, with one scale per key 164), which is 4 % faster than two; the build checks it.
+// the 168 registers of three on its own (152, causal 156, with one scale per key 164), which is 4 % faster than two; the build checks it.
 __global__ void __launch_bounds__(NW * 64, NW == 4 && SAGE_QS == 1 ? 2 : 1)
 sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                  const int8_t* __restrict__ ki, const float* __restrict__ ksc,
@@ -392,6 +392,13 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     v4i pk[QS][2][2];        // P~^T as FP16 pairs: [sub-tile][32-key half][16-key group]
     float m_run[QS], sc[QS], bias[QS], m_cand[QS];
     bool off_grid[QS];       // the running maximum is not on the grid on which this tile's bias is exact
+    // Key scales above coarse_dk make a tile coarse: sc > 1, one unit of its integer scores is more than 2 in the weights (a query
+    // of 60 and a key of 60000 in one channel have sc = 40).  The grid is about as wide as sc: a maximum that moved onto it could
+    // leave the range that FP16 has for the weights of this tile or, rescaled, of the one that waits for its product.  In a
+    // coarse tile the seed is taken off the scores, which is exact, the bias is the maximum alone and needs no grid; the tile
+    // always takes the path of a new maximum, where the scores, of either sign now, are compared as numbers.
+    int coarse_dk = 0, tile_dk = 0;       // (their bits: neither is negative)
+    auto coarse = [&]() { return !KTOK && tile_dk > coarse_dk; };
     int pmax[QS][DT];        // partial integer row maxima of the current tile
     float pmaxf[QS][DT];     // ... floating-point ones when every key has its own scale
     // P~V groups (of DT matrix instructions) that a step issues before the softmax starts, i.e.
@@ -496,7 +503,15 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             const int jn = j + 1 < kv_tiles_all ? j + 1 : j;
             dk_next = ksc_bh[(jn * KTILE) >> shift_k];
         }
-        const bool need_mask = (kv0 + KTILE > N) || (CAUSAL && kv0 + KTILE - 1 > qrow0 + coff);
+        // the last tile that holds no hidden key starts here or before; a coarse tile takes the branch as well, and is off every
+        // grid: NaN is not equal to any maximum
+        int unmasked = (CAUSAL && qrow0 + coff + 1 < N ? qrow0 + coff + 1 : N) - KTILE, minus_seed = as_i32(-MAGIC_F);
+        if constexpr (!KTOK) {
+            tile_dk = as_i32(dk);
+            unmasked = coarse() ? -1 : unmasked;
+            minus_seed = coarse() ? 0x7FC00000 : minus_seed;
+            asm volatile("" : "+s"(unmasked), "+s"(minus_seed), "+s"(tile_dk));
+        }
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             // a zero scale (all-zero quantization block) would turn -inf * scale into NaN
@@ -525,9 +540,16 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 // the bias, the second what the bias really subtracts besides the seed
                 const float sum = __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
                 bias[qs] = sum;
-                off_grid[qs] = __builtin_fmaf(-MAGIC_F, sc[qs], sum) != m_run[qs];
+                off_grid[qs] = __builtin_fmaf(as_f32(minus_seed), sc[qs], sum) != m_run[qs];
             }
-            if (need_mask) {
+            if (kv0 > unmasked) {
+                // (of a coarse tile the scores lose the constant that they are seeded with, see coarse_dk)
+                if (coarse()) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc_s[qs][s][r] = as_i32(as_f32(acc_s[qs][s][r]) - MAGIC_F);
+                }
                 // keys of the lane's half that the row sees, counted from the tile's first: one comparison per score
                 int seen = N - kv0;
                 if (CAUSAL && seen > qrow0 + 32 * qs + ql + coff + 1 - kv0) seen = qrow0 + 32 * qs + ql + coff + 1 - kv0;
@@ -610,6 +632,12 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 const int mi = max((int)r[0], (int)r[1]);      // signed: the hidden pattern is negative
                 // a row whose keys are all hidden holds the pattern of -inf, and stays -inf here
                 m_cand[qs] = (as_f32(mi) - MAGIC_F) * sc[qs];
+                if (coarse()) {
+                    float mf = as_f32(acc_s[qs][0][0]);
+#pragma unroll
+                    for (int f = 1; f < 32; ++f) mf = __builtin_fmaxf(mf, as_f32(acc_s[qs][f >> 4][f & 15]));
+                    m_cand[qs] = pair32_max(mf) * sc[qs];
+                }
             }
         }
     };
@@ -626,7 +654,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
             float m_new = __builtin_fmaxf(m_run[qs], m_cand[qs]);
-            if constexpr (!KTOK)        // onto the grid on which the bias is exact
+            if (!KTOK && !coarse())       // onto the grid on which the bias is exact
                 m_new = __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_new));
             const float alpha = __builtin_amdgcn_exp2f(m_run[qs] - m_new);
             m_run[qs] = m_new;
@@ -654,7 +682,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     auto set_bias = [&]() {
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs)       // exp2 argument = acc*sc - bias
-            bias[qs] = KTOK ? m_run[qs] : __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
+            bias[qs] = KTOK || coarse() ? m_run[qs] : __builtin_fmaf(MAGIC_F, sc[qs], m_run[qs]);
     };
 
     // ---- one pipeline step: softmax of tile j (scores in acc_s), P~V of tile j-1, K^Q^^T of tile
@@ -823,7 +851,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
         finish_max();
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs)
-            m_run[qs] = KTOK ? m_cand[qs] : __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_cand[qs]));
+            m_run[qs] = KTOK || coarse() ? m_cand[qs] : __builtin_fmaf(-MAGIC_F, sc[qs], __builtin_fmaf(MAGIC_F, sc[qs], m_cand[qs]));
         set_bias();
         static_for<PD>([&](auto O) { load_operand(std::integral_constant<int, 4 * DT + IDX(O)>{}, 1, 1); });
         ticks(std::integral_constant<int, 0>{}, std::integral_constant<int, NCH / 2>{});
@@ -901,6 +929,14 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
     tiles_ready_barrier();
     qk_half(0, std::integral_constant<int, 0>{});
     qk_half(0, std::integral_constant<int, 1>{});
+    if constexpr (!DUMP && !KTOK) {
+        float dq_top = dq[0];
+#pragma unroll
+        for (int qs = 1; qs < QS; ++qs) dq_top = __builtin_fmaxf(dq_top, dq[qs]);
+        if (shift_q < 5) dq_top = lanes_max<64>(dq_top);           // otherwise one for all 32 rows
+        coarse_dk = __builtin_amdgcn_readfirstlane(as_i32(__builtin_amdgcn_rcpf(dq_top)));
+        asm volatile("" : "+s"(coarse_dk));
+    }
 
     // ---- main loop.  Time slot j lies between barriers j and j+1.  At barrier j the tiles
     // requested in slot j-1 have landed and the buffers of V(j-2) and K^(j) are free (their last
