@@ -63,7 +63,7 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
     unsigned char* const kl = pool;
     unsigned char* const vl = pool + KMAX * D;
     __shared__ __attribute__((aligned(16))) float s_mean[D];
-    __shared__ float s_max[KMAX / 32];
+    __shared__ __attribute__((aligned(16))) float s_max[KMAX / 32];
     __shared__ __attribute__((aligned(16))) float s_scale[KTOK ? KMAX : KMAX / 64];
     __shared__ __attribute__((aligned(16))) float s_bias[KTOK ? KMAX : 4];       // -12582912 * s_scale
     __shared__ float s_q[2][RT];
@@ -182,6 +182,7 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
         for (int e = 0; e < 8; e += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(f[e])), __builtin_fabsf(f[e + 1]));
         return m;
     };
+    float k_top = 0.0f;              // one scale per block: the largest key of all
     if (KTOK) {
 #pragma unroll
         for (int gr = 0; gr < GPW; ++gr) {
@@ -215,6 +216,8 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
             if (lane == 0) s_max[wave * GPW + gr] = gm[gr];
         }
         __syncthreads();
+#pragma unroll
+        for (int i = 0; i < KMAX / 32; ++i) k_top = __builtin_fmaxf(k_top, s_max[i]);       // (a group past the end has 0)
 #pragma unroll
         for (int gr = 0; gr < GPW; ++gr) {
             const int row = wave * (GPW * 32) + gr * 32;
@@ -274,8 +277,11 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
         // keys this wavefront sees; a tile of which it sees only the first half is done by halves
         int seen = causal ? row0 + 32 + coff : N;
         seen = seen < N ? seen : N;
-        auto tile = [&](int j, auto HALVES) {
+        // COARSE: the scales make the grid of the maximum wider than 1 (coarse_dk in sage_attn.hip); the scores lose their seed,
+        // which is exact, and need no grid.
+        auto tile = [&](int j, auto HALVES, auto COARSE) {
             constexpr int NH = HALVES.value;
+            constexpr bool seeded = !KTOK && COARSE.value == 0;
             const unsigned char* kt = kl + j * (64 * D);
             s16i s[NH];
 #pragma unroll
@@ -283,6 +289,12 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
                     s[h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const s4i*)(kt + h * (32 * D) + k_off[ks]), q[ks], ks == 0 ? magic : s[h], 0, 0, 0);
+            }
+            if (COARSE.value != 0) {
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[h][r] = (int)as_u(as_f((unsigned)s[h][r]) - SHORT_MAGIC);
             }
             // register r of half h: key 64 j + 32 h + 8 (r / 4) + 4 g + r % 4
             const float sc = KTOK ? __builtin_fmaxf(dq, 1e-30f) : as_f(as_u(__builtin_fmaxf(dq * s_scale[j], 1e-30f)) & ~3u);
@@ -322,6 +334,18 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
                     }
                 bias = -m_run;
                 want = __builtin_fmaf(mf, sc, bias) > SHORT_SLACK;
+            } else if (!seeded) {
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) y[h][r] = as_f((unsigned)s[h][r]);
+                mf = y[0][0];
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mf = __builtin_fmaxf(mf, y[h][r]);
+                bias = -m_run;
+                want = __builtin_fmaf(mf, sc, bias) > SHORT_SLACK;
             } else {
                 mi = s[0][0];
 #pragma unroll
@@ -340,7 +364,7 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
             if (__builtin_amdgcn_ballot_w64(want) != 0ull) {
                 // (on the first tile every row that sees a key is here)
                 float top;
-                if (KTOK) {
+                if (!seeded) {
                     auto x = __builtin_amdgcn_permlane32_swap(as_u(mf), as_u(mf), false, false);
                     top = __builtin_fmaxf(as_f(x[0]), as_f(x[1])) * sc;
                 } else {
@@ -348,10 +372,10 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
                     top = (as_f((unsigned)max((int)x[0], (int)x[1])) - SHORT_MAGIC) * sc;
                 }
                 float m_new = __builtin_fmaxf(m_run, top);
-                if (!KTOK) m_new = __builtin_fmaf(-SHORT_MAGIC, sc, __builtin_fmaf(SHORT_MAGIC, sc, m_new));
+                if (seeded) m_new = __builtin_fmaf(-SHORT_MAGIC, sc, __builtin_fmaf(SHORT_MAGIC, sc, m_new));
                 const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
-                bias = KTOK ? -m_run : -__builtin_fmaf(SHORT_MAGIC, sc, m_run);
+                bias = !seeded ? -m_run : -__builtin_fmaf(SHORT_MAGIC, sc, m_run);
                 if (!fresh) {
                     lsum *= alpha;
 #pragma unroll
@@ -387,9 +411,15 @@ __device__ __forceinline__ void short_pass(const _Float16* __restrict__ qf, cons
                 }
         };
         const int whole = (seen + 31) / 64;
+        auto tiles_seen = [&](auto COARSE) {
+            for (int j = kpart; j < whole; j += KSP) tile(j, std::integral_constant<int, 2>{}, COARSE);
+            if (whole * 64 < seen && (KSP == 1 || whole % KSP == kpart)) tile(whole, std::integral_constant<int, 1>{}, COARSE);
+        };
         if (KSP == 1 || row0 < Nq) {
-            for (int j = kpart; j < whole; j += KSP) tile(j, std::integral_constant<int, 2>{});
-            if (whole * 64 < seen && (KSP == 1 || whole % KSP == kpart)) tile(whole, std::integral_constant<int, 1>{});
+            if (!KTOK && __builtin_expect(__builtin_amdgcn_ballot_w64(qmax * k_top > 127.0f * 127.0f / SHORT_LOG2E) != 0ull, 0))
+                tiles_seen(std::integral_constant<int, 1>{});
+            else
+                tiles_seen(std::integral_constant<int, 0>{});
         }
         float l = (lane & 16) ? lsum[1] : lsum[0];
         if constexpr (KSP == 2) {

@@ -16,9 +16,11 @@ from gpu_util import assert_output_close, bits
 pytestmark = pytest.mark.gpu
 
 
-def softmax_of_codes(qq, qs, kq, ks, v):
-    """Attention of one slab over codes and scales (one per row and key), without a mask, in 64 bits."""
+def softmax_of_codes(qq, qs, kq, ks, v, causal=False):
+    """Attention of one slab over codes and scales (one per row and key) in 64 bits."""
     s = (qq.double() @ kq.double().T) * qs.double()[:, None] * ks.double()[None, :]
+    if causal:
+        s = s.masked_fill(torch.ones_like(s, dtype=torch.bool).triu(1), -math.inf)
     return torch.softmax(s, dim=1) @ v.double()
 
 
@@ -150,4 +152,30 @@ def test_scales_that_make_one_unit_of_a_score_a_range_of_weights(slabs, N, D, bl
         qs, ks = q_scale[0, s].repeat_interleave(128)[:N], k_scale[0, s].repeat_interleave(block_k)[:N]
         assert block_k == 1 or float((qs.max() * ks.max()) * math.log2(math.e)) > 24
         ref = softmax_of_codes(q_i8[0, s], qs, k_i8[0, s], ks, v[0, s]).cpu().numpy()
+        assert_output_close(out[0, s].cpu().numpy(), ref, f"slab {s}")
+
+
+# slabs, N, D, block_q, block_k, causal: short sequences, one and two wavefronts per query tile
+SHORT = [(500, 200, 64, 128, 64, False), (500, 197, 64, 128, 128, True), (2, 256, 64, 128, 64, False), (2, 400, 64, 64, 128, True), (3, 97, 64, 64, 64, False),
+         (2, 256, 128, 128, 64, False), (300, 250, 128, 64, 64, True), (2, 256, 64, 1, 1, False), (300, 255, 128, 1, 1, True)]
+
+
+@pytest.mark.parametrize("q_large,k_large", [(60.0, -60000.0), (100.0, 60000.0), (3000.0, 50000.0), (3000.0, -50000.0)])
+@pytest.mark.parametrize("where", ["first", "middle", "last"])
+@pytest.mark.parametrize("slabs,N,D,block_q,block_k,causal", SHORT)
+def test_such_scales_in_short_sequences(slabs, N, D, block_q, block_k, causal, where, q_large, k_large):
+    print(f"[case] {slabs} x {N} x {D} causal={causal}, scales {block_q}x{block_k}, {where} key {k_large}, queries {q_large}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + D)
+    normal = lambda: torch.randn((1, slabs, N, D), generator=gen, device="cuda")
+    q, k, v = normal(), normal(), normal().clamp(-1.99, 1.99).half()
+    q[:, :, ::16, 3] = q_large
+    k[:, :, {"first": 0, "middle": N // 2 + 1, "last": N - 1}[where], 3] = k_large
+    q, k, sm = q.half(), k.half(), D ** -0.5
+    out = sage.sageattn(q, k, v, causal, sm, block_q, block_k)
+    k_i8, k_scale, _ = sage.sage_smooth_quant_k(k, block_k)
+    q_i8, q_scale = sage.sage_quant_q(q, sm, block_q)
+    for s in {0, slabs - 1}:
+        qs, ks = q_scale[0, s].repeat_interleave(block_q)[:N], k_scale[0, s].repeat_interleave(block_k)[:N]
+        ref = softmax_of_codes(q_i8[0, s], qs, k_i8[0, s], ks, v[0, s], causal).cpu().numpy()
         assert_output_close(out[0, s].cpu().numpy(), ref, f"slab {s}")
