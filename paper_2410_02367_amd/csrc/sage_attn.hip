@@ -544,7 +544,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
             }
             if (kv0 > unmasked) {
                 // (of a coarse tile the scores lose the constant that they are seeded with, see coarse_dk)
-                if (coarse()) {
+                if (__builtin_expect(coarse(), 0)) {
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -632,7 +632,7 @@ sage_attn_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qsc,
                 const int mi = max((int)r[0], (int)r[1]);      // signed: the hidden pattern is negative
                 // a row whose keys are all hidden holds the pattern of -inf, and stays -inf here
                 m_cand[qs] = (as_f32(mi) - MAGIC_F) * sc[qs];
-                if (coarse()) {
+                if (__builtin_expect(coarse(), 0)) {
                     float mf = as_f32(acc_s[qs][0][0]);
 #pragma unroll
                     for (int f = 1; f < 32; ++f) mf = __builtin_fmaxf(mf, as_f32(acc_s[qs][f >> 4][f & 15]));
