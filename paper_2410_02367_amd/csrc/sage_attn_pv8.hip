@@ -348,13 +348,9 @@ sage_attn_pv8_kernel(const int8_t* __restrict__ qi, const float* __restrict__ qs
             for (int r = 0; r < 16; ++r) tmax = __builtin_fmaxf(tmax, y[kb][r]);
         tmax *= sc;
         tmax = pair32_max(tmax);
-        float m_new = __builtin_fmaxf(m_run, tmax);
+        const float m_new = __builtin_fmaxf(m_run, tmax);
         ++since;
         if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0ull || since >= PV8_FLUSH_TILES) {
-            // Rounding the scores, their maximum and mb can take the largest weight two halves of a unit of m above 1.  From
-            // 2^16 on that is 2^(1/128), and its code 128, a negative one: there the maximum lies two units or more higher,
-            // up to 2^15 it is what it was.
-            m_new = __builtin_fmaxf(m_run, __builtin_fmaf(__builtin_fmaxf(__builtin_fabsf(tmax) - 0x1p15f, 0.0f), 0x1p-21f, tmax));
             // O relative to the running maximum is g * of + A with a per-lane factor g that takes
             // the rescaling: (g of + A) alpha = (g alpha) (of + A / g), so a flush is one conversion and
             // one FMA per element, of += A * (1 / g), and then g *= alpha.  1 / g = 2^(rise of the
