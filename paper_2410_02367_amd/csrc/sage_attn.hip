@@ -1156,7 +1156,7 @@ static hipError_t launch_d(const Queries& q, const int8_t* kq, const float* ksca
     if (sdump && wg_rows != 0) small = wg_rows == 4 * WROWS;
     if (clocks != nullptr) small = false;       // the measurement build has the 256-row shape only
     if constexpr (D == 64 && QS == 1) {
-        if (!sdump && two_halves(D, BH, Nq, N, causal != 0, sp.n_splits))
+        if (!sdump && two_halves(D, BH, Nq, N, sp.n_splits))
             return launch_dn<64, 8, 2>(q, kq, kscale, v, o, nullptr, BH, Nq, N, causal, block_q, block_k, sp, st);
     }
     if (small) return launch_dn<D, 4>(q, kq, kscale, v, o, sdump, BH, Nq, N, causal, block_q, block_k, sp, st);

@@ -36,13 +36,15 @@ inline bool small_workgroups(int D, int BH, int Nq, int N, bool causal, int n_sp
 }
 
 // Whether the 128-row workgroups of a launch are made of two sets of 4 wavefronts, each with half of the keys (HALVES in
-// sage_attn.hip): where a CU has one of them at most, and with it one wavefront per SIMD.  us for the calls of a whole pass
-// with one / two sets, D = 64: 1 slab of 20000 182 / 134, of 32000 causal 287 / 210, 2 of 8192 80.5 / 62.1, 8 of 4096 causal
-// 47.8 / 39.7, 12 of 2600 causal 45.7 / 37.4, 32 of 1024 causal 30.3 / 26.6, 60 of 512 22.7 / 20.8, 40 of 400 20.9 / 19.6, 10 of
-// 300 18.2 / 18.1.  Not with few keys under a mask, where the first tiles of rows have nothing to share: 85 of 384 21.1 / 23.7,
-// 64 of 512 22.8 / 21.6.  Not at D = 128, where the rule above counts on it that a row's bits do not depend on the shape.
-inline bool two_halves(int D, int BH, int Nq, int N, bool causal, int n_splits) {
-    return D == 64 && n_splits == 1 && N >= (causal ? 512 : 257) && (long)BH * ((Nq + 127) / 128) <= 256;
+// sage_attn.hip): where a CU has one of them at most, and with it one wavefront per SIMD.  us of the attention call with one /
+// two sets, D = 64: 1 slab of 1024 11.9 / 11.1, 32 of 1024 13.9 / 13.8, causal 13.4 / 13.2, 16 of 2048 22.9 / 21.7, causal 21.9 /
+// 19.9, 8 of 4096 39.4 / 36.2, causal 38.4 / 32.3, 1 of 6000 54.3 / 43.0; with one scale per key 32 of 1024 16.4 / 14.9; whole
+// pass, 1 slab of 20000 183 / 154.  With fewer keys the merge and the rows that see the first set's keys alone cost more than the
+// shorter chain saves: 36 of 800 12.3 / 12.3, 51 of 600 causal 10.2 / 12.2, 85 of 300 7.5 / 8.3.
+// The sums of two sets are added in another order than one set's: at D = 64 the last bits of a row depend on whether the call
+// has few slabs.  Not so at D = 128, where the rule above counts on it that a row's bits do not depend on the shape.
+inline bool two_halves(int D, int BH, int Nq, int N, int n_splits) {
+    return D == 64 && n_splits == 1 && N >= 1024 && (long)BH * ((Nq + 127) / 128) <= 256;
 }
 
 }  // namespace sage

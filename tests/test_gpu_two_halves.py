@@ -14,32 +14,31 @@ from gpu_util import assert_output_close, to_dev
 from paper_2410_02367_amd import build
 
 SHIM = """#include "sage_shape.h"
-extern "C" int two_halves(int D, int BH, int Nq, int N, int causal, int n_splits) {
-    return sage::two_halves(D, BH, Nq, N, causal != 0, n_splits);
+extern "C" int two_halves(int D, int BH, int Nq, int N, int n_splits) {
+    return sage::two_halves(D, BH, Nq, N, n_splits);
 }
 """
 
 
-@pytest.mark.parametrize("D,slabs,Nq,N,causal,n_splits,two", [
-    (64, 1, 257, 257, False, 1, True), (64, 1, 256, 256, False, 1, False), (64, 1, 512, 512, True, 1, True),
-    (64, 1, 511, 511, True, 1, False), (64, 32, 1024, 1024, False, 1, True), (64, 32, 1025, 1025, False, 1, False),
-    (64, 256, 128, 300, False, 1, True), (64, 257, 128, 300, False, 1, False), (64, 1, 300, 9000, True, 2, False),
-    (128, 1, 4096, 4096, False, 1, False)])
-def test_the_rule_for_two_sets(tmp_path, D, slabs, Nq, N, causal, n_splits, two):
+@pytest.mark.parametrize("D,slabs,Nq,N,n_splits,two", [
+    (64, 1, 1024, 1024, 1, True), (64, 1, 1023, 1023, 1, False), (64, 32, 1024, 1024, 1, True), (64, 32, 1025, 1025, 1, False),
+    (64, 256, 128, 1500, 1, True), (64, 257, 128, 1500, 1, False), (64, 1, 300, 9000, 2, False), (128, 1, 4096, 4096, 1, False)])
+def test_the_rule_for_two_sets(tmp_path, D, slabs, Nq, N, n_splits, two):
     src, lib = tmp_path / "shape.cpp", tmp_path / "shape.so"
     src.write_text(SHIM)
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + build.CSRC, "-o", str(lib), str(src)], check=True)
-    assert bool(ctypes.CDLL(str(lib)).two_halves(D, slabs, Nq, N, int(causal), n_splits)) == two
+    assert bool(ctypes.CDLL(str(lib)).two_halves(D, slabs, Nq, N, n_splits)) == two
 
 
-# (slabs, Nq, Nkv, causal, block_q, block_k, rising).  257, 320, 321: the second set has one key, one tile, two; 64-key blocks
-# and 128-key ones, whose boundary the cut keeps to; causal: rows whose first keys are the first set's alone (both sets then
-# walk all keys), queries that are the last of the keys; rising: scores that leave the range of FP16 in either half.
+# (slabs, Nq, Nkv, causal, block_q, block_k, rising).  1024, 1025, 1087: sets of the same number of keys, a second set that ends
+# on a tile of one key or one that lacks one; 64-key blocks and 128-key ones, whose boundary the cut keeps to; causal: rows whose
+# first keys are the first set's alone (both sets then walk all keys), queries that are the last of the keys; rising: a maximum
+# that rises in either half.
 CASES = [
-    (2, 257, 257, False, 128, 64, False), (2, 320, 320, False, 64, 128, False), (1, 321, 321, False, 1, 1, False),
-    (3, 385, 385, False, 128, 128, False), (2, 1000, 1000, False, 128, 64, True), (2, 512, 512, True, 128, 64, False),
-    (2, 577, 577, True, 128, 128, False), (1, 1111, 1111, True, 1, 1, False), (2, 1200, 1200, True, 64, 64, True),
-    (2, 130, 700, True, 128, 64, False), (2, 90, 513, True, 32, 128, True), (3, 333, 450, False, 128, 1, False),
+    (2, 1024, 1024, False, 128, 64, False), (2, 1025, 1025, False, 64, 128, False), (1, 1087, 1087, False, 1, 1, False),
+    (3, 1153, 1153, False, 128, 128, False), (2, 1500, 1500, False, 128, 64, True), (2, 1024, 1024, True, 128, 64, False),
+    (2, 1089, 1089, True, 128, 128, False), (1, 1111, 1111, True, 1, 1, False), (2, 1200, 1200, True, 64, 64, True),
+    (2, 130, 1400, True, 128, 64, False), (2, 90, 1025, True, 32, 128, True), (3, 333, 1050, False, 128, 1, False),
 ]
 
 

@@ -100,8 +100,8 @@ def test_the_denominator_sums_the_weights_that_multiply_the_values(slabs, D, blo
     """64 equal weights wait for their product when the second tile's one visible key raises the maximum by 0.8 to 1 in the
     exponent (one row in 32 by 10, which makes the wavefront raise).  A factor of 2^-0.8 to 2^-1 is rounded by up to 2^-12,
     relatively 2^-11; where the sum held other weights than the product, rows would come out as 1 - 2^-11."""
-    print(f"[case] {slabs} x 256 against 768 x {D}, keys scaled per {block_k}", flush=True)
-    Nq, N = 256, 768
+    print(f"[case] {slabs} x 256 against 1088 x {D}, keys scaled per {block_k}", flush=True)
+    Nq, N = 256, 1088
     qq = torch.zeros((1, slabs, Nq, D), dtype=torch.int8)
     qq[..., 0] = 127
     qq[..., 1] = 100
