@@ -123,18 +123,20 @@ def test_the_denominator_sums_the_weights_that_multiply_the_values(slabs, D, blo
     assert (out.cpu() == 1.0).all()
 
 
-# slabs, N, D, block_k, n_splits: workgroups of either shape, one and two sets of wavefronts, keys in chunks, one scale per key
-COARSE = [(2, 1024, 64, 64, 1), (40, 1000, 64, 128, 1), (2, 1024, 64, 64, 3), (2, 1024, 128, 64, 1), (17, 2100, 128, 128, 1), (2, 1000, 128, 64, 4),
-          (2, 1024, 64, 1, 1), (2, 1024, 128, 1, 1)]
+# slabs, N, D, block_q, block_k, n_splits (0: the whole call, which quantizes the queries in the kernel): workgroups of either
+# shape, one and two sets of wavefronts, keys in chunks, scales that differ within a wavefront, one scale per key
+COARSE = [(2, 1024, 64, 128, 64, 1), (40, 1000, 64, 128, 128, 1), (2, 1024, 64, 128, 64, 3), (2, 1024, 128, 128, 64, 1), (17, 2100, 128, 128, 128, 1),
+          (2, 1000, 128, 128, 64, 4), (2, 1024, 64, 1, 64, 1), (40, 1000, 64, 32, 64, 1), (2, 1000, 128, 1, 128, 1), (2, 1100, 64, 128, 64, 0),
+          (40, 1000, 64, 1, 64, 0), (2, 700, 128, 64, 64, 0), (2, 1024, 64, 1, 1, 1), (2, 1024, 128, 1, 1, 1)]
 
 
 @pytest.mark.parametrize("q_large,k_large", [(60.0, -60000.0), (100.0, 60000.0), (731.0, -4321.0), (3000.0, 50000.0)])
 @pytest.mark.parametrize("where", ["first", "middle", "last"])
-@pytest.mark.parametrize("slabs,N,D,block_k,n_splits", COARSE)
-def test_scales_that_make_one_unit_of_a_score_a_range_of_weights(slabs, N, D, block_k, n_splits, where, q_large, k_large):
+@pytest.mark.parametrize("slabs,N,D,block_q,block_k,n_splits", COARSE)
+def test_scales_that_make_one_unit_of_a_score_a_range_of_weights(slabs, N, D, block_q, block_k, n_splits, where, q_large, k_large):
     """One channel of a key and of every 16th query is so large that one unit of an integer score is 2^24 to 2^1700 in the weights:
     the maximum of a row cannot lie on a grid of such units, neither in that tile nor in the ones before and after it."""
-    print(f"[case] {slabs} x {N} x {D}, keys scaled per {block_k}, {n_splits} chunks, {where} key {k_large}, queries {q_large}", flush=True)
+    print(f"[case] {slabs} x {N} x {D}, scales {block_q}x{block_k}, {n_splits} chunks, {where} key {k_large}, queries {q_large}", flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(N + D)
     normal = lambda: torch.randn((1, slabs, N, D), generator=gen, device="cuda")
@@ -143,13 +145,15 @@ def test_scales_that_make_one_unit_of_a_score_a_range_of_weights(slabs, N, D, bl
     k[:, :, {"first": 0, "middle": N // 2 + 1, "last": N - 1}[where], 3] = k_large
     sm = D ** -0.5
     k_i8, k_scale, _ = sage.sage_smooth_quant_k(k.half(), block_k)
-    q_i8, q_scale = sage.sage_quant_q(q.half(), sm, 128)
-    if n_splits == 1:
-        out = sage.sage_attn_fwd(q_i8, q_scale, k_i8, k_scale, v, False, sm, 128, block_k)
+    q_i8, q_scale = sage.sage_quant_q(q.half(), sm, block_q)
+    if n_splits == 0:
+        out = sage.sageattn(q.half(), k.half(), v, False, sm, block_q, block_k)
+    elif n_splits == 1:
+        out = sage.sage_attn_fwd(q_i8, q_scale, k_i8, k_scale, v, False, sm, block_q, block_k)
     else:
-        out = sage.sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, False, sm, 128, block_k, n_splits=n_splits)
+        out = sage.sage_attn_cross_split_fwd(q_i8, q_scale, k_i8, k_scale, v, False, sm, block_q, block_k, n_splits=n_splits)
     for s in {0, slabs - 1}:
-        qs, ks = q_scale[0, s].repeat_interleave(128)[:N], k_scale[0, s].repeat_interleave(block_k)[:N]
+        qs, ks = q_scale[0, s].repeat_interleave(block_q)[:N], k_scale[0, s].repeat_interleave(block_k)[:N]
         assert block_k == 1 or float((qs.max() * ks.max()) * math.log2(math.e)) > 24
         ref = softmax_of_codes(q_i8[0, s], qs, k_i8[0, s], ks, v[0, s]).cpu().numpy()
         assert_output_close(out[0, s].cpu().numpy(), ref, f"slab {s}")
